@@ -108,7 +108,7 @@ int upload_array(Uploader& up, const std::vector<T>& h, T** d) {
 
 void free_device(rsh::DevicePlan& d) {
     void* ptrs[] = {d.win_row, d.win_tile_off, d.tile_colid, d.tile_mask, d.tile_val_off, d.tile_val,
-                    d.tile_item, d.panel_col0, d.panel_off, d.panel_ent, d.irr_col, d.irr_val, d.irr_wave, d.irr_row, d.combine, d.scratch,
+                    d.tile_item, d.panel_col0, d.panel_off, d.panel_ent, d.panel_quad0, d.panel_meta, d.panel_qoff, d.panel_val, d.irr_col, d.irr_val, d.irr_wave, d.irr_row, d.combine, d.scratch,
                     d.b_pad, d.c_pad, d.bias_pad};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
@@ -116,6 +116,43 @@ void free_device(rsh::DevicePlan& d) {
     if (d.ev_join) (void)hipEventDestroy((hipEvent_t)d.ev_join);
     if (d.side) (void)hipStreamDestroy((hipStream_t)d.side);
     d = rsh::DevicePlan{};
+}
+
+// The entries of a panel-form plan are turned on the device into the form the kernel reads (panel.hpp);
+// what was uploaded for that is given back.
+int upload_panel_units(Uploader& up, const rsh::HostPlan& h, rsh::DevicePlan& d) {
+    const int64_t n_windows = (int64_t)h.win_tile_off.size() - 1, n_units = (int64_t)h.panel_off.size() - 1;
+    std::vector<uint32_t> quad0((size_t)n_windows + 1, 0);
+    for (int64_t w = 0; w < n_windows; ++w)
+        quad0[(size_t)w + 1] = quad0[(size_t)w] + (uint32_t)h.geo.panel_groups * ((h.win_tile_off[(size_t)w + 1] - h.win_tile_off[(size_t)w] + 3) / 4);
+    const size_t n_quads = quad0[(size_t)n_windows];
+    int rc;
+    if ((rc = upload_array(up, quad0, &d.panel_quad0))) return rc;
+    if (!hip_ok(hipMalloc((void**)&d.panel_meta, (n_quads + 1) * 1024))) return RSH_ERR_OOM;
+    if (!hip_ok(hipMalloc((void**)&d.panel_qoff, (n_quads + 1) * 4))) return RSH_ERR_OOM;
+    if (n_units <= 0) return RSH_OK;
+    uint32_t* counts = nullptr;
+    struct Temporary {
+        rsh::DevicePlan& d;
+        uint32_t*& counts;
+        ~Temporary() {
+            if (d.panel_off) (void)hipFree(d.panel_off);
+            if (d.panel_ent) (void)hipFree(d.panel_ent);
+            if (counts) (void)hipFree(counts);
+            d.panel_off = d.panel_ent = nullptr;
+        }
+    } temporary{d, counts};
+    if ((rc = upload_array(up, h.panel_off, &d.panel_off))) return rc;
+    if ((rc = upload_array(up, h.panel_ent, &d.panel_ent))) return rc;
+    if (!hip_ok(hipMalloc((void**)&counts, (size_t)(n_units + 1) * 4))) return RSH_ERR_OOM;
+    uint32_t total = 0;
+    if (!hip_ok(hipMemsetAsync(d.panel_meta, 0, (n_quads + 1) * 1024, up.stream))) return RSH_ERR_HIP;
+    if ((rc = rsh::launch_panel_masks(d, n_windows, n_units, counts, up.stream))) return rc;
+    if (!hip_ok(hipMemcpyAsync(&total, counts + n_units, 4, hipMemcpyDeviceToHost, up.stream)) || !hip_ok(hipStreamSynchronize(up.stream)))
+        return RSH_ERR_HIP;
+    if (!hip_ok(hipMalloc((void**)&d.panel_val, ((size_t)total + 64) * 4))) return RSH_ERR_OOM;   // a lane reads 4 dwords from its start
+    if ((rc = rsh::launch_panel_values(d, n_windows, counts, up.stream))) return rc;
+    return hip_ok(hipStreamSynchronize(up.stream)) ? RSH_OK : RSH_ERR_HIP;
 }
 
 int upload_plan(rsh_plan& p) {
@@ -143,9 +180,7 @@ int upload_plan(rsh_plan& p) {
     if ((rc = upload_array(up, h.tile_val, &d.tile_val))) return rc;
     if ((rc = upload_array(up, h.tile_item, &d.tile_item))) return rc;
     if ((rc = upload_array(up, h.panel_col0, &d.panel_col0))) return rc;
-    if ((rc = upload_array(up, h.panel_off, &d.panel_off))) return rc;
-    if ((rc = upload_array(up, h.panel_ent, &d.panel_ent))) return rc;
-    d.n_panel_ent = (uint32_t)h.panel_ent.size();
+    if (h.geo.panel && (rc = upload_panel_units(up, h, d))) return rc;
     if ((rc = upload_array(up, h.irr_col, &d.irr_col))) return rc;
     if ((rc = upload_array(up, h.irr_val, &d.irr_val))) return rc;
     if ((rc = upload_array(up, h.irr_wave, &d.irr_wave))) return rc;

@@ -1,0 +1,104 @@
+// Device helpers shared by the kernel files: vector types, work-item look-up, cross-lane moves, and
+// where finished rows of C go.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <hip/hip_fp16.h>
+
+#include "launch.hpp"
+
+namespace rsh {
+
+typedef _Float16 half4_t __attribute__((ext_vector_type(4)));
+typedef _Float16 half8_t __attribute__((ext_vector_type(8)));
+typedef float float4_t __attribute__((ext_vector_type(4)));
+typedef float float16_t __attribute__((ext_vector_type(16)));
+typedef short short4_t __attribute__((ext_vector_type(4)));
+typedef unsigned int uint4_t __attribute__((ext_vector_type(4)));
+typedef unsigned int uint2_t __attribute__((ext_vector_type(2)));
+
+constexpr int kWavesPerBlock = 4;
+
+// Workgroups are dealt to the 8 XCDs round-robin; each XCD has its own L2.  Block b
+// therefore serves XCD b % 8 and takes the (b / 8)-th group of kWavesPerBlock items of
+// that XCD's contiguous, cost-balanced part of the work list, so that items which are
+// neighbours in the plan share an L2.  Returns false when the part is exhausted.
+__device__ __forceinline__ bool xcd_work_item(const XcdSplit& xs, uint32_t* item) {
+    const uint32_t x = blockIdx.x & 7u;
+    const uint32_t i = xs.start[x] + (blockIdx.x >> 3) * kWavesPerBlock + (threadIdx.x >> 6);
+    *item = __builtin_amdgcn_readfirstlane(i);
+    return i < xs.start[x + 1];
+}
+
+__device__ __forceinline__ int shfl_i32(int v, int src_lane) { return __builtin_amdgcn_ds_bpermute(src_lane << 2, v); }
+__device__ __forceinline__ float shfl_f32(float v, int src_lane) {
+    return __int_as_float(__builtin_amdgcn_ds_bpermute(src_lane << 2, __float_as_int(v)));
+}
+
+// Value held by lane (l ^ 8): rotation by 8 inside each row of 16 lanes.
+__device__ __forceinline__ int swap_lane8(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x128, 0xf, 0xf, false); }
+
+// Sum of v over the lanes that differ from this one by a multiple of TPR (TPR = 2, 4, 8, 16):
+// after the call every lane holds the sum of its counterparts in all 64 / TPR teams.  Inside a
+// row of 16 lanes v += v rotated by 8, 4, ... TPR lanes (DPP row_ror); across rows a cross-lane
+// read of lane ^ 16 and lane ^ 32.  (v_permlane16_swap / v_permlane32_swap do the second part in
+// registers as well, and measured 6 % slower on the 16-lane teams of N >= 128.)
+template <int TPR>
+__device__ __forceinline__ float sum_over_teams(float v, int lane) {
+    if constexpr (TPR <= 8) v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xf, 0xf, false));
+    if constexpr (TPR <= 4) v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x124, 0xf, 0xf, false));
+    if constexpr (TPR <= 2) v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x122, 0xf, 0xf, false));
+    v += shfl_f32(v, lane ^ 16);
+    v += shfl_f32(v, lane ^ 32);
+    return v;
+}
+
+// Number of set bits of a 64-bit wave-uniform mask below this lane.
+__device__ __forceinline__ uint32_t bits_below_lane(uint64_t m) {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+}
+
+// Rows of C are written once and never read back by these kernels.  Stored the ordinary way
+// they pass through the XCD's L2 and displace the rows of B that the gathers reuse; the
+// streaming (nontemporal) form keeps them from doing so.  Partial sums for the combine pass:
+// the irregular kernel streams them too (measured faster), the tile kernel stores them the
+// ordinary way (measured faster for the combine pass that follows).  A streaming store and an
+// ordinary one must not sit on sibling paths that end alike (the compiler folds the two into one
+// store and drops the hint): the streaming path then ends in keep_streaming_hint().
+__device__ __forceinline__ void store_c_streaming(float* p, float4_t v) {
+    __builtin_nontemporal_store(v, reinterpret_cast<float4_t*>(p));
+}
+__device__ __forceinline__ void keep_streaming_hint() { asm volatile("" ::: "memory"); }
+
+// Where finished rows go.  OutPlain: the fp32 sums as they are.  OutFused: binary16 of
+// act(sum + bias), the form in which a GCN layer hands its features on (paper, Section 4.4);
+// bias (may be null) and activation are chosen at run time, uniformly for the launch.
+struct OutPlain {
+    static constexpr bool kFused = false;
+    float* C;
+};
+struct OutFused {
+    static constexpr bool kFused = true;
+    _Float16* C;
+    const float* bias;
+    int relu;
+};
+
+// act(v + bias[f .. f+3]) rounded to binary16 (to nearest even), as two packed words
+__device__ __forceinline__ uint2_t finish4(const OutFused& o, int f, float4_t v) {
+    if (o.bias) v += *reinterpret_cast<const float4_t*>(o.bias + f);
+    if (o.relu) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = fmaxf(v[i], 0.f);
+    }
+    const half4_t h = {(_Float16)v[0], (_Float16)v[1], (_Float16)v[2], (_Float16)v[3]};
+    return __builtin_bit_cast(uint2_t, h);
+}
+
+__device__ __forceinline__ void panel_store(const OutPlain& o, size_t row, int N, int f, float4_t v) {
+    store_c_streaming(o.C + row * N + f, v);
+}
+__device__ __forceinline__ void panel_store(const OutFused& o, size_t row, int N, int f, float4_t v) {
+    __builtin_nontemporal_store(finish4(o, f, v), reinterpret_cast<uint2_t*>(o.C + row * N + f));
+}
+
+}  // namespace rsh

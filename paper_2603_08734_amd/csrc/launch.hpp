@@ -19,9 +19,12 @@ struct DevicePlan {
     uint16_t* tile_val = nullptr;
     uint32_t* tile_item = nullptr;
     int32_t* panel_col0 = nullptr;
-    uint32_t* panel_off = nullptr;
+    uint32_t* panel_off = nullptr;     // only while the plan is uploaded
     uint32_t* panel_ent = nullptr;
-    uint32_t n_panel_ent = 0;   // words in panel_ent (tail padding included)
+    uint32_t* panel_quad0 = nullptr;   // panel entries in the form the kernel reads (panel.hpp)
+    uint32_t* panel_meta = nullptr;
+    uint32_t* panel_qoff = nullptr;
+    uint32_t* panel_val = nullptr;
     int32_t* irr_col = nullptr;
     uint16_t* irr_val = nullptr;
     uint32_t* irr_wave = nullptr;
@@ -44,6 +47,11 @@ struct DevicePlan {
 // `events` is not null it points at four hipEvent_t recorded before the tile kernel and
 // after each of the three kernels.
 int launch_spmm(const DevicePlan& d, const void* B_dev, void* C_dev, void* stream, void* const* events);
+
+// Plan upload, panel form: cell masks and dword counts of all units (then prefix-summed, total last), and with
+// room for their values made, the value stream.  Both read panel_off / panel_ent.
+int launch_panel_masks(const DevicePlan& d, int64_t n_windows, int64_t n_units, uint32_t* unit_dwords, void* stream);
+int launch_panel_values(const DevicePlan& d, int64_t n_windows, const uint32_t* unit_start, void* stream);
 
 // Bytes of the library-owned partial-sum array that every GPU holds for rsh_spmm_noalloc, and its
 // address on the current device (looked up on the first call per device; allocates nothing).

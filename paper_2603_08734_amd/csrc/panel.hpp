@@ -1,0 +1,506 @@
+// Tall windows: the kernel for windows of 128 or 256 rows, and the kernels that turn a plan's panel entries
+// into the form it reads.  Included by kernels.hip.
+//
+// Where many rows name the same columns (a pruned weight matrix: every window covers nearly all columns) the
+// dense-fragment path is bound by its own instructions, not by memory.
+//   * A window is 128 or 256 rows, one workgroup of four or eight waves, each wave owning a row group of 32
+//     rows and a feature panel of up to 128 on v_mfma_f32_32x32x16_f16.
+//   * A fragment's 32 B rows are staged in LDS once per workgroup, in one of four tiles (fragment s in tile
+//     s mod 4), requested five fragments ahead and staged two ahead, with one barrier per pair of fragments.
+//     Loads return in order, so the shortest lead of any of them is the lead of all: values, column ids and
+//     rows of B are all requested four or five fragments ahead.
+//   * Of the 32 x 16 operand of a K step a lane owns 8 cells (row = lane % 32, columns 8 * (lane / 32) .. + 7).
+//     Its stored values are consecutive, start at a 4-byte boundary and arrive with one 16-byte load per lane
+//     and unit: a load instruction takes 16 cycles of the vector memory path whatever its width as long as it
+//     is 4-byte aligned, 59 when it is only 2-byte aligned.  An 8-bit mask says which cells they go to:
+//     v_perm_b32 with selectors from a 16-entry table (one 4-cell half of the mask per look-up, an LDS read
+//     without bank conflicts) spreads them over the operand in registers.  Placing the entries by LDS scatter
+//     stores instead (zeroed tile, four exec-masked stores and a read back per unit: 24 LDS cycles where the
+//     look-ups take 8) measured, for a 28672 x 8192 weight at a density of 0.2, 81 us against 63 at 32
+//     features, 176 against 149 at 256 and 633 against 542 at 1024; at 128 features both take 94 us.
+//   * The operands of a K step are made one K step before its multiply-adds, the look-ups two before.
+//   * Sums are kept in two levels (every 1024 condensed columns the running sums are added to a second set and
+//     cleared), which bounds the fp32 accumulation chain whatever the item length, so windows are cut into
+//     few, long items and few partial sums cross HBM.
+// What bounds it: a fragment of a 256-row window at 128 features takes 1090 cycles of a compute unit, 512 of
+// them of the matrix units; 8 reads of B, 24 vector and 12 scalar instructions share the issue slots of two
+// waves per SIMD with them (a loop of the same multiply-adds, reads and vector instructions alone takes 710
+// cycles), at 2.0-2.2 GHz under that load.  One wave per SIMD with two row groups each (half the reads of B)
+// took 1690 cycles.
+// The product is formed transposed as in the fragment kernel: features along M (operand A, from the
+// staged B rows through the transposing read), window rows along N (operand B, the expanded piece
+// of the sparse matrix).
+//
+// v_mfma_f32_32x32x16_f16 operand layout (lane l, j = 0..7, v = 0..15):
+//   A[m = l%32][k = 8*(l/32)+j]   B[k = 8*(l/32)+j][n = l%32]   D[m = 8*(v/4) + 4*(l/32) + v%4][n = l%32]
+#pragma once
+#include <algorithm>
+
+#include "device.hpp"
+
+namespace rsh {
+
+namespace {
+
+// ---------------------------------------------------------------------------
+// Packing.  Input: PANEL_OFF / PANEL_ENT (include/rsh_spmm.h).  Output:
+//   meta  u32 [quad][lane][4]: fragments come in quads of a window's row group (the last quad of a group is
+//         filled up with zeros); word (lane, t % 4) holds, for K step h in bits 16h .. 16h+15, the lane's
+//         cell mask << 8 | start of its values in dwords from the start of the unit's values.  Quad (g, q)
+//         of window w is quad0[w] + g * ceil(nt / 4) + q.
+//   val   binary16: per unit, lane by lane, each lane's values padded to whole dwords.
+//   qoff  u32 per quad: start of the quad's first unit in val, in dwords (units of a row group follow each
+//         other, so a wave keeps the running sum).
+// A lane has at most 8 values = 4 dwords, a unit at most 256: the start fits 8 bits.
+// ---------------------------------------------------------------------------
+// Masks of one unit in LDS, from its entries (one wave).
+__device__ __forceinline__ void collect_masks(const uint32_t* ent, uint32_t b, uint32_t e, uint32_t* mask, int lane) {
+    mask[lane] = 0;
+    __builtin_amdgcn_wave_barrier();
+    for (uint32_t q = b + lane; q < e; q += 64) {
+        const uint32_t addr = ent[q] >> 16;
+        if (addr < 1024) atomicOr(&mask[addr >> 4], 1u << ((addr >> 1) & 7));
+    }
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+}
+
+// Inclusive sum over the lanes of a wave.
+__device__ __forceinline__ uint32_t wave_scan(uint32_t v, int lane) {
+#pragma unroll
+    for (int d = 1; d < 64; d *= 2) {
+        const uint32_t o = (uint32_t)shfl_i32((int)v, (lane - d) & 63);
+        if (lane >= d) v += o;
+    }
+    return v;
+}
+
+// grid: x = window, y = share of its units; one wave per unit.  Writes meta and the unit's dword count.
+__global__ __launch_bounds__(256) void rsh_panel_masks_kernel(const uint32_t* __restrict__ win_tile_off, const uint32_t* __restrict__ quad0,
+                                                              int groups, const uint32_t* __restrict__ unit_off, const uint32_t* __restrict__ ent,
+                                                              uint16_t* __restrict__ meta, uint32_t* __restrict__ unit_dwords) {
+    __shared__ uint32_t masks[4][64];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const uint32_t w = blockIdx.x, t0 = win_tile_off[w], nt = win_tile_off[w + 1] - t0, nq = (nt + 3) / 4;
+    const uint32_t units = 2u * (uint32_t)groups * nt, first = 2u * (uint32_t)groups * t0;
+    for (uint32_t i = blockIdx.y * 4 + wv; i < units; i += gridDim.y * 4) {
+        collect_masks(ent, unit_off[first + i], unit_off[first + i + 1], masks[wv], lane);
+        const uint32_t m = masks[wv][lane], dw = (__popc(m) + 1) / 2;
+        const uint32_t sum = wave_scan(dw, lane);
+        const uint32_t g = i / (2 * nt), r = i - g * 2 * nt, t = r >> 1, h = r & 1;
+        meta[(((size_t)(quad0[w] + g * nq + t / 4) * 64 + lane) * 4 + t % 4) * 2 + h] = (uint16_t)(m << 8 | (sum - dw));
+        if (lane == 63) unit_dwords[first + i] = sum;
+    }
+}
+
+// Exclusive prefix sum of n counts, in place; the total goes to counts[n].  One workgroup.
+__global__ __launch_bounds__(1024) void rsh_panel_scan_kernel(uint32_t* __restrict__ counts, uint32_t n) {
+    __shared__ uint32_t wave_sum[16];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const uint32_t per = (n + 1023) / 1024, b = min(n, per * tid), e = min(n, b + per);
+    uint32_t s = 0;
+    for (uint32_t i = b; i < e; ++i) s += counts[i];
+    const uint32_t in_wave = wave_scan(s, lane);
+    if (lane == 63) wave_sum[tid >> 6] = in_wave;
+    __syncthreads();
+    uint32_t at = in_wave - s;
+    for (int i = 0; i < (tid >> 6); ++i) at += wave_sum[i];
+    for (uint32_t i = b; i < e; ++i) {
+        const uint32_t c = counts[i];
+        counts[i] = at;
+        at += c;
+    }
+    if (tid == 1023) counts[n] = at;
+}
+
+__global__ __launch_bounds__(256) void rsh_panel_values_kernel(const uint32_t* __restrict__ win_tile_off, const uint32_t* __restrict__ quad0,
+                                                               int groups, const uint32_t* __restrict__ unit_off, const uint32_t* __restrict__ ent,
+                                                               const uint16_t* __restrict__ meta, const uint32_t* __restrict__ unit_start,
+                                                               uint32_t* __restrict__ qoff, uint16_t* __restrict__ val) {
+    __shared__ uint32_t lds[4][64];
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const uint32_t w = blockIdx.x, t0 = win_tile_off[w], nt = win_tile_off[w + 1] - t0, nq = (nt + 3) / 4;
+    const uint32_t units = 2u * (uint32_t)groups * nt, first = 2u * (uint32_t)groups * t0;
+    for (uint32_t i = blockIdx.y * 4 + wv; i < units; i += gridDim.y * 4) {
+        const uint32_t g = i / (2 * nt), r = i - g * 2 * nt, t = r >> 1, h = r & 1;
+        const uint32_t quad = quad0[w] + g * nq + t / 4;
+        lds[wv][lane] = meta[(((size_t)quad * 64 + lane) * 4 + t % 4) * 2 + h];
+        __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront", "local");
+        __builtin_amdgcn_wave_barrier();
+        if (lane == 0 && t % 4 == 0 && h == 0) qoff[quad] = unit_start[first + i];
+        uint16_t* out = val + 2 * (size_t)unit_start[first + i];
+        for (uint32_t q = unit_off[first + i] + lane; q < unit_off[first + i + 1]; q += 64) {
+            const uint32_t x = ent[q], addr = x >> 16;
+            if (addr >= 1024) continue;
+            const uint32_t m = lds[wv][addr >> 4], cell = (addr >> 1) & 7;
+            out[2 * (m & 0xffu) + __popc((m >> 8) & ((1u << cell) - 1u))] = (uint16_t)x;
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
+// ---------------------------------------------------------------------------
+// The product.  NG row groups of 32 rows per window, panels of 32 * NCH32 features.
+// ---------------------------------------------------------------------------
+template <int NCH32, int NG>
+struct PanelGeom {
+    static constexpr int P = 32 * NCH32;
+    static constexpr int WAVES = NG;
+    static constexpr int THREADS = 64 * WAVES;
+    static constexpr int TPR = P / 8;                         // 16-byte pieces per staged B row
+    static constexpr int LDB = P >= 64 ? P + 32 : 32;         // LDS row stride in halves: rows 16 banks apart (mod 64)
+    static constexpr int PIECES = kPanelK * TPR;
+    static constexpr int NLD = (PIECES + THREADS - 1) / THREADS;   // 1, or pieces of THREADS that fill the tile
+    static constexpr int IDLE = NLD * THREADS - PIECES;       // threads without a piece stage into spare space
+    static constexpr int TILE_HALVES = kPanelK * LDB + 8 * IDLE;
+    static constexpr int NBUF = 4;                            // staged B tiles (fragment s lives in tile s mod 4)
+    static constexpr int LUT_BYTES = 128;
+    static constexpr int LOOP_BYTES = LUT_BYTES + NBUF * TILE_HALVES * 2;
+    static constexpr int STAGE_STRIDE = 36;                   // floats per staged output row (32 + pad)
+    static constexpr int STAGE_BYTES = WAVES * 32 * STAGE_STRIDE * 4;
+    static constexpr int SMEM_BYTES = LOOP_BYTES > STAGE_BYTES ? LOOP_BYTES : STAGE_BYTES;
+};
+
+struct __attribute__((packed, aligned(4))) Dwords4 {
+    uint32_t d[4];
+};
+
+// Barrier that orders LDS traffic only: global loads stay in flight across it.
+__device__ __forceinline__ void block_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// The products of one item, fragments [t_begin, t_end) of window `win`, added to acc + acc2.  RUN: the window's
+// condensed columns are one run of columns that fills whole fragments, so its rows of B need no ids.
+template <int NCH32, int NG, bool RUN>
+__device__ __forceinline__ void panel_item(unsigned char* smem, uint32_t win, uint32_t t_begin, uint32_t t_end, uint32_t t0, uint32_t nt,
+                                            int32_t col0, const int32_t* __restrict__ tile_colid, const uint32_t* __restrict__ quad0,
+                                            const uint4_t* __restrict__ meta, const uint32_t* __restrict__ qoff,
+                                            const uint32_t* __restrict__ val, const __half* __restrict__ B, int N, int panel,
+                                            float16_t (&acc)[NCH32], float16_t (&acc2)[NCH32]) {
+    using Gm = PanelGeom<NCH32, NG>;
+    // fragments ahead at which rows of B are requested, and how much earlier their column ids; where a thread
+    // holds two pieces of each row (128-row windows at 128 features) more would spill registers
+    constexpr int LB = Gm::NLD > 1 ? 3 : 5, LC = Gm::NLD > 1 ? 2 : 4;
+    constexpr int TPR = Gm::TPR, LDB = Gm::LDB, NLD = Gm::NLD, KT = kPanelK, THREADS = Gm::THREADS;
+    _Float16* const lds_b = reinterpret_cast<_Float16*>(smem + Gm::LUT_BYTES);
+    const int lane = threadIdx.x & 63;
+    const uint32_t group = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // this wave's row group
+    // The item runs over whole quads of fragments; fragments of its first and last quad that belong to
+    // another item (or to none) have their masks cleared.  Fragment s is fragment f0 + s of the window.
+    const uint32_t lo = t_begin - t0, hi = t_end - t0, nq = (nt + 3) / 4;
+    const uint32_t q_first = lo / 4, quads = (hi + 3) / 4 - q_first, f0 = 4 * q_first;
+    const uint32_t last = nt - 1;
+    const int tix = threadIdx.x;
+    // thread tix stages 16-byte piece j * THREADS + tix of the KT x TPR pieces, i.e. the same piece of rows
+    // row0, row0 + THREADS / TPR, ...; threads without a piece (narrow panels) stage into spare space
+    constexpr int kRowStep = THREADS / TPR;
+    const uint32_t row_bytes = 2u * (uint32_t)N;
+    const int row0 = (tix / TPR) & (KT - 1), piece = tix % TPR;
+    const uint32_t ld_lds = tix < Gm::PIECES ? (uint32_t)(row0 * LDB + piece * 8) : (uint32_t)(KT * LDB + (tix - Gm::PIECES) * 8);
+    // a piece past the last feature (partial last panel) reads the panel's first piece; its products land in
+    // features that are never stored
+    const uint32_t ld_byte = (panel + 8 * piece < N ? 16u * (uint32_t)piece : 0u) + (RUN ? (uint32_t)row0 * row_bytes : 0u);
+    // RUN: the window's columns are one run, a fragment's rows of B follow each other
+    const char* Bbytes = reinterpret_cast<const char*>(B + panel) + (RUN ? (size_t)(uint32_t)col0 * row_bytes : 0);
+    const int g4 = lane >> 4, rr4 = (lane & 15) >> 2, ss4 = lane & 3;
+    const int tr_off = (8 * (g4 >> 1) + rr4) * LDB + 16 * (g4 & 1) + 4 * ss4;
+
+    const uint32_t my_quad = quad0[win] + group * nq + q_first;
+    const uint4_t* my_meta = meta + (size_t)my_quad * 64 + lane;
+    const uint32_t* vbase = val + qoff[my_quad];   // start of the values of the next unit to be requested (wave-uniform)
+
+    uint4_t m_cur, m_nxt, m_req;
+    Dwords4 vals[4][2];
+    uint4_t breg[4][NLD];
+    int cid_ring[RUN ? 1 : 4][NLD];
+    struct Operands {
+        half8_t b[NCH32];
+        half8_t a;
+    };
+    struct Selectors {
+        uint2_t lo, hi;
+    };
+    Operands op[2];
+    Selectors sel[2];
+
+    auto fetch_meta = [&](uint32_t q, uint4_t& m) {
+        m = my_meta[(size_t)min(q, quads - 1) * 64];
+    };
+    // Words of fragments outside the item: past its last quad there is nothing to place and nothing to skip;
+    // inside its first and last quad there are values to skip but none to place.
+    auto clip_quads = [&](uint32_t q, uint4_t& m) {
+        const uint32_t keep = q < quads ? ~0u : 0u;
+        m &= keep;
+    };
+    auto clip_fragments = [&](uint32_t q, uint4_t& m) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const uint32_t f = f0 + 4 * q + (uint32_t)i, keep = f >= lo && f < hi ? ~0u : 0u;
+            m[i] &= keep;
+        }
+    };
+    // Values of a fragment's units: one 16-byte load per lane and unit, at the lane's dword offset from the
+    // unit's start; the next unit starts behind the last lane's values.
+    auto issue_values = [&](const uint4_t& m, int i, Dwords4 (&v)[2]) {
+        const uint32_t w = m[i], w63 = (uint32_t)__builtin_amdgcn_readlane((int)w, 63);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const uint32_t off = (w >> (16 * h)) & 0xffu;
+            v[h] = *reinterpret_cast<const Dwords4*>(reinterpret_cast<const char*>(vbase) + 4u * off);
+            const uint32_t e = w63 >> (16 * h);
+            vbase += (e & 0xffu) + ((uint32_t)__builtin_popcount(e & 0xff00u) + 1u) / 2u;
+        }
+    };
+    auto fetch_colids = [&](uint32_t step, int (&cid)[NLD]) {
+        if constexpr (!RUN) {
+#pragma unroll
+            for (int j = 0; j < NLD; ++j) cid[j] = tile_colid[(size_t)(t0 + min(f0 + step, last)) * KT + row0 + j * kRowStep];
+        }
+    };
+    auto issue_b = [&](uint32_t step, const int (&cid)[NLD], uint4_t (&b)[NLD]) {
+        const char* from = RUN ? Bbytes + (size_t)min(f0 + step, last) * (KT * row_bytes) : Bbytes;
+#pragma unroll
+        for (int j = 0; j < NLD; ++j) b[j] = *reinterpret_cast<const uint4_t*>(RUN ? from + (size_t)j * kRowStep * row_bytes + ld_byte : from + ((uint32_t)cid[j] * row_bytes + ld_byte));
+    };
+    auto stage_b = [&](const uint4_t (&b)[NLD], int buf) {
+        _Float16* sb = lds_b + buf * Gm::TILE_HALVES;
+#pragma unroll
+        for (int j = 0; j < NLD; ++j) *reinterpret_cast<uint4_t*>(sb + ld_lds + j * kRowStep * LDB) = b[j];
+    };
+    auto read_b = [&](int buf, int h, Operands& x) {
+        const _Float16* sb = lds_b + buf * Gm::TILE_HALVES + tr_off + (16 * h) * LDB;
+#pragma unroll
+        for (int c = 0; c < NCH32; ++c) {
+            const half4_t l = __builtin_bit_cast(half4_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                (short4_t __attribute__((address_space(3)))*)(sb + 32 * c)));
+            const half4_t u = __builtin_bit_cast(half4_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
+                (short4_t __attribute__((address_space(3)))*)(sb + 4 * LDB + 32 * c)));
+            x.b[c] = (half8_t){l[0], l[1], l[2], l[3], u[0], u[1], u[2], u[3]};
+        }
+    };
+    auto look_up = [&](const uint4_t& m, int i, int h, Selectors& y) {
+        const uint32_t w = m[i];
+        y.lo = *reinterpret_cast<const uint2_t*>(smem + ((h ? w >> 21 : w >> 5) & 0x78u));
+        y.hi = *reinterpret_cast<const uint2_t*>(smem + ((h ? w >> 25 : w >> 9) & 0x78u));
+    };
+    // The lane's 8 cells of K step h: the values of cells 0-3 start at the first register, those of cells
+    // 4-7 behind them, i.e. at a half that depends on the lane: the registers are funnelled down by it.
+    auto expand = [&](const uint4_t& m, int i, int h, const Dwords4 (&v)[2], const Selectors& y, Operands& x) {
+        const uint32_t n = (uint32_t)__builtin_popcount(m[i] & (h ? 0x0f000000u : 0x0f00u));   // values of cells 0-3
+        const uint32_t* d = v[h].d;
+        const bool two = n >= 2, four = n >= 4;
+        uint32_t a0 = two ? d[1] : d[0], a1 = two ? d[2] : d[1];
+        const uint32_t a2 = two ? d[3] : d[2];
+        a0 = four ? d[2] : a0;
+        a1 = four ? d[3] : a1;
+        const uint32_t w0 = __builtin_amdgcn_alignbit(a1, a0, n << 4), w1 = __builtin_amdgcn_alignbit(a2, a1, n << 4);   // shift mod 32
+        const uint4_t r = {__builtin_amdgcn_perm(d[1], d[0], y.lo[0]), __builtin_amdgcn_perm(d[1], d[0], y.lo[1]),
+                           __builtin_amdgcn_perm(w1, w0, y.hi[0]), __builtin_amdgcn_perm(w1, w0, y.hi[1])};
+        x.a = __builtin_bit_cast(half8_t, r);
+    };
+    auto multiply = [&](const Operands& x) {
+#pragma unroll
+        for (int c = 0; c < NCH32; ++c)
+            acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_f16(x.b[c], x.a, acc[c], 0, 0, 0);
+    };
+
+    // ---- prologue: masks of quads 0-2, values of quad 0, B rows of fragments 0 .. LB-1 requested; fragments 0 and 1
+    //      staged; the operands of the first K step and the selectors of the second in registers ----
+    fetch_meta(0, m_cur);
+    fetch_meta(1, m_nxt);
+    fetch_meta(2, m_req);
+#pragma unroll
+    for (int d = 0; d < 4; ++d) fetch_colids((uint32_t)d, cid_ring[RUN ? 0 : d]);
+#pragma unroll
+    for (int d = 0; d < (LB < 4 ? LB : 4); ++d) issue_b((uint32_t)d, cid_ring[RUN ? 0 : d], breg[d]);
+#pragma unroll
+    for (int d = 0; d < 4; ++d) issue_values(m_cur, d, vals[d]);
+    clip_quads(1, m_nxt);
+    clip_fragments(0, m_cur);
+#pragma unroll
+    for (int d = 4; d < (LB + LC < 8 ? LB + LC : 8); ++d) fetch_colids((uint32_t)d, cid_ring[RUN ? 0 : d & 3]);
+    stage_b(breg[0], 0);
+    stage_b(breg[1], 1);
+    if constexpr (LB == 5) {
+        issue_b(4, cid_ring[0], breg[0]);
+        fetch_colids(8, cid_ring[0]);
+    }
+    block_barrier();
+    read_b(0, 0, op[0]);
+    look_up(m_cur, 0, 0, sel[0]);
+    expand(m_cur, 0, 0, vals[0], sel[0], op[0]);
+    look_up(m_cur, 0, 1, sel[1]);
+
+    // K step k of a quad (fragment u = k / 2 in B tile u, half h = k % 2): under its multiply-adds run the
+    // reads of B and the expansion for step k + 1 and the selector look-ups for step k + 2.  The two
+    // fragments of the next pair are staged in the first three steps of a pair; the barrier stands before
+    // its last step, whose operands have been read by then and under which the first tile of the next pair
+    // is read.  A tile is overwritten in the pair after the one that read it.
+    for (uint32_t q = 0; q < quads; ++q) {
+        const uint32_t s = 4 * q;
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int u = k / 2, h = k & 1, k1 = k + 1, k2 = k + 2;
+            if (k == 7) {   // the next quad's masks become current; the values of its fragments are on their way
+                m_cur = m_nxt;
+                clip_fragments(q + 1, m_cur);
+            }
+            read_b((k1 / 2) & 3, k1 & 1, op[k1 & 1]);
+            if (k == 6) {
+                uint4_t m2 = m_nxt;
+                clip_fragments(q + 1, m2);
+                look_up(m2, 0, 0, sel[k & 1]);
+            } else look_up(m_cur, (k2 / 2) & 3, k2 & 1, sel[k & 1]);
+            expand(m_cur, (k1 / 2) & 3, k1 & 1, vals[(k1 / 2) & 3], sel[k1 & 1], op[k1 & 1]);
+            if (h == 0) {   // the fragment's values are used up: request those of fragment s + u + 4, and a fragment of B
+                issue_b(s + u + LB, cid_ring[RUN ? 0 : (u + LB) & 3], breg[(u + LB) & 3]);
+                fetch_colids(s + u + LB + LC, cid_ring[RUN ? 0 : (u + LB + LC) & 3]);
+                issue_values(m_nxt, u, vals[u]);
+            }
+            if ((k & 3) == 1 || (k & 3) == 2) stage_b(breg[(2 * (k / 4) + 1 + (k & 3)) & 3], (2 * (k / 4) + 1 + (k & 3)) & 3);
+            multiply(op[h]);
+            if ((k & 3) == 2) block_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        m_nxt = m_req;
+        clip_quads(q + 2, m_nxt);
+        fetch_meta(q + 3, m_req);
+        if ((q & 7u) == 7u) {   // 32 fragments = 1024 condensed columns: second level
+#pragma unroll
+            for (int c = 0; c < NCH32; ++c) {
+                acc2[c] += acc[c];
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[c][v] = 0.f;
+            }
+        }
+    }
+}
+
+template <int NCH32, int NG, class OUT>
+__global__ __launch_bounds__(64 * NG) __attribute__((amdgpu_waves_per_eu(2, NCH32 == 4 ? 2 : 4))) void rsh_panel_kernel(
+    const uint4* __restrict__ items, XcdSplit xs, const int32_t* __restrict__ win_row,
+    const uint32_t* __restrict__ win_tile_off, const int32_t* __restrict__ win_col0,
+    const int32_t* __restrict__ tile_colid, const uint32_t* __restrict__ quad0, const uint4_t* __restrict__ meta,
+    const uint32_t* __restrict__ qoff, const uint32_t* __restrict__ val, const __half* __restrict__ B, const OUT out,
+    float* __restrict__ scratch, int N, int feature0) {
+    using Gm = PanelGeom<NCH32, NG>;
+    constexpr int P = Gm::P;
+    __shared__ __attribute__((aligned(16))) unsigned char smem[Gm::SMEM_BYTES];
+
+    const int lane = threadIdx.x & 63;
+    const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave = row group
+    uint32_t item;
+    {
+        const uint32_t x = blockIdx.x & 7u;
+        const uint32_t i = xs.start[x] + (blockIdx.x >> 3);
+        item = __builtin_amdgcn_readfirstlane(i);
+        if (i >= xs.start[x + 1]) return;   // uniform per block
+    }
+    const uint4 it = items[item];
+    const uint32_t win = __builtin_amdgcn_readfirstlane(it.x), t_begin = __builtin_amdgcn_readfirstlane(it.y);
+    const uint32_t t_end = __builtin_amdgcn_readfirstlane(it.z), dst = __builtin_amdgcn_readfirstlane(it.w);
+    const uint32_t t0 = win_tile_off[win], nt = win_tile_off[win + 1] - t0;
+    const int panel = feature0 + blockIdx.y * P;
+    const int row = win_row[(size_t)win * (32 * NG) + wv * 32 + (lane & 31)];
+
+    // Selector table: entry m (a 4-cell mask) holds for each cell which of the next four values it takes (bytes
+    // 2i, 2i + 1 of the pair of registers that holds them), or zero (selector 0x0c).
+    if (threadIdx.x < 64) {
+        const uint32_t m = threadIdx.x >> 2, c = threadIdx.x & 3;
+        const uint32_t i = (uint32_t)__builtin_popcount(m & ((1u << c) - 1u));
+        reinterpret_cast<uint16_t*>(smem)[threadIdx.x] = (uint16_t)((m >> c) & 1u ? 0x0100u + 0x0202u * i : 0x0c0cu);
+    }
+
+    float16_t acc[NCH32], acc2[NCH32];
+#pragma unroll
+    for (int c = 0; c < NCH32; ++c)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[c][v] = acc2[c][v] = 0.f;
+
+    if (t_begin < t_end) {
+        const int32_t col0 = win_col0[win];
+        if (col0 >= 0)
+            panel_item<NCH32, NG, true>(smem, win, t_begin, t_end, t0, nt, col0, tile_colid, quad0, meta, qoff, val, B, N, panel, acc, acc2);
+        else
+            panel_item<NCH32, NG, false>(smem, win, t_begin, t_end, t0, nt, col0, tile_colid, quad0, meta, qoff, val, B, N, panel, acc, acc2);
+    }
+
+    // ---- output: each group's 32 rows x 32 features take a turn through LDS and leave as whole lines ----
+    block_barrier();
+    float* const stage = reinterpret_cast<float*>(smem) + wv * (32 * Gm::STAGE_STRIDE);
+    const int n = lane & 31, hh = lane >> 5;
+#pragma unroll
+    for (int c = 0; c < NCH32; ++c) {
+        const float16_t sum = acc2[c] + acc[c];
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            *reinterpret_cast<float4_t*>(stage + n * Gm::STAGE_STRIDE + 8 * q + 4 * hh) =
+                (float4_t){sum[4 * q], sum[4 * q + 1], sum[4 * q + 2], sum[4 * q + 3]};
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+        __builtin_amdgcn_wave_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int id = i * 64 + lane, pr = id >> 3, fp = id & 7;
+            const float4_t v = *reinterpret_cast<const float4_t*>(stage + pr * Gm::STAGE_STRIDE + 4 * fp);
+            const int f = panel + 32 * c + 4 * fp;
+            const int prow = shfl_i32(row, pr);
+            if (f >= N) continue;
+            if (dst != kNoDst) {
+                *reinterpret_cast<float4_t*>(scratch + ((size_t)dst + wv * 32 + pr) * N + f) = v;   // partial sums: ordinary stores
+            } else if (prow >= 0) {
+                panel_store(out, (size_t)prow, N, f, v);
+                keep_streaming_hint();
+            }
+        }
+    }
+}
+
+template <int NCH32, int NG, class OUT>
+void launch_panel_t(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st, int feature0, int panels) {
+    uint32_t longest = 0;
+    for (int x = 0; x < 8; ++x) longest = std::max(longest, d.tile_split.start[x + 1] - d.tile_split.start[x]);
+    hipLaunchKernelGGL((rsh_panel_kernel<NCH32, NG, OUT>), dim3(8u * longest, (unsigned)panels), dim3(64 * NG), 0, st,
+                       (const uint4*)d.tile_item, d.tile_split, d.win_row, d.win_tile_off, d.panel_col0, d.tile_colid,
+                       d.panel_quad0, (const uint4_t*)d.panel_meta, d.panel_qoff, d.panel_val, (const __half*)B, out, d.scratch, d.geo.N,
+                       feature0);
+}
+template <int NCH32, class OUT>
+void launch_panel_g(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st, int feature0, int panels) {
+    if (d.geo.panel_groups == 8) launch_panel_t<NCH32, 8>(d, B, out, st, feature0, panels);
+    else launch_panel_t<NCH32, 4>(d, B, out, st, feature0, panels);
+}
+
+template <class OUT>
+int launch_panels(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st) {
+    const int full = d.geo.N / 128, rest = d.geo.N % 128;
+    if (full > 0) launch_panel_g<4>(d, B, out, st, 0, full);
+    if (rest > 64) launch_panel_g<4>(d, B, out, st, 128 * full, 1);
+    else if (rest > 32) launch_panel_g<2>(d, B, out, st, 128 * full, 1);
+    else if (rest > 0) launch_panel_g<1>(d, B, out, st, 128 * full, 1);
+    return RSH_OK;
+}
+
+}  // namespace
+
+int launch_panel_masks(const DevicePlan& d, int64_t n_windows, int64_t n_units, uint32_t* unit_dwords, void* stream) {
+    hipStream_t st = (hipStream_t)stream;
+    const dim3 grid((unsigned)n_windows, (unsigned)std::max<int64_t>(1, std::min<int64_t>(64, 8192 / n_windows)));
+    hipLaunchKernelGGL(rsh_panel_masks_kernel, grid, dim3(256), 0, st, d.win_tile_off, d.panel_quad0, d.geo.panel_groups, d.panel_off, d.panel_ent,
+                       (uint16_t*)d.panel_meta, unit_dwords);
+    hipLaunchKernelGGL(rsh_panel_scan_kernel, dim3(1), dim3(1024), 0, st, unit_dwords, (uint32_t)n_units);
+    return hipGetLastError() == hipSuccess ? RSH_OK : RSH_ERR_HIP;
+}
+
+int launch_panel_values(const DevicePlan& d, int64_t n_windows, const uint32_t* unit_start, void* stream) {
+    const dim3 grid((unsigned)n_windows, (unsigned)std::max<int64_t>(1, std::min<int64_t>(64, 8192 / n_windows)));
+    hipLaunchKernelGGL(rsh_panel_values_kernel, grid, dim3(256), 0, (hipStream_t)stream, d.win_tile_off, d.panel_quad0, d.geo.panel_groups, d.panel_off,
+                       d.panel_ent, (const uint16_t*)d.panel_meta, unit_start, d.panel_qoff, (uint16_t*)d.panel_val);
+    return hipGetLastError() == hipSuccess ? RSH_OK : RSH_ERR_HIP;
+}
+
+}  // namespace rsh

@@ -35,7 +35,6 @@ struct Geometry {
     int cpl = 4;        // cells per MFMA lane = bitmap words per sub-fragment = tile_k / 4
     int panel = 0;      // 1 = tall windows in the panel form (win_rows == 128 or 256, tile_k == 32)
     int panel_groups = 0; // panel form: row groups of 32 rows per window = win_rows / 32
-    int panel_rounds = 0; // panel form: 16-byte loads per lane that cover the largest unit (256 entries each): 1 or 2
 };
 Geometry make_geometry(int N, int window_rows, int tile_k);
 

@@ -487,14 +487,11 @@ static std::vector<int64_t> schedule_windows(const rsh_csr_t& a, const HostPlan&
 // sorted distinct columns are cut into fragments of 32 (two MFMA K steps of 16).  The stored entries
 // of row group g, fragment t, K step h form one unit -- the 32 x 16 operand of one
 // v_mfma_f32_32x32x16_f16 -- and each entry carries the byte address of its cell in that operand as
-// the instruction wants it in registers (lane = row + 32 * (k / 8), element k % 8, 16 bytes per lane):
-// the kernel scatters a unit's entries into a zeroed 1 KB tile and reads the operand back with one
-// 16-byte read per lane, so the work per unit grows with its entries, not with its 512 cells (the
-// bitmap form expands cell by cell).  A unit is padded to a multiple of four entries (one 16-byte
-// load per lane fetches four); padding entries carry an address past the tile (>= 1024) that the
-// kernel's scatter sends to a spare word.  Units are stored row group by row group, so that the
-// stream a wave reads is contiguous: unit (g, t, h) of window w is 8 * first_fragment(w) +
-// (g * fragments(w) + (t - first_fragment(w))) * 2 + h.
+// the instruction wants it in registers (lane = row + 32 * (k / 8), element k % 8, 16 bytes per lane).
+// A unit is padded to a multiple of four entries; padding entries carry an address past the operand
+// (>= 1024).  Units are stored row group by row group: unit (g, t, h) of window w is
+// 2 * groups * first_fragment(w) + (g * fragments(w) + (t - first_fragment(w))) * 2 + h.  Uploading turns the
+// entries into cell masks and bare values, a lane's values next to each other (panel.hpp).
 // ---------------------------------------------------------------------------
 static inline uint32_t panel_unit_of(uint32_t row, uint32_t u, uint32_t nt) {
     return ((row / 32) * nt + u / kPanelK) * 2 + (u % kPanelK) / 16;
@@ -599,7 +596,6 @@ static int pack_panel_windows(const rsh_csr_t& a, const Partition& part, HostPla
     plan.tile_val_off.clear();
     plan.tile_val.clear();
     // pass 2: fill
-    std::vector<uint32_t> win_max_unit((size_t)n_win, 0);
     parallel_dynamic(n_win, threads, 1, [&](int64_t b, int64_t e, int) {
         WindowColumns wc;
         std::vector<uint32_t> start, fill, half;
@@ -627,13 +623,10 @@ static int pack_panel_windows(const rsh_csr_t& a, const Partition& part, HostPla
                 }
             }
             start.assign(nu + 1, 0);
-            uint32_t most = 0;
             for (size_t q = 0; q < nu; ++q) {   // start[q] = padded entries of units before q
                 const uint32_t padded = (half[2 * q] + half[2 * q + 1] + 3u) & ~3u;
-                most = std::max(most, padded);
                 start[q + 1] = start[q] + padded;
             }
-            win_max_unit[(size_t)w] = most;
             const size_t ub = (size_t)t0 * 2 * G;
             for (size_t q = 0; q < nu; ++q) plan.panel_off[ub + q] = (uint32_t)(win_ent_off[w] + start[q]);
             uint32_t* out = &plan.panel_ent[(size_t)win_ent_off[w]];
@@ -659,10 +652,28 @@ static int pack_panel_windows(const rsh_csr_t& a, const Partition& part, HostPla
         }
     });
     plan.panel_off[n_units] = (uint32_t)win_ent_off[n_win];
-    uint32_t most = 0;
-    for (uint32_t m : win_max_unit) most = std::max(most, m);
-    plan.geo.panel_rounds = most <= 256 ? 1 : 2;   // 16-byte loads per lane that cover the largest unit
     return RSH_OK;
+}
+
+// Parts that tall windows are cut into.  The kernel's workgroups (window parts x feature panels of 128) run one
+// per compute unit, in rounds of 256, and a round takes as long as its longest item: the item's fragments plus
+// what its start and end cost (about 10 us, as much as 20 fragments).  Cut windows leave partial sums: a combine
+// launch (another 10 fragments' time) and 8 bytes a part, row and feature through memory (at 5 TB/s, 0.5 us a
+// fragment).  The cheapest number of parts by this count is taken; parts are not cut below 16 fragments.
+// Measured for 112 windows of 256 fragments: N = 128 one part 133 us, two 99, four 108; N = 256 164, 189, 221;
+// N = 1024 556, 634, 735 us.
+static int64_t choose_panel_parts(int64_t n_win, int64_t n_tiles, const Geometry& geo) {
+    if (n_win == 0 || n_tiles == 0) return 1;
+    const int64_t panels = (geo.N + 127) / 128, nt = (n_tiles + n_win - 1) / n_win;
+    int64_t best = 1;
+    double best_cost = 0.0;
+    for (int64_t parts = 1; parts == 1 || nt >= 16 * parts; ++parts) {
+        const double rounds = (double)((n_win * parts * panels + 255) / 256);
+        double cost = rounds * (20.0 + (double)((nt + parts - 1) / parts));
+        if (parts > 1) cost += 10.0 + (double)(n_win * geo.win_rows * parts) * geo.N * 8.0 / 2.5e6;
+        if (parts == 1 || cost < best_cost) best = parts, best_cost = cost;
+    }
+    return best;
 }
 
 int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int threads) {
@@ -802,14 +813,10 @@ int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int thr
 
     // ---- tile work items (bounded fragments per item, Section 3.3.3) --------------------
     int64_t t_max = plan.opts.max_tiles_per_item;
+    int64_t panel_parts = 1;   // parts a tall window is cut into when the caller leaves it open
     if (t_max <= 0 && geo.panel) {
-        // Tall windows: a workgroup sums an item's fragments in two levels (every 1024 condensed
-        // columns the running sums are added to a second set), so an item may be long; windows are
-        // only cut to hand every compute unit the workgroups it can hold (two of 128 rows, one of
-        // 256), never below 1024 columns; the cap keeps the second level's chain at a few hundred
-        // additions (an item is at most 1.5 times this long).
-        const int64_t target_items = geo.win_rows >= 256 ? 256 : 512;
-        t_max = std::min<int64_t>(8192, std::max<int64_t>(1024 / kPanelK, (n_tiles + target_items - 1) / target_items));
+        panel_parts = choose_panel_parts(n_win, n_tiles, geo);
+        t_max = n_tiles;
     } else if (t_max <= 0) {
         int64_t per = (n_tiles + 4095) / 4096, p2 = 1;
         while (p2 < per) p2 <<= 1;
@@ -825,11 +832,12 @@ int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int thr
     for (int64_t wi = 0; wi < n_win; ++wi) {
         const int64_t w = worder[(size_t)wi];
         const uint32_t t0 = plan.win_tile_off[w], nt = plan.win_tile_off[w + 1] - t0;
-        // the panel form cuts a window into the nearest whole number of parts (items of about t_max
-        // fragments), the bitmap form into the fewest parts of at most t_max fragments
-        const uint32_t parts = geo.panel && plan.opts.max_tiles_per_item <= 0
-                                   ? (uint32_t)std::max<int64_t>(1, (2 * (int64_t)nt + t_max) / (2 * t_max))
-                                   : (uint32_t)std::max<int64_t>(1, (nt + t_max - 1) / t_max);
+        // the panel form cuts a window between quads of fragments (the kernel runs over whole quads), into parts
+        // of at most 8192 fragments whatever was chosen; the bitmap form into the fewest parts of at most t_max
+        const bool quads = geo.panel && plan.opts.max_tiles_per_item <= 0;
+        const uint32_t nq = (nt + 3) / 4;
+        const uint32_t parts = quads ? (uint32_t)std::max<int64_t>(1, std::min<int64_t>(nq, std::max<int64_t>(panel_parts, (nt + 8191) / 8192)))
+                                     : (uint32_t)std::max<int64_t>(1, (nt + t_max - 1) / t_max);
         if (element_level && !win_spill[(size_t)w].empty()) {
             // Rows of this window receive a second contribution from the residual path: the window's
             // parts go to scratch, one more slot per row takes the row's spilled entries, and the
@@ -858,8 +866,8 @@ int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int thr
         }
         ++n_split_windows;
         for (uint32_t p = 0; p < parts; ++p) {
-            const uint32_t b = t0 + (uint32_t)((uint64_t)nt * p / parts);
-            const uint32_t e = t0 + (uint32_t)((uint64_t)nt * (p + 1) / parts);
+            const uint32_t b = t0 + (quads ? std::min(nt, 4 * (uint32_t)((uint64_t)nq * p / parts)) : (uint32_t)((uint64_t)nt * p / parts));
+            const uint32_t e = t0 + (quads ? std::min(nt, 4 * (uint32_t)((uint64_t)nq * (p + 1) / parts)) : (uint32_t)((uint64_t)nt * (p + 1) / parts));
             plan.tile_item.insert(plan.tile_item.end(), {(uint32_t)w, b, e, (uint32_t)(slots + (int64_t)p * W)});
         }
         for (int r = 0; r < W; ++r) {
