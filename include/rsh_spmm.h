@@ -168,14 +168,15 @@ int rsh_plan_opts_default(rsh_plan_opts_t *opts);
  * HIP device.  opts == NULL means defaults.
  * Limits: nnz and n_rows must be below 2^31, n_cols * (2 NR) below 2^32 (NR = the run width,
  * below); otherwise RSH_ERR_TOO_LARGE.
- * Feature width: the kernels work at multiples of 16, in feature panels of up to 128 columns
- * (irregular kernel; a last partial panel idles lanes) and 256, 128, ... 16 columns (tile kernel;
- * widest first), one pass over the matrix per panel.  When N is not a multiple of 16 (or
- * opts->run_width asks for it) the kernels run at a width NR > N: the plan then owns a binary16
- * buffer [n_cols][NR] and an fp32 buffer [n_rows][NR] on the device, every product first copies
- * B into the wide buffer (pad columns zero) and last copies the N columns of the result into C,
- * and B, C and bias then only need the alignment of their element type.  Results are those of
- * the padded product, column for
+ * Feature width: the kernels take rows of any even number of features from 16 on, in feature panels of
+ * up to 128 columns (irregular kernel; a last partial panel idles lanes; tall windows) and 256, 128, ... 16
+ * columns (tile kernel; the last panel ends with the row), one pass over the matrix per panel.  B, C and
+ * bias then need 16-byte alignment where N is a multiple of 16, else 4-byte alignment.  For other widths
+ * (odd ones, those below 16, a run_width the caller chose, operands with less alignment) the kernels run at
+ * a width NR > N: whenever N is not a multiple of 16 (or opts->run_width asks for it) the plan owns a
+ * binary16 buffer [n_cols][NR] and an fp32 buffer [n_rows][NR] on the device, and such a product first
+ * copies B into the wide buffer (pad columns zero) and last copies the N columns of the result into C;
+ * B, C and bias then only need the alignment of their element type.  Results are the same, column for
  * column; the cost is one more pass over B and C.
  */
 int rsh_plan_create(const rsh_csr_t *csr, int32_t N, const rsh_plan_opts_t *opts, rsh_plan_t **out);

@@ -393,12 +393,16 @@ int rsh_plan_create(const rsh_csr_t* csr, int32_t N, const rsh_plan_opts_t* opts
 
 namespace {
 
-// Common checks of the three launch entry points; *padded tells whether the operands pass through
-// the plan's buffers of the padded width (then only element alignment is needed).
-int check_launch(const rsh_plan_t* plan, const void* B, const void* C, const void* bias, int c_elem, bool* padded) {
+// Common checks of the launch entry points; *padded tells whether the operands pass through the plan's buffers
+// of the run width (then only element alignment is needed), *width the features of their rows otherwise.  The
+// kernels take rows of any even number of features from 16 on at 4-byte aligned addresses; what is left for the
+// copies is odd widths, widths below 16, a run width the caller chose and operands aligned to less.
+int check_launch(const rsh_plan_t* plan, const void* B, const void* C, const void* bias, int c_elem, bool* padded, int* width) {
     if (!plan) return RSH_ERR_NULL;
     if (!plan->uploaded) return RSH_ERR_NOT_UPLOADED;
-    *padded = plan->dev.n_user != plan->dev.geo.N;
+    const int n = plan->dev.n_user;
+    *padded = n != plan->dev.geo.N;
+    *width = plan->dev.geo.N;
     // the plan's arrays live on the device that was current when it was created
     int device = -1;
     if (!hip_ok(hipGetDevice(&device))) return RSH_ERR_HIP;
@@ -408,6 +412,10 @@ int check_launch(const rsh_plan_t* plan, const void* B, const void* C, const voi
     if (!C || (!B && (plan->host.nnz > 0 || (*padded && plan->host.n_cols > 0)))) return RSH_ERR_NULL;
     const uintptr_t mb = *padded ? 1u : 15u, mc = *padded ? (uintptr_t)c_elem - 1u : 15u, mbias = *padded ? 3u : 15u;
     if (((uintptr_t)B & mb) || ((uintptr_t)C & mc) || ((uintptr_t)bias & mbias)) return RSH_ERR_BAD_OPTION;
+    if (*padded && n >= 16 && n % 2 == 0 && plan->dev.geo.N == auto_run_width(n) && !(((uintptr_t)B | (uintptr_t)C) & 3u)) {
+        *padded = false;
+        *width = n;
+    }
     return RSH_OK;
 }
 
@@ -422,14 +430,15 @@ int widen_operands(const rsh::DevicePlan& d, int64_t n_cols, const void* B, cons
 
 int rsh_spmm(const rsh_plan_t* plan, const void* B_dev, void* C_dev, void* hip_stream) {
     bool padded = false;
-    int rc = check_launch(plan, B_dev, C_dev, nullptr, 4, &padded);
+    int width = 0;
+    int rc = check_launch(plan, B_dev, C_dev, nullptr, 4, &padded, &width);
     if (rc != RSH_OK || plan->host.n_rows == 0) return rc;
     const rsh::DevicePlan& d = plan->dev;
     if (!padded) {
-        rc = rsh::launch_spmm(d, B_dev, C_dev, hip_stream, nullptr);
+        rc = rsh::launch_spmm(d, B_dev, C_dev, width, width, hip_stream, nullptr);
     } else {
         rc = widen_operands(d, plan->host.n_cols, B_dev, nullptr, hip_stream);
-        if (rc == RSH_OK) rc = rsh::launch_spmm(d, d.b_pad, d.c_pad, hip_stream, nullptr);
+        if (rc == RSH_OK) rc = rsh::launch_spmm(d, d.b_pad, d.c_pad, width, width, hip_stream, nullptr);
         if (rc == RSH_OK) rc = rsh::launch_narrow_rows(d.c_pad, C_dev, plan->host.n_rows, d.n_user, d.geo.N, 4, hip_stream);
     }
     if (rc == RSH_ERR_HIP) g_hip_error = "kernel launch failed";
@@ -438,7 +447,8 @@ int rsh_spmm(const rsh_plan_t* plan, const void* B_dev, void* C_dev, void* hip_s
 
 int rsh_spmm_noalloc(const rsh_plan_t* plan, const void* B_dev, void* C_dev, void* hip_stream) {
     bool padded = false;
-    int rc = check_launch(plan, B_dev, C_dev, nullptr, 4, &padded);
+    int width = 0;
+    int rc = check_launch(plan, B_dev, C_dev, nullptr, 4, &padded, &width);
     if (rc != RSH_OK || plan->host.n_rows == 0) return rc;
     const size_t need = (size_t)plan->host.n_scratch_slots * (size_t)plan->host.geo.N * sizeof(float);
     if (need > rsh::kStaticScratchBytes) {
@@ -453,10 +463,10 @@ int rsh_spmm_noalloc(const rsh_plan_t* plan, const void* B_dev, void* C_dev, voi
         return rc;
     }
     if (!padded) {
-        rc = rsh::launch_spmm(d, B_dev, C_dev, hip_stream, nullptr);
+        rc = rsh::launch_spmm(d, B_dev, C_dev, width, width, hip_stream, nullptr);
     } else {
         rc = widen_operands(d, plan->host.n_cols, B_dev, nullptr, hip_stream);
-        if (rc == RSH_OK) rc = rsh::launch_spmm(d, d.b_pad, d.c_pad, hip_stream, nullptr);
+        if (rc == RSH_OK) rc = rsh::launch_spmm(d, d.b_pad, d.c_pad, width, width, hip_stream, nullptr);
         if (rc == RSH_OK) rc = rsh::launch_narrow_rows(d.c_pad, C_dev, plan->host.n_rows, d.n_user, d.geo.N, 4, hip_stream);
     }
     if (rc == RSH_ERR_HIP) g_hip_error = "kernel launch failed";
@@ -467,14 +477,15 @@ int rsh_spmm_f16(const rsh_plan_t* plan, const void* B_dev, void* C16_dev, const
                  void* hip_stream) {
     if (relu != 0 && relu != 1) return plan ? RSH_ERR_BAD_OPTION : RSH_ERR_NULL;
     bool padded = false;
-    int rc = check_launch(plan, B_dev, C16_dev, bias_dev, 2, &padded);
+    int width = 0;
+    int rc = check_launch(plan, B_dev, C16_dev, bias_dev, 2, &padded, &width);
     if (rc != RSH_OK || plan->host.n_rows == 0) return rc;
     const rsh::DevicePlan& d = plan->dev;
     if (!padded) {
-        rc = rsh::launch_spmm_f16(d, B_dev, C16_dev, bias_dev, relu, hip_stream, nullptr);
+        rc = rsh::launch_spmm_f16(d, B_dev, C16_dev, bias_dev, relu, width, width, hip_stream, nullptr);
     } else {
         rc = widen_operands(d, plan->host.n_cols, B_dev, bias_dev, hip_stream);
-        if (rc == RSH_OK) rc = rsh::launch_spmm_f16(d, d.b_pad, d.c_pad, bias_dev ? d.bias_pad : nullptr, relu, hip_stream, nullptr);
+        if (rc == RSH_OK) rc = rsh::launch_spmm_f16(d, d.b_pad, d.c_pad, bias_dev ? d.bias_pad : nullptr, relu, width, width, hip_stream, nullptr);
         if (rc == RSH_OK) rc = rsh::launch_narrow_rows(d.c_pad, C16_dev, plan->host.n_rows, d.n_user, d.geo.N, 2, hip_stream);
     }
     if (rc == RSH_ERR_HIP) g_hip_error = "kernel launch failed";
@@ -485,7 +496,8 @@ int rsh_spmm_profile(const rsh_plan_t* plan, const void* B_dev, void* C_dev, voi
     if (!out) return RSH_ERR_NULL;
     out->ms_tile = out->ms_irregular = out->ms_combine = 0.f;
     bool padded = false;
-    int rc = check_launch(plan, B_dev, C_dev, nullptr, 4, &padded);
+    int width = 0;
+    int rc = check_launch(plan, B_dev, C_dev, nullptr, 4, &padded, &width);
     if (rc != RSH_OK || plan->host.n_rows == 0) return rc;
     const rsh::DevicePlan& d = plan->dev;
     hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};
@@ -494,10 +506,10 @@ int rsh_spmm_profile(const rsh_plan_t* plan, const void* B_dev, void* C_dev, voi
     if (rc == RSH_OK) {
         void* evp[4] = {ev[0], ev[1], ev[2], ev[3]};
         if (!padded) {
-            rc = rsh::launch_spmm(d, B_dev, C_dev, hip_stream, evp);
+            rc = rsh::launch_spmm(d, B_dev, C_dev, width, width, hip_stream, evp);
         } else {   // the copies to and from the padded width lie outside the three timed kernels
             rc = widen_operands(d, plan->host.n_cols, B_dev, nullptr, hip_stream);
-            if (rc == RSH_OK) rc = rsh::launch_spmm(d, d.b_pad, d.c_pad, hip_stream, evp);
+            if (rc == RSH_OK) rc = rsh::launch_spmm(d, d.b_pad, d.c_pad, width, width, hip_stream, evp);
             if (rc == RSH_OK) rc = rsh::launch_narrow_rows(d.c_pad, C_dev, plan->host.n_rows, d.n_user, d.geo.N, 4, hip_stream);
         }
         if (!hip_ok(hipStreamSynchronize((hipStream_t)hip_stream))) rc = RSH_ERR_HIP;

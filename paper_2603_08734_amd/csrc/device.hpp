@@ -15,6 +15,13 @@ typedef float float16_t __attribute__((ext_vector_type(16)));
 typedef short short4_t __attribute__((ext_vector_type(4)));
 typedef unsigned int uint4_t __attribute__((ext_vector_type(4)));
 typedef unsigned int uint2_t __attribute__((ext_vector_type(2)));
+typedef float float2_t __attribute__((ext_vector_type(2)));
+// The same vectors where only 4-byte alignment is known: rows of B and C whose length is even but not a multiple
+// of 8 or 4 elements.  gfx950 takes one 16-byte access at any 4-byte boundary at the rate of an aligned one.
+typedef unsigned int uint4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef unsigned int uint2_a4 __attribute__((ext_vector_type(2), aligned(4)));
+typedef float float4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef float float2_a4 __attribute__((ext_vector_type(2), aligned(4)));
 
 constexpr int kWavesPerBlock = 4;
 
@@ -65,7 +72,7 @@ __device__ __forceinline__ uint32_t bits_below_lane(uint64_t m) {
 // ordinary one must not sit on sibling paths that end alike (the compiler folds the two into one
 // store and drops the hint): the streaming path then ends in keep_streaming_hint().
 __device__ __forceinline__ void store_c_streaming(float* p, float4_t v) {
-    __builtin_nontemporal_store(v, reinterpret_cast<float4_t*>(p));
+    __builtin_nontemporal_store(v, reinterpret_cast<float4_a4*>(p));
 }
 __device__ __forceinline__ void keep_streaming_hint() { asm volatile("" ::: "memory"); }
 
@@ -85,7 +92,7 @@ struct OutFused {
 
 // act(v + bias[f .. f+3]) rounded to binary16 (to nearest even), as two packed words
 __device__ __forceinline__ uint2_t finish4(const OutFused& o, int f, float4_t v) {
-    if (o.bias) v += *reinterpret_cast<const float4_t*>(o.bias + f);
+    if (o.bias) v += *reinterpret_cast<const float4_a4*>(o.bias + f);
     if (o.relu) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) v[i] = fmaxf(v[i], 0.f);
@@ -94,11 +101,24 @@ __device__ __forceinline__ uint2_t finish4(const OutFused& o, int f, float4_t v)
     return __builtin_bit_cast(uint2_t, h);
 }
 
-__device__ __forceinline__ void panel_store(const OutPlain& o, size_t row, int N, int f, float4_t v) {
-    store_c_streaming(o.C + row * N + f, v);
+// Four features of a row of C of `nv` features (even), or its last two.
+__device__ __forceinline__ void panel_store(const OutPlain& o, size_t row, int nv, int f, float4_t v) {
+    float* p = o.C + row * nv + f;
+    if (f + 4 <= nv) store_c_streaming(p, v);
+    else __builtin_nontemporal_store((float2_t){v[0], v[1]}, reinterpret_cast<float2_a4*>(p));
 }
-__device__ __forceinline__ void panel_store(const OutFused& o, size_t row, int N, int f, float4_t v) {
-    __builtin_nontemporal_store(finish4(o, f, v), reinterpret_cast<uint2_t*>(o.C + row * N + f));
+__device__ __forceinline__ void panel_store(const OutFused& o, size_t row, int nv, int f, float4_t v) {
+    _Float16* p = o.C + row * nv + f;
+    if (f + 4 <= nv) {
+        __builtin_nontemporal_store(finish4(o, f, v), reinterpret_cast<uint2_a4*>(p));
+    } else {
+        float2_t t = {v[0], v[1]};
+        if (o.bias) t += *reinterpret_cast<const float2_a4*>(o.bias + f);
+        if (o.relu) t = (float2_t){fmaxf(t[0], 0.f), fmaxf(t[1], 0.f)};
+        typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+        const half2_t h = {(_Float16)t[0], (_Float16)t[1]};
+        __builtin_nontemporal_store(__builtin_bit_cast(uint32_t, h), reinterpret_cast<uint32_t*>(p));
+    }
 }
 
 }  // namespace rsh

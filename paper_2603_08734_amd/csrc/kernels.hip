@@ -26,44 +26,48 @@ namespace rsh {
 // stores of consecutive 16-byte pieces (lane t writes pieces t and TPR + t), i.e. whole lines, after
 // a turn through the team's LDS stage; lane-owned pieces would make every store a half-written
 // 32-byte sector, which the streaming path handles at a third of the rate.
-// Which of a lane's two 16-byte pieces of an fp32 panel row exist: all of them except in the last
-// panel of a width that is not a multiple of the panel, where pieces past the last feature are
-// not stored.
-struct PanelPieces {
-    bool first, second;   // pieces tl and TPR + tl
-};
+// A partial panel (PARTIAL: the last one of a width that is not a multiple of the panel) has `live` features, an
+// even number from 8 on.  Its last lane takes the eight features that end with the row, so that no lane reads
+// past the row; lanes behind it repeat that piece, and pieces past the last feature are not stored.
 template <int TPR, bool PARTIAL>
-__device__ __forceinline__ PanelPieces panel_pieces(int N, int panel, int tl) {
-    if constexpr (!PARTIAL) return {true, true};
-    const int live = min(8 * TPR, N - panel);   // features of this panel, a multiple of 16
-    return {4 * tl < live, 4 * TPR + 4 * tl < live};
+__device__ __forceinline__ int lane_features(int live, int tl) { return PARTIAL ? min(8 * tl, live - 8) : 8 * tl; }
+template <bool PARTIAL>
+__device__ __forceinline__ void store_piece(float* out_row, int live, int f, float4_t v) {
+    if (!PARTIAL || f + 4 <= live) store_c_streaming(out_row + f, v);
+    else if (f < live) __builtin_nontemporal_store((float2_t){v[0], v[1]}, reinterpret_cast<float2_a4*>(out_row + f));
 }
-template <int TPR>
-__device__ __forceinline__ void store_row_streaming(float* out_row, const float (&acc)[8], float* stage, int tl, PanelPieces keep) {
-    *reinterpret_cast<float4_t*>(stage + 8 * tl) = (float4_t){acc[0], acc[1], acc[2], acc[3]};
-    *reinterpret_cast<float4_t*>(stage + 8 * tl + 4) = (float4_t){acc[4], acc[5], acc[6], acc[7]};
+template <int TPR, bool PARTIAL>
+__device__ __forceinline__ void store_row_streaming(float* out_row, const float (&acc)[8], float* stage, int tl, int live) {
+    if constexpr (PARTIAL) {
+        float2_t* to = reinterpret_cast<float2_t*>(stage + lane_features<TPR, true>(live, tl));
+#pragma unroll
+        for (int i = 0; i < 4; ++i) to[i] = (float2_t){acc[2 * i], acc[2 * i + 1]};
+    } else {
+        *reinterpret_cast<float4_t*>(stage + 8 * tl) = (float4_t){acc[0], acc[1], acc[2], acc[3]};
+        *reinterpret_cast<float4_t*>(stage + 8 * tl + 4) = (float4_t){acc[4], acc[5], acc[6], acc[7]};
+    }
     const float4_t v0 = *reinterpret_cast<const float4_t*>(stage + 4 * tl);
     const float4_t v1 = *reinterpret_cast<const float4_t*>(stage + 4 * TPR + 4 * tl);
-    if (keep.first) store_c_streaming(out_row + 4 * tl, v0);
-    if (keep.second) store_c_streaming(out_row + 4 * TPR + 4 * tl, v1);
+    store_piece<PARTIAL>(out_row, live, 4 * tl, v0);
+    store_piece<PARTIAL>(out_row, live, 4 * TPR + 4 * tl, v1);
 }
 
-// A team's finished row `row` of C, panel starting at feature `panel`.  In binary16 a lane's
+// A team's finished row `row` of C (nv features), panel starting at feature `panel`.  In binary16 a lane's
 // eight features are one 16-byte piece and the team's pieces are consecutive, so the row
 // leaves as one store of whole lines without a turn through LDS.
 template <int TPR, bool PARTIAL>
-__device__ __forceinline__ void emit_row(const OutPlain& o, size_t row, int N, int panel, const float (&acc)[8],
+__device__ __forceinline__ void emit_row(const OutPlain& o, size_t row, int nv, int panel, const float (&acc)[8],
                                          float* stage, int tl) {
-    store_row_streaming<TPR>(o.C + row * N + panel, acc, stage, tl, panel_pieces<TPR, PARTIAL>(N, panel, tl));
+    store_row_streaming<TPR, PARTIAL>(o.C + row * nv + panel, acc, stage, tl, nv - panel);
 }
 template <int TPR, bool PARTIAL>
-__device__ __forceinline__ void emit_row(const OutFused& o, size_t row, int N, int panel, const float (&acc)[8],
+__device__ __forceinline__ void emit_row(const OutFused& o, size_t row, int nv, int panel, const float (&acc)[8],
                                          float*, int tl) {
-    const int f = panel + 8 * tl;
-    if (PARTIAL && f >= N) return;   // lane past the last feature of a partial panel
+    if (PARTIAL && panel + 8 * tl >= nv) return;   // lane past the last feature of a partial panel
+    const int f = panel + lane_features<TPR, PARTIAL>(nv - panel, tl);
     const uint2_t lo = finish4(o, f, (float4_t){acc[0], acc[1], acc[2], acc[3]});
     const uint2_t hi = finish4(o, f + 4, (float4_t){acc[4], acc[5], acc[6], acc[7]});
-    __builtin_nontemporal_store((uint4_t){lo[0], lo[1], hi[0], hi[1]}, reinterpret_cast<uint4_t*>(o.C + row * N + f));
+    __builtin_nontemporal_store((uint4_t){lo[0], lo[1], hi[0], hi[1]}, reinterpret_cast<uint4_a4*>(o.C + row * nv + f));
 }
 
 // ---------------------------------------------------------------------------
@@ -87,10 +91,10 @@ __device__ __forceinline__ void emit_row(const OutFused& o, size_t row, int N, i
 // n_cols * 2N < 2^32): one address register per load in flight instead of two.
 struct BRows {
     const char* base;      // B + first feature of the panel (wave-uniform)
-    uint32_t row_bytes;    // 2N
-    uint32_t lane_byte;    // 16 * lane-in-team
-    __device__ __forceinline__ const uint4_t* row(int c) const {
-        return reinterpret_cast<const uint4_t*>(base + ((uint32_t)c * row_bytes + lane_byte));
+    uint32_t row_bytes;    // 2 * features of a row of B
+    uint32_t lane_byte;    // the lane's eight features from the panel's first
+    __device__ __forceinline__ const uint4_a4* row(int c) const {
+        return reinterpret_cast<const uint4_a4*>(base + ((uint32_t)c * row_bytes + lane_byte));
     }
 };
 
@@ -123,7 +127,7 @@ template <class OUT>
 struct ShortRowState {
     const OUT& out;
     float* stage;    // the team's LDS stage
-    int N, panel, tl, L, k, rq;
+    int nv, panel, tl, L, k, rq;
 };
 
 template <int U, int TPR, bool PARTIAL, class OUT>
@@ -150,7 +154,7 @@ __device__ __forceinline__ void short_rows_group(const BRows& Bp, int my_col, fl
             st.k = 0;
             const int row = shfl_i32(my_row, team_base + st.rq);
             ++st.rq;
-            if (row >= 0) emit_row<TPR, PARTIAL>(st.out, (size_t)row, st.N, st.panel, acc, st.stage, st.tl);
+            if (row >= 0) emit_row<TPR, PARTIAL>(st.out, (size_t)row, st.nv, st.panel, acc, st.stage, st.tl);
 #pragma unroll
             for (int i = 0; i < 8; ++i) acc[i] = 0.f;
         }
@@ -173,14 +177,14 @@ __device__ __forceinline__ void gather_steps(const BRows& Bp, int my_col, float 
     if (steps & 1) gather_group<1>(Bp, my_col, my_val, team_base + j, acc);
 }
 
-// PARTIAL: the panel (there is one, the last) holds fewer than 8 * TPR features; lanes past the last
-// feature gather the panel's first piece and store nothing.  Full panels carry no such checks.
+// PARTIAL: the panel (there is one, the last) holds fewer than 8 * TPR features.  Full panels carry no checks.
+// N: features of a partial row in scratch; nb, nv: of a row of B and of C.
 template <int TPR, class OUT, bool PARTIAL>
 __global__ __launch_bounds__(64 * kWavesPerBlock) __attribute__((amdgpu_waves_per_eu(8, 8))) void rsh_irregular_kernel(
     const uint4* __restrict__ waves, XcdSplit xs,
     const int32_t* __restrict__ irr_row, const int32_t* __restrict__ irr_col,
     const uint16_t* __restrict__ irr_val, const __half* __restrict__ B, const OUT out,
-    float* __restrict__ scratch, int N, int feature0) {
+    float* __restrict__ scratch, int N, int nb, int nv, int feature0) {
     constexpr int G = 64 / TPR;
     __shared__ __attribute__((aligned(16))) float lds_stage[kWavesPerBlock][64 * 8];
     const int lane = threadIdx.x & 63;
@@ -194,9 +198,8 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) __attribute__((amdgpu_waves_pe
     const uint32_t start = __builtin_amdgcn_readfirstlane(d.x), count = __builtin_amdgcn_readfirstlane(d.y);
     const uint32_t dst = __builtin_amdgcn_readfirstlane(d.z), info = __builtin_amdgcn_readfirstlane(d.w);
     const uint32_t kind = info & kWaveKindMask;
-    // a lane past the last feature (partial last panel) reads the panel's first piece and stores nothing
-    const BRows Bp{reinterpret_cast<const char*>(B + panel), 2u * (uint32_t)N,
-                   (!PARTIAL || panel + 8 * tl < N) ? 16u * (uint32_t)tl : 0u};
+    const int live = nv - panel;
+    const BRows Bp{reinterpret_cast<const char*>(B + panel), 2u * (uint32_t)nb, 2u * (uint32_t)lane_features<TPR, PARTIAL>(live, tl)};
 
     float acc[8];
 #pragma unroll
@@ -205,12 +208,11 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) __attribute__((amdgpu_waves_pe
     if (kind == kWaveZeroRows) {
         for (uint32_t q = team; q < count; q += G) {
             if constexpr (OUT::kFused) {
-                emit_row<TPR, PARTIAL>(out, (size_t)irr_row[dst + q], N, panel, acc, stage, tl);   // act(bias)
+                emit_row<TPR, PARTIAL>(out, (size_t)irr_row[dst + q], nv, panel, acc, stage, tl);   // act(bias)
             } else {
-                float* o = out.C + (size_t)irr_row[dst + q] * N + panel;
-                const PanelPieces keep = panel_pieces<TPR, PARTIAL>(N, panel, tl);
-                if (keep.first) store_c_streaming(o + 4 * tl, (float4_t){0.f, 0.f, 0.f, 0.f});
-                if (keep.second) store_c_streaming(o + 4 * TPR + 4 * tl, (float4_t){0.f, 0.f, 0.f, 0.f});
+                float* o = out.C + (size_t)irr_row[dst + q] * nv + panel;
+                store_piece<PARTIAL>(o, live, 4 * tl, (float4_t){0.f, 0.f, 0.f, 0.f});
+                store_piece<PARTIAL>(o, live, 4 * TPR + 4 * tl, (float4_t){0.f, 0.f, 0.f, 0.f});
             }
         }
         return;
@@ -227,7 +229,7 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) __attribute__((amdgpu_waves_pe
         const int my_row = tl < n_rows_mine ? irr_row[dst + q0 + tl] : -1;
         // R rows of L entries back to back: the loads of up to eight steps are in flight together,
         // whatever rows they belong to; after every L consumed steps a row is complete and stored
-        ShortRowState<OUT> st{out, stage, N, panel, tl, L, 0, 0};
+        ShortRowState<OUT> st{out, stage, nv, panel, tl, L, 0, 0};
         const int steps = R * L;
         int j = 0;
         for (; j + 8 <= steps; j += 8) short_rows_group<8, TPR, PARTIAL>(Bp, my_col, my_val, my_row, team_base, j, acc, st);
@@ -265,11 +267,11 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) __attribute__((amdgpu_waves_pe
     for (int i = 0; i < 8; ++i) acc[i] = sum_over_teams<TPR>(acc[i], lane);
     if (team != 0) return;
     if constexpr (OUT::kFused) {
-        if (info & kWaveToScratch) store_row_streaming<TPR>(scratch + (size_t)dst * N + panel, acc, stage, tl, panel_pieces<TPR, PARTIAL>(N, panel, tl));
-        else emit_row<TPR, PARTIAL>(out, (size_t)dst, N, panel, acc, stage, tl);
+        if (info & kWaveToScratch) store_row_streaming<TPR, PARTIAL>(scratch + (size_t)dst * N + panel, acc, stage, tl, live);
+        else emit_row<TPR, PARTIAL>(out, (size_t)dst, nv, panel, acc, stage, tl);
     } else {
-        store_row_streaming<TPR>(((info & kWaveToScratch) ? scratch : out.C) + (size_t)dst * N + panel, acc, stage, tl,
-                                 panel_pieces<TPR, PARTIAL>(N, panel, tl));
+        store_row_streaming<TPR, PARTIAL>((info & kWaveToScratch) ? scratch + (size_t)dst * N + panel : out.C + (size_t)dst * nv + panel, acc,
+                                          stage, tl, live);
     }
 }
 
@@ -325,7 +327,7 @@ __global__ __launch_bounds__(NW == 1 ? 64 * kWavesPerBlock : 64 * NW) void rsh_t
     const int32_t* __restrict__ win_row, const int32_t* __restrict__ tile_colid,
     const uint64_t* __restrict__ tile_mask, const uint32_t* __restrict__ tile_val_off,
     const uint16_t* __restrict__ tile_val, const __half* __restrict__ B, const OUT out,
-    float* __restrict__ scratch, int N, int feature0) {
+    float* __restrict__ scratch, int N, int nb, int nv, int feature0) {
     using Gm = TileGeom<NCH, NW, KT>;
     constexpr int P = Gm::P, TPR = Gm::TPR, NLD = Gm::NLD, LDB = Gm::LDB, THREADS = Gm::THREADS, CPL = Gm::CPL;
     using vals_t = typename std::conditional<KT == 16, uint2_t, uint4_t>::type;   // CPL halves per lane
@@ -370,7 +372,7 @@ __global__ __launch_bounds__(NW == 1 ? 64 * kWavesPerBlock : 64 * NW) void rsh_t
     // B rows are addressed as a wave-uniform base plus a 32-bit byte offset (the plan guarantees
     // n_cols * 2N < 2^32), which leaves the address arithmetic at one multiply-add per load
     const char* Bbytes = reinterpret_cast<const char*>(B + panel);
-    const uint32_t row_bytes = 2u * (uint32_t)N;
+    const uint32_t row_bytes = 2u * (uint32_t)nb;
     uint32_t ld_byte[NLD];
 #pragma unroll
     for (int j = 0; j < NLD; ++j) ld_byte[j] = 2u * (uint32_t)ld_col[j];
@@ -415,7 +417,7 @@ __global__ __launch_bounds__(NW == 1 ? 64 * kWavesPerBlock : 64 * NW) void rsh_t
 #pragma unroll
                 for (int j = 0; j < NLD; ++j) {
                     const int c = shfl_i32(colid_c[d], ld_row[j] & (KT - 1));
-                    breg[d][j] = *reinterpret_cast<const uint4_t*>(Bbytes + ((uint32_t)c * row_bytes + ld_byte[j]));
+                    breg[d][j] = *reinterpret_cast<const uint4_a4*>(Bbytes + ((uint32_t)c * row_bytes + ld_byte[j]));
                 }
                 vreg[d] = *reinterpret_cast<const vals_t*>(tile_val + voff + lane * CPL);
                 const uint32_t tn = min(t_begin + (uint32_t)(D + d), t_last);
@@ -457,7 +459,7 @@ __global__ __launch_bounds__(NW == 1 ? 64 * kWavesPerBlock : 64 * NW) void rsh_t
 #pragma unroll
                 for (int j = 0; j < NLD; ++j) {
                     const int c = shfl_i32(colid_n[d], ld_row[j] & (KT - 1));
-                    breg[d][j] = *reinterpret_cast<const uint4_t*>(Bbytes + ((uint32_t)c * row_bytes + ld_byte[j]));
+                    breg[d][j] = *reinterpret_cast<const uint4_a4*>(Bbytes + ((uint32_t)c * row_bytes + ld_byte[j]));
                 }
                 vreg[d] = *reinterpret_cast<const vals_t*>(tile_val + voff_n[d] + lane * CPL);
                 const uint32_t t2 = min(t + 2u * D, t_last);
@@ -516,7 +518,7 @@ __global__ __launch_bounds__(NW == 1 ? 64 * kWavesPerBlock : 64 * NW) void rsh_t
         // when these went through L2)
         float* o = scratch + ((size_t)dst + r) * N + panel + 4 * q;
 #pragma unroll
-        for (int c = 0; c < NCH; ++c) *reinterpret_cast<float4_t*>(o + 16 * c) = acc[c];
+        for (int c = 0; c < NCH; ++c) *reinterpret_cast<float4_a4*>(o + 16 * c) = acc[c];
         return;
     }
     if constexpr (OUT::kFused) {
@@ -545,7 +547,7 @@ __global__ __launch_bounds__(NW == 1 ? 64 * kWavesPerBlock : 64 * NW) void rsh_t
             const int prow = shfl_i32(row, pr);
             if (piece < kPieces && prow >= 0) {
                 const uint4_t v = *reinterpret_cast<const uint4_t*>(so + pr * LDB + 8 * pc);
-                __builtin_nontemporal_store(v, reinterpret_cast<uint4_t*>(out.C + (size_t)prow * N + panel + 8 * pc));
+                __builtin_nontemporal_store(v, reinterpret_cast<uint4_a4*>(out.C + (size_t)prow * nv + panel + 8 * pc));
             }
         }
     } else if constexpr (NCH % 2 == 0) {
@@ -555,8 +557,8 @@ __global__ __launch_bounds__(NW == 1 ? 64 * kWavesPerBlock : 64 * NW) void rsh_t
         const bool low = (lane & 8) == 0;
         const int row_other = swap_lane8(row);
         const int row_a = low ? row : row_other, row_b = low ? row_other : row;
-        float* out_a = out.C + (size_t)row_a * N + panel + 4 * q + (low ? 0 : 16);
-        float* out_b = out.C + (size_t)row_b * N + panel + 4 * q + (low ? 0 : 16);
+        float* out_a = out.C + (size_t)row_a * nv + panel + 4 * q + (low ? 0 : 16);
+        float* out_b = out.C + (size_t)row_b * nv + panel + 4 * q + (low ? 0 : 16);
 #pragma unroll
         for (int c = 0; c < NCH; c += 2) {
             float4_t send, recv;
@@ -575,7 +577,7 @@ __global__ __launch_bounds__(NW == 1 ? 64 * kWavesPerBlock : 64 * NW) void rsh_t
         }
     } else {
         if (row < 0) return;
-        float* o = out.C + (size_t)row * N + panel + 4 * q;
+        float* o = out.C + (size_t)row * nv + panel + 4 * q;
 #pragma unroll
         for (int c = 0; c < NCH; ++c) store_c_streaming(o + 16 * c, acc[c]);
     }
@@ -589,40 +591,28 @@ __global__ __launch_bounds__(NW == 1 ? 64 * kWavesPerBlock : 64 * NW) void rsh_t
 template <class OUT>
 __global__ __launch_bounds__(64 * kWavesPerBlock) void rsh_combine_kernel(
     const uint4* __restrict__ entries, uint32_t n_entries, const float* __restrict__ scratch,
-    const OUT out, int N) {
+    const OUT out, int N, int nv) {
     const int lane = threadIdx.x & 63;
     const uint32_t e = __builtin_amdgcn_readfirstlane(blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6));
     if (e >= n_entries) return;
     const uint4 en = entries[e];
     const uint32_t row = en.x, first = en.y, parts = en.z, stride = en.w;
-    for (int f = lane * 4; f < N; f += 256) {
-        float4 s0 = make_float4(0, 0, 0, 0), s1 = s0, s2 = s0, s3 = s0;
+    for (int f0 = lane * 4; f0 < nv; f0 += 256) {
+        const int f = min(f0, nv - 4);   // four features that end with the row where it is not a multiple of four
+        float4_t s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0, s2 = s0, s3 = s0;
+        const auto part = [&](uint32_t p) { return *reinterpret_cast<const float4_a4*>(scratch + ((size_t)first + (size_t)p * stride) * N + f); };
         uint32_t p = 0;
         for (; p + 4 <= parts; p += 4) {
-            const float4 a = *reinterpret_cast<const float4*>(scratch + ((size_t)first + (size_t)(p + 0) * stride) * N + f);
-            const float4 b = *reinterpret_cast<const float4*>(scratch + ((size_t)first + (size_t)(p + 1) * stride) * N + f);
-            const float4 c = *reinterpret_cast<const float4*>(scratch + ((size_t)first + (size_t)(p + 2) * stride) * N + f);
-            const float4 d = *reinterpret_cast<const float4*>(scratch + ((size_t)first + (size_t)(p + 3) * stride) * N + f);
-            s0.x += a.x; s0.y += a.y; s0.z += a.z; s0.w += a.w;
-            s1.x += b.x; s1.y += b.y; s1.z += b.z; s1.w += b.w;
-            s2.x += c.x; s2.y += c.y; s2.z += c.z; s2.w += c.w;
-            s3.x += d.x; s3.y += d.y; s3.z += d.z; s3.w += d.w;
+            const float4_t a = part(p), b = part(p + 1), c = part(p + 2), d = part(p + 3);
+            s0 += a;
+            s1 += b;
+            s2 += c;
+            s3 += d;
         }
-        for (; p < parts; ++p) {
-            const float4 a = *reinterpret_cast<const float4*>(scratch + ((size_t)first + (size_t)p * stride) * N + f);
-            s0.x += a.x; s0.y += a.y; s0.z += a.z; s0.w += a.w;
-        }
-        float4 o;
-        o.x = (s0.x + s1.x) + (s2.x + s3.x);
-        o.y = (s0.y + s1.y) + (s2.y + s3.y);
-        o.z = (s0.z + s1.z) + (s2.z + s3.z);
-        o.w = (s0.w + s1.w) + (s2.w + s3.w);
-        if constexpr (OUT::kFused) {
-            __builtin_nontemporal_store(finish4(out, f, (float4_t){o.x, o.y, o.z, o.w}),
-                                        reinterpret_cast<uint2_t*>(out.C + (size_t)row * N + f));
-        } else {
-            store_c_streaming(out.C + (size_t)row * N + f, (float4_t){o.x, o.y, o.z, o.w});
-        }
+        for (; p < parts; ++p) s0 += part(p);
+        const float4_t o = (s0 + s1) + (s2 + s3);
+        if constexpr (OUT::kFused) __builtin_nontemporal_store(finish4(out, f, o), reinterpret_cast<uint2_a4*>(out.C + (size_t)row * nv + f));
+        else store_c_streaming(out.C + (size_t)row * nv + f, o);
     }
 }
 
@@ -786,55 +776,57 @@ static inline uint32_t grid_for(const XcdSplit& xs) {
     return 8u * ((longest + kWavesPerBlock - 1) / kWavesPerBlock);
 }
 
-// Full panels in one launch; a last partial panel (N not a multiple of the panel) in a launch of its own.
+// Feature widths of a launch: `nb` of a row of B, `nv` of a row of C (equal, or of the padded copies).  Both are
+// even and at least 16; partial sums have rows of geo.N >= nv.
+// Full panels in one launch; a last partial panel (nv not a multiple of the panel) in a launch of its own, which
+// starts early enough to hold eight features (those it shares with the panel before come out the same twice).
 template <int TPR, class OUT>
-static void launch_irregular_t(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st) {
-    const int full = d.geo.N / d.geo.irr_panel;
-    if (full > 0)
-        hipLaunchKernelGGL((rsh_irregular_kernel<TPR, OUT, false>), dim3(grid_for(d.irr_split), (unsigned)full), dim3(64 * kWavesPerBlock),
+static void launch_irregular_t(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st, int nb, int nv) {
+    const int full = nv / d.geo.irr_panel;
+    auto launch = [&](auto kernel, int panels, int feature0) {
+        hipLaunchKernelGGL(kernel, dim3(grid_for(d.irr_split), (unsigned)panels), dim3(64 * kWavesPerBlock),
                            0, st, (const uint4*)d.irr_wave, d.irr_split, d.irr_row, d.irr_col, d.irr_val, (const __half*)B, out,
-                           d.scratch, d.geo.N, 0);
-    if (d.geo.N % d.geo.irr_panel)
-        hipLaunchKernelGGL((rsh_irregular_kernel<TPR, OUT, true>), dim3(grid_for(d.irr_split), 1u), dim3(64 * kWavesPerBlock),
-                           0, st, (const uint4*)d.irr_wave, d.irr_split, d.irr_row, d.irr_col, d.irr_val, (const __half*)B, out,
-                           d.scratch, d.geo.N, full * d.geo.irr_panel);
+                           d.scratch, d.geo.N, nb, nv, feature0);
+    };
+    if (full > 0) launch(rsh_irregular_kernel<TPR, OUT, false>, full, 0);
+    if (nv % d.geo.irr_panel) launch(rsh_irregular_kernel<TPR, OUT, true>, 1, std::min(full * d.geo.irr_panel, nv - 8));
 }
 
 // `panels` panels of 16 * NCH features starting at feature `feature0`
 template <int NCH, int NW, int D, int KT, class OUT>
-static void launch_tile_t(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st, int feature0, int panels) {
+static void launch_tile_t(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st, int nb, int nv, int feature0, int panels) {
     constexpr int items_per_block = NW == 1 ? kWavesPerBlock : 1;
     uint32_t longest = 0;
     for (int x = 0; x < 8; ++x) longest = std::max(longest, d.tile_split.start[x + 1] - d.tile_split.start[x]);
     dim3 grid(8u * ((longest + items_per_block - 1) / items_per_block), (unsigned)panels);
     hipLaunchKernelGGL((rsh_tile_kernel<NCH, NW, D, KT, OUT>), grid, dim3(NW == 1 ? 64 * kWavesPerBlock : 64 * NW), 0, st,
                        (const uint4*)d.tile_item, d.tile_split, d.win_row, d.tile_colid, d.tile_mask, d.tile_val_off,
-                       d.tile_val, (const __half*)B, out, d.scratch, d.geo.N, feature0);
+                       d.tile_val, (const __half*)B, out, d.scratch, d.geo.N, nb, nv, feature0);
 }
 
 // Fragments in flight per thread: one for 16-row windows, two when the waves of a window share
 // the staging (measured best of 1, 2, 3).
 template <int NCH, int NW, class OUT>
-static int launch_tile_d(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st, int feature0, int panels) {
+static int launch_tile_d(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st, int nb, int nv, int feature0, int panels) {
     constexpr int D = NW == 1 ? 1 : 2;
-    if (d.geo.tile_k == 16) launch_tile_t<NCH, NW, D, 16>(d, B, out, st, feature0, panels);
-    else if (d.geo.tile_k == 32) launch_tile_t<NCH, NW, D, 32>(d, B, out, st, feature0, panels);
+    if (d.geo.tile_k == 16) launch_tile_t<NCH, NW, D, 16>(d, B, out, st, nb, nv, feature0, panels);
+    else if (d.geo.tile_k == 32) launch_tile_t<NCH, NW, D, 32>(d, B, out, st, nb, nv, feature0, panels);
     else return RSH_ERR_BAD_OPTION;
     return RSH_OK;
 }
 
 template <int NCH, class OUT>
-static int launch_tile_nw(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st, int feature0, int panels) {
+static int launch_tile_nw(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st, int nb, int nv, int feature0, int panels) {
     switch (d.geo.nw) {
-        case 1: return launch_tile_d<NCH, 1>(d, B, out, st, feature0, panels);
-        case 2: return launch_tile_d<NCH, 2>(d, B, out, st, feature0, panels);
-        case 4: return launch_tile_d<NCH, 4>(d, B, out, st, feature0, panels);
+        case 1: return launch_tile_d<NCH, 1>(d, B, out, st, nb, nv, feature0, panels);
+        case 2: return launch_tile_d<NCH, 2>(d, B, out, st, nb, nv, feature0, panels);
+        case 4: return launch_tile_d<NCH, 4>(d, B, out, st, nb, nv, feature0, panels);
         default: return RSH_ERR_BAD_OPTION;
     }
 }
 
 template <class OUT>
-static int launch_all(const DevicePlan& d, const void* B, const OUT& out, void* stream, void* const* events) {
+static int launch_all(const DevicePlan& d, const void* B, const OUT& out, int nb, int nv, void* stream, void* const* events) {
     const hipStream_t caller = (hipStream_t)stream;
     auto mark = [&](int i) {
         if (events) (void)hipEventRecord((hipEvent_t)events[i], caller);
@@ -852,25 +844,28 @@ static int launch_all(const DevicePlan& d, const void* B, const OUT& out, void* 
     }
     hipStream_t st = forked ? (hipStream_t)d.side : caller;
     if (d.n_tile_items > 0 && d.geo.panel) {
-        rc = launch_panels(d, B, out, st);
+        rc = launch_panels(d, B, out, st, nb, nv);
         if (rc != RSH_OK) return rc;
     } else if (d.n_tile_items > 0) {
-        // The feature width in 16-column chunks is covered by panels of 16, 8, 4, 2 and 1 chunks,
-        // widest first (N = 160: one panel of 128 columns and one of 32), one launch per panel width.
-        int chunks = d.geo.N / 16, feature0 = 0;
-        for (int nch = 16; nch >= 1 && rc == RSH_OK; nch /= 2) {
-            const int panels = chunks / nch;
-            if (panels == 0) continue;
-            switch (nch) {
-                case 1: rc = launch_tile_nw<1>(d, B, out, st, feature0, panels); break;
-                case 2: rc = launch_tile_nw<2>(d, B, out, st, feature0, panels); break;
-                case 4: rc = launch_tile_nw<4>(d, B, out, st, feature0, panels); break;
-                case 8: rc = launch_tile_nw<8>(d, B, out, st, feature0, panels); break;
-                default: rc = launch_tile_nw<16>(d, B, out, st, feature0, panels); break;
+        // As many panels of the widest kind (256, 128, ... 16 features) as fit, and for the rest one of the smallest
+        // kind that holds it, placed so that it ends with the row: N = 160 takes 128 + 32, N = 100 takes 64 and
+        // features 36 .. 99 (those it shares with the panel before come out the same twice).
+        int wide = 16;
+        while (wide < 256 && 2 * wide <= nv) wide *= 2;
+        const int rest = nv % wide;
+        int last = 16;
+        while (last < rest) last *= 2;
+        auto launch = [&](int features, int feature0, int panels) {
+            switch (features) {
+                case 16: return launch_tile_nw<1>(d, B, out, st, nb, nv, feature0, panels);
+                case 32: return launch_tile_nw<2>(d, B, out, st, nb, nv, feature0, panels);
+                case 64: return launch_tile_nw<4>(d, B, out, st, nb, nv, feature0, panels);
+                case 128: return launch_tile_nw<8>(d, B, out, st, nb, nv, feature0, panels);
+                default: return launch_tile_nw<16>(d, B, out, st, nb, nv, feature0, panels);
             }
-            feature0 += panels * nch * 16;
-            chunks -= panels * nch;
-        }
+        };
+        rc = launch(wide, 0, nv / wide);
+        if (rc == RSH_OK && rest > 0) rc = launch(last, nv - last, 1);
         if (rc != RSH_OK) return rc;
     }
     if (forked && hipEventRecord((hipEvent_t)d.ev_join, (hipStream_t)d.side) != hipSuccess) return RSH_ERR_HIP;
@@ -878,10 +873,10 @@ static int launch_all(const DevicePlan& d, const void* B, const OUT& out, void* 
     mark(1);
     if (d.n_irr_waves > 0) {
         switch (d.geo.irr_tpr) {
-            case 2: launch_irregular_t<2>(d, B, out, st); break;
-            case 4: launch_irregular_t<4>(d, B, out, st); break;
-            case 8: launch_irregular_t<8>(d, B, out, st); break;
-            case 16: launch_irregular_t<16>(d, B, out, st); break;
+            case 2: launch_irregular_t<2>(d, B, out, st, nb, nv); break;
+            case 4: launch_irregular_t<4>(d, B, out, st, nb, nv); break;
+            case 8: launch_irregular_t<8>(d, B, out, st, nb, nv); break;
+            case 16: launch_irregular_t<16>(d, B, out, st, nb, nv); break;
             default: return RSH_ERR_UNSUPPORTED_N;
         }
     }
@@ -890,14 +885,14 @@ static int launch_all(const DevicePlan& d, const void* B, const OUT& out, void* 
     if (d.n_combine > 0) {
         const uint32_t n = (uint32_t)d.n_combine;
         hipLaunchKernelGGL(rsh_combine_kernel<OUT>, dim3((n + kWavesPerBlock - 1) / kWavesPerBlock), dim3(64 * kWavesPerBlock),
-                           0, st, (const uint4*)d.combine, n, d.scratch, out, d.geo.N);
+                           0, st, (const uint4*)d.combine, n, d.scratch, out, d.geo.N, nv);
     }
     mark(3);
     return hipGetLastError() == hipSuccess ? RSH_OK : RSH_ERR_HIP;
 }
 
-int launch_spmm(const DevicePlan& d, const void* B, void* C, void* stream, void* const* events) {
-    return launch_all(d, B, OutPlain{(float*)C}, stream, events);
+int launch_spmm(const DevicePlan& d, const void* B, void* C, int nb, int nv, void* stream, void* const* events) {
+    return launch_all(d, B, OutPlain{(float*)C}, nb, nv, stream, events);
 }
 
 // ---------------------------------------------------------------------------
@@ -926,8 +921,9 @@ int static_scratch(float** ptr) {
     return RSH_OK;
 }
 
-int launch_spmm_f16(const DevicePlan& d, const void* B, void* C16, const float* bias, int relu, void* stream, void* const* events) {
-    return launch_all(d, B, OutFused{(_Float16*)C16, bias, relu}, stream, events);
+int launch_spmm_f16(const DevicePlan& d, const void* B, void* C16, const float* bias, int relu, int nb, int nv, void* stream,
+                    void* const* events) {
+    return launch_all(d, B, OutFused{(_Float16*)C16, bias, relu}, nb, nv, stream, events);
 }
 
 }  // namespace rsh

@@ -45,8 +45,9 @@ struct DevicePlan {
 
 // Enqueue the tile, irregular and combine kernels on `stream` (a hipStream_t).  When
 // `events` is not null it points at four hipEvent_t recorded before the tile kernel and
-// after each of the three kernels.
-int launch_spmm(const DevicePlan& d, const void* B_dev, void* C_dev, void* stream, void* const* events);
+// after each of the three kernels.  nb, nv: features of a row of B and of C, both even and at least 16
+// (or both geo.N).
+int launch_spmm(const DevicePlan& d, const void* B_dev, void* C_dev, int nb, int nv, void* stream, void* const* events);
 
 // Plan upload, panel form: cell masks and dword counts of all units (then prefix-summed, total last), and with
 // room for their values made, the value stream.  Both read panel_off / panel_ent.
@@ -60,8 +61,8 @@ int static_scratch(float** ptr);
 
 // Same kernels with the fused epilogue: C16 (binary16, n_rows x N) = act(A B + bias); bias is a
 // device array of N floats or null, relu != 0 selects max(x, 0).
-int launch_spmm_f16(const DevicePlan& d, const void* B_dev, void* C16_dev, const float* bias_dev, int relu,
-                    void* stream, void* const* events);
+int launch_spmm_f16(const DevicePlan& d, const void* B_dev, void* C16_dev, const float* bias_dev, int relu, int nb,
+                    int nv, void* stream, void* const* events);
 
 // Row-wise copies between a matrix of `n` columns and one of `n_pad` >= n columns (`elem` bytes per
 // element, 2 or 4): widen (pad columns become zero) and narrow (pad columns are dropped).

@@ -174,11 +174,11 @@ __device__ __forceinline__ void block_barrier() {
 
 // The products of one item, fragments [t_begin, t_end) of window `win`, added to acc + acc2.  RUN: the window's
 // condensed columns are one run of columns that fills whole fragments, so its rows of B need no ids.
-template <int NCH32, int NG, bool RUN>
+template <int NCH32, int NG, bool RUN, bool RAGGED>
 __device__ __forceinline__ void panel_item(unsigned char* smem, uint32_t win, uint32_t t_begin, uint32_t t_end, uint32_t t0, uint32_t nt,
                                             int32_t col0, const int32_t* __restrict__ tile_colid, const uint32_t* __restrict__ quad0,
                                             const uint4_t* __restrict__ meta, const uint32_t* __restrict__ qoff,
-                                            const uint32_t* __restrict__ val, const __half* __restrict__ B, int N, int panel,
+                                            const uint32_t* __restrict__ val, const __half* __restrict__ B, int nb, int panel,
                                             float16_t (&acc)[NCH32], float16_t (&acc2)[NCH32]) {
     using Gm = PanelGeom<NCH32, NG>;
     // fragments ahead at which rows of B are requested, and how much earlier their column ids; where a thread
@@ -197,14 +197,17 @@ __device__ __forceinline__ void panel_item(unsigned char* smem, uint32_t win, ui
     // thread tix stages 16-byte piece j * THREADS + tix of the KT x TPR pieces, i.e. the same piece of rows
     // row0, row0 + THREADS / TPR, ...; threads without a piece (narrow panels) stage into spare space
     constexpr int kRowStep = THREADS / TPR;
-    const uint32_t row_bytes = 2u * (uint32_t)N;
+    const uint32_t row_bytes = 2u * (uint32_t)nb;
     const int row0 = (tix / TPR) & (KT - 1), piece = tix % TPR;
     const uint32_t ld_lds = tix < Gm::PIECES ? (uint32_t)(row0 * LDB + piece * 8) : (uint32_t)(KT * LDB + (tix - Gm::PIECES) * 8);
-    // a piece past the last feature (partial last panel) reads the panel's first piece; its products land in
-    // features that are never stored
-    const uint32_t ld_byte = (panel + 8 * piece < N ? 16u * (uint32_t)piece : 0u) + (RUN ? (uint32_t)row0 * row_bytes : 0u);
+    // A piece past the last feature (partial last panel) reads the row's first piece; its products land in
+    // features that are never stored.  A piece that crosses the end of the row (nb is even) is read where it
+    // ends with the row, so that nothing behind B is touched, and moved down by whole dwords when it is staged.
+    const int f_piece = panel + 8 * piece, over = f_piece < nb && f_piece + 8 > nb ? (f_piece + 8 - nb) / 2 : 0;
+    [[maybe_unused]] const bool over1 = over == 1, over2 = over == 2, over3 = over == 3;
+    const uint32_t ld_byte = (f_piece + 8 <= nb ? 2u * (uint32_t)f_piece : RAGGED && over ? 2u * (uint32_t)(nb - 8) : 0u) + (RUN ? (uint32_t)row0 * row_bytes : 0u);
     // RUN: the window's columns are one run, a fragment's rows of B follow each other
-    const char* Bbytes = reinterpret_cast<const char*>(B + panel) + (RUN ? (size_t)(uint32_t)col0 * row_bytes : 0);
+    const char* Bbytes = reinterpret_cast<const char*>(B) + (RUN ? (size_t)(uint32_t)col0 * row_bytes : 0);
     const int g4 = lane >> 4, rr4 = (lane & 15) >> 2, ss4 = lane & 3;
     const int tr_off = (8 * (g4 >> 1) + rr4) * LDB + 16 * (g4 & 1) + 4 * ss4;
 
@@ -263,12 +266,20 @@ __device__ __forceinline__ void panel_item(unsigned char* smem, uint32_t win, ui
     auto issue_b = [&](uint32_t step, const int (&cid)[NLD], uint4_t (&b)[NLD]) {
         const char* from = RUN ? Bbytes + (size_t)min(f0 + step, last) * (KT * row_bytes) : Bbytes;
 #pragma unroll
-        for (int j = 0; j < NLD; ++j) b[j] = *reinterpret_cast<const uint4_t*>(RUN ? from + (size_t)j * kRowStep * row_bytes + ld_byte : from + ((uint32_t)cid[j] * row_bytes + ld_byte));
+        for (int j = 0; j < NLD; ++j) b[j] = *reinterpret_cast<const uint4_a4*>(RUN ? from + (size_t)j * kRowStep * row_bytes + ld_byte : from + ((uint32_t)cid[j] * row_bytes + ld_byte));
     };
     auto stage_b = [&](const uint4_t (&b)[NLD], int buf) {
         _Float16* sb = lds_b + buf * Gm::TILE_HALVES;
 #pragma unroll
-        for (int j = 0; j < NLD; ++j) *reinterpret_cast<uint4_t*>(sb + ld_lds + j * kRowStep * LDB) = b[j];
+        for (int j = 0; j < NLD; ++j) {
+            uint4_t x = b[j];
+            if constexpr (RAGGED) {
+                x[0] = over1 ? x[1] : over2 ? x[2] : over3 ? x[3] : x[0];
+                x[1] = over1 ? x[2] : over2 ? x[3] : x[1];
+                x[2] = over1 ? x[3] : x[2];
+            }
+            *reinterpret_cast<uint4_t*>(sb + ld_lds + j * kRowStep * LDB) = x;
+        }
     };
     auto read_b = [&](int buf, int h, Operands& x) {
         const _Float16* sb = lds_b + buf * Gm::TILE_HALVES + tr_off + (16 * h) * LDB;
@@ -379,13 +390,15 @@ __device__ __forceinline__ void panel_item(unsigned char* smem, uint32_t win, ui
     }
 }
 
-template <int NCH32, int NG, class OUT>
+// RAGGED: rows of B end inside a 16-byte piece (nb is not a multiple of 8).  Moving the broken piece costs 3 % of
+// the kernel at 128 features, so the other widths have a kernel without it.
+template <int NCH32, int NG, bool RAGGED, class OUT>
 __global__ __launch_bounds__(64 * NG) __attribute__((amdgpu_waves_per_eu(2, NCH32 == 4 ? 2 : 4))) void rsh_panel_kernel(
     const uint4* __restrict__ items, XcdSplit xs, const int32_t* __restrict__ win_row,
     const uint32_t* __restrict__ win_tile_off, const int32_t* __restrict__ win_col0,
     const int32_t* __restrict__ tile_colid, const uint32_t* __restrict__ quad0, const uint4_t* __restrict__ meta,
     const uint32_t* __restrict__ qoff, const uint32_t* __restrict__ val, const __half* __restrict__ B, const OUT out,
-    float* __restrict__ scratch, int N, int feature0) {
+    float* __restrict__ scratch, int N, int nb, int nv, int feature0) {
     using Gm = PanelGeom<NCH32, NG>;
     constexpr int P = Gm::P;
     __shared__ __attribute__((aligned(16))) unsigned char smem[Gm::SMEM_BYTES];
@@ -423,9 +436,9 @@ __global__ __launch_bounds__(64 * NG) __attribute__((amdgpu_waves_per_eu(2, NCH3
     if (t_begin < t_end) {
         const int32_t col0 = win_col0[win];
         if (col0 >= 0)
-            panel_item<NCH32, NG, true>(smem, win, t_begin, t_end, t0, nt, col0, tile_colid, quad0, meta, qoff, val, B, N, panel, acc, acc2);
+            panel_item<NCH32, NG, true, RAGGED>(smem, win, t_begin, t_end, t0, nt, col0, tile_colid, quad0, meta, qoff, val, B, nb, panel, acc, acc2);
         else
-            panel_item<NCH32, NG, false>(smem, win, t_begin, t_end, t0, nt, col0, tile_colid, quad0, meta, qoff, val, B, N, panel, acc, acc2);
+            panel_item<NCH32, NG, false, RAGGED>(smem, win, t_begin, t_end, t0, nt, col0, tile_colid, quad0, meta, qoff, val, B, nb, panel, acc, acc2);
     }
 
     // ---- output: each group's 32 rows x 32 features take a turn through LDS and leave as whole lines ----
@@ -449,39 +462,50 @@ __global__ __launch_bounds__(64 * NG) __attribute__((amdgpu_waves_per_eu(2, NCH3
             const float4_t v = *reinterpret_cast<const float4_t*>(stage + pr * Gm::STAGE_STRIDE + 4 * fp);
             const int f = panel + 32 * c + 4 * fp;
             const int prow = shfl_i32(row, pr);
-            if (f >= N) continue;
+            if (f >= nv) continue;
             if (dst != kNoDst) {
                 *reinterpret_cast<float4_t*>(scratch + ((size_t)dst + wv * 32 + pr) * N + f) = v;   // partial sums: ordinary stores
             } else if (prow >= 0) {
-                panel_store(out, (size_t)prow, N, f, v);
+                panel_store(out, (size_t)prow, nv, f, v);
                 keep_streaming_hint();
             }
         }
     }
 }
 
-template <int NCH32, int NG, class OUT>
-void launch_panel_t(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st, int feature0, int panels) {
+template <int NCH32, int NG, bool RAGGED, class OUT>
+void launch_panel_t(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st, int nb, int nv, int feature0, int panels) {
     uint32_t longest = 0;
     for (int x = 0; x < 8; ++x) longest = std::max(longest, d.tile_split.start[x + 1] - d.tile_split.start[x]);
-    hipLaunchKernelGGL((rsh_panel_kernel<NCH32, NG, OUT>), dim3(8u * longest, (unsigned)panels), dim3(64 * NG), 0, st,
+    hipLaunchKernelGGL((rsh_panel_kernel<NCH32, NG, RAGGED, OUT>), dim3(8u * longest, (unsigned)panels), dim3(64 * NG), 0, st,
                        (const uint4*)d.tile_item, d.tile_split, d.win_row, d.win_tile_off, d.panel_col0, d.tile_colid,
                        d.panel_quad0, (const uint4_t*)d.panel_meta, d.panel_qoff, d.panel_val, (const __half*)B, out, d.scratch, d.geo.N,
-                       feature0);
+                       nb, nv, feature0);
 }
 template <int NCH32, class OUT>
-void launch_panel_g(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st, int feature0, int panels) {
-    if (d.geo.panel_groups == 8) launch_panel_t<NCH32, 8>(d, B, out, st, feature0, panels);
-    else launch_panel_t<NCH32, 4>(d, B, out, st, feature0, panels);
+void launch_panel_g(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st, int nb, int nv, int feature0, int panels) {
+    if (d.geo.panel_groups == 8) {
+        if (nb % 8) launch_panel_t<NCH32, 8, true>(d, B, out, st, nb, nv, feature0, panels);
+        else launch_panel_t<NCH32, 8, false>(d, B, out, st, nb, nv, feature0, panels);
+    } else if (nb % 8 == 0) {
+        launch_panel_t<NCH32, 4, false>(d, B, out, st, nb, nv, feature0, panels);
+    } else if constexpr (NCH32 < 4) {   // see launch_panels
+        launch_panel_t<NCH32, 4, true>(d, B, out, st, nb, nv, feature0, panels);
+    }
 }
 
 template <class OUT>
-int launch_panels(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st) {
-    const int full = d.geo.N / 128, rest = d.geo.N % 128;
-    if (full > 0) launch_panel_g<4>(d, B, out, st, 0, full);
-    if (rest > 64) launch_panel_g<4>(d, B, out, st, 128 * full, 1);
-    else if (rest > 32) launch_panel_g<2>(d, B, out, st, 128 * full, 1);
-    else if (rest > 0) launch_panel_g<1>(d, B, out, st, 128 * full, 1);
+int launch_panels(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st, int nb, int nv) {
+    // Panels of 128 features in one launch, the rest in a panel of 32, 64 or 128; panels of 64 where the row ends
+    // inside a 16-byte piece and the window has 128 rows (a thread then stages two pieces of a 128-feature row
+    // and has no registers left to move the broken one).
+    const int wide = d.geo.panel_groups == 4 && nb % 8 ? 64 : 128;
+    const int full = nv / wide, rest = nv % wide;
+    if (full > 0 && wide == 64) launch_panel_g<2>(d, B, out, st, nb, nv, 0, full);
+    else if (full > 0) launch_panel_g<4>(d, B, out, st, nb, nv, 0, full);
+    if (rest > 64) launch_panel_g<4>(d, B, out, st, nb, nv, wide * full, 1);
+    else if (rest > 32) launch_panel_g<2>(d, B, out, st, nb, nv, wide * full, 1);
+    else if (rest > 0) launch_panel_g<1>(d, B, out, st, nb, nv, wide * full, 1);
     return RSH_OK;
 }
 

@@ -41,3 +41,44 @@ def test_units_quads_and_parts(N, density, cols, window_rows, parts):
     assert not np.isnan(got).any()
     assert np.all(np.abs(got.astype(np.float64) - C_ref) <= 1e-4 * S)
     plan.destroy()
+
+
+# Even widths that are not multiples of 16 run without copies of the operands: rows end inside 16-byte pieces of
+# B (8 features) and of C (4 features), inside a feature panel, and one or two pieces into one.  Every kernel takes
+# them: windows of 16 rows, tall windows (128-row ones in panels of their own), residual rows of all kinds with
+# their combine pass, empty rows.  B and C end with their allocation's last row, canaries follow C.
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("N", [16, 18, 22, 50, 100, 124, 126, 130, 134, 258, 300])
+@pytest.mark.parametrize("opts", [dict(force_path=2), dict(force_path=2, window_rows=128), dict(force_path=2, window_rows=256, max_tiles_per_item=3),
+                                  dict(force_path=1, max_nnz_per_slice=40), dict(force_path=1, xcd_partition_nnz=32)],
+                         ids=["tile", "w128", "w256", "residual", "xcd"])
+def test_even_widths_without_copies(opts, N, fused):
+    import torch
+    from paper_2603_08734_amd import Plan
+    rng = np.random.default_rng(11)
+    dense = rng.random((90, 333)) < np.linspace(0.0, 0.4, 90)[:, None]     # row 0 is empty, rows of every length
+    r, c = np.nonzero(dense)
+    A = from_coo(r, c, rng.standard_normal(r.size), 90, 333)
+    print(f"case width N={N} opts={opts} fused={fused}", flush=True)
+    plan = Plan(A.row_ptr, A.col_idx, A.val, A.n_cols, N, **opts)
+    B = dense_B(A.n_cols, N, "normal", seed=N)
+    Bd = torch.from_numpy(B.view(np.int16)).cuda().view(torch.float16)
+    C_ref, S, _ = oracle.spmm(A.row_ptr, A.col_idx, A.val, B)
+    dtype, pad = (torch.float16 if fused else torch.float32), 64
+    flat = torch.full((A.n_rows * N + pad,), float("nan"), dtype=dtype, device="cuda")
+    C = flat[:A.n_rows * N].view(A.n_rows, N)
+    if fused:
+        bias = torch.from_numpy(rng.standard_normal(N).astype(np.float32)).cuda()
+        plan.spmm_f16(Bd, C, bias, relu=True)
+        C_ref = np.maximum(C_ref + bias.cpu().numpy().astype(np.float64), 0.0)
+        # the fp32 bound, the addition of the bias, one rounding to binary16
+        bound = 1e-4 * S + 2.0 ** -24 * np.abs(C_ref) + 2.0 ** -11 * np.abs(C_ref) * 1.001 + 2.0 ** -24
+    else:
+        plan.spmm(Bd, C)
+        bound = 1e-4 * S
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(flat[A.n_rows * N:]).all()), "stores past the end of C"
+    got = C.cpu().numpy().astype(np.float64)
+    assert not np.isnan(got).any()
+    assert np.all(np.abs(got - C_ref) <= bound)
+    plan.destroy()
