@@ -174,10 +174,9 @@ int rsh_plan_opts_default(rsh_plan_opts_t *opts);
  * bias then need 16-byte alignment where N is a multiple of 16, else 4-byte alignment.  For other widths
  * (odd ones, those below 16, a run_width the caller chose, operands with less alignment) the kernels run at
  * a width NR > N: whenever N is not a multiple of 16 (or opts->run_width asks for it) the plan owns a
- * binary16 buffer [n_cols][NR] and an fp32 buffer [n_rows][NR] on the device, and such a product first
- * copies B into the wide buffer (pad columns zero) and last copies the N columns of the result into C;
- * B, C and bias then only need the alignment of their element type.  Results are the same, column for
- * column; the cost is one more pass over B and C.
+ * binary16 buffer [n_cols][NR] on the device, and such a product first copies B into it (pad columns zero);
+ * the kernels then store the N columns of the result into C themselves.  B, C and bias then only need the
+ * alignment of their element type.  Results are the same, column for column; the cost is one more pass over B.
  */
 int rsh_plan_create(const rsh_csr_t *csr, int32_t N, const rsh_plan_opts_t *opts, rsh_plan_t **out);
 

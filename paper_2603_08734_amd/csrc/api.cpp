@@ -109,7 +109,7 @@ int upload_array(Uploader& up, const std::vector<T>& h, T** d) {
 void free_device(rsh::DevicePlan& d) {
     void* ptrs[] = {d.win_row, d.win_tile_off, d.tile_colid, d.tile_mask, d.tile_val_off, d.tile_val,
                     d.tile_item, d.panel_col0, d.panel_off, d.panel_ent, d.panel_quad0, d.panel_meta, d.panel_qoff, d.panel_val, d.irr_col, d.irr_val, d.irr_wave, d.irr_row, d.combine, d.scratch,
-                    d.b_pad, d.c_pad, d.bias_pad};
+                    d.b_pad};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
     if (d.ev_fork) (void)hipEventDestroy((hipEvent_t)d.ev_fork);
@@ -188,12 +188,7 @@ int upload_plan(rsh_plan& p) {
     if ((rc = upload_array(up, h.combine, &d.combine))) return rc;
     const size_t sbytes = (size_t)std::max<int64_t>(1, h.n_scratch_slots) * (size_t)h.geo.N * sizeof(float);
     if (!hip_ok(hipMalloc((void**)&d.scratch, sbytes))) return RSH_ERR_OOM;
-    if (d.n_user != h.geo.N) {
-        const size_t np = (size_t)h.geo.N;
-        if (!hip_ok(hipMalloc(&d.b_pad, (size_t)std::max<int64_t>(1, h.n_cols) * np * 2))) return RSH_ERR_OOM;
-        if (!hip_ok(hipMalloc(&d.c_pad, (size_t)std::max<int64_t>(1, h.n_rows) * np * 4))) return RSH_ERR_OOM;
-        if (!hip_ok(hipMalloc((void**)&d.bias_pad, np * 4))) return RSH_ERR_OOM;
-    }
+    if (d.n_user != h.geo.N && !hip_ok(hipMalloc(&d.b_pad, (size_t)std::max<int64_t>(1, h.n_cols) * (size_t)h.geo.N * 2))) return RSH_ERR_OOM;
     if (h.opts.side_stream) {   // default priority, like every stream this library touches
         hipStream_t side = nullptr;
         hipEvent_t fork = nullptr, join = nullptr;
@@ -393,10 +388,10 @@ int rsh_plan_create(const rsh_csr_t* csr, int32_t N, const rsh_plan_opts_t* opts
 
 namespace {
 
-// Common checks of the launch entry points; *padded tells whether the operands pass through the plan's buffers
-// of the run width (then only element alignment is needed), *width the features of their rows otherwise.  The
-// kernels take rows of any even number of features from 16 on at 4-byte aligned addresses; what is left for the
-// copies is odd widths, widths below 16, a run width the caller chose and operands aligned to less.
+// Common checks of the launch entry points; *padded tells whether B passes through the plan's buffer of the run
+// width (then B, C and bias need their element's alignment only), *width the features of the rows the kernels read.
+// The kernels read rows of any even number of features from 16 on at 4-byte aligned addresses; what is left for
+// the copy is odd widths, widths below 16, a run width the caller chose and operands aligned to less.
 int check_launch(const rsh_plan_t* plan, const void* B, const void* C, const void* bias, int c_elem, bool* padded, int* width) {
     if (!plan) return RSH_ERR_NULL;
     if (!plan->uploaded) return RSH_ERR_NOT_UPLOADED;
@@ -419,10 +414,11 @@ int check_launch(const rsh_plan_t* plan, const void* B, const void* C, const voi
     return RSH_OK;
 }
 
-// B (and bias) into the padded buffers before the kernels, C out of its padded buffer after them.
-int widen_operands(const rsh::DevicePlan& d, int64_t n_cols, const void* B, const float* bias, void* stream) {
-    int rc = rsh::launch_widen_rows(B, d.b_pad, n_cols, d.n_user, d.geo.N, 2, stream);
-    if (rc == RSH_OK && bias) rc = rsh::launch_widen_rows(bias, d.bias_pad, 1, d.n_user, d.geo.N, 4, stream);
+// The rows of B that the kernels read: the caller's, or the plan's padded copy of them.
+int readable_rows(const rsh::DevicePlan& d, int64_t n_cols, bool padded, const void** B, void* stream) {
+    if (!padded) return RSH_OK;
+    const int rc = rsh::launch_widen_rows(*B, d.b_pad, n_cols, d.n_user, d.geo.N, stream);
+    *B = d.b_pad;
     return rc;
 }
 
@@ -434,13 +430,8 @@ int rsh_spmm(const rsh_plan_t* plan, const void* B_dev, void* C_dev, void* hip_s
     int rc = check_launch(plan, B_dev, C_dev, nullptr, 4, &padded, &width);
     if (rc != RSH_OK || plan->host.n_rows == 0) return rc;
     const rsh::DevicePlan& d = plan->dev;
-    if (!padded) {
-        rc = rsh::launch_spmm(d, B_dev, C_dev, width, width, hip_stream, nullptr);
-    } else {
-        rc = widen_operands(d, plan->host.n_cols, B_dev, nullptr, hip_stream);
-        if (rc == RSH_OK) rc = rsh::launch_spmm(d, d.b_pad, d.c_pad, width, width, hip_stream, nullptr);
-        if (rc == RSH_OK) rc = rsh::launch_narrow_rows(d.c_pad, C_dev, plan->host.n_rows, d.n_user, d.geo.N, 4, hip_stream);
-    }
+    rc = readable_rows(d, plan->host.n_cols, padded, &B_dev, hip_stream);
+    if (rc == RSH_OK) rc = rsh::launch_spmm(d, B_dev, C_dev, width, padded ? d.n_user : width, hip_stream, nullptr);
     if (rc == RSH_ERR_HIP) g_hip_error = "kernel launch failed";
     return rc;
 }
@@ -462,13 +453,8 @@ int rsh_spmm_noalloc(const rsh_plan_t* plan, const void* B_dev, void* C_dev, voi
         g_hip_error = "hipGetSymbolAddress failed for the library-owned scratch array";
         return rc;
     }
-    if (!padded) {
-        rc = rsh::launch_spmm(d, B_dev, C_dev, width, width, hip_stream, nullptr);
-    } else {
-        rc = widen_operands(d, plan->host.n_cols, B_dev, nullptr, hip_stream);
-        if (rc == RSH_OK) rc = rsh::launch_spmm(d, d.b_pad, d.c_pad, width, width, hip_stream, nullptr);
-        if (rc == RSH_OK) rc = rsh::launch_narrow_rows(d.c_pad, C_dev, plan->host.n_rows, d.n_user, d.geo.N, 4, hip_stream);
-    }
+    rc = readable_rows(d, plan->host.n_cols, padded, &B_dev, hip_stream);
+    if (rc == RSH_OK) rc = rsh::launch_spmm(d, B_dev, C_dev, width, padded ? d.n_user : width, hip_stream, nullptr);
     if (rc == RSH_ERR_HIP) g_hip_error = "kernel launch failed";
     return rc;
 }
@@ -481,13 +467,8 @@ int rsh_spmm_f16(const rsh_plan_t* plan, const void* B_dev, void* C16_dev, const
     int rc = check_launch(plan, B_dev, C16_dev, bias_dev, 2, &padded, &width);
     if (rc != RSH_OK || plan->host.n_rows == 0) return rc;
     const rsh::DevicePlan& d = plan->dev;
-    if (!padded) {
-        rc = rsh::launch_spmm_f16(d, B_dev, C16_dev, bias_dev, relu, width, width, hip_stream, nullptr);
-    } else {
-        rc = widen_operands(d, plan->host.n_cols, B_dev, bias_dev, hip_stream);
-        if (rc == RSH_OK) rc = rsh::launch_spmm_f16(d, d.b_pad, d.c_pad, bias_dev ? d.bias_pad : nullptr, relu, width, width, hip_stream, nullptr);
-        if (rc == RSH_OK) rc = rsh::launch_narrow_rows(d.c_pad, C16_dev, plan->host.n_rows, d.n_user, d.geo.N, 2, hip_stream);
-    }
+    rc = readable_rows(d, plan->host.n_cols, padded, &B_dev, hip_stream);
+    if (rc == RSH_OK) rc = rsh::launch_spmm_f16(d, B_dev, C16_dev, bias_dev, relu, width, padded ? d.n_user : width, hip_stream, nullptr);
     if (rc == RSH_ERR_HIP) g_hip_error = "kernel launch failed";
     return rc;
 }
@@ -505,13 +486,9 @@ int rsh_spmm_profile(const rsh_plan_t* plan, const void* B_dev, void* C_dev, voi
         if (!hip_ok(hipEventCreate(&ev[i]))) rc = RSH_ERR_HIP;
     if (rc == RSH_OK) {
         void* evp[4] = {ev[0], ev[1], ev[2], ev[3]};
-        if (!padded) {
-            rc = rsh::launch_spmm(d, B_dev, C_dev, width, width, hip_stream, evp);
-        } else {   // the copies to and from the padded width lie outside the three timed kernels
-            rc = widen_operands(d, plan->host.n_cols, B_dev, nullptr, hip_stream);
-            if (rc == RSH_OK) rc = rsh::launch_spmm(d, d.b_pad, d.c_pad, width, width, hip_stream, evp);
-            if (rc == RSH_OK) rc = rsh::launch_narrow_rows(d.c_pad, C_dev, plan->host.n_rows, d.n_user, d.geo.N, 4, hip_stream);
-        }
+        // the copy to the padded width lies outside the three timed kernels
+        rc = readable_rows(d, plan->host.n_cols, padded, &B_dev, hip_stream);
+        if (rc == RSH_OK) rc = rsh::launch_spmm(d, B_dev, C_dev, width, padded ? d.n_user : width, hip_stream, evp);
         if (!hip_ok(hipStreamSynchronize((hipStream_t)hip_stream))) rc = RSH_ERR_HIP;
         if (rc == RSH_OK) {
             float ms = 0.f;

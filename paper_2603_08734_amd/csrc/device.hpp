@@ -20,6 +20,8 @@ typedef float float2_t __attribute__((ext_vector_type(2)));
 // of 8 or 4 elements.  gfx950 takes one 16-byte access at any 4-byte boundary at the rate of an aligned one.
 typedef unsigned int uint4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef unsigned int uint2_a4 __attribute__((ext_vector_type(2), aligned(4)));
+typedef unsigned int uint4_a2 __attribute__((ext_vector_type(4), aligned(2)));   // rows of an odd number of halves
+typedef unsigned int uint2_a2 __attribute__((ext_vector_type(2), aligned(2)));
 typedef float float4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef float float2_a4 __attribute__((ext_vector_type(2), aligned(4)));
 
@@ -79,20 +81,37 @@ __device__ __forceinline__ void keep_streaming_hint() { asm volatile("" ::: "mem
 // Where finished rows go.  OutPlain: the fp32 sums as they are.  OutFused: binary16 of
 // act(sum + bias), the form in which a GCN layer hands its features on (paper, Section 4.4);
 // bias (may be null) and activation are chosen at run time, uniformly for the launch.
-struct OutPlain {
-    static constexpr bool kFused = false;
+// kAny: rows of C of any number of features, aligned to their element only, shorter than the rows of B (a padded
+// copy); features from nv on are not stored and have no bias.  Otherwise rows of B and C are equally long, of an
+// even number of features from 16 on, and 4-byte aligned.
+template <bool ANY>
+struct OutPlainT {
+    static constexpr bool kFused = false, kAny = ANY;
     float* C;
 };
-struct OutFused {
-    static constexpr bool kFused = true;
+template <bool ANY>
+struct OutFusedT {
+    static constexpr bool kFused = true, kAny = ANY;
     _Float16* C;
     const float* bias;
     int relu;
 };
+using OutPlain = OutPlainT<false>;
+using OutFused = OutFusedT<false>;
 
+// `end`: one past the last feature of the row (kAny).
 // act(v + bias[f .. f+3]) rounded to binary16 (to nearest even), as two packed words
-__device__ __forceinline__ uint2_t finish4(const OutFused& o, int f, float4_t v) {
-    if (o.bias) v += *reinterpret_cast<const float4_a4*>(o.bias + f);
+template <bool ANY>
+__device__ __forceinline__ uint2_t finish4(const OutFusedT<ANY>& o, int f, int end, float4_t v) {
+    if (o.bias) {
+        if (!ANY || f + 4 <= end) {
+            v += *reinterpret_cast<const float4_a4*>(o.bias + f);
+        } else {
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+                if (f + i < end) v[i] += o.bias[f + i];
+        }
+    }
     if (o.relu) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) v[i] = fmaxf(v[i], 0.f);
@@ -101,16 +120,58 @@ __device__ __forceinline__ uint2_t finish4(const OutFused& o, int f, float4_t v)
     return __builtin_bit_cast(uint2_t, h);
 }
 
-// Four features of a row of C of `nv` features (even), or its last two.
-__device__ __forceinline__ void panel_store(const OutPlain& o, size_t row, int nv, int f, float4_t v) {
+// The first `live` < 4 of four features, one by one (none where live <= 0).
+__device__ __forceinline__ void store_tail(float* p, int live, float4_t v) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+        if (i < live) __builtin_nontemporal_store(v[i], p + i);
+}
+
+// Eight finished features f .. f+7 of a row of C.
+template <bool ANY>
+__device__ __forceinline__ void store_halves(const OutFusedT<ANY>& o, size_t row, int nv, int f, int end, uint4_t v) {
+    _Float16* p = o.C + row * nv + f;
+    if constexpr (!ANY) {
+        __builtin_nontemporal_store(v, reinterpret_cast<uint4_a4*>(p));
+    } else if (f + 8 <= end) {
+        __builtin_nontemporal_store(v, reinterpret_cast<uint4_a2*>(p));
+    } else {
+#pragma unroll
+        for (int i = 0; i < 7; ++i)
+            if (f + i < end) __builtin_nontemporal_store((uint16_t)(v[i / 2] >> (16 * (i & 1))), reinterpret_cast<uint16_t*>(p + i));
+    }
+}
+
+// Four features of a row of C that is whole in every panel, unless kAny.
+template <bool ANY>
+__device__ __forceinline__ void tile_store(const OutPlainT<ANY>& o, size_t row, int nv, int f, float4_t v) {
+    float* p = o.C + row * nv + f;
+    if (!ANY || f + 4 <= nv) store_c_streaming(p, v);
+    else store_tail(p, nv - f, v);
+}
+
+// Four features of a row of C of `nv` features (even), or its last two; any number of them for kAny.
+template <bool ANY>
+__device__ __forceinline__ void panel_store(const OutPlainT<ANY>& o, size_t row, int nv, int f, float4_t v) {
     float* p = o.C + row * nv + f;
     if (f + 4 <= nv) store_c_streaming(p, v);
+    else if constexpr (ANY) store_tail(p, nv - f, v);
     else __builtin_nontemporal_store((float2_t){v[0], v[1]}, reinterpret_cast<float2_a4*>(p));
 }
-__device__ __forceinline__ void panel_store(const OutFused& o, size_t row, int nv, int f, float4_t v) {
+template <bool ANY>
+__device__ __forceinline__ void panel_store(const OutFusedT<ANY>& o, size_t row, int nv, int f, float4_t v) {
     _Float16* p = o.C + row * nv + f;
-    if (f + 4 <= nv) {
-        __builtin_nontemporal_store(finish4(o, f, v), reinterpret_cast<uint2_a4*>(p));
+    if constexpr (ANY) {
+        const uint2_t h = finish4(o, f, nv, v);
+        if (f + 4 <= nv) {
+            __builtin_nontemporal_store(h, reinterpret_cast<uint2_a2*>(p));
+        } else {
+#pragma unroll
+            for (int i = 0; i < 3; ++i)
+                if (f + i < nv) __builtin_nontemporal_store((uint16_t)(h[i / 2] >> (16 * (i & 1))), reinterpret_cast<uint16_t*>(p + i));
+        }
+    } else if (f + 4 <= nv) {
+        __builtin_nontemporal_store(finish4(o, f, nv, v), reinterpret_cast<uint2_a4*>(p));
     } else {
         float2_t t = {v[0], v[1]};
         if (o.bias) t += *reinterpret_cast<const float2_a4*>(o.bias + f);

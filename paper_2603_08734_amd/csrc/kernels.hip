@@ -6,8 +6,9 @@
 //   rsh_irregular_kernel residual rows (Section 3.3.2, "CUDA path"), teams of lanes own
 //                        feature columns, long rows arrive as bounded slices (Section 3.3.3)
 //   rsh_combine_kernel   fixed-order sum of the partial results of split windows / rows
-//   rsh_widen_rows_kernel / rsh_narrow_rows_kernel   copies to and from the run width for feature
-//                        widths that are not a multiple of 16
+//   rsh_fragment_any_kernel, rsh_residual_any_kernel, rsh_sum_any_kernel   the first, third and fourth for rows of
+//                        C of any length and alignment beside a padded copy of B
+//   rsh_widen_rows_kernel   copies B to the run width where its rows cannot be read as they are
 // Each of the first three exists for two outputs: the fp32 sums (OutPlain) and binary16 of
 // act(sum + bias) (OutFused, the GCN layer of Section 4.4).
 #include <hip/hip_runtime.h>
@@ -27,19 +28,22 @@ namespace rsh {
 // a turn through the team's LDS stage; lane-owned pieces would make every store a half-written
 // 32-byte sector, which the streaming path handles at a third of the rate.
 // A partial panel (PARTIAL: the last one of a width that is not a multiple of the panel) has `live` features, an
-// even number from 8 on.  Its last lane takes the eight features that end with the row, so that no lane reads
-// past the row; lanes behind it repeat that piece, and pieces past the last feature are not stored.
+// even number from 8 on; where the rows of B are the padded copy and longer than those of C (OUT::kAny), any number
+// from 1 on.  Its last lane takes the eight features that end with the row of B, so that no lane reads past the
+// row; lanes behind it repeat that piece, and pieces past the last feature are not stored.
 template <int TPR, bool PARTIAL>
-__device__ __forceinline__ int lane_features(int live, int tl) { return PARTIAL ? min(8 * tl, live - 8) : 8 * tl; }
-template <bool PARTIAL>
+__device__ __forceinline__ int lane_features(int live_b, int tl) { return PARTIAL ? min(8 * tl, live_b - 8) : 8 * tl; }
+template <bool PARTIAL, bool ANY>
 __device__ __forceinline__ void store_piece(float* out_row, int live, int f, float4_t v) {
     if (!PARTIAL || f + 4 <= live) store_c_streaming(out_row + f, v);
+    else if constexpr (ANY) store_tail(out_row + f, live - f, v);
     else if (f < live) __builtin_nontemporal_store((float2_t){v[0], v[1]}, reinterpret_cast<float2_a4*>(out_row + f));
 }
-template <int TPR, bool PARTIAL>
-__device__ __forceinline__ void store_row_streaming(float* out_row, const float (&acc)[8], float* stage, int tl, int live) {
+// lane_f: lane_features of this lane
+template <int TPR, bool PARTIAL, bool ANY>
+__device__ __forceinline__ void store_row_streaming(float* out_row, const float (&acc)[8], float* stage, int tl, int lane_f, int live) {
     if constexpr (PARTIAL) {
-        float2_t* to = reinterpret_cast<float2_t*>(stage + lane_features<TPR, true>(live, tl));
+        float2_t* to = reinterpret_cast<float2_t*>(stage + lane_f);
 #pragma unroll
         for (int i = 0; i < 4; ++i) to[i] = (float2_t){acc[2 * i], acc[2 * i + 1]};
     } else {
@@ -48,26 +52,27 @@ __device__ __forceinline__ void store_row_streaming(float* out_row, const float 
     }
     const float4_t v0 = *reinterpret_cast<const float4_t*>(stage + 4 * tl);
     const float4_t v1 = *reinterpret_cast<const float4_t*>(stage + 4 * TPR + 4 * tl);
-    store_piece<PARTIAL>(out_row, live, 4 * tl, v0);
-    store_piece<PARTIAL>(out_row, live, 4 * TPR + 4 * tl, v1);
+    store_piece<PARTIAL, ANY>(out_row, live, 4 * tl, v0);
+    store_piece<PARTIAL, ANY>(out_row, live, 4 * TPR + 4 * tl, v1);
 }
 
 // A team's finished row `row` of C (nv features), panel starting at feature `panel`.  In binary16 a lane's
 // eight features are one 16-byte piece and the team's pieces are consecutive, so the row
 // leaves as one store of whole lines without a turn through LDS.
-template <int TPR, bool PARTIAL>
-__device__ __forceinline__ void emit_row(const OutPlain& o, size_t row, int nv, int panel, const float (&acc)[8],
-                                         float* stage, int tl) {
-    store_row_streaming<TPR, PARTIAL>(o.C + row * nv + panel, acc, stage, tl, nv - panel);
+template <int TPR, bool PARTIAL, bool ANY>
+__device__ __forceinline__ void emit_row(const OutPlainT<ANY>& o, size_t row, int nv, int panel, const float (&acc)[8],
+                                         float* stage, int tl, int lane_f) {
+    store_row_streaming<TPR, PARTIAL, ANY>(o.C + row * nv + panel, acc, stage, tl, lane_f, nv - panel);
 }
-template <int TPR, bool PARTIAL>
-__device__ __forceinline__ void emit_row(const OutFused& o, size_t row, int nv, int panel, const float (&acc)[8],
-                                         float*, int tl) {
+template <int TPR, bool PARTIAL, bool ANY>
+__device__ __forceinline__ void emit_row(const OutFusedT<ANY>& o, size_t row, int nv, int panel, const float (&acc)[8],
+                                         float*, int tl, int lane_f) {
     if (PARTIAL && panel + 8 * tl >= nv) return;   // lane past the last feature of a partial panel
-    const int f = panel + lane_features<TPR, PARTIAL>(nv - panel, tl);
-    const uint2_t lo = finish4(o, f, (float4_t){acc[0], acc[1], acc[2], acc[3]});
-    const uint2_t hi = finish4(o, f + 4, (float4_t){acc[4], acc[5], acc[6], acc[7]});
-    __builtin_nontemporal_store((uint4_t){lo[0], lo[1], hi[0], hi[1]}, reinterpret_cast<uint4_a4*>(o.C + row * nv + f));
+    const int f = panel + lane_f;
+    const int end = PARTIAL ? nv : 0x7fffffff;   // full panels carry no checks
+    const uint2_t lo = finish4(o, f, end, (float4_t){acc[0], acc[1], acc[2], acc[3]});
+    const uint2_t hi = finish4(o, f + 4, end, (float4_t){acc[4], acc[5], acc[6], acc[7]});
+    store_halves(o, row, nv, f, end, (uint4_t){lo[0], lo[1], hi[0], hi[1]});
 }
 
 // ---------------------------------------------------------------------------
@@ -127,7 +132,7 @@ template <class OUT>
 struct ShortRowState {
     const OUT& out;
     float* stage;    // the team's LDS stage
-    int nv, panel, tl, L, k, rq;
+    int nv, panel, tl, lane_f, L, k, rq;
 };
 
 template <int U, int TPR, bool PARTIAL, class OUT>
@@ -154,7 +159,7 @@ __device__ __forceinline__ void short_rows_group(const BRows& Bp, int my_col, fl
             st.k = 0;
             const int row = shfl_i32(my_row, team_base + st.rq);
             ++st.rq;
-            if (row >= 0) emit_row<TPR, PARTIAL>(st.out, (size_t)row, st.nv, st.panel, acc, st.stage, st.tl);
+            if (row >= 0) emit_row<TPR, PARTIAL>(st.out, (size_t)row, st.nv, st.panel, acc, st.stage, st.tl, st.lane_f);
 #pragma unroll
             for (int i = 0; i < 8; ++i) acc[i] = 0.f;
         }
@@ -180,8 +185,8 @@ __device__ __forceinline__ void gather_steps(const BRows& Bp, int my_col, float 
 // PARTIAL: the panel (there is one, the last) holds fewer than 8 * TPR features.  Full panels carry no checks.
 // N: features of a partial row in scratch; nb, nv: of a row of B and of C.
 template <int TPR, class OUT, bool PARTIAL>
-__global__ __launch_bounds__(64 * kWavesPerBlock) __attribute__((amdgpu_waves_per_eu(8, 8))) void rsh_irregular_kernel(
-    const uint4* __restrict__ waves, XcdSplit xs,
+__device__ __forceinline__ void irregular_body(
+    const uint4* __restrict__ waves, const XcdSplit& xs,
     const int32_t* __restrict__ irr_row, const int32_t* __restrict__ irr_col,
     const uint16_t* __restrict__ irr_val, const __half* __restrict__ B, const OUT out,
     float* __restrict__ scratch, int N, int nb, int nv, int feature0) {
@@ -198,8 +203,8 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) __attribute__((amdgpu_waves_pe
     const uint32_t start = __builtin_amdgcn_readfirstlane(d.x), count = __builtin_amdgcn_readfirstlane(d.y);
     const uint32_t dst = __builtin_amdgcn_readfirstlane(d.z), info = __builtin_amdgcn_readfirstlane(d.w);
     const uint32_t kind = info & kWaveKindMask;
-    const int live = nv - panel;
-    const BRows Bp{reinterpret_cast<const char*>(B + panel), 2u * (uint32_t)nb, 2u * (uint32_t)lane_features<TPR, PARTIAL>(live, tl)};
+    const int live = nv - panel, lane_f = lane_features<TPR, PARTIAL>(nb - panel, tl);
+    const BRows Bp{reinterpret_cast<const char*>(B + panel), 2u * (uint32_t)nb, 2u * (uint32_t)lane_f};
 
     float acc[8];
 #pragma unroll
@@ -208,11 +213,11 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) __attribute__((amdgpu_waves_pe
     if (kind == kWaveZeroRows) {
         for (uint32_t q = team; q < count; q += G) {
             if constexpr (OUT::kFused) {
-                emit_row<TPR, PARTIAL>(out, (size_t)irr_row[dst + q], nv, panel, acc, stage, tl);   // act(bias)
+                emit_row<TPR, PARTIAL>(out, (size_t)irr_row[dst + q], nv, panel, acc, stage, tl, lane_f);   // act(bias)
             } else {
                 float* o = out.C + (size_t)irr_row[dst + q] * nv + panel;
-                store_piece<PARTIAL>(o, live, 4 * tl, (float4_t){0.f, 0.f, 0.f, 0.f});
-                store_piece<PARTIAL>(o, live, 4 * TPR + 4 * tl, (float4_t){0.f, 0.f, 0.f, 0.f});
+                store_piece<PARTIAL, OUT::kAny>(o, live, 4 * tl, (float4_t){0.f, 0.f, 0.f, 0.f});
+                store_piece<PARTIAL, OUT::kAny>(o, live, 4 * TPR + 4 * tl, (float4_t){0.f, 0.f, 0.f, 0.f});
             }
         }
         return;
@@ -229,7 +234,7 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) __attribute__((amdgpu_waves_pe
         const int my_row = tl < n_rows_mine ? irr_row[dst + q0 + tl] : -1;
         // R rows of L entries back to back: the loads of up to eight steps are in flight together,
         // whatever rows they belong to; after every L consumed steps a row is complete and stored
-        ShortRowState<OUT> st{out, stage, nv, panel, tl, L, 0, 0};
+        ShortRowState<OUT> st{out, stage, nv, panel, tl, lane_f, L, 0, 0};
         const int steps = R * L;
         int j = 0;
         for (; j + 8 <= steps; j += 8) short_rows_group<8, TPR, PARTIAL>(Bp, my_col, my_val, my_row, team_base, j, acc, st);
@@ -266,14 +271,31 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) __attribute__((amdgpu_waves_pe
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] = sum_over_teams<TPR>(acc[i], lane);
     if (team != 0) return;
-    if constexpr (OUT::kFused) {
-        if (info & kWaveToScratch) store_row_streaming<TPR, PARTIAL>(scratch + (size_t)dst * N + panel, acc, stage, tl, live);
-        else emit_row<TPR, PARTIAL>(out, (size_t)dst, nv, panel, acc, stage, tl);
+    if constexpr (OUT::kFused || OUT::kAny) {
+        // rows of scratch are as long as the rows of B or longer
+        if (info & kWaveToScratch) store_row_streaming<TPR, PARTIAL, false>(scratch + (size_t)dst * N + panel, acc, stage, tl, lane_f, nb - panel);
+        else emit_row<TPR, PARTIAL>(out, (size_t)dst, nv, panel, acc, stage, tl, lane_f);
     } else {
-        store_row_streaming<TPR, PARTIAL>((info & kWaveToScratch) ? scratch + (size_t)dst * N + panel : out.C + (size_t)dst * nv + panel, acc,
-                                          stage, tl, live);
+        store_row_streaming<TPR, PARTIAL, false>((info & kWaveToScratch) ? scratch + (size_t)dst * N + panel : out.C + (size_t)dst * nv + panel, acc,
+                                                 stage, tl, lane_f, live);
     }
 }
+
+#define RSH_IRREGULAR_PARAMS                                                                                                              \
+    const uint4 *__restrict__ waves, XcdSplit xs, const int32_t *__restrict__ irr_row, const int32_t *__restrict__ irr_col,               \
+        const uint16_t *__restrict__ irr_val, const __half *__restrict__ B, const OUT out, float *__restrict__ scratch, int N, int nb,    \
+        int nv, int feature0
+template <int TPR, class OUT, bool PARTIAL>
+__global__ __launch_bounds__(64 * kWavesPerBlock) __attribute__((amdgpu_waves_per_eu(8, 8))) void rsh_irregular_kernel(RSH_IRREGULAR_PARAMS) {
+    static_assert(!OUT::kAny);
+    irregular_body<TPR, OUT, PARTIAL>(waves, xs, irr_row, irr_col, irr_val, B, out, scratch, N, nb, nv, feature0);
+}
+template <int TPR, class OUT, bool PARTIAL>
+__global__ __launch_bounds__(64 * kWavesPerBlock) __attribute__((amdgpu_waves_per_eu(7, 7))) void rsh_residual_any_kernel(RSH_IRREGULAR_PARAMS) {
+    static_assert(OUT::kAny);
+    irregular_body<TPR, OUT, PARTIAL>(waves, xs, irr_row, irr_col, irr_val, B, out, scratch, N, nb, nv, feature0);
+}
+#undef RSH_IRREGULAR_PARAMS
 
 // ---------------------------------------------------------------------------
 // Dense fragments.  One wave per work item (a window or a bounded run of its
@@ -322,8 +344,8 @@ struct TileGeom {
 // (v_mfma_f32_16x16x32_f16, 8 cells per lane: lane l holds k = 8*(l/16) .. 8*(l/16)+7, fed by two
 // transposing reads four staged rows apart).
 template <int NCH, int NW, int D, int KT, class OUT>
-__global__ __launch_bounds__(NW == 1 ? 64 * kWavesPerBlock : 64 * NW) void rsh_tile_kernel(
-    const uint4* __restrict__ items, XcdSplit xs,
+__device__ __forceinline__ void tile_body(
+    const uint4* __restrict__ items, const XcdSplit& xs,
     const int32_t* __restrict__ win_row, const int32_t* __restrict__ tile_colid,
     const uint64_t* __restrict__ tile_mask, const uint32_t* __restrict__ tile_val_off,
     const uint16_t* __restrict__ tile_val, const __half* __restrict__ B, const OUT out,
@@ -535,7 +557,7 @@ __global__ __launch_bounds__(NW == 1 ? 64 * kWavesPerBlock : 64 * NW) void rsh_t
         _Float16* so = sb0 + (NW == 1 ? 0 : sub * 16 * LDB);
 #pragma unroll
         for (int c = 0; c < NCH; ++c)
-            *reinterpret_cast<uint2_t*>(so + m * LDB + 16 * c + 4 * q) = finish4(out, panel + 16 * c + 4 * q, acc[c]);
+            *reinterpret_cast<uint2_t*>(so + m * LDB + 16 * c + 4 * q) = finish4(out, panel + 16 * c + 4 * q, nv, acc[c]);
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
         __builtin_amdgcn_wave_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
@@ -547,7 +569,7 @@ __global__ __launch_bounds__(NW == 1 ? 64 * kWavesPerBlock : 64 * NW) void rsh_t
             const int prow = shfl_i32(row, pr);
             if (piece < kPieces && prow >= 0) {
                 const uint4_t v = *reinterpret_cast<const uint4_t*>(so + pr * LDB + 8 * pc);
-                __builtin_nontemporal_store(v, reinterpret_cast<uint4_a4*>(out.C + (size_t)prow * nv + panel + 8 * pc));
+                store_halves(out, (size_t)prow, nv, panel + 8 * pc, nv, v);
             }
         }
     } else if constexpr (NCH % 2 == 0) {
@@ -557,8 +579,7 @@ __global__ __launch_bounds__(NW == 1 ? 64 * kWavesPerBlock : 64 * NW) void rsh_t
         const bool low = (lane & 8) == 0;
         const int row_other = swap_lane8(row);
         const int row_a = low ? row : row_other, row_b = low ? row_other : row;
-        float* out_a = out.C + (size_t)row_a * nv + panel + 4 * q + (low ? 0 : 16);
-        float* out_b = out.C + (size_t)row_b * nv + panel + 4 * q + (low ? 0 : 16);
+        const int f = panel + 4 * q + (low ? 0 : 16);
 #pragma unroll
         for (int c = 0; c < NCH; c += 2) {
             float4_t send, recv;
@@ -572,33 +593,49 @@ __global__ __launch_bounds__(NW == 1 ? 64 * kWavesPerBlock : 64 * NW) void rsh_t
                 va[i] = low ? acc[c][i] : recv[i];
                 vb[i] = low ? recv[i] : acc[c + 1][i];
             }
-            if (row_a >= 0) store_c_streaming(out_a + 16 * c, va);
-            if (row_b >= 0) store_c_streaming(out_b + 16 * c, vb);
+            if (row_a >= 0) tile_store(out, (size_t)row_a, nv, f + 16 * c, va);
+            if (row_b >= 0) tile_store(out, (size_t)row_b, nv, f + 16 * c, vb);
         }
     } else {
         if (row < 0) return;
-        float* o = out.C + (size_t)row * nv + panel + 4 * q;
 #pragma unroll
-        for (int c = 0; c < NCH; ++c) store_c_streaming(o + 16 * c, acc[c]);
+        for (int c = 0; c < NCH; ++c) tile_store(out, (size_t)row, nv, panel + 4 * q + 16 * c, acc[c]);
     }
     keep_streaming_hint();
 }
+
+#define RSH_TILE_PARAMS                                                                                                                   \
+    const uint4 *__restrict__ items, XcdSplit xs, const int32_t *__restrict__ win_row, const int32_t *__restrict__ tile_colid,            \
+        const uint64_t *__restrict__ tile_mask, const uint32_t *__restrict__ tile_val_off, const uint16_t *__restrict__ tile_val,         \
+        const __half *__restrict__ B, const OUT out, float *__restrict__ scratch, int N, int nb, int nv, int feature0
+template <int NCH, int NW, int D, int KT, class OUT>
+__global__ __launch_bounds__(NW == 1 ? 64 * kWavesPerBlock : 64 * NW) void rsh_tile_kernel(RSH_TILE_PARAMS) {
+    static_assert(!OUT::kAny);
+    tile_body<NCH, NW, D, KT>(items, xs, win_row, tile_colid, tile_mask, tile_val_off, tile_val, B, out, scratch, N, nb, nv, feature0);
+}
+template <int NCH, int NW, int D, int KT, class OUT>
+__global__ __launch_bounds__(NW == 1 ? 64 * kWavesPerBlock : 64 * NW) void rsh_fragment_any_kernel(RSH_TILE_PARAMS) {
+    static_assert(OUT::kAny);
+    tile_body<NCH, NW, D, KT>(items, xs, win_row, tile_colid, tile_mask, tile_val_off, tile_val, B, out, scratch, N, nb, nv, feature0);
+}
+#undef RSH_TILE_PARAMS
 
 // ---------------------------------------------------------------------------
 // Combine: C[row] = sum over parts of scratch[first + p*stride], in a fixed order
 // (four interleaved running sums, then a fixed tree), one wave per entry.
 // ---------------------------------------------------------------------------
 template <class OUT>
-__global__ __launch_bounds__(64 * kWavesPerBlock) void rsh_combine_kernel(
-    const uint4* __restrict__ entries, uint32_t n_entries, const float* __restrict__ scratch,
-    const OUT out, int N, int nv) {
+__device__ __forceinline__ void combine_body(const uint4* __restrict__ entries, uint32_t n_entries, const float* __restrict__ scratch,
+                                             const OUT& out, int N, int nv) {
     const int lane = threadIdx.x & 63;
     const uint32_t e = __builtin_amdgcn_readfirstlane(blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6));
     if (e >= n_entries) return;
     const uint4 en = entries[e];
     const uint32_t row = en.x, first = en.y, parts = en.z, stride = en.w;
     for (int f0 = lane * 4; f0 < nv; f0 += 256) {
-        const int f = min(f0, nv - 4);   // four features that end with the row where it is not a multiple of four
+        // four features that end with the row where it is not a multiple of four; rows of scratch that are longer
+        // than those of C (kAny) are multiples of 16
+        const int f = OUT::kAny ? f0 : min(f0, nv - 4);
         float4_t s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0, s2 = s0, s3 = s0;
         const auto part = [&](uint32_t p) { return *reinterpret_cast<const float4_a4*>(scratch + ((size_t)first + (size_t)p * stride) * N + f); };
         uint32_t p = 0;
@@ -611,9 +648,21 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void rsh_combine_kernel(
         }
         for (; p < parts; ++p) s0 += part(p);
         const float4_t o = (s0 + s1) + (s2 + s3);
-        if constexpr (OUT::kFused) __builtin_nontemporal_store(finish4(out, f, o), reinterpret_cast<uint2_a4*>(out.C + (size_t)row * nv + f));
+        if constexpr (OUT::kAny) panel_store(out, (size_t)row, nv, f, o);
+        else if constexpr (OUT::kFused) __builtin_nontemporal_store(finish4(out, f, nv, o), reinterpret_cast<uint2_a4*>(out.C + (size_t)row * nv + f));
         else store_c_streaming(out.C + (size_t)row * nv + f, o);
     }
+}
+
+template <class OUT>
+__global__ __launch_bounds__(64 * kWavesPerBlock) void rsh_combine_kernel(const uint4* __restrict__ entries, uint32_t n_entries,
+                                                                          const float* __restrict__ scratch, const OUT out, int N, int nv) {
+    combine_body(entries, n_entries, scratch, out, N, nv);
+}
+template <class OUT>
+__global__ __launch_bounds__(64 * kWavesPerBlock) void rsh_sum_any_kernel(const uint4* __restrict__ entries, uint32_t n_entries,
+                                                                          const float* __restrict__ scratch, const OUT out, int N, int nv) {
+    combine_body(entries, n_entries, scratch, out, N, nv);
 }
 
 // ---------------------------------------------------------------------------
@@ -626,78 +675,40 @@ __global__ __launch_bounds__(256) void rsh_copy_probe_kernel(const uint4* __rest
 }
 
 // ---------------------------------------------------------------------------
-// Feature widths the kernels do not run at: the kernels above work on whole 16-byte pieces of
-// rows whose length is a multiple of 32 bytes, so such operands are copied row by row into
-// (B, bias) and out of (C) plan-owned buffers of the run width.  A lane moves one vector per
-// step; the vector is the widest of 16, 8, 4, 2 bytes that divides a narrow row and the
-// caller's alignment (the wide rows are multiples of 32 bytes at 256-byte aligned bases).
+// Rows of B that the kernels do not read as they are (an odd number of features, fewer than 16, a run width the
+// caller chose, or an address that is not a multiple of 4) are copied into the plan's buffer of the run width; the
+// result needs no copy, whatever its width.  One thread makes one 16-byte piece of a wide row, from one load at
+// whatever alignment the narrow row has (2 bytes: 59 cycles of the vector memory path per wave instead of 16,
+// which is still twice what memory delivers); only the piece that holds the row's end is put together from
+// single elements.  One thread per element, with a 64-bit division each, took 12.6 us for 512000 rows of 3 -> 16.
 // ---------------------------------------------------------------------------
-template <class VT>
-__global__ __launch_bounds__(256) void rsh_widen_rows_kernel(const VT* __restrict__ src, VT* __restrict__ dst, size_t rows, uint32_t n, uint32_t n_wide) {
-    const size_t total = rows * (size_t)n_wide, stride = (size_t)gridDim.x * blockDim.x;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += stride) {
-        const size_t r = i / n_wide;
-        const uint32_t j = (uint32_t)(i - r * n_wide);
-        VT v = {};
-        if (j < n) v = src[r * n + j];
-        dst[i] = v;
+struct __attribute__((packed, aligned(2))) Halves8 {
+    uint4_t v;
+};
+__global__ __launch_bounds__(256) void rsh_widen_rows_kernel(const uint16_t* __restrict__ src, uint4_t* __restrict__ dst, uint32_t n_pieces,
+                                                             uint32_t n, uint32_t pieces_per_row) {
+    const uint32_t i = blockIdx.x * 256u + threadIdx.x;
+    if (i >= n_pieces) return;
+    const uint32_t r = i / pieces_per_row, j = 8u * (i - r * pieces_per_row);
+    const uint16_t* from = src + (size_t)r * n + j;
+    uint4_t v = {0, 0, 0, 0};
+    if (j + 8u <= n) {
+        v = reinterpret_cast<const Halves8*>(from)->v;
+    } else if (j < n) {
+#pragma unroll
+        for (uint32_t k = 0; k < 7; ++k) {
+            const uint32_t x = j + k < n ? from[k] : 0u;
+            v[k / 2] |= x << (16 * (k & 1));
+        }
     }
-}
-template <class VT>
-__global__ __launch_bounds__(256) void rsh_narrow_rows_kernel(const VT* __restrict__ src, VT* __restrict__ dst, size_t rows, uint32_t n, uint32_t n_wide) {
-    const size_t total = rows * (size_t)n, stride = (size_t)gridDim.x * blockDim.x;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total; i += stride) {
-        const size_t r = i / n;
-        const uint32_t j = (uint32_t)(i - r * n);
-        dst[i] = src[r * n_wide + j];
-    }
+    dst[i] = v;
 }
 
-static unsigned copy_blocks(size_t vectors) { return (unsigned)std::min<size_t>((vectors + 255) / 256, 256 * 64); }
-
-// widest vector (bytes) that divides a narrow row of `row_bytes` and the alignment of `narrow`
-static int copy_vector_bytes(const void* narrow, size_t row_bytes, int elem) {
-    int v = 16;
-    while (v > elem && (row_bytes % (size_t)v || (uintptr_t)narrow % (uintptr_t)v)) v /= 2;
-    return v;
-}
-
-template <class VT>
-static void widen_t(const void* src, void* dst, int64_t rows, size_t row_bytes, size_t wide_bytes, hipStream_t st) {
-    const uint32_t n = (uint32_t)(row_bytes / sizeof(VT)), nw = (uint32_t)(wide_bytes / sizeof(VT));
-    hipLaunchKernelGGL(rsh_widen_rows_kernel<VT>, dim3(copy_blocks((size_t)rows * nw)), dim3(256), 0, st,
-                       (const VT*)src, (VT*)dst, (size_t)rows, n, nw);
-}
-template <class VT>
-static void narrow_t(const void* src, void* dst, int64_t rows, size_t row_bytes, size_t wide_bytes, hipStream_t st) {
-    const uint32_t n = (uint32_t)(row_bytes / sizeof(VT)), nw = (uint32_t)(wide_bytes / sizeof(VT));
-    hipLaunchKernelGGL(rsh_narrow_rows_kernel<VT>, dim3(copy_blocks((size_t)rows * n)), dim3(256), 0, st,
-                       (const VT*)src, (VT*)dst, (size_t)rows, n, nw);
-}
-
-int launch_widen_rows(const void* src, void* dst, int64_t rows, int n, int n_pad, int elem, void* stream) {
+int launch_widen_rows(const void* src, void* dst, int64_t rows, int n, int n_wide, void* stream) {
     if (rows <= 0) return RSH_OK;
-    const size_t rb = (size_t)n * elem, wb = (size_t)n_pad * elem;
-    hipStream_t st = (hipStream_t)stream;
-    switch (copy_vector_bytes(src, rb, elem)) {
-        case 16: widen_t<uint4_t>(src, dst, rows, rb, wb, st); break;
-        case 8: widen_t<uint2_t>(src, dst, rows, rb, wb, st); break;
-        case 4: widen_t<uint32_t>(src, dst, rows, rb, wb, st); break;
-        default: widen_t<uint16_t>(src, dst, rows, rb, wb, st); break;
-    }
-    return hipGetLastError() == hipSuccess ? RSH_OK : RSH_ERR_HIP;
-}
-
-int launch_narrow_rows(const void* src, void* dst, int64_t rows, int n, int n_pad, int elem, void* stream) {
-    if (rows <= 0) return RSH_OK;
-    const size_t rb = (size_t)n * elem, wb = (size_t)n_pad * elem;
-    hipStream_t st = (hipStream_t)stream;
-    switch (copy_vector_bytes(dst, rb, elem)) {
-        case 16: narrow_t<uint4_t>(src, dst, rows, rb, wb, st); break;
-        case 8: narrow_t<uint2_t>(src, dst, rows, rb, wb, st); break;
-        case 4: narrow_t<uint32_t>(src, dst, rows, rb, wb, st); break;
-        default: narrow_t<uint16_t>(src, dst, rows, rb, wb, st); break;
-    }
+    const uint32_t ppr = (uint32_t)n_wide / 8u, pieces = (uint32_t)rows * ppr;   // rows * 2 n_wide < 2^32
+    hipLaunchKernelGGL(rsh_widen_rows_kernel, dim3((pieces + 255) / 256), dim3(256), 0, (hipStream_t)stream, (const uint16_t*)src, (uint4_t*)dst,
+                       pieces, (uint32_t)n, ppr);
     return hipGetLastError() == hipSuccess ? RSH_OK : RSH_ERR_HIP;
 }
 
@@ -776,8 +787,8 @@ static inline uint32_t grid_for(const XcdSplit& xs) {
     return 8u * ((longest + kWavesPerBlock - 1) / kWavesPerBlock);
 }
 
-// Feature widths of a launch: `nb` of a row of B, `nv` of a row of C (equal, or of the padded copies).  Both are
-// even and at least 16; partial sums have rows of geo.N >= nv.
+// Feature widths of a launch: `nb` of a row of B, `nv` of a row of C.  Equal, even and at least 16; or (OUT::kAny)
+// nb is the padded width, a multiple of 16, and nv any width up to it.  Partial sums have rows of geo.N >= nb.
 // Full panels in one launch; a last partial panel (nv not a multiple of the panel) in a launch of its own, which
 // starts early enough to hold eight features (those it shares with the panel before come out the same twice).
 template <int TPR, class OUT>
@@ -788,8 +799,14 @@ static void launch_irregular_t(const DevicePlan& d, const void* B, const OUT& ou
                            0, st, (const uint4*)d.irr_wave, d.irr_split, d.irr_row, d.irr_col, d.irr_val, (const __half*)B, out,
                            d.scratch, d.geo.N, nb, nv, feature0);
     };
-    if (full > 0) launch(rsh_irregular_kernel<TPR, OUT, false>, full, 0);
-    if (nv % d.geo.irr_panel) launch(rsh_irregular_kernel<TPR, OUT, true>, 1, std::min(full * d.geo.irr_panel, nv - 8));
+    const int rest0 = std::min(full * d.geo.irr_panel, nb - 8);
+    if constexpr (OUT::kAny) {
+        if (full > 0) launch(rsh_residual_any_kernel<TPR, OUT, false>, full, 0);
+        if (nv % d.geo.irr_panel) launch(rsh_residual_any_kernel<TPR, OUT, true>, 1, rest0);
+    } else {
+        if (full > 0) launch(rsh_irregular_kernel<TPR, OUT, false>, full, 0);
+        if (nv % d.geo.irr_panel) launch(rsh_irregular_kernel<TPR, OUT, true>, 1, rest0);
+    }
 }
 
 // `panels` panels of 16 * NCH features starting at feature `feature0`
@@ -799,9 +816,12 @@ static void launch_tile_t(const DevicePlan& d, const void* B, const OUT& out, hi
     uint32_t longest = 0;
     for (int x = 0; x < 8; ++x) longest = std::max(longest, d.tile_split.start[x + 1] - d.tile_split.start[x]);
     dim3 grid(8u * ((longest + items_per_block - 1) / items_per_block), (unsigned)panels);
-    hipLaunchKernelGGL((rsh_tile_kernel<NCH, NW, D, KT, OUT>), grid, dim3(NW == 1 ? 64 * kWavesPerBlock : 64 * NW), 0, st,
-                       (const uint4*)d.tile_item, d.tile_split, d.win_row, d.tile_colid, d.tile_mask, d.tile_val_off,
-                       d.tile_val, (const __half*)B, out, d.scratch, d.geo.N, nb, nv, feature0);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(NW == 1 ? 64 * kWavesPerBlock : 64 * NW), 0, st, (const uint4*)d.tile_item, d.tile_split, d.win_row,
+                           d.tile_colid, d.tile_mask, d.tile_val_off, d.tile_val, (const __half*)B, out, d.scratch, d.geo.N, nb, nv, feature0);
+    };
+    if constexpr (OUT::kAny) launch(rsh_fragment_any_kernel<NCH, NW, D, KT, OUT>);
+    else launch(rsh_tile_kernel<NCH, NW, D, KT, OUT>);
 }
 
 // Fragments in flight per thread: one for 16-row windows, two when the waves of a window share
@@ -850,9 +870,11 @@ static int launch_all(const DevicePlan& d, const void* B, const OUT& out, int nb
         // As many panels of the widest kind (256, 128, ... 16 features) as fit, and for the rest one of the smallest
         // kind that holds it, placed so that it ends with the row: N = 160 takes 128 + 32, N = 100 takes 64 and
         // features 36 .. 99 (those it shares with the panel before come out the same twice).
+        // With rows of B longer than those of C the panels cover the next multiple of 16.
+        const int cover = OUT::kAny ? (nv + 15) / 16 * 16 : nv;
         int wide = 16;
-        while (wide < 256 && 2 * wide <= nv) wide *= 2;
-        const int rest = nv % wide;
+        while (wide < 256 && 2 * wide <= cover) wide *= 2;
+        const int rest = cover % wide;
         int last = 16;
         while (last < rest) last *= 2;
         auto launch = [&](int features, int feature0, int panels) {
@@ -864,8 +886,8 @@ static int launch_all(const DevicePlan& d, const void* B, const OUT& out, int nb
                 default: return launch_tile_nw<16>(d, B, out, st, nb, nv, feature0, panels);
             }
         };
-        rc = launch(wide, 0, nv / wide);
-        if (rc == RSH_OK && rest > 0) rc = launch(last, nv - last, 1);
+        rc = launch(wide, 0, cover / wide);
+        if (rc == RSH_OK && rest > 0) rc = launch(last, cover - last, 1);
         if (rc != RSH_OK) return rc;
     }
     if (forked && hipEventRecord((hipEvent_t)d.ev_join, (hipStream_t)d.side) != hipSuccess) return RSH_ERR_HIP;
@@ -884,14 +906,19 @@ static int launch_all(const DevicePlan& d, const void* B, const OUT& out, int nb
     if (forked && hipStreamWaitEvent(caller, (hipEvent_t)d.ev_join, 0) != hipSuccess) return RSH_ERR_HIP;
     if (d.n_combine > 0) {
         const uint32_t n = (uint32_t)d.n_combine;
-        hipLaunchKernelGGL(rsh_combine_kernel<OUT>, dim3((n + kWavesPerBlock - 1) / kWavesPerBlock), dim3(64 * kWavesPerBlock),
-                           0, st, (const uint4*)d.combine, n, d.scratch, out, d.geo.N, nv);
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3((n + kWavesPerBlock - 1) / kWavesPerBlock), dim3(64 * kWavesPerBlock), 0, st, (const uint4*)d.combine, n,
+                               d.scratch, out, d.geo.N, nv);
+        };
+        if constexpr (OUT::kAny) launch(rsh_sum_any_kernel<OUT>);
+        else launch(rsh_combine_kernel<OUT>);
     }
     mark(3);
     return hipGetLastError() == hipSuccess ? RSH_OK : RSH_ERR_HIP;
 }
 
 int launch_spmm(const DevicePlan& d, const void* B, void* C, int nb, int nv, void* stream, void* const* events) {
+    if (nb != nv) return launch_all(d, B, OutPlainT<true>{(float*)C}, nb, nv, stream, events);
     return launch_all(d, B, OutPlain{(float*)C}, nb, nv, stream, events);
 }
 
@@ -923,6 +950,7 @@ int static_scratch(float** ptr) {
 
 int launch_spmm_f16(const DevicePlan& d, const void* B, void* C16, const float* bias, int relu, int nb, int nv, void* stream,
                     void* const* events) {
+    if (nb != nv) return launch_all(d, B, OutFusedT<true>{(_Float16*)C16, bias, relu}, nb, nv, stream, events);
     return launch_all(d, B, OutFused{(_Float16*)C16, bias, relu}, nb, nv, stream, events);
 }
 

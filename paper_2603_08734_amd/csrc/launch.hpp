@@ -31,12 +31,10 @@ struct DevicePlan {
     int32_t* irr_row = nullptr;
     uint32_t* combine = nullptr;
     float* scratch = nullptr;
-    // feature widths that are not a multiple of 16 (n_user != geo.N): operands pass through these
-    // plan-owned buffers of the padded width
+    // rows of B that the kernels cannot read as they are pass through this plan-owned buffer of the run width
+    // (made where n_user != geo.N)
     int n_user = 0;
     void* b_pad = nullptr;      // binary16 [n_cols][geo.N]
-    void* c_pad = nullptr;      // fp32 (or binary16) [n_rows][geo.N]
-    float* bias_pad = nullptr;  // fp32 [geo.N]
     // optional second stream for the dense-fragment kernel (rsh_plan_opts_t::side_stream)
     void* side = nullptr;       // hipStream_t
     void* ev_fork = nullptr;    // hipEvent_t: caller's stream -> side stream
@@ -45,8 +43,8 @@ struct DevicePlan {
 
 // Enqueue the tile, irregular and combine kernels on `stream` (a hipStream_t).  When
 // `events` is not null it points at four hipEvent_t recorded before the tile kernel and
-// after each of the three kernels.  nb, nv: features of a row of B and of C, both even and at least 16
-// (or both geo.N).
+// after each of the three kernels.  nb, nv: features of a row of B and of C; equal, even and at least
+// 16, or nb == geo.N and nv < nb any number, C then aligned to its element only.
 int launch_spmm(const DevicePlan& d, const void* B_dev, void* C_dev, int nb, int nv, void* stream, void* const* events);
 
 // Plan upload, panel form: cell masks and dword counts of all units (then prefix-summed, total last), and with
@@ -64,10 +62,9 @@ int static_scratch(float** ptr);
 int launch_spmm_f16(const DevicePlan& d, const void* B_dev, void* C16_dev, const float* bias_dev, int relu, int nb,
                     int nv, void* stream, void* const* events);
 
-// Row-wise copies between a matrix of `n` columns and one of `n_pad` >= n columns (`elem` bytes per
-// element, 2 or 4): widen (pad columns become zero) and narrow (pad columns are dropped).
-int launch_widen_rows(const void* src, void* dst, int64_t rows, int n, int n_pad, int elem, void* stream);
-int launch_narrow_rows(const void* src, void* dst, int64_t rows, int n, int n_pad, int elem, void* stream);
+// Row-wise copy of a binary16 matrix of `n` columns into one of n_wide >= n columns, a multiple of 8, at a 16-byte
+// aligned address; the columns from n on become zero.
+int launch_widen_rows(const void* src, void* dst, int64_t rows, int n, int n_wide, void* stream);
 
 // Plain device-to-device copy of `bytes` (multiple of 16) used to calibrate traffic counters.
 int launch_copy_probe(const void* src_dev, void* dst_dev, size_t bytes, void* stream);

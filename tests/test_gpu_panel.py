@@ -82,3 +82,47 @@ def test_even_widths_without_copies(opts, N, fused):
     assert not np.isnan(got).any()
     assert np.all(np.abs(got - C_ref) <= bound)
     plan.destroy()
+
+
+# Odd widths, widths below 16 and operands aligned to their element only: B is copied to the run width, rows of C are
+# written as they are.  Rows end inside the pieces of 4 (fp32) and 8 (binary16) features, with one feature in the
+# last panel, and with whole panels; C and B begin one element past a 16-byte boundary, canaries stand on both sides
+# of C, and the bias ends with its allocation's last element.
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("N", [1, 2, 3, 5, 8, 15, 17, 33, 64, 65, 127, 129, 257])
+@pytest.mark.parametrize("opts", [dict(force_path=2), dict(force_path=2, window_rows=64, max_tiles_per_item=2),
+                                  dict(force_path=2, window_rows=128), dict(force_path=2, window_rows=256, max_tiles_per_item=3),
+                                  dict(force_path=1, max_nnz_per_slice=40), dict(force_path=1, xcd_partition_nnz=32)],
+                         ids=["tile", "w64", "w128", "w256", "residual", "xcd"])
+def test_rows_of_c_of_any_width_and_alignment(opts, N, fused):
+    import torch
+    from paper_2603_08734_amd import Plan
+    rng = np.random.default_rng(13)
+    dense = rng.random((90, 333)) < np.linspace(0.0, 0.4, 90)[:, None]     # row 0 is empty, rows of every length
+    r, c = np.nonzero(dense)
+    A = from_coo(r, c, rng.standard_normal(r.size), 90, 333)
+    print(f"case any width N={N} opts={opts} fused={fused}", flush=True)
+    run_width = N if N % 16 else N + 16     # a chosen run width takes multiples of 16 through the copy as well
+    plan = Plan(A.row_ptr, A.col_idx, A.val, A.n_cols, N, run_width=(run_width + 15) // 16 * 16, **opts)
+    B = dense_B(A.n_cols, N, "normal", seed=N)
+    Bd = torch.empty(A.n_cols * N + 1, dtype=torch.float16, device="cuda")[1:].view(A.n_cols, N)
+    Bd.copy_(torch.from_numpy(B.view(np.int16)).cuda().view(torch.float16))
+    C_ref, S, _ = oracle.spmm(A.row_ptr, A.col_idx, A.val, B)
+    dtype, pad = (torch.float16 if fused else torch.float32), 65
+    flat = torch.full((A.n_rows * N + 2 * pad,), float("nan"), dtype=dtype, device="cuda")
+    C = flat[pad:pad + A.n_rows * N].view(A.n_rows, N)
+    if fused:
+        bias = torch.from_numpy(rng.standard_normal(N).astype(np.float32)).cuda()
+        plan.spmm_f16(Bd, C, bias, relu=True)
+        C_ref = np.maximum(C_ref + bias.cpu().numpy().astype(np.float64), 0.0)
+        # the fp32 bound, the addition of the bias, one rounding to binary16
+        bound = 1e-4 * S + 2.0 ** -24 * np.abs(C_ref) + 2.0 ** -11 * np.abs(C_ref) * 1.001 + 2.0 ** -24
+    else:
+        plan.spmm(Bd, C)
+        bound = 1e-4 * S
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(flat[:pad]).all()) and bool(torch.isnan(flat[pad + A.n_rows * N:]).all()), "stores outside C"
+    got = C.cpu().numpy().astype(np.float64)
+    assert not np.isnan(got).any()
+    assert np.all(np.abs(got - C_ref) <= bound)
+    plan.destroy()
