@@ -234,6 +234,26 @@ int rsh_spmm_f16(const rsh_plan_t *plan, const void *B_dev, void *C16_dev, const
                  void *hip_stream);
 
 /*
+ * The dense half of a GCN layer on binary16 row-major device matrices with n > 0 rows, enqueued on hip_stream;
+ * fp32 sums, each result rounded once.  Widths d_in, d_out: RSH_DENSE_MIN .. RSH_DENSE_MAX, any number; no
+ * alignment beyond the element's.  work_dev: fp32 [RSH_GRADIENT_PARTS * d_in * d_out], rewritten by every call.
+ *   rsh_dense_forward   P = H W               H [n][d_in], W [d_in][d_out], P [n][d_out]
+ *   rsh_dense_backward  dH = dP W^T (NULL: not wanted; W may then be NULL), dW = H^T dP
+ *   rsh_act_backward    dZ = dY * (Y > 0) and dbias = column sums of dZ, for any width d > 0.  Y and dZ both NULL:
+ *                       no activation, dZ is dY.  dbias (fp32 [d], 4-byte aligned) NULL: not wanted, otherwise
+ *                       work_dev holds fp32 [RSH_GRADIENT_PARTS * d].
+ * RSH_ERR_NULL for a missing operand, RSH_ERR_BAD_OPTION for a size or alignment out of range.
+ */
+#define RSH_DENSE_MIN 8
+#define RSH_DENSE_MAX 64
+#define RSH_GRADIENT_PARTS 512
+int rsh_dense_forward(const void *H_dev, const void *W_dev, void *P_dev, int64_t n, int32_t d_in, int32_t d_out, void *hip_stream);
+int rsh_dense_backward(const void *H_dev, const void *W_dev, const void *dP_dev, void *dH_dev, void *dW_dev, float *work_dev, int64_t n,
+                       int32_t d_in, int32_t d_out, void *hip_stream);
+int rsh_act_backward(const void *dY_dev, const void *Y_dev, void *dZ_dev, float *dbias_dev, float *work_dev, int64_t n, int32_t d,
+                     void *hip_stream);
+
+/*
  * Same work as rsh_spmm, but brackets each kernel with HIP events on hip_stream,
  * waits for the stream, and reports the elapsed milliseconds of the tile kernel,
  * the irregular kernel and the combine kernel (0 for a kernel that was not

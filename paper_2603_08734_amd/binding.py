@@ -32,7 +32,8 @@ _ARRAY_DTYPES = {
 }
 
 EXPORTED_SYMBOLS = [
-    "rsh_plan_opts_default", "rsh_plan_create", "rsh_spmm", "rsh_spmm_noalloc", "rsh_spmm_f16", "rsh_spmm_profile", "rsh_copy_probe", "rsh_plan_destroy", "rsh_plan_stats",
+    "rsh_plan_opts_default", "rsh_plan_create", "rsh_spmm", "rsh_spmm_noalloc", "rsh_spmm_f16", "rsh_spmm_profile",
+    "rsh_dense_forward", "rsh_dense_backward", "rsh_act_backward", "rsh_copy_probe", "rsh_plan_destroy", "rsh_plan_stats",
     "rsh_plan_decode", "rsh_plan_row_order", "rsh_reorder_knn", "rsh_plan_array", "rsh_plan_teams_per_wave",
     "rsh_struct_sizes", "rsh_status_string", "rsh_last_hip_error",
 ]
@@ -113,6 +114,9 @@ def lib() -> ctypes.CDLL:
         L.rsh_spmm_noalloc.argtypes = [vp, vp, vp, vp]
         L.rsh_spmm_f16.argtypes = [vp, vp, vp, vp, i32, vp]
         L.rsh_spmm_profile.argtypes = [vp, vp, vp, vp, ctypes.POINTER(rsh_kernel_times_t)]
+        L.rsh_dense_forward.argtypes = [vp, vp, vp, ctypes.c_int64, i32, i32, vp]
+        L.rsh_dense_backward.argtypes = [vp, vp, vp, vp, vp, vp, ctypes.c_int64, i32, i32, vp]
+        L.rsh_act_backward.argtypes = [vp, vp, vp, vp, vp, ctypes.c_int64, i32, vp]
         L.rsh_copy_probe.argtypes = [vp, vp, ctypes.c_int64, vp]
         L.rsh_plan_destroy.argtypes = [vp]
         L.rsh_plan_stats.argtypes = [vp, ctypes.POINTER(rsh_plan_stats_t)]
@@ -155,6 +159,50 @@ def rsh_plan_opts_default() -> rsh_plan_opts_t:
     o = rsh_plan_opts_t()
     _check(lib().rsh_plan_opts_default(ctypes.byref(o)))
     return o
+
+
+DENSE_MIN, DENSE_MAX = 8, 64     # RSH_DENSE_MIN, RSH_DENSE_MAX
+GRADIENT_PARTS = 512             # RSH_GRADIENT_PARTS
+
+
+def _address(t):
+    return None if t is None else t.data_ptr()
+
+
+def dense_forward(H, W):
+    """P = H W (rsh_dense_forward); contiguous binary16 device tensors."""
+    import torch
+    (n, d_in), d_out = H.shape, W.shape[1]
+    P = torch.empty((n, d_out), dtype=torch.float16, device=H.device)
+    _check(lib().rsh_dense_forward(H.data_ptr(), W.data_ptr(), P.data_ptr(), n, d_in, d_out, torch.cuda.current_stream().cuda_stream))
+    return P
+
+
+def dense_backward(H, W, dP, want_dH: bool):
+    """(dP W^T or None, H^T dP) (rsh_dense_backward); contiguous binary16 device tensors."""
+    import torch
+    (n, d_in), d_out = H.shape, W.shape[1]
+    dH = torch.empty_like(H) if want_dH else None
+    dW = torch.empty_like(W)
+    work = torch.empty(GRADIENT_PARTS * d_in * d_out, dtype=torch.float32, device=H.device)
+    _check(lib().rsh_dense_backward(H.data_ptr(), W.data_ptr(), dP.data_ptr(), _address(dH), dW.data_ptr(), work.data_ptr(), n, d_in, d_out,
+                                    torch.cuda.current_stream().cuda_stream))
+    return dH, dW
+
+
+def act_backward(dY, Y, want_dbias: bool):
+    """(dZ, dbias or None) of Z -> Y = relu(Z), or of the identity where Y is None (rsh_act_backward);
+    contiguous binary16 device tensors."""
+    import torch
+    n, d = dY.shape
+    dZ = dY if Y is None else torch.empty_like(dY)
+    if Y is None and not want_dbias:
+        return dZ, None
+    dbias = torch.empty(d, dtype=torch.float32, device=dY.device) if want_dbias else None
+    work = torch.empty(GRADIENT_PARTS * d, dtype=torch.float32, device=dY.device) if want_dbias else None
+    _check(lib().rsh_act_backward(dY.data_ptr(), _address(Y), None if Y is None else dZ.data_ptr(), _address(dbias), _address(work), n, d,
+                                  torch.cuda.current_stream().cuda_stream))
+    return dZ, dbias
 
 
 def rsh_copy_probe(src, dst, nbytes: int, stream=None) -> None:

@@ -8,7 +8,7 @@ import subprocess
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "librsh.so")
-SOURCES = ["kernels.hip", "api.cpp", "planner.cpp", "reorder.cpp"]
+SOURCES = ["kernels.hip", "dense.hip", "api.cpp", "planner.cpp", "reorder.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
          # packed-fp32 VALU forms are switched off for device code on the test machines

@@ -3,6 +3,7 @@
 
 #include <chrono>
 #include <cstring>
+#include <initializer_list>
 #include <new>
 #include <string>
 
@@ -500,6 +501,40 @@ int rsh_spmm_profile(const rsh_plan_t* plan, const void* B_dev, void* C_dev, voi
     for (int i = 0; i < 4; ++i)
         if (ev[i]) (void)hipEventDestroy(ev[i]);
     return rc;
+}
+
+namespace {
+bool dense_widths_ok(int64_t n, int32_t d_in, int32_t d_out) {
+    return n > 0 && d_in >= RSH_DENSE_MIN && d_in <= RSH_DENSE_MAX && d_out >= RSH_DENSE_MIN && d_out <= RSH_DENSE_MAX;
+}
+bool aligned_to(std::initializer_list<const void*> ptrs, uintptr_t bytes) {
+    for (const void* p : ptrs)
+        if ((uintptr_t)p & (bytes - 1)) return false;
+    return true;
+}
+int launch_status(int rc) {
+    if (rc == RSH_ERR_HIP) g_hip_error = "kernel launch failed";
+    return rc;
+}
+}  // namespace
+
+int rsh_dense_forward(const void* H, const void* W, void* P, int64_t n, int32_t d_in, int32_t d_out, void* hip_stream) {
+    if (!H || !W || !P) return RSH_ERR_NULL;
+    if (!dense_widths_ok(n, d_in, d_out) || !aligned_to({H, W, P}, 2)) return RSH_ERR_BAD_OPTION;
+    return launch_status(rsh::launch_dense_forward(H, W, P, n, d_in, d_out, hip_stream));
+}
+
+int rsh_dense_backward(const void* H, const void* W, const void* dP, void* dH, void* dW, float* work, int64_t n, int32_t d_in, int32_t d_out,
+                       void* hip_stream) {
+    if (!H || (dH && !W) || !dP || !dW || !work) return RSH_ERR_NULL;
+    if (!dense_widths_ok(n, d_in, d_out) || !aligned_to({H, W, dP, dH, dW}, 2) || !aligned_to({work}, 4)) return RSH_ERR_BAD_OPTION;
+    return launch_status(rsh::launch_dense_backward(H, W, dP, dH, dW, work, n, d_in, d_out, hip_stream));
+}
+
+int rsh_act_backward(const void* dY, const void* Y, void* dZ, float* dbias, float* work, int64_t n, int32_t d, void* hip_stream) {
+    if (!dY || !Y != !dZ || (dbias && !work) || (!Y && !dbias)) return RSH_ERR_NULL;
+    if (n <= 0 || d <= 0 || !aligned_to({dY, Y, dZ}, 2) || !aligned_to({dbias, work}, 4)) return RSH_ERR_BAD_OPTION;
+    return launch_status(rsh::launch_act_backward(dY, Y, dZ, dbias, work, n, d, hip_stream));
 }
 
 int rsh_copy_probe(const void* src_dev, void* dst_dev, int64_t bytes, void* hip_stream) {

@@ -66,6 +66,15 @@ int launch_spmm_f16(const DevicePlan& d, const void* B_dev, void* C16_dev, const
 // aligned address; the columns from n on become zero.
 int launch_widen_rows(const void* src, void* dst, int64_t rows, int n, int n_wide, void* stream);
 
+// The dense half of a GCN layer (dense.hip).  Widths 8 .. 64 for the products, any for the activation; n > 0.
+// dH may be null; Y and dZ may both be null, dbias too.  work: kGradientParts * d_in * d_out floats, for the
+// activation kGradientParts * d.
+constexpr int kGradientParts = RSH_GRADIENT_PARTS;
+int launch_dense_forward(const void* H, const void* W, void* P, int64_t n, int d_in, int d_out, void* stream);
+int launch_dense_backward(const void* H, const void* W, const void* dP, void* dH, void* dW, float* work, int64_t n, int d_in, int d_out,
+                          void* stream);
+int launch_act_backward(const void* dY, const void* Y, void* dZ, float* dbias, float* work, int64_t n, int d, void* stream);
+
 // Plain device-to-device copy of `bytes` (multiple of 16) used to calibrate traffic counters.
 int launch_copy_probe(const void* src_dev, void* dst_dev, size_t bytes, void* stream);
 

@@ -1,8 +1,9 @@
 """GCN layers H' = act(A H W + b) on the sparse kernels (paper, Section 4.4).
 
 The sparse products -- A times a dense operand in the forward pass, A^T times a dense operand in
-the backward pass -- run through ``rsh_spmm_f16``; the two small dense products per pass are plain
-library GEMMs (``torch.matmul`` on binary16 operands, fp32 accumulation).  Two association orders:
+the backward pass -- run through ``rsh_spmm_f16``; the dense products of narrow layers and the gradient of
+bias and activation run on kernels of the library too (``rsh_dense_*``, ``rsh_act_backward``), wider ones are
+plain library GEMMs (``torch.matmul`` on binary16 operands, fp32 accumulation).  Two association orders:
 
   "A_HW": Y = act(A (H W) + b)   the GEMM shrinks the features first; bias, activation and the
                                  rounding to binary16 are fused into the sparse kernels
@@ -19,7 +20,25 @@ from __future__ import annotations
 
 import torch
 
+from . import binding
 from .binding import Plan
+
+
+def _plain(*tensors) -> bool:
+    """Whether the library's own dense kernels may take these operands: binary16 matrices with rows, row-major
+    without gaps, on the current device, and nobody is recording or rewriting operations (a second derivative,
+    autocast, a compiler).  Everything else goes through torch."""
+    if torch.is_grad_enabled() or torch.is_autocast_enabled() or torch.compiler.is_compiling():
+        return False
+    device = tensors[0].device
+    return (device.type == "cuda" and device.index == torch.cuda.current_device() and
+            all(type(t) in (torch.Tensor, torch.nn.Parameter) and t.dtype == torch.float16 and t.dim() == 2 and t.device == device and
+                t.numel() > 0 and t.is_contiguous() for t in tensors))
+
+
+def _narrow(H, W) -> bool:
+    """Widths for which the weight, or its gradient, fits the registers of a wave (rsh_dense_forward)."""
+    return all(binding.DENSE_MIN <= d <= binding.DENSE_MAX for d in W.shape) and H.shape[1] == W.shape[0]
 
 
 class Adjacency:
@@ -63,29 +82,42 @@ class _SparseProduct(torch.autograd.Function):
     def backward(ctx, dY):
         (Y,) = ctx.saved_tensors
         dZ = dY.to(torch.float16)
-        if ctx.relu:
-            dZ = dZ * (Y > 0)
-        dZ = dZ.contiguous()
+        want_dbias = ctx.has_bias and ctx.needs_input_grad[2]
+        dbias = None
+        if _plain(dZ, *((Y,) if ctx.relu else ())):
+            dZ, dbias = binding.act_backward(dZ, Y, want_dbias)
+        else:
+            if ctx.relu:
+                dZ = dZ * (Y > 0)
+            dZ = dZ.contiguous()
+            if want_dbias:
+                dbias = dZ.sum(dim=0, dtype=torch.float32)
+        if not ctx.needs_input_grad[1]:
+            return None, None, dbias, None
         plan_t = ctx.adj.plan(dZ.shape[1], transposed=True)
         dX = torch.empty((plan_t.n_rows, plan_t.N), dtype=torch.float16, device=dZ.device)
         plan_t.spmm_f16(dZ, dX, None, False)
-        dbias = dZ.sum(dim=0, dtype=torch.float32) if ctx.has_bias else None
         return None, dX, dbias, None
 
 
 class _DenseProduct(torch.autograd.Function):
-    """H W with library GEMMs.  The weight gradient H^T dZ reduces over all rows of the graph into a
-    d_in x d_out result; as one GEMM that is a single output tile (one workgroup streams the whole
+    """H W.  Narrow weights (8 .. 64 features on both sides) run on the library's own kernels, which read H and dZ once
+    for both gradients; others are library GEMMs.  The weight gradient H^T dZ reduces over all rows of the graph
+    into a d_in x d_out result; as one GEMM that is a single output tile (one workgroup streams the whole
     of H), so it is issued as a batched GEMM over row slabs whose partial results are then added."""
 
     @staticmethod
     def forward(ctx, H, W):
         ctx.save_for_backward(H, W)
+        if _plain(H, W) and _narrow(H, W):
+            return binding.dense_forward(H, W)
         return H @ W
 
     @staticmethod
     def backward(ctx, dZ):
         H, W = ctx.saved_tensors
+        if ctx.needs_input_grad[1] and _plain(dZ, H, W) and _narrow(H, W):
+            return binding.dense_backward(H, W, dZ, ctx.needs_input_grad[0])
         dH = dZ @ W.t() if ctx.needs_input_grad[0] else None
         dW = None
         if ctx.needs_input_grad[1]:
