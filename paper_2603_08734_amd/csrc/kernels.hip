@@ -349,7 +349,7 @@ __device__ __forceinline__ void tile_body(
     const int32_t* __restrict__ win_row, const int32_t* __restrict__ tile_colid,
     const uint64_t* __restrict__ tile_mask, const uint32_t* __restrict__ tile_val_off,
     const uint16_t* __restrict__ tile_val, const __half* __restrict__ B, const OUT out,
-    float* __restrict__ scratch, int N, int nb, int nv, int feature0) {
+    float* __restrict__ scratch, int N, int nb, int nv, int feature0, int last0) {
     using Gm = TileGeom<NCH, NW, KT>;
     constexpr int P = Gm::P, TPR = Gm::TPR, NLD = Gm::NLD, LDB = Gm::LDB, THREADS = Gm::THREADS, CPL = Gm::CPL;
     using vals_t = typename std::conditional<KT == 16, uint2_t, uint4_t>::type;   // CPL halves per lane
@@ -373,7 +373,7 @@ __device__ __forceinline__ void tile_body(
     const uint4 it = items[item];
     const uint32_t win = __builtin_amdgcn_readfirstlane(it.x), t_begin = __builtin_amdgcn_readfirstlane(it.y);
     const uint32_t t_end = __builtin_amdgcn_readfirstlane(it.z), dst = __builtin_amdgcn_readfirstlane(it.w);
-    const int panel = feature0 + blockIdx.y * P;
+    const int panel = min(feature0 + (int)blockIdx.y * P, last0);   // the last panel ends with the row
     _Float16* sb0 = lds_b[NW == 1 ? wib : 0];
     uint16_t* sv = lds_v[wib];
 
@@ -607,16 +607,16 @@ __device__ __forceinline__ void tile_body(
 #define RSH_TILE_PARAMS                                                                                                                   \
     const uint4 *__restrict__ items, XcdSplit xs, const int32_t *__restrict__ win_row, const int32_t *__restrict__ tile_colid,            \
         const uint64_t *__restrict__ tile_mask, const uint32_t *__restrict__ tile_val_off, const uint16_t *__restrict__ tile_val,         \
-        const __half *__restrict__ B, const OUT out, float *__restrict__ scratch, int N, int nb, int nv, int feature0
+        const __half *__restrict__ B, const OUT out, float *__restrict__ scratch, int N, int nb, int nv, int feature0, int last0
 template <int NCH, int NW, int D, int KT, class OUT>
 __global__ __launch_bounds__(NW == 1 ? 64 * kWavesPerBlock : 64 * NW) void rsh_tile_kernel(RSH_TILE_PARAMS) {
     static_assert(!OUT::kAny);
-    tile_body<NCH, NW, D, KT>(items, xs, win_row, tile_colid, tile_mask, tile_val_off, tile_val, B, out, scratch, N, nb, nv, feature0);
+    tile_body<NCH, NW, D, KT>(items, xs, win_row, tile_colid, tile_mask, tile_val_off, tile_val, B, out, scratch, N, nb, nv, feature0, last0);
 }
 template <int NCH, int NW, int D, int KT, class OUT>
 __global__ __launch_bounds__(NW == 1 ? 64 * kWavesPerBlock : 64 * NW) void rsh_fragment_any_kernel(RSH_TILE_PARAMS) {
     static_assert(OUT::kAny);
-    tile_body<NCH, NW, D, KT>(items, xs, win_row, tile_colid, tile_mask, tile_val_off, tile_val, B, out, scratch, N, nb, nv, feature0);
+    tile_body<NCH, NW, D, KT>(items, xs, win_row, tile_colid, tile_mask, tile_val_off, tile_val, B, out, scratch, N, nb, nv, feature0, last0);
 }
 #undef RSH_TILE_PARAMS
 
@@ -809,16 +809,16 @@ static void launch_irregular_t(const DevicePlan& d, const void* B, const OUT& ou
     }
 }
 
-// `panels` panels of 16 * NCH features starting at feature `feature0`
+// `panels` panels of 16 * NCH features starting at feature `feature0`; one that would pass feature `cover` ends there
 template <int NCH, int NW, int D, int KT, class OUT>
-static void launch_tile_t(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st, int nb, int nv, int feature0, int panels) {
+static void launch_tile_t(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st, int nb, int nv, int feature0, int panels, int cover) {
     constexpr int items_per_block = NW == 1 ? kWavesPerBlock : 1;
     uint32_t longest = 0;
     for (int x = 0; x < 8; ++x) longest = std::max(longest, d.tile_split.start[x + 1] - d.tile_split.start[x]);
     dim3 grid(8u * ((longest + items_per_block - 1) / items_per_block), (unsigned)panels);
     auto launch = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, grid, dim3(NW == 1 ? 64 * kWavesPerBlock : 64 * NW), 0, st, (const uint4*)d.tile_item, d.tile_split, d.win_row,
-                           d.tile_colid, d.tile_mask, d.tile_val_off, d.tile_val, (const __half*)B, out, d.scratch, d.geo.N, nb, nv, feature0);
+                           d.tile_colid, d.tile_mask, d.tile_val_off, d.tile_val, (const __half*)B, out, d.scratch, d.geo.N, nb, nv, feature0, cover - 16 * NCH);
     };
     if constexpr (OUT::kAny) launch(rsh_fragment_any_kernel<NCH, NW, D, KT, OUT>);
     else launch(rsh_tile_kernel<NCH, NW, D, KT, OUT>);
@@ -827,23 +827,26 @@ static void launch_tile_t(const DevicePlan& d, const void* B, const OUT& out, hi
 // Fragments in flight per thread: one for 16-row windows, two when the waves of a window share
 // the staging (measured best of 1, 2, 3).
 template <int NCH, int NW, class OUT>
-static int launch_tile_d(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st, int nb, int nv, int feature0, int panels) {
+static int launch_tile_d(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st, int nb, int nv, int feature0, int panels, int cover) {
     constexpr int D = NW == 1 ? 1 : 2;
-    if (d.geo.tile_k == 16) launch_tile_t<NCH, NW, D, 16>(d, B, out, st, nb, nv, feature0, panels);
-    else if (d.geo.tile_k == 32) launch_tile_t<NCH, NW, D, 32>(d, B, out, st, nb, nv, feature0, panels);
+    if (d.geo.tile_k == 16) launch_tile_t<NCH, NW, D, 16>(d, B, out, st, nb, nv, feature0, panels, cover);
+    else if (d.geo.tile_k == 32) launch_tile_t<NCH, NW, D, 32>(d, B, out, st, nb, nv, feature0, panels, cover);
     else return RSH_ERR_BAD_OPTION;
     return RSH_OK;
 }
 
 template <int NCH, class OUT>
-static int launch_tile_nw(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st, int nb, int nv, int feature0, int panels) {
+static int launch_tile_nw(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st, int nb, int nv, int feature0, int panels, int cover) {
     switch (d.geo.nw) {
-        case 1: return launch_tile_d<NCH, 1>(d, B, out, st, nb, nv, feature0, panels);
-        case 2: return launch_tile_d<NCH, 2>(d, B, out, st, nb, nv, feature0, panels);
-        case 4: return launch_tile_d<NCH, 4>(d, B, out, st, nb, nv, feature0, panels);
+        case 1: return launch_tile_d<NCH, 1>(d, B, out, st, nb, nv, feature0, panels, cover);
+        case 2: return launch_tile_d<NCH, 2>(d, B, out, st, nb, nv, feature0, panels, cover);
+        case 4: return launch_tile_d<NCH, 4>(d, B, out, st, nb, nv, feature0, panels, cover);
         default: return RSH_ERR_BAD_OPTION;
     }
 }
+
+// Waves of the fragment kernel up to which a launch leaves half of the chip's wave slots idle.
+constexpr int64_t kIdleWaves = 2048;
 
 template <class OUT>
 static int launch_all(const DevicePlan& d, const void* B, const OUT& out, int nb, int nv, void* stream, void* const* events) {
@@ -868,8 +871,10 @@ static int launch_all(const DevicePlan& d, const void* B, const OUT& out, int nb
         if (rc != RSH_OK) return rc;
     } else if (d.n_tile_items > 0) {
         // As many panels of the widest kind (256, 128, ... 16 features) as fit, and for the rest one of the smallest
-        // kind that holds it, placed so that it ends with the row: N = 160 takes 128 + 32, N = 100 takes 64 and
-        // features 36 .. 99 (those it shares with the panel before come out the same twice).
+        // kind that holds it, placed so that it ends with the row: N = 160 takes 128 + 32, N = 100 takes features
+        // 0 .. 63 and 36 .. 99 (those that two panels share come out the same twice).  The rest takes a launch of
+        // its own where it is of another kind, unless the whole product leaves the chip half idle: then a kernel takes
+        // as long as its longest item whatever the width, and a panel of the widest kind in the same launch is less.
         // With rows of B longer than those of C the panels cover the next multiple of 16.
         const int cover = OUT::kAny ? (nv + 15) / 16 * 16 : nv;
         int wide = 16;
@@ -877,17 +882,19 @@ static int launch_all(const DevicePlan& d, const void* B, const OUT& out, int nb
         const int rest = cover % wide;
         int last = 16;
         while (last < rest) last *= 2;
+        if (d.n_tile_items * d.geo.nw * (cover / wide + 1) <= kIdleWaves) last = wide;
         auto launch = [&](int features, int feature0, int panels) {
             switch (features) {
-                case 16: return launch_tile_nw<1>(d, B, out, st, nb, nv, feature0, panels);
-                case 32: return launch_tile_nw<2>(d, B, out, st, nb, nv, feature0, panels);
-                case 64: return launch_tile_nw<4>(d, B, out, st, nb, nv, feature0, panels);
-                case 128: return launch_tile_nw<8>(d, B, out, st, nb, nv, feature0, panels);
-                default: return launch_tile_nw<16>(d, B, out, st, nb, nv, feature0, panels);
+                case 16: return launch_tile_nw<1>(d, B, out, st, nb, nv, feature0, panels, cover);
+                case 32: return launch_tile_nw<2>(d, B, out, st, nb, nv, feature0, panels, cover);
+                case 64: return launch_tile_nw<4>(d, B, out, st, nb, nv, feature0, panels, cover);
+                case 128: return launch_tile_nw<8>(d, B, out, st, nb, nv, feature0, panels, cover);
+                default: return launch_tile_nw<16>(d, B, out, st, nb, nv, feature0, panels, cover);
             }
         };
-        rc = launch(wide, 0, cover / wide);
-        if (rc == RSH_OK && rest > 0) rc = launch(last, cover - last, 1);
+        const bool together = rest > 0 && last == wide;
+        rc = launch(wide, 0, cover / wide + together);
+        if (rc == RSH_OK && rest > 0 && !together) rc = launch(last, cover - last, 1);
         if (rc != RSH_OK) return rc;
     }
     if (forked && hipEventRecord((hipEvent_t)d.ev_join, (hipStream_t)d.side) != hipSuccess) return RSH_ERR_HIP;

@@ -500,12 +500,12 @@ int launch_panels(const DevicePlan& d, const void* B, const OUT& out, hipStream_
     // inside a 16-byte piece and the window has 128 rows (a thread then stages two pieces of a 128-feature row
     // and has no registers left to move the broken one).
     const int wide = d.geo.panel_groups == 4 && nb % 8 ? 64 : 128;
-    const int full = nv / wide, rest = nv % wide;
+    const int rest = nv % wide, full = nv / wide + (rest > wide / 2);   // a rest of the same kind goes along
     if (full > 0 && wide == 64) launch_panel_g<2>(d, B, out, st, nb, nv, 0, full);
     else if (full > 0) launch_panel_g<4>(d, B, out, st, nb, nv, 0, full);
-    if (rest > 64) launch_panel_g<4>(d, B, out, st, nb, nv, wide * full, 1);
-    else if (rest > 32) launch_panel_g<2>(d, B, out, st, nb, nv, wide * full, 1);
-    else if (rest > 0) launch_panel_g<1>(d, B, out, st, nb, nv, wide * full, 1);
+    if (rest > wide / 2 || rest == 0) return RSH_OK;
+    if (rest > 32) launch_panel_g<2>(d, B, out, st, nb, nv, nv - rest, 1);
+    else launch_panel_g<1>(d, B, out, st, nb, nv, nv - rest, 1);
     return RSH_OK;
 }
 
