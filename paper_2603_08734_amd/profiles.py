@@ -31,7 +31,7 @@ _MARK = "<!-- profile-data -->"
 
 
 def _short(name: str) -> str:
-    return name.split("(")[0].replace("void ", "").strip()
+    return name.replace("(anonymous namespace)::", "").split("(")[0].replace("void ", "").strip()
 
 
 def _find(run_dir: str, sub: str, pattern: str):

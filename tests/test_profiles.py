@@ -43,3 +43,9 @@ def test_lookup_prefers_the_plain_command(tmp_path, monkeypatch):
 def test_committed_summaries_parse():
     names = [name for name, data in profiles._blocks() if {"workload", "N", "plan_options", "kernels"} <= set(data)]
     assert names, "profiles/ holds no summary in the format bench.py reads"
+
+
+def test_kernel_names_keep_what_follows_an_anonymous_namespace():
+    assert profiles._short("void rsh::(anonymous namespace)::rsh_panel_kernel<4, 8, false, rsh::OutPlainT<false> >(uint4 const*, int)") == \
+        "rsh::rsh_panel_kernel<4, 8, false, rsh::OutPlainT<false> >"
+    assert profiles._short("rsh::rsh_copy_probe_kernel(uint4 const*)") == "rsh::rsh_copy_probe_kernel"
