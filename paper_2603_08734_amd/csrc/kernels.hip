@@ -6,6 +6,7 @@
 //   rsh_irregular_kernel residual rows (Section 3.3.2, "CUDA path"), teams of lanes own
 //                        feature columns, long rows arrive as bounded slices (Section 3.3.3)
 //   rsh_combine_kernel   fixed-order sum of the partial results of split windows / rows
+//   rsh_sum_narrow_kernel   the same for rows of up to 16 features, several rows per wave
 //   rsh_fragment_any_kernel, rsh_residual_any_kernel, rsh_sum_any_kernel   the first, third and fourth for rows of
 //                        C of any length and alignment beside a padded copy of B
 //   rsh_widen_rows_kernel   copies B to the run width where its rows cannot be read as they are
@@ -622,16 +623,23 @@ __global__ __launch_bounds__(NW == 1 ? 64 * kWavesPerBlock : 64 * NW) void rsh_f
 
 // ---------------------------------------------------------------------------
 // Combine: C[row] = sum over parts of scratch[first + p*stride], in a fixed order
-// (four interleaved running sums, then a fixed tree), one wave per entry.
+// (four interleaved running sums, then a fixed tree).  Four features a lane: a wave takes one entry, or, of rows of
+// up to 16 features (SHARED), as many as it has teams of 2^log_lanes lanes: 16 to 64.  The narrow pass is bound by the
+// latency of entry and parts per wave.  28672 x 8192 weight at density 0.2, N = 1 (28672 entries of two parts): the
+// product takes 58.7 us where a wave an entry took 63.6.  Two entries a wave at 128 features gain nothing (92.6 and
+// 93.3 us) and cost the power-law graph of 2^20 vertices 4 us of 744, whose pass already streams 250 MB at 5 TB/s.
 // ---------------------------------------------------------------------------
-template <class OUT>
+template <bool SHARED, class OUT>
 __device__ __forceinline__ void combine_body(const uint4* __restrict__ entries, uint32_t n_entries, const float* __restrict__ scratch,
-                                             const OUT& out, int N, int nv) {
-    const int lane = threadIdx.x & 63;
-    const uint32_t e = __builtin_amdgcn_readfirstlane(blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6));
+                                             const OUT& out, int N, int nv, int log_lanes) {
+    constexpr int kWhole = 6;
+    const int shift = SHARED ? log_lanes : kWhole;
+    const uint32_t mine = threadIdx.x >> shift;
+    const uint32_t e = blockIdx.x * (64u * kWavesPerBlock >> shift) + (SHARED ? mine : __builtin_amdgcn_readfirstlane(mine));
     if (e >= n_entries) return;
     const uint4 en = entries[e];
     const uint32_t row = en.x, first = en.y, parts = en.z, stride = en.w;
+    const int lane = threadIdx.x & ((1u << shift) - 1u);
     for (int f0 = lane * 4; f0 < nv; f0 += 256) {
         // four features that end with the row where it is not a multiple of four; rows of scratch that are longer
         // than those of C (kAny) are multiples of 16
@@ -656,13 +664,18 @@ __device__ __forceinline__ void combine_body(const uint4* __restrict__ entries, 
 
 template <class OUT>
 __global__ __launch_bounds__(64 * kWavesPerBlock) void rsh_combine_kernel(const uint4* __restrict__ entries, uint32_t n_entries,
-                                                                          const float* __restrict__ scratch, const OUT out, int N, int nv) {
-    combine_body(entries, n_entries, scratch, out, N, nv);
+                                                                          const float* __restrict__ scratch, const OUT out, int N, int nv, int log_lanes) {
+    combine_body<false>(entries, n_entries, scratch, out, N, nv, log_lanes);
 }
 template <class OUT>
 __global__ __launch_bounds__(64 * kWavesPerBlock) void rsh_sum_any_kernel(const uint4* __restrict__ entries, uint32_t n_entries,
-                                                                          const float* __restrict__ scratch, const OUT out, int N, int nv) {
-    combine_body(entries, n_entries, scratch, out, N, nv);
+                                                                          const float* __restrict__ scratch, const OUT out, int N, int nv, int log_lanes) {
+    combine_body<false>(entries, n_entries, scratch, out, N, nv, log_lanes);
+}
+template <class OUT>
+__global__ __launch_bounds__(64 * kWavesPerBlock) void rsh_sum_narrow_kernel(const uint4* __restrict__ entries, uint32_t n_entries,
+                                                                             const float* __restrict__ scratch, const OUT out, int N, int nv, int log_lanes) {
+    combine_body<true>(entries, n_entries, scratch, out, N, nv, log_lanes);
 }
 
 // ---------------------------------------------------------------------------
@@ -913,11 +926,15 @@ static int launch_all(const DevicePlan& d, const void* B, const OUT& out, int nb
     if (forked && hipStreamWaitEvent(caller, (hipEvent_t)d.ev_join, 0) != hipSuccess) return RSH_ERR_HIP;
     if (d.n_combine > 0) {
         const uint32_t n = (uint32_t)d.n_combine;
+        int log_lanes = 0;   // lanes per entry, at four features each
+        while (log_lanes < 6 && (4 << log_lanes) < nv) ++log_lanes;
+        const uint32_t per_block = 64u * kWavesPerBlock >> log_lanes;
         auto launch = [&](auto kernel) {
-            hipLaunchKernelGGL(kernel, dim3((n + kWavesPerBlock - 1) / kWavesPerBlock), dim3(64 * kWavesPerBlock), 0, st, (const uint4*)d.combine, n,
-                               d.scratch, out, d.geo.N, nv);
+            hipLaunchKernelGGL(kernel, dim3((n + per_block - 1) / per_block), dim3(64 * kWavesPerBlock), 0, st, (const uint4*)d.combine, n,
+                               d.scratch, out, d.geo.N, nv, log_lanes);
         };
-        if constexpr (OUT::kAny) launch(rsh_sum_any_kernel<OUT>);
+        if (log_lanes <= 2) launch(rsh_sum_narrow_kernel<OUT>);   // the line: combine_body's comment
+        else if constexpr (OUT::kAny) launch(rsh_sum_any_kernel<OUT>);
         else launch(rsh_combine_kernel<OUT>);
     }
     mark(3);

@@ -126,3 +126,33 @@ def test_rows_of_c_of_any_width_and_alignment(opts, N, fused):
     assert not np.isnan(got).any()
     assert np.all(np.abs(got - C_ref) <= bound)
     plan.destroy()
+
+
+# Partial sums of rows of up to 16 features are added by teams of lanes, several rows to a wave (16 features: 16,
+# one to four features: 64); wider ones take a wave a row.  600 rows of three or more parts fill several workgroups
+# and leave the last one ragged at every width.
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("N", [1, 4, 5, 8, 9, 16, 17, 32, 128])
+@pytest.mark.parametrize("opts", [dict(force_path=2, max_tiles_per_item=3), dict(force_path=1, max_nnz_per_slice=16)], ids=["windows", "rows"])
+def test_partial_sums_of_several_rows_in_a_wave(opts, N, fused):
+    import torch
+    from paper_2603_08734_amd import Plan
+    A = random_matrix(600, 400, 0.2, 17)
+    print(f"case partial sums N={N} opts={opts} fused={fused}", flush=True)
+    plan = Plan(A.row_ptr, A.col_idx, A.val, A.n_cols, N, **opts)
+    assert plan.stats()["n_combine"] >= 500
+    B = dense_B(A.n_cols, N, "normal", seed=N)
+    Bd = torch.from_numpy(B.view(np.int16)).cuda().view(torch.float16)
+    C_ref, S, _ = oracle.spmm(A.row_ptr, A.col_idx, A.val, B)
+    C = torch.full((A.n_rows, N), float("nan"), dtype=torch.float16 if fused else torch.float32, device="cuda")
+    if fused:
+        plan.spmm_f16(Bd, C, None, False)
+        bound = 1e-4 * S + 2.0 ** -11 * np.abs(C_ref) * 1.001 + 2.0 ** -24   # the fp32 bound and one rounding to binary16
+    else:
+        plan.spmm(Bd, C)
+        bound = 1e-4 * S
+    torch.cuda.synchronize()
+    got = C.cpu().numpy().astype(np.float64)
+    assert not np.isnan(got).any()
+    assert np.all(np.abs(got - C_ref) <= bound)
+    plan.destroy()
