@@ -928,12 +928,13 @@ static int launch_all(const DevicePlan& d, const void* B, const OUT& out, int nb
         const uint32_t n = (uint32_t)d.n_combine;
         int log_lanes = 0;   // lanes per entry, at four features each
         while (log_lanes < 6 && (4 << log_lanes) < nv) ++log_lanes;
+        if (log_lanes > 2) log_lanes = 6;   // a wave each; the line: combine_body's comment
         const uint32_t per_block = 64u * kWavesPerBlock >> log_lanes;
         auto launch = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, dim3((n + per_block - 1) / per_block), dim3(64 * kWavesPerBlock), 0, st, (const uint4*)d.combine, n,
                                d.scratch, out, d.geo.N, nv, log_lanes);
         };
-        if (log_lanes <= 2) launch(rsh_sum_narrow_kernel<OUT>);   // the line: combine_body's comment
+        if (log_lanes < 6) launch(rsh_sum_narrow_kernel<OUT>);
         else if constexpr (OUT::kAny) launch(rsh_sum_any_kernel<OUT>);
         else launch(rsh_combine_kernel<OUT>);
     }
