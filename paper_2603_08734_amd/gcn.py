@@ -24,16 +24,26 @@ from . import binding
 from .binding import Plan
 
 
+def _has_memory(t) -> bool:
+    """Whether the tensor's elements lie behind an address.  Those of a batched gradient (``torch.autograd.grad`` with
+    ``is_grads_batched``) do not, though it has the type, sizes and strides of a matrix that does."""
+    try:
+        t.data_ptr()
+    except RuntimeError:
+        return False
+    return True
+
+
 def _plain(*tensors) -> bool:
     """Whether the library's own dense kernels may take these operands: binary16 matrices with rows, row-major
     without gaps, on the current device, and nobody is recording or rewriting operations (a second derivative,
-    autocast, a compiler).  Everything else goes through torch."""
+    a batch of gradients, autocast, a compiler).  Everything else goes through torch."""
     if torch.is_grad_enabled() or torch.is_autocast_enabled() or torch.compiler.is_compiling():
         return False
     device = tensors[0].device
     return (device.type == "cuda" and device.index == torch.cuda.current_device() and
             all(type(t) in (torch.Tensor, torch.nn.Parameter) and t.dtype == torch.float16 and t.dim() == 2 and t.device == device and
-                t.numel() > 0 and t.is_contiguous() for t in tensors))
+                t.numel() > 0 and t.is_contiguous() and _has_memory(t) for t in tensors))
 
 
 def _narrow(H, W) -> bool:

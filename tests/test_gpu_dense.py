@@ -171,3 +171,27 @@ def test_layers_around_the_dense_kernels(way):
     for x, y in zip(got, want):
         assert (x.double() - y.double()).abs().max() <= 2.0 ** -8 * y.abs().max()
     adj.destroy()
+
+
+@pytest.mark.parametrize("way", ["weight", "bias"])
+def test_batched_gradients_of_a_layer(way):
+    """torch.autograd.grad(..., is_grads_batched=True) hands the layer gradients without memory of their own.  Where no
+    sparse product lies behind them -- the weight of a layer whose features need no gradient, a bias alone -- the
+    result equals that of one gradient after the other, up to the binary16 roundings of another order of sums."""
+    import torch
+    from paper_2603_08734_amd.gcn import Adjacency, GCNLayer
+    from workloads import make_config
+    A, _, _ = make_config(2, small=True)
+    d, g = 24, torch.Generator(device="cuda").manual_seed(5)
+    adj = Adjacency(A.row_ptr, A.col_idx, A.val, A.n_cols, symmetric=True)
+    layer = GCNLayer(adj, d, d, order="AH_W" if way == "weight" else "A_HW")
+    H = torch.randn((A.n_cols, d), device="cuda", generator=g).half()
+    W = (torch.randn((d, d), device="cuda", generator=g) / d ** 0.5).half().requires_grad_(way == "weight")
+    b = torch.randn(d, device="cuda", generator=g).requires_grad_(way == "bias")
+    Y, wanted = layer(H, W, b, True), W if way == "weight" else b
+    G = torch.randn((3, *Y.shape), device="cuda", generator=g).half()
+    got, = torch.autograd.grad(Y, wanted, G, is_grads_batched=True, retain_graph=True)
+    for x, one in zip(got, G):
+        want, = torch.autograd.grad(Y, wanted, one, retain_graph=True)
+        assert (x.double() - want.double()).abs().max() <= 2.0 ** -8 * want.abs().max()
+    adj.destroy()
