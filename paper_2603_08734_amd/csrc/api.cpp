@@ -164,6 +164,7 @@ int upload_plan(rsh_plan& p) {
     d.n_irr_waves = (int64_t)h.irr_wave.size() / 4;
     d.n_combine = (int64_t)h.combine.size() / 4;
     d.n_scratch_slots = h.n_scratch_slots;
+    d.n_split_rows = h.stats.n_split_rows;
     d.tile_split = h.tile_split;
     d.irr_split = h.irr_split;
     Uploader up;

@@ -626,8 +626,13 @@ __global__ __launch_bounds__(NW == 1 ? 64 * kWavesPerBlock : 64 * NW) void rsh_f
 // (four interleaved running sums, then a fixed tree).  Four features a lane: a wave takes one entry, or, of rows of
 // up to 16 features (SHARED), as many as it has teams of 2^log_lanes lanes: 16 to 64.  The narrow pass is bound by the
 // latency of entry and parts per wave.  28672 x 8192 weight at density 0.2, N = 1 (28672 entries of two parts): the
-// product takes 58.7 us where a wave an entry took 63.6.  Two entries a wave at 128 features gain nothing (92.6 and
-// 93.3 us) and cost the power-law graph of 2^20 vertices 4 us of 744, whose pass already streams 250 MB at 5 TB/s.
+// product takes 58.7 us where a wave an entry took 63.6.  That holds for the parts of windows, whose rows have the
+// same number of them (1024 x 4096 weight, 1024 entries: 15.3 us, 16.1 with a wave each).  The slices of long rows are
+// fewer entries of two to dozens of parts, and rows that share a wave wait for its longest: power-law graph of 2^16
+// vertices, 16 features, 22.1 us shared, 21.1 with a wave each, the combine pass 5.0 and 4.0 of them; of 2^20 vertices,
+// N = 1, 308.3 and 302.8.  So plans whose entries are mostly rows take a wave each.
+// Two entries a wave at 128 features gain nothing (92.6 and 93.3 us) and cost the power-law graph of 2^20 vertices 4 us
+// of 744, whose pass already streams 250 MB at 5 TB/s.
 // ---------------------------------------------------------------------------
 template <bool SHARED, class OUT>
 __device__ __forceinline__ void combine_body(const uint4* __restrict__ entries, uint32_t n_entries, const float* __restrict__ scratch,
@@ -928,7 +933,7 @@ static int launch_all(const DevicePlan& d, const void* B, const OUT& out, int nb
         const uint32_t n = (uint32_t)d.n_combine;
         int log_lanes = 0;   // lanes per entry, at four features each
         while (log_lanes < 6 && (4 << log_lanes) < nv) ++log_lanes;
-        if (log_lanes > 2) log_lanes = 6;   // a wave each; the line: combine_body's comment
+        if (log_lanes > 2 || 2 * d.n_split_rows > d.n_combine) log_lanes = 6;   // a wave each; the lines: combine_body's comment
         const uint32_t per_block = 64u * kWavesPerBlock >> log_lanes;
         auto launch = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, dim3((n + per_block - 1) / per_block), dim3(64 * kWavesPerBlock), 0, st, (const uint4*)d.combine, n,

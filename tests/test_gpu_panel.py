@@ -128,8 +128,8 @@ def test_rows_of_c_of_any_width_and_alignment(opts, N, fused):
     plan.destroy()
 
 
-# Partial sums of rows of up to 16 features are added by teams of lanes, several rows to a wave (16 features: 16,
-# one to four features: 64); wider ones take a wave a row.  600 rows of three or more parts fill several workgroups
+# Partial sums of windows' rows of up to 16 features are added by teams of lanes, several rows to a wave (16 features: 16,
+# one to four features: 64); wider ones and those of long rows' slices take a wave a row.  600 rows of three or more parts fill several workgroups
 # and leave the last one ragged at every width.
 @pytest.mark.parametrize("fused", [False, True])
 @pytest.mark.parametrize("N", [1, 4, 5, 8, 9, 16, 17, 32, 128])
