@@ -81,30 +81,39 @@ __device__ __forceinline__ void keep_streaming_hint() { asm volatile("" ::: "mem
 // Where finished rows go.  OutPlain: the fp32 sums as they are.  OutFused: binary16 of
 // act(sum + bias), the form in which a GCN layer hands its features on (paper, Section 4.4);
 // bias (may be null) and activation are chosen at run time, uniformly for the launch.
-// kAny: rows of C of any number of features, aligned to their element only, shorter than the rows of B (a padded
-// copy); features from nv on are not stored and have no bias.  Otherwise rows of B and C are equally long, of an
-// even number of features from 16 on, and 4-byte aligned.
-template <bool ANY>
+// Rows of B and C come in three kinds:
+//   kRowsWhole  equally long, a multiple of 16 features, every panel beginning at a multiple of its own width.  With
+//               the next kind's clamping of panels and pieces these launches were 1 to 3 % slower (power-law graph of
+//               2^18 vertices, 160 features: 247.2 us and 243.9; 27-point stencil on 80^3 in binary16, 64 features:
+//               58.2 and 56.8)
+//   kRowsEven   equally long, an even number of features from 16 on, 4-byte aligned
+//   kRowsAny    rows of C of any number of features, aligned to their element only, shorter than the rows of B (a
+//               padded copy); features from nv on are not stored and have no bias
+enum Rows { kRowsWhole, kRowsEven, kRowsAny };
+template <int ROWS>
 struct OutPlainT {
-    static constexpr bool kFused = false, kAny = ANY;
+    static constexpr bool kFused = false, kAny = ROWS == kRowsAny, kWhole = ROWS == kRowsWhole;
+    static constexpr int kRows = ROWS;
     float* C;
+    // the same rows for a kernel that makes no use of their being whole
+    OutPlainT<kAny ? kRowsAny : kRowsEven> general() const { return {C}; }
 };
-template <bool ANY>
+template <int ROWS>
 struct OutFusedT {
-    static constexpr bool kFused = true, kAny = ANY;
+    static constexpr bool kFused = true, kAny = ROWS == kRowsAny, kWhole = ROWS == kRowsWhole;
+    static constexpr int kRows = ROWS;
     _Float16* C;
     const float* bias;
     int relu;
+    OutFusedT<kAny ? kRowsAny : kRowsEven> general() const { return {C, bias, relu}; }
 };
-using OutPlain = OutPlainT<false>;
-using OutFused = OutFusedT<false>;
 
 // `end`: one past the last feature of the row (kAny).
 // act(v + bias[f .. f+3]) rounded to binary16 (to nearest even), as two packed words
-template <bool ANY>
-__device__ __forceinline__ uint2_t finish4(const OutFusedT<ANY>& o, int f, int end, float4_t v) {
+template <int ROWS>
+__device__ __forceinline__ uint2_t finish4(const OutFusedT<ROWS>& o, int f, int end, float4_t v) {
     if (o.bias) {
-        if (!ANY || f + 4 <= end) {
+        if (ROWS != kRowsAny || f + 4 <= end) {
             v += *reinterpret_cast<const float4_a4*>(o.bias + f);
         } else {
 #pragma unroll
@@ -128,10 +137,10 @@ __device__ __forceinline__ void store_tail(float* p, int live, float4_t v) {
 }
 
 // Eight finished features f .. f+7 of a row of C.
-template <bool ANY>
-__device__ __forceinline__ void store_halves(const OutFusedT<ANY>& o, size_t row, int nv, int f, int end, uint4_t v) {
+template <int ROWS>
+__device__ __forceinline__ void store_halves(const OutFusedT<ROWS>& o, size_t row, int nv, int f, int end, uint4_t v) {
     _Float16* p = o.C + row * nv + f;
-    if constexpr (!ANY) {
+    if constexpr (ROWS != kRowsAny) {
         __builtin_nontemporal_store(v, reinterpret_cast<uint4_a4*>(p));
     } else if (f + 8 <= end) {
         __builtin_nontemporal_store(v, reinterpret_cast<uint4_a2*>(p));
@@ -143,25 +152,25 @@ __device__ __forceinline__ void store_halves(const OutFusedT<ANY>& o, size_t row
 }
 
 // Four features of a row of C that is whole in every panel, unless kAny.
-template <bool ANY>
-__device__ __forceinline__ void tile_store(const OutPlainT<ANY>& o, size_t row, int nv, int f, float4_t v) {
+template <int ROWS>
+__device__ __forceinline__ void tile_store(const OutPlainT<ROWS>& o, size_t row, int nv, int f, float4_t v) {
     float* p = o.C + row * nv + f;
-    if (!ANY || f + 4 <= nv) store_c_streaming(p, v);
+    if (ROWS != kRowsAny || f + 4 <= nv) store_c_streaming(p, v);
     else store_tail(p, nv - f, v);
 }
 
 // Four features of a row of C of `nv` features (even), or its last two; any number of them for kAny.
-template <bool ANY>
-__device__ __forceinline__ void panel_store(const OutPlainT<ANY>& o, size_t row, int nv, int f, float4_t v) {
+template <int ROWS>
+__device__ __forceinline__ void panel_store(const OutPlainT<ROWS>& o, size_t row, int nv, int f, float4_t v) {
     float* p = o.C + row * nv + f;
     if (f + 4 <= nv) store_c_streaming(p, v);
-    else if constexpr (ANY) store_tail(p, nv - f, v);
+    else if constexpr (ROWS == kRowsAny) store_tail(p, nv - f, v);
     else __builtin_nontemporal_store((float2_t){v[0], v[1]}, reinterpret_cast<float2_a4*>(p));
 }
-template <bool ANY>
-__device__ __forceinline__ void panel_store(const OutFusedT<ANY>& o, size_t row, int nv, int f, float4_t v) {
+template <int ROWS>
+__device__ __forceinline__ void panel_store(const OutFusedT<ROWS>& o, size_t row, int nv, int f, float4_t v) {
     _Float16* p = o.C + row * nv + f;
-    if constexpr (ANY) {
+    if constexpr (ROWS == kRowsAny) {
         const uint2_t h = finish4(o, f, nv, v);
         if (f + 4 <= nv) {
             __builtin_nontemporal_store(h, reinterpret_cast<uint2_a2*>(p));

@@ -7,8 +7,10 @@
 //                        feature columns, long rows arrive as bounded slices (Section 3.3.3)
 //   rsh_combine_kernel   fixed-order sum of the partial results of split windows / rows
 //   rsh_sum_narrow_kernel   the same for rows of up to 16 features, several rows per wave
-//   rsh_fragment_any_kernel, rsh_residual_any_kernel, rsh_sum_any_kernel   the first, third and fourth for rows of
-//                        C of any length and alignment beside a padded copy of B
+//   rsh_fragment_even_kernel, rsh_residual_even_kernel, rsh_sum_even_kernel   the first, third (its partial panel) and
+//                        fourth for rows of an even number of features (device.hpp, Rows)
+//   rsh_fragment_any_kernel, rsh_residual_any_kernel, rsh_sum_any_kernel   the first, third and fourth
+//                        for rows of C of any length and alignment beside a padded copy of B
 //   rsh_widen_rows_kernel   copies B to the run width where its rows cannot be read as they are
 // Each of the first three exists for two outputs: the fp32 sums (OutPlain) and binary16 of
 // act(sum + bias) (OutFused, the GCN layer of Section 4.4).
@@ -28,22 +30,26 @@ namespace rsh {
 // stores of consecutive 16-byte pieces (lane t writes pieces t and TPR + t), i.e. whole lines, after
 // a turn through the team's LDS stage; lane-owned pieces would make every store a half-written
 // 32-byte sector, which the streaming path handles at a third of the rate.
-// A partial panel (PARTIAL: the last one of a width that is not a multiple of the panel) has `live` features, an
+// A partial panel of whole rows ends with a lane: the lanes behind it read the panel's first piece and store nothing.
+// Any other partial panel (PARTIAL: the last one of a width that is not a multiple of the panel) has `live` features, an
 // even number from 8 on; where the rows of B are the padded copy and longer than those of C (OUT::kAny), any number
 // from 1 on.  Its last lane takes the eight features that end with the row of B, so that no lane reads past the
 // row; lanes behind it repeat that piece, and pieces past the last feature are not stored.
-template <int TPR, bool PARTIAL>
-__device__ __forceinline__ int lane_features(int live_b, int tl) { return PARTIAL ? min(8 * tl, live_b - 8) : 8 * tl; }
-template <bool PARTIAL, bool ANY>
+template <bool PARTIAL, int ROWS>
+__device__ __forceinline__ int lane_features(int live_b, int tl) {
+    if (ROWS == kRowsWhole) return PARTIAL && 8 * tl >= live_b ? 0 : 8 * tl;
+    return PARTIAL ? min(8 * tl, live_b - 8) : 8 * tl;
+}
+template <bool PARTIAL, int ROWS>
 __device__ __forceinline__ void store_piece(float* out_row, int live, int f, float4_t v) {
     if (!PARTIAL || f + 4 <= live) store_c_streaming(out_row + f, v);
-    else if constexpr (ANY) store_tail(out_row + f, live - f, v);
-    else if (f < live) __builtin_nontemporal_store((float2_t){v[0], v[1]}, reinterpret_cast<float2_a4*>(out_row + f));
+    else if constexpr (ROWS == kRowsAny) store_tail(out_row + f, live - f, v);
+    else if (ROWS == kRowsEven && f < live) __builtin_nontemporal_store((float2_t){v[0], v[1]}, reinterpret_cast<float2_a4*>(out_row + f));
 }
 // lane_f: lane_features of this lane
-template <int TPR, bool PARTIAL, bool ANY>
+template <int TPR, bool PARTIAL, int ROWS>
 __device__ __forceinline__ void store_row_streaming(float* out_row, const float (&acc)[8], float* stage, int tl, int lane_f, int live) {
-    if constexpr (PARTIAL) {
+    if constexpr (PARTIAL && ROWS != kRowsWhole) {
         float2_t* to = reinterpret_cast<float2_t*>(stage + lane_f);
 #pragma unroll
         for (int i = 0; i < 4; ++i) to[i] = (float2_t){acc[2 * i], acc[2 * i + 1]};
@@ -53,20 +59,20 @@ __device__ __forceinline__ void store_row_streaming(float* out_row, const float 
     }
     const float4_t v0 = *reinterpret_cast<const float4_t*>(stage + 4 * tl);
     const float4_t v1 = *reinterpret_cast<const float4_t*>(stage + 4 * TPR + 4 * tl);
-    store_piece<PARTIAL, ANY>(out_row, live, 4 * tl, v0);
-    store_piece<PARTIAL, ANY>(out_row, live, 4 * TPR + 4 * tl, v1);
+    store_piece<PARTIAL, ROWS>(out_row, live, 4 * tl, v0);
+    store_piece<PARTIAL, ROWS>(out_row, live, 4 * TPR + 4 * tl, v1);
 }
 
 // A team's finished row `row` of C (nv features), panel starting at feature `panel`.  In binary16 a lane's
 // eight features are one 16-byte piece and the team's pieces are consecutive, so the row
 // leaves as one store of whole lines without a turn through LDS.
-template <int TPR, bool PARTIAL, bool ANY>
-__device__ __forceinline__ void emit_row(const OutPlainT<ANY>& o, size_t row, int nv, int panel, const float (&acc)[8],
+template <int TPR, bool PARTIAL, int ROWS>
+__device__ __forceinline__ void emit_row(const OutPlainT<ROWS>& o, size_t row, int nv, int panel, const float (&acc)[8],
                                          float* stage, int tl, int lane_f) {
-    store_row_streaming<TPR, PARTIAL, ANY>(o.C + row * nv + panel, acc, stage, tl, lane_f, nv - panel);
+    store_row_streaming<TPR, PARTIAL, ROWS>(o.C + row * nv + panel, acc, stage, tl, lane_f, nv - panel);
 }
-template <int TPR, bool PARTIAL, bool ANY>
-__device__ __forceinline__ void emit_row(const OutFusedT<ANY>& o, size_t row, int nv, int panel, const float (&acc)[8],
+template <int TPR, bool PARTIAL, int ROWS>
+__device__ __forceinline__ void emit_row(const OutFusedT<ROWS>& o, size_t row, int nv, int panel, const float (&acc)[8],
                                          float*, int tl, int lane_f) {
     if (PARTIAL && panel + 8 * tl >= nv) return;   // lane past the last feature of a partial panel
     const int f = panel + lane_f;
@@ -184,14 +190,15 @@ __device__ __forceinline__ void gather_steps(const BRows& Bp, int my_col, float 
 }
 
 // PARTIAL: the panel (there is one, the last) holds fewer than 8 * TPR features.  Full panels carry no checks.
-// N: features of a partial row in scratch; nb, nv: of a row of B and of C.
+// N: features of a row of B; nv: of a row of C (N unless kAny); ns: of a partial row in scratch (N for whole rows).
 template <int TPR, class OUT, bool PARTIAL>
 __device__ __forceinline__ void irregular_body(
     const uint4* __restrict__ waves, const XcdSplit& xs,
     const int32_t* __restrict__ irr_row, const int32_t* __restrict__ irr_col,
     const uint16_t* __restrict__ irr_val, const __half* __restrict__ B, const OUT out,
-    float* __restrict__ scratch, int N, int nb, int nv, int feature0) {
+    float* __restrict__ scratch, int N, int feature0, int nv, int ns) {
     constexpr int G = 64 / TPR;
+    if constexpr (!OUT::kAny) nv = N;
     __shared__ __attribute__((aligned(16))) float lds_stage[kWavesPerBlock][64 * 8];
     const int lane = threadIdx.x & 63;
     uint32_t wave;
@@ -204,8 +211,8 @@ __device__ __forceinline__ void irregular_body(
     const uint32_t start = __builtin_amdgcn_readfirstlane(d.x), count = __builtin_amdgcn_readfirstlane(d.y);
     const uint32_t dst = __builtin_amdgcn_readfirstlane(d.z), info = __builtin_amdgcn_readfirstlane(d.w);
     const uint32_t kind = info & kWaveKindMask;
-    const int live = nv - panel, lane_f = lane_features<TPR, PARTIAL>(nb - panel, tl);
-    const BRows Bp{reinterpret_cast<const char*>(B + panel), 2u * (uint32_t)nb, 2u * (uint32_t)lane_f};
+    const int live = nv - panel, lane_f = lane_features<PARTIAL, OUT::kRows>(N - panel, tl);
+    const BRows Bp{reinterpret_cast<const char*>(B + panel), 2u * (uint32_t)N, 2u * (uint32_t)lane_f};
 
     float acc[8];
 #pragma unroll
@@ -217,8 +224,8 @@ __device__ __forceinline__ void irregular_body(
                 emit_row<TPR, PARTIAL>(out, (size_t)irr_row[dst + q], nv, panel, acc, stage, tl, lane_f);   // act(bias)
             } else {
                 float* o = out.C + (size_t)irr_row[dst + q] * nv + panel;
-                store_piece<PARTIAL, OUT::kAny>(o, live, 4 * tl, (float4_t){0.f, 0.f, 0.f, 0.f});
-                store_piece<PARTIAL, OUT::kAny>(o, live, 4 * TPR + 4 * tl, (float4_t){0.f, 0.f, 0.f, 0.f});
+                store_piece<PARTIAL, OUT::kRows>(o, live, 4 * tl, (float4_t){0.f, 0.f, 0.f, 0.f});
+                store_piece<PARTIAL, OUT::kRows>(o, live, 4 * TPR + 4 * tl, (float4_t){0.f, 0.f, 0.f, 0.f});
             }
         }
         return;
@@ -272,29 +279,39 @@ __device__ __forceinline__ void irregular_body(
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] = sum_over_teams<TPR>(acc[i], lane);
     if (team != 0) return;
+    constexpr int kScratchRows = OUT::kWhole ? kRowsWhole : kRowsEven;
     if constexpr (OUT::kFused || OUT::kAny) {
-        // rows of scratch are as long as the rows of B or longer
-        if (info & kWaveToScratch) store_row_streaming<TPR, PARTIAL, false>(scratch + (size_t)dst * N + panel, acc, stage, tl, lane_f, nb - panel);
+        if (info & kWaveToScratch) store_row_streaming<TPR, PARTIAL, kScratchRows>(scratch + (size_t)dst * ns + panel, acc, stage, tl, lane_f, N - panel);
         else emit_row<TPR, PARTIAL>(out, (size_t)dst, nv, panel, acc, stage, tl, lane_f);
     } else {
-        store_row_streaming<TPR, PARTIAL, false>((info & kWaveToScratch) ? scratch + (size_t)dst * N + panel : out.C + (size_t)dst * nv + panel, acc,
-                                                 stage, tl, lane_f, live);
+        store_row_streaming<TPR, PARTIAL, kScratchRows>((info & kWaveToScratch) ? scratch + (size_t)dst * ns + panel : out.C + (size_t)dst * N + panel, acc, stage, tl, lane_f, live);
     }
 }
 
 #define RSH_IRREGULAR_PARAMS                                                                                                              \
     const uint4 *__restrict__ waves, XcdSplit xs, const int32_t *__restrict__ irr_row, const int32_t *__restrict__ irr_col,               \
-        const uint16_t *__restrict__ irr_val, const __half *__restrict__ B, const OUT out, float *__restrict__ scratch, int N, int nb,    \
-        int nv, int feature0
+        const uint16_t *__restrict__ irr_val, const __half *__restrict__ B, const OUT out, float *__restrict__ scratch, int N,            \
+        int feature0, int nv, int ns
 template <int TPR, class OUT, bool PARTIAL>
 __global__ __launch_bounds__(64 * kWavesPerBlock) __attribute__((amdgpu_waves_per_eu(8, 8))) void rsh_irregular_kernel(RSH_IRREGULAR_PARAMS) {
-    static_assert(!OUT::kAny);
-    irregular_body<TPR, OUT, PARTIAL>(waves, xs, irr_row, irr_col, irr_val, B, out, scratch, N, nb, nv, feature0);
+    static_assert(OUT::kRows == (PARTIAL ? kRowsWhole : kRowsEven));   // full panels of whole rows are no different
+    irregular_body<TPR, OUT, PARTIAL>(waves, xs, irr_row, irr_col, irr_val, B, out, scratch, N, feature0, nv, ns);
+}
+// Eight waves per SIMD take registers from the fp32 form's gather loops (rows of 100 features of the power-law graph of
+// 2^18 vertices: 157.0 us, 147.0 with seven; 50 features 110.1 and 101.5).  The binary16 form gains as much at panels
+// of 64 features (2^17 vertices, 58 features: 62.9 and 57.2), not at 128 (100 features: 73.6 and 74.8).
+template <int TPR, class OUT>
+constexpr int kEvenWaves = OUT::kFused && TPR == 16 ? 8 : 7;
+template <int TPR, class OUT>
+__global__ __launch_bounds__(64 * kWavesPerBlock) __attribute__((amdgpu_waves_per_eu(kEvenWaves<TPR, OUT>, kEvenWaves<TPR, OUT>)))
+void rsh_residual_even_kernel(RSH_IRREGULAR_PARAMS) {
+    static_assert(OUT::kRows == kRowsEven);
+    irregular_body<TPR, OUT, true>(waves, xs, irr_row, irr_col, irr_val, B, out, scratch, N, feature0, nv, ns);
 }
 template <int TPR, class OUT, bool PARTIAL>
 __global__ __launch_bounds__(64 * kWavesPerBlock) __attribute__((amdgpu_waves_per_eu(7, 7))) void rsh_residual_any_kernel(RSH_IRREGULAR_PARAMS) {
     static_assert(OUT::kAny);
-    irregular_body<TPR, OUT, PARTIAL>(waves, xs, irr_row, irr_col, irr_val, B, out, scratch, N, nb, nv, feature0);
+    irregular_body<TPR, OUT, PARTIAL>(waves, xs, irr_row, irr_col, irr_val, B, out, scratch, N, feature0, nv, ns);
 }
 #undef RSH_IRREGULAR_PARAMS
 
@@ -350,11 +367,13 @@ __device__ __forceinline__ void tile_body(
     const int32_t* __restrict__ win_row, const int32_t* __restrict__ tile_colid,
     const uint64_t* __restrict__ tile_mask, const uint32_t* __restrict__ tile_val_off,
     const uint16_t* __restrict__ tile_val, const __half* __restrict__ B, const OUT out,
-    float* __restrict__ scratch, int N, int nb, int nv, int feature0, int last0) {
+    float* __restrict__ scratch, int N, int feature0, int nv, int ns, int last0) {
     using Gm = TileGeom<NCH, NW, KT>;
     constexpr int P = Gm::P, TPR = Gm::TPR, NLD = Gm::NLD, LDB = Gm::LDB, THREADS = Gm::THREADS, CPL = Gm::CPL;
     using vals_t = typename std::conditional<KT == 16, uint2_t, uint4_t>::type;   // CPL halves per lane
     using frag_t = typename std::conditional<KT == 16, half4_t, half8_t>::type;
+    if constexpr (!OUT::kAny) nv = N;
+    if constexpr (OUT::kWhole) ns = N;
     // the staged tiles; the binary16 epilogue reuses the space as 16 output rows per wave
     constexpr int kTileHalves = Gm::NBUF * KT * LDB;
     constexpr int kSlotHalves = (OUT::kFused && NW > 1 && NW * 16 * LDB > kTileHalves) ? NW * 16 * LDB : kTileHalves;
@@ -374,7 +393,8 @@ __device__ __forceinline__ void tile_body(
     const uint4 it = items[item];
     const uint32_t win = __builtin_amdgcn_readfirstlane(it.x), t_begin = __builtin_amdgcn_readfirstlane(it.y);
     const uint32_t t_end = __builtin_amdgcn_readfirstlane(it.z), dst = __builtin_amdgcn_readfirstlane(it.w);
-    const int panel = min(feature0 + (int)blockIdx.y * P, last0);   // the last panel ends with the row
+    int panel = feature0 + (int)blockIdx.y * P;
+    if constexpr (!OUT::kWhole) panel = min(panel, last0);   // the last panel ends with the row
     _Float16* sb0 = lds_b[NW == 1 ? wib : 0];
     uint16_t* sv = lds_v[wib];
 
@@ -395,7 +415,7 @@ __device__ __forceinline__ void tile_body(
     // B rows are addressed as a wave-uniform base plus a 32-bit byte offset (the plan guarantees
     // n_cols * 2N < 2^32), which leaves the address arithmetic at one multiply-add per load
     const char* Bbytes = reinterpret_cast<const char*>(B + panel);
-    const uint32_t row_bytes = 2u * (uint32_t)nb;
+    const uint32_t row_bytes = 2u * (uint32_t)N;
     uint32_t ld_byte[NLD];
 #pragma unroll
     for (int j = 0; j < NLD; ++j) ld_byte[j] = 2u * (uint32_t)ld_col[j];
@@ -539,7 +559,7 @@ __device__ __forceinline__ void tile_body(
     if (dst != kNoDst) {
         // partial sums of a split window: ordinary stores (measured: the combine pass is faster
         // when these went through L2)
-        float* o = scratch + ((size_t)dst + r) * N + panel + 4 * q;
+        float* o = scratch + ((size_t)dst + r) * ns + panel + 4 * q;
 #pragma unroll
         for (int c = 0; c < NCH; ++c) *reinterpret_cast<float4_a4*>(o + 16 * c) = acc[c];
         return;
@@ -570,7 +590,10 @@ __device__ __forceinline__ void tile_body(
             const int prow = shfl_i32(row, pr);
             if (piece < kPieces && prow >= 0) {
                 const uint4_t v = *reinterpret_cast<const uint4_t*>(so + pr * LDB + 8 * pc);
-                store_halves(out, (size_t)prow, nv, panel + 8 * pc, nv, v);
+                // the row's start first: with panel + 8 * pc in a register of its own the compiler moves the column ids'
+                // cross-lane reads to the head of the loop, before its waits (27-point stencil on 60^3, 64 features: 30.2 us, 29.4 so)
+                if constexpr (OUT::kAny) store_halves(out, (size_t)prow, nv, panel + 8 * pc, nv, v);
+                else __builtin_nontemporal_store(v, reinterpret_cast<uint4_a4*>(out.C + (size_t)prow * nv + panel + 8 * pc));
             }
         }
     } else if constexpr (NCH % 2 == 0) {
@@ -608,16 +631,21 @@ __device__ __forceinline__ void tile_body(
 #define RSH_TILE_PARAMS                                                                                                                   \
     const uint4 *__restrict__ items, XcdSplit xs, const int32_t *__restrict__ win_row, const int32_t *__restrict__ tile_colid,            \
         const uint64_t *__restrict__ tile_mask, const uint32_t *__restrict__ tile_val_off, const uint16_t *__restrict__ tile_val,         \
-        const __half *__restrict__ B, const OUT out, float *__restrict__ scratch, int N, int nb, int nv, int feature0, int last0
+        const __half *__restrict__ B, const OUT out, float *__restrict__ scratch, int N, int feature0, int nv, int ns, int last0
 template <int NCH, int NW, int D, int KT, class OUT>
 __global__ __launch_bounds__(NW == 1 ? 64 * kWavesPerBlock : 64 * NW) void rsh_tile_kernel(RSH_TILE_PARAMS) {
-    static_assert(!OUT::kAny);
-    tile_body<NCH, NW, D, KT>(items, xs, win_row, tile_colid, tile_mask, tile_val_off, tile_val, B, out, scratch, N, nb, nv, feature0, last0);
+    static_assert(OUT::kWhole);
+    tile_body<NCH, NW, D, KT>(items, xs, win_row, tile_colid, tile_mask, tile_val_off, tile_val, B, out, scratch, N, feature0, nv, ns, last0);
+}
+template <int NCH, int NW, int D, int KT, class OUT>
+__global__ __launch_bounds__(NW == 1 ? 64 * kWavesPerBlock : 64 * NW) void rsh_fragment_even_kernel(RSH_TILE_PARAMS) {
+    static_assert(OUT::kRows == kRowsEven);
+    tile_body<NCH, NW, D, KT>(items, xs, win_row, tile_colid, tile_mask, tile_val_off, tile_val, B, out, scratch, N, feature0, nv, ns, last0);
 }
 template <int NCH, int NW, int D, int KT, class OUT>
 __global__ __launch_bounds__(NW == 1 ? 64 * kWavesPerBlock : 64 * NW) void rsh_fragment_any_kernel(RSH_TILE_PARAMS) {
     static_assert(OUT::kAny);
-    tile_body<NCH, NW, D, KT>(items, xs, win_row, tile_colid, tile_mask, tile_val_off, tile_val, B, out, scratch, N, nb, nv, feature0, last0);
+    tile_body<NCH, NW, D, KT>(items, xs, win_row, tile_colid, tile_mask, tile_val_off, tile_val, B, out, scratch, N, feature0, nv, ns, last0);
 }
 #undef RSH_TILE_PARAMS
 
@@ -636,9 +664,10 @@ __global__ __launch_bounds__(NW == 1 ? 64 * kWavesPerBlock : 64 * NW) void rsh_f
 // ---------------------------------------------------------------------------
 template <bool SHARED, class OUT>
 __device__ __forceinline__ void combine_body(const uint4* __restrict__ entries, uint32_t n_entries, const float* __restrict__ scratch,
-                                             const OUT& out, int N, int nv, int log_lanes) {
-    constexpr int kWhole = 6;
-    const int shift = SHARED ? log_lanes : kWhole;
+                                             const OUT& out, int ns, int nv, int log_lanes) {
+    constexpr int kWaveLanes = 6;
+    if constexpr (OUT::kWhole) nv = ns;
+    const int shift = SHARED ? log_lanes : kWaveLanes;
     const uint32_t mine = threadIdx.x >> shift;
     const uint32_t e = blockIdx.x * (64u * kWavesPerBlock >> shift) + (SHARED ? mine : __builtin_amdgcn_readfirstlane(mine));
     if (e >= n_entries) return;
@@ -646,11 +675,11 @@ __device__ __forceinline__ void combine_body(const uint4* __restrict__ entries, 
     const uint32_t row = en.x, first = en.y, parts = en.z, stride = en.w;
     const int lane = threadIdx.x & ((1u << shift) - 1u);
     for (int f0 = lane * 4; f0 < nv; f0 += 256) {
-        // four features that end with the row where it is not a multiple of four; rows of scratch that are longer
-        // than those of C (kAny) are multiples of 16
-        const int f = OUT::kAny ? f0 : min(f0, nv - 4);
+        // four features that end with the row where it is not a multiple of four; rows of scratch, longer
+        // than those of C (kAny), are multiples of 16
+        const int f = OUT::kAny || OUT::kWhole ? f0 : min(f0, nv - 4);
         float4_t s0 = {0.f, 0.f, 0.f, 0.f}, s1 = s0, s2 = s0, s3 = s0;
-        const auto part = [&](uint32_t p) { return *reinterpret_cast<const float4_a4*>(scratch + ((size_t)first + (size_t)p * stride) * N + f); };
+        const auto part = [&](uint32_t p) { return *reinterpret_cast<const float4_a4*>(scratch + ((size_t)first + (size_t)p * stride) * ns + f); };
         uint32_t p = 0;
         for (; p + 4 <= parts; p += 4) {
             const float4_t a = part(p), b = part(p + 1), c = part(p + 2), d = part(p + 3);
@@ -669,18 +698,23 @@ __device__ __forceinline__ void combine_body(const uint4* __restrict__ entries, 
 
 template <class OUT>
 __global__ __launch_bounds__(64 * kWavesPerBlock) void rsh_combine_kernel(const uint4* __restrict__ entries, uint32_t n_entries,
-                                                                          const float* __restrict__ scratch, const OUT out, int N, int nv, int log_lanes) {
-    combine_body<false>(entries, n_entries, scratch, out, N, nv, log_lanes);
+                                                                          const float* __restrict__ scratch, const OUT out, int ns, int nv, int log_lanes) {
+    combine_body<false>(entries, n_entries, scratch, out, ns, nv, log_lanes);
+}
+template <class OUT>
+__global__ __launch_bounds__(64 * kWavesPerBlock) void rsh_sum_even_kernel(const uint4* __restrict__ entries, uint32_t n_entries,
+                                                                           const float* __restrict__ scratch, const OUT out, int ns, int nv, int log_lanes) {
+    combine_body<false>(entries, n_entries, scratch, out, ns, nv, log_lanes);
 }
 template <class OUT>
 __global__ __launch_bounds__(64 * kWavesPerBlock) void rsh_sum_any_kernel(const uint4* __restrict__ entries, uint32_t n_entries,
-                                                                          const float* __restrict__ scratch, const OUT out, int N, int nv, int log_lanes) {
-    combine_body<false>(entries, n_entries, scratch, out, N, nv, log_lanes);
+                                                                          const float* __restrict__ scratch, const OUT out, int ns, int nv, int log_lanes) {
+    combine_body<false>(entries, n_entries, scratch, out, ns, nv, log_lanes);
 }
 template <class OUT>
 __global__ __launch_bounds__(64 * kWavesPerBlock) void rsh_sum_narrow_kernel(const uint4* __restrict__ entries, uint32_t n_entries,
-                                                                             const float* __restrict__ scratch, const OUT out, int N, int nv, int log_lanes) {
-    combine_body<true>(entries, n_entries, scratch, out, N, nv, log_lanes);
+                                                                             const float* __restrict__ scratch, const OUT out, int ns, int nv, int log_lanes) {
+    combine_body<true>(entries, n_entries, scratch, out, ns, nv, log_lanes);
 }
 
 // ---------------------------------------------------------------------------
@@ -805,25 +839,30 @@ static inline uint32_t grid_for(const XcdSplit& xs) {
     return 8u * ((longest + kWavesPerBlock - 1) / kWavesPerBlock);
 }
 
-// Feature widths of a launch: `nb` of a row of B, `nv` of a row of C.  Equal, even and at least 16; or (OUT::kAny)
+// Feature widths of a launch: `nb` of a row of B, `nv` of a row of C.  Equal, even and at least 16 (whole rows: equal to
+// geo.N, a multiple of 16); or (OUT::kAny)
 // nb is the padded width, a multiple of 16, and nv any width up to it.  Partial sums have rows of geo.N >= nb.
 // Full panels in one launch; a last partial panel (nv not a multiple of the panel) in a launch of its own, which
 // starts early enough to hold eight features (those it shares with the panel before come out the same twice).
 template <int TPR, class OUT>
 static void launch_irregular_t(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st, int nb, int nv) {
     const int full = nv / d.geo.irr_panel;
-    auto launch = [&](auto kernel, int panels, int feature0) {
+    const auto launch = [&](auto kernel, const auto& to, int panels, int feature0) {
         hipLaunchKernelGGL(kernel, dim3(grid_for(d.irr_split), (unsigned)panels), dim3(64 * kWavesPerBlock),
-                           0, st, (const uint4*)d.irr_wave, d.irr_split, d.irr_row, d.irr_col, d.irr_val, (const __half*)B, out,
-                           d.scratch, d.geo.N, nb, nv, feature0);
+                           0, st, (const uint4*)d.irr_wave, d.irr_split, d.irr_row, d.irr_col, d.irr_val, (const __half*)B, to,
+                           d.scratch, nb, feature0, nv, d.geo.N);
     };
     const int rest0 = std::min(full * d.geo.irr_panel, nb - 8);
     if constexpr (OUT::kAny) {
-        if (full > 0) launch(rsh_residual_any_kernel<TPR, OUT, false>, full, 0);
-        if (nv % d.geo.irr_panel) launch(rsh_residual_any_kernel<TPR, OUT, true>, 1, rest0);
+        if (full > 0) launch(rsh_residual_any_kernel<TPR, OUT, false>, out, full, 0);
+        if (nv % d.geo.irr_panel) launch(rsh_residual_any_kernel<TPR, OUT, true>, out, 1, rest0);
     } else {
-        if (full > 0) launch(rsh_irregular_kernel<TPR, OUT, false>, full, 0);
-        if (nv % d.geo.irr_panel) launch(rsh_irregular_kernel<TPR, OUT, true>, 1, rest0);
+        const auto even = out.general();
+        using Even = std::decay_t<decltype(even)>;
+        if (full > 0) launch(rsh_irregular_kernel<TPR, Even, false>, even, full, 0);
+        if (nv % d.geo.irr_panel == 0) return;
+        if constexpr (OUT::kWhole) launch(rsh_irregular_kernel<TPR, OUT, true>, out, 1, full * d.geo.irr_panel);
+        else launch(rsh_residual_even_kernel<TPR, OUT>, out, 1, rest0);
     }
 }
 
@@ -834,12 +873,18 @@ static void launch_tile_t(const DevicePlan& d, const void* B, const OUT& out, hi
     uint32_t longest = 0;
     for (int x = 0; x < 8; ++x) longest = std::max(longest, d.tile_split.start[x + 1] - d.tile_split.start[x]);
     dim3 grid(8u * ((longest + items_per_block - 1) / items_per_block), (unsigned)panels);
-    auto launch = [&](auto kernel) {
+    auto launch = [&](auto kernel, const auto& to) {
         hipLaunchKernelGGL(kernel, grid, dim3(NW == 1 ? 64 * kWavesPerBlock : 64 * NW), 0, st, (const uint4*)d.tile_item, d.tile_split, d.win_row,
-                           d.tile_colid, d.tile_mask, d.tile_val_off, d.tile_val, (const __half*)B, out, d.scratch, d.geo.N, nb, nv, feature0, cover - 16 * NCH);
+                           d.tile_colid, d.tile_mask, d.tile_val_off, d.tile_val, (const __half*)B, to, d.scratch, nb, feature0, nv, d.geo.N, cover - 16 * NCH);
     };
-    if constexpr (OUT::kAny) launch(rsh_fragment_any_kernel<NCH, NW, D, KT, OUT>);
-    else launch(rsh_tile_kernel<NCH, NW, D, KT, OUT>);
+    if constexpr (OUT::kAny) {
+        launch(rsh_fragment_any_kernel<NCH, NW, D, KT, OUT>, out);
+    } else {
+        if constexpr (OUT::kWhole)
+            if (feature0 + panels * 16 * NCH <= cover) return launch(rsh_tile_kernel<NCH, NW, D, KT, OUT>, out);
+        const auto even = out.general();
+        launch(rsh_fragment_even_kernel<NCH, NW, D, KT, std::decay_t<decltype(even)>>, even);
+    }
 }
 
 // Fragments in flight per thread: one for 16-row windows, two when the waves of a window share
@@ -885,7 +930,7 @@ static int launch_all(const DevicePlan& d, const void* B, const OUT& out, int nb
     }
     hipStream_t st = forked ? (hipStream_t)d.side : caller;
     if (d.n_tile_items > 0 && d.geo.panel) {
-        rc = launch_panels(d, B, out, st, nb, nv);
+        rc = launch_panels(d, B, out.general(), st, nb, nv);
         if (rc != RSH_OK) return rc;
     } else if (d.n_tile_items > 0) {
         // As many panels of the widest kind (256, 128, ... 16 features) as fit, and for the rest one of the smallest
@@ -935,21 +980,25 @@ static int launch_all(const DevicePlan& d, const void* B, const OUT& out, int nb
         while (log_lanes < 6 && (4 << log_lanes) < nv) ++log_lanes;
         if (log_lanes > 2 || 2 * d.n_split_rows > d.n_combine) log_lanes = 6;   // a wave each; the lines: combine_body's comment
         const uint32_t per_block = 64u * kWavesPerBlock >> log_lanes;
-        auto launch = [&](auto kernel) {
+        auto launch = [&](auto kernel, const auto& to) {
             hipLaunchKernelGGL(kernel, dim3((n + per_block - 1) / per_block), dim3(64 * kWavesPerBlock), 0, st, (const uint4*)d.combine, n,
-                               d.scratch, out, d.geo.N, nv, log_lanes);
+                               d.scratch, to, d.geo.N, nv, log_lanes);
         };
-        if (log_lanes < 6) launch(rsh_sum_narrow_kernel<OUT>);
-        else if constexpr (OUT::kAny) launch(rsh_sum_any_kernel<OUT>);
-        else launch(rsh_combine_kernel<OUT>);
+        const auto general = out.general();
+        using General = std::decay_t<decltype(general)>;
+        if (log_lanes < 6) launch(rsh_sum_narrow_kernel<General>, general);
+        else if constexpr (OUT::kAny) launch(rsh_sum_any_kernel<OUT>, out);
+        else if constexpr (OUT::kWhole) launch(rsh_combine_kernel<OUT>, out);
+        else launch(rsh_sum_even_kernel<OUT>, out);
     }
     mark(3);
     return hipGetLastError() == hipSuccess ? RSH_OK : RSH_ERR_HIP;
 }
 
 int launch_spmm(const DevicePlan& d, const void* B, void* C, int nb, int nv, void* stream, void* const* events) {
-    if (nb != nv) return launch_all(d, B, OutPlainT<true>{(float*)C}, nb, nv, stream, events);
-    return launch_all(d, B, OutPlain{(float*)C}, nb, nv, stream, events);
+    if (nb != nv) return launch_all(d, B, OutPlainT<kRowsAny>{(float*)C}, nb, nv, stream, events);
+    if (nb == d.geo.N) return launch_all(d, B, OutPlainT<kRowsWhole>{(float*)C}, nb, nv, stream, events);
+    return launch_all(d, B, OutPlainT<kRowsEven>{(float*)C}, nb, nv, stream, events);
 }
 
 // ---------------------------------------------------------------------------
@@ -980,8 +1029,9 @@ int static_scratch(float** ptr) {
 
 int launch_spmm_f16(const DevicePlan& d, const void* B, void* C16, const float* bias, int relu, int nb, int nv, void* stream,
                     void* const* events) {
-    if (nb != nv) return launch_all(d, B, OutFusedT<true>{(_Float16*)C16, bias, relu}, nb, nv, stream, events);
-    return launch_all(d, B, OutFused{(_Float16*)C16, bias, relu}, nb, nv, stream, events);
+    if (nb != nv) return launch_all(d, B, OutFusedT<kRowsAny>{(_Float16*)C16, bias, relu}, nb, nv, stream, events);
+    if (nb == d.geo.N) return launch_all(d, B, OutFusedT<kRowsWhole>{(_Float16*)C16, bias, relu}, nb, nv, stream, events);
+    return launch_all(d, B, OutFusedT<kRowsEven>{(_Float16*)C16, bias, relu}, nb, nv, stream, events);
 }
 
 }  // namespace rsh

@@ -178,7 +178,7 @@ template <int NCH32, int NG, bool RUN, bool RAGGED>
 __device__ __forceinline__ void panel_item(unsigned char* smem, uint32_t win, uint32_t t_begin, uint32_t t_end, uint32_t t0, uint32_t nt,
                                             int32_t col0, const int32_t* __restrict__ tile_colid, const uint32_t* __restrict__ quad0,
                                             const uint4_t* __restrict__ meta, const uint32_t* __restrict__ qoff,
-                                            const uint32_t* __restrict__ val, const __half* __restrict__ B, int nb, int panel,
+                                            const uint32_t* __restrict__ val, const __half* __restrict__ B, int N, int panel,
                                             float16_t (&acc)[NCH32], float16_t (&acc2)[NCH32]) {
     using Gm = PanelGeom<NCH32, NG>;
     // fragments ahead at which rows of B are requested, and how much earlier their column ids; where a thread
@@ -197,15 +197,15 @@ __device__ __forceinline__ void panel_item(unsigned char* smem, uint32_t win, ui
     // thread tix stages 16-byte piece j * THREADS + tix of the KT x TPR pieces, i.e. the same piece of rows
     // row0, row0 + THREADS / TPR, ...; threads without a piece (narrow panels) stage into spare space
     constexpr int kRowStep = THREADS / TPR;
-    const uint32_t row_bytes = 2u * (uint32_t)nb;
+    const uint32_t row_bytes = 2u * (uint32_t)N;
     const int row0 = (tix / TPR) & (KT - 1), piece = tix % TPR;
     const uint32_t ld_lds = tix < Gm::PIECES ? (uint32_t)(row0 * LDB + piece * 8) : (uint32_t)(KT * LDB + (tix - Gm::PIECES) * 8);
     // A piece past the last feature (partial last panel) reads the row's first piece; its products land in
-    // features that are never stored.  A piece that crosses the end of the row (nb is even) is read where it
+    // features that are never stored.  A piece that crosses the end of the row (N is even) is read where it
     // ends with the row, so that nothing behind B is touched, and moved down by whole dwords when it is staged.
-    const int f_piece = panel + 8 * piece, over = f_piece < nb && f_piece + 8 > nb ? (f_piece + 8 - nb) / 2 : 0;
+    const int f_piece = panel + 8 * piece, over = f_piece < N && f_piece + 8 > N ? (f_piece + 8 - N) / 2 : 0;
     [[maybe_unused]] const bool over1 = over == 1, over2 = over == 2, over3 = over == 3;
-    const uint32_t ld_byte = (f_piece + 8 <= nb ? 2u * (uint32_t)f_piece : RAGGED && over ? 2u * (uint32_t)(nb - 8) : 0u) + (RUN ? (uint32_t)row0 * row_bytes : 0u);
+    const uint32_t ld_byte = (f_piece + 8 <= N ? 2u * (uint32_t)f_piece : RAGGED && over ? 2u * (uint32_t)(N - 8) : 0u) + (RUN ? (uint32_t)row0 * row_bytes : 0u);
     // RUN: the window's columns are one run, a fragment's rows of B follow each other
     const char* Bbytes = reinterpret_cast<const char*>(B) + (RUN ? (size_t)(uint32_t)col0 * row_bytes : 0);
     const int g4 = lane >> 4, rr4 = (lane & 15) >> 2, ss4 = lane & 3;
@@ -390,7 +390,7 @@ __device__ __forceinline__ void panel_item(unsigned char* smem, uint32_t win, ui
     }
 }
 
-// RAGGED: rows of B end inside a 16-byte piece (nb is not a multiple of 8).  Moving the broken piece costs 3 % of
+// RAGGED: rows of B end inside a 16-byte piece (N is not a multiple of 8).  Moving the broken piece costs 3 % of
 // the kernel at 128 features, so the other widths have a kernel without it.
 template <int NCH32, int NG, bool RAGGED, class OUT>
 __global__ __launch_bounds__(64 * NG) __attribute__((amdgpu_waves_per_eu(2, NCH32 == 4 ? 2 : 4))) void rsh_panel_kernel(
@@ -398,9 +398,10 @@ __global__ __launch_bounds__(64 * NG) __attribute__((amdgpu_waves_per_eu(2, NCH3
     const uint32_t* __restrict__ win_tile_off, const int32_t* __restrict__ win_col0,
     const int32_t* __restrict__ tile_colid, const uint32_t* __restrict__ quad0, const uint4_t* __restrict__ meta,
     const uint32_t* __restrict__ qoff, const uint32_t* __restrict__ val, const __half* __restrict__ B, const OUT out,
-    float* __restrict__ scratch, int N, int nb, int nv, int feature0) {
+    float* __restrict__ scratch, int N, int feature0, int nv, int ns) {
     using Gm = PanelGeom<NCH32, NG>;
     constexpr int P = Gm::P;
+    if constexpr (!OUT::kAny) nv = N;
     __shared__ __attribute__((aligned(16))) unsigned char smem[Gm::SMEM_BYTES];
 
     const int lane = threadIdx.x & 63;
@@ -436,9 +437,9 @@ __global__ __launch_bounds__(64 * NG) __attribute__((amdgpu_waves_per_eu(2, NCH3
     if (t_begin < t_end) {
         const int32_t col0 = win_col0[win];
         if (col0 >= 0)
-            panel_item<NCH32, NG, true, RAGGED>(smem, win, t_begin, t_end, t0, nt, col0, tile_colid, quad0, meta, qoff, val, B, nb, panel, acc, acc2);
+            panel_item<NCH32, NG, true, RAGGED>(smem, win, t_begin, t_end, t0, nt, col0, tile_colid, quad0, meta, qoff, val, B, N, panel, acc, acc2);
         else
-            panel_item<NCH32, NG, false, RAGGED>(smem, win, t_begin, t_end, t0, nt, col0, tile_colid, quad0, meta, qoff, val, B, nb, panel, acc, acc2);
+            panel_item<NCH32, NG, false, RAGGED>(smem, win, t_begin, t_end, t0, nt, col0, tile_colid, quad0, meta, qoff, val, B, N, panel, acc, acc2);
     }
 
     // ---- output: each group's 32 rows x 32 features take a turn through LDS and leave as whole lines ----
@@ -464,7 +465,7 @@ __global__ __launch_bounds__(64 * NG) __attribute__((amdgpu_waves_per_eu(2, NCH3
             const int prow = shfl_i32(row, pr);
             if (f >= nv) continue;
             if (dst != kNoDst) {
-                *reinterpret_cast<float4_t*>(scratch + ((size_t)dst + wv * 32 + pr) * N + f) = v;   // partial sums: ordinary stores
+                *reinterpret_cast<float4_t*>(scratch + ((size_t)dst + wv * 32 + pr) * ns + f) = v;   // partial sums: ordinary stores
             } else if (prow >= 0) {
                 panel_store(out, (size_t)prow, nv, f, v);
                 keep_streaming_hint();
@@ -479,8 +480,8 @@ void launch_panel_t(const DevicePlan& d, const void* B, const OUT& out, hipStrea
     for (int x = 0; x < 8; ++x) longest = std::max(longest, d.tile_split.start[x + 1] - d.tile_split.start[x]);
     hipLaunchKernelGGL((rsh_panel_kernel<NCH32, NG, RAGGED, OUT>), dim3(8u * longest, (unsigned)panels), dim3(64 * NG), 0, st,
                        (const uint4*)d.tile_item, d.tile_split, d.win_row, d.win_tile_off, d.panel_col0, d.tile_colid,
-                       d.panel_quad0, (const uint4_t*)d.panel_meta, d.panel_qoff, d.panel_val, (const __half*)B, out, d.scratch, d.geo.N,
-                       nb, nv, feature0);
+                       d.panel_quad0, (const uint4_t*)d.panel_meta, d.panel_qoff, d.panel_val, (const __half*)B, out, d.scratch, nb,
+                       feature0, nv, d.geo.N);
 }
 template <int NCH32, class OUT>
 void launch_panel_g(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st, int nb, int nv, int feature0, int panels) {
