@@ -10,6 +10,7 @@
 #include <algorithm>
 #include <chrono>
 #include <cstring>
+#include <limits>
 #include <numeric>
 
 namespace rsh {
@@ -655,25 +656,71 @@ static int pack_panel_windows(const rsh_csr_t& a, const Partition& part, HostPla
     return RSH_OK;
 }
 
-// Parts that tall windows are cut into.  The kernel's workgroups (window parts x feature panels of 128) run one
-// per compute unit, in rounds of 256, and a round takes as long as its longest item: the item's fragments plus
-// what its start and end cost (about 10 us, as much as 20 fragments).  Cut windows leave partial sums: a combine
-// launch (another 10 fragments' time) and 8 bytes a part, row and feature through memory (at 5 TB/s, 0.5 us a
-// fragment).  The cheapest number of parts by this count is taken; parts are not cut below 16 fragments.
-// Measured for 112 windows of 256 fragments: N = 128 one part 133 us, two 99, four 108; N = 256 164, 189, 221;
-// N = 1024 556, 634, 735 us.
-static int64_t choose_panel_parts(int64_t n_win, int64_t n_tiles, const Geometry& geo) {
-    if (n_win == 0 || n_tiles == 0) return 1;
-    const int64_t panels = (geo.N + 127) / 128, nt = (n_tiles + n_win - 1) / n_win;
-    int64_t best = 1;
+// Parts that every tall window is cut into, when the caller leaves it open.  The kernel's workgroups (window parts x
+// feature panels) run one per compute unit.  A workgroup takes as long as its fragments plus what its start and end cost (about 10 us, as much as 20
+// fragments); cut windows leave partial sums: a combine launch (another 10 fragments' time) and 8 bytes a part, row
+// and feature through memory (at 5 TB/s, 0.5 us a fragment).  Item lengths are tried from the longest window whole
+// downwards; a window is cut by its own length into quads of fragments (the kernel runs over whole quads), never below
+// 16 fragments, and the length whose workgroups end first, dealt in order to whichever place is free, is taken.
+// The 20, 10 and 0.5 us come from 256-row windows of one weight, 112 of them with 256 fragments: N = 128 one part
+// 133 us, two 99, four 108; N = 256 164, 189, 221; N = 1024 556, 634, 735 us.  Beside one number of parts for all
+// windows, from their mean length: 256 windows of which 16 are three times longer, N = 512, 219 us, cut by their own
+// length 190; 8 windows of 256 fragments before 118 of 29, N = 128, 98.5 and 86.6 us.
+static std::vector<uint32_t> cut_tall_windows(const HostPlan& plan, int64_t n_win, const std::vector<int64_t>& order) {
+    const Geometry& geo = plan.geo;
+    std::vector<uint32_t> parts((size_t)n_win, 1u);
+    const auto quads = [&](int64_t w) { return (int64_t)(plan.win_tile_off[(size_t)w + 1] - plan.win_tile_off[(size_t)w] + 3) / 4; };
+    int64_t longest = 0, shortest = std::numeric_limits<int64_t>::max();
+    for (int64_t w = 0; w < n_win; ++w) longest = std::max(longest, quads(w)), shortest = std::min(shortest, quads(w));
+    if (longest == 0) return parts;
+    const int64_t panels = (geo.N + 127) / 128;
+    constexpr size_t places = 256;
+    const auto parts_of = [](int64_t nq, int64_t length) { return std::max<int64_t>(1, std::min((nq + length - 1) / length, nq / 4)); };
+    std::vector<double> free_at;
+    const auto cost_of = [&](int64_t length) {
+        int64_t items = 0, slots = 0, work = 0, most = 0;
+        for (int64_t w = 0; w < n_win; ++w) {
+            const int64_t nq = quads(w), p = parts_of(nq, length);
+            items += p;
+            slots += p > 1 ? p * geo.win_rows : 0;
+            most = std::max(most, (nq + p - 1) / p);
+            work += 20 * p + 4 * nq;
+        }
+        double end;
+        if (shortest == longest) {   // equal items: whole rounds
+            end = (double)((items * panels + (int64_t)places - 1) / (int64_t)places) * (20.0 + 4.0 * (double)most);
+        } else if (items * panels > (int64_t)places * 4) {   // many rounds: every place is busy until the last items
+            end = (double)(work * panels) / (double)places + (20.0 + 4.0 * (double)most) / 2;
+        } else {
+            free_at.assign(places, 0.0);   // heap, earliest first
+            const auto later = [](double x, double y) { return x > y; };
+            end = 0.0;
+            for (int64_t f = 0; f < panels; ++f)
+                for (int64_t w : order) {
+                    const int64_t nq = quads(w), p = parts_of(nq, length);
+                    for (int64_t i = 0; i < p; ++i) {
+                        std::pop_heap(free_at.begin(), free_at.end(), later);
+                        free_at.back() += 20.0 + 4.0 * (double)(nq * (i + 1) / p - nq * i / p);
+                        end = std::max(end, free_at.back());
+                        std::push_heap(free_at.begin(), free_at.end(), later);
+                    }
+                }
+        }
+        return end + (slots > 0 ? 10.0 + (double)slots * geo.N * 8.0 / 2.5e6 : 0.0);
+    };
+    // a lane's sums have a second level every 32 fragments, and an item at most 256 additions on it
+    const int64_t fewest = (longest + 2047) / 2048;
+    int64_t best = 0, last = 0;
     double best_cost = 0.0;
-    for (int64_t parts = 1; parts == 1 || nt >= 16 * parts; ++parts) {
-        const double rounds = (double)((n_win * parts * panels + 255) / 256);
-        double cost = rounds * (20.0 + (double)((nt + parts - 1) / parts));
-        if (parts > 1) cost += 10.0 + (double)(n_win * geo.win_rows * parts) * geo.N * 8.0 / 2.5e6;
-        if (parts == 1 || cost < best_cost) best = parts, best_cost = cost;
+    for (int64_t p = fewest; p == fewest || 4 * p <= longest; p += std::max<int64_t>(1, p / 16)) {
+        const int64_t length = (longest + p - 1) / p;
+        if (length == last) continue;
+        last = length;
+        const double cost = cost_of(length);
+        if (best == 0 || cost < best_cost) best = length, best_cost = cost;
     }
-    return best;
+    for (int64_t w = 0; w < n_win; ++w) parts[(size_t)w] = (uint32_t)parts_of(quads(w), best);
+    return parts;
 }
 
 int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int threads) {
@@ -813,11 +860,8 @@ int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int thr
 
     // ---- tile work items (bounded fragments per item, Section 3.3.3) --------------------
     int64_t t_max = plan.opts.max_tiles_per_item;
-    int64_t panel_parts = 1;   // parts a tall window is cut into when the caller leaves it open
-    if (t_max <= 0 && geo.panel) {
-        panel_parts = choose_panel_parts(n_win, n_tiles, geo);
-        t_max = n_tiles;
-    } else if (t_max <= 0) {
+    const bool choose_parts = geo.panel && t_max <= 0;
+    if (t_max <= 0) {
         int64_t per = (n_tiles + 4095) / 4096, p2 = 1;
         while (p2 < per) p2 <<= 1;
         // 512 .. 1024 condensed columns per item: the upper end keeps the fp32 accumulation chain of
@@ -829,15 +873,15 @@ int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int thr
     int64_t slots = 0, n_split_windows = 0;
     std::vector<int64_t> spill_slot(element_level ? (size_t)n_win : 0, -1);   // first slot of a window's spilled rows
     const std::vector<int64_t> worder = schedule_windows(a, plan, n_win, &plan.stats.schedule_cols_given, &plan.stats.schedule_cols_found);
+    std::vector<uint32_t> panel_parts;
+    if (choose_parts) panel_parts = cut_tall_windows(plan, n_win, worder);
     for (int64_t wi = 0; wi < n_win; ++wi) {
         const int64_t w = worder[(size_t)wi];
         const uint32_t t0 = plan.win_tile_off[w], nt = plan.win_tile_off[w + 1] - t0;
-        // the panel form cuts a window between quads of fragments (the kernel runs over whole quads), into parts
-        // of at most 8192 fragments whatever was chosen; the bitmap form into the fewest parts of at most t_max
-        const bool quads = geo.panel && plan.opts.max_tiles_per_item <= 0;
+        // tall windows are cut between quads of fragments, any others into the fewest parts of at most t_max
+        const bool quads = choose_parts;
         const uint32_t nq = (nt + 3) / 4;
-        const uint32_t parts = quads ? (uint32_t)std::max<int64_t>(1, std::min<int64_t>(nq, std::max<int64_t>(panel_parts, (nt + 8191) / 8192)))
-                                     : (uint32_t)std::max<int64_t>(1, (nt + t_max - 1) / t_max);
+        const uint32_t parts = quads ? panel_parts[(size_t)w] : (uint32_t)std::max<int64_t>(1, (nt + t_max - 1) / t_max);
         if (element_level && !win_spill[(size_t)w].empty()) {
             // Rows of this window receive a second contribution from the residual path: the window's
             // parts go to scratch, one more slot per row takes the row's spilled entries, and the

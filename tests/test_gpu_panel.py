@@ -156,3 +156,29 @@ def test_partial_sums_of_several_rows_in_a_wave(opts, N, fused):
     assert not np.isnan(got).any()
     assert np.all(np.abs(got - C_ref) <= bound)
     plan.destroy()
+
+
+# Windows that the planner cuts into different numbers of parts, and not at all, in one product.
+@pytest.mark.parametrize("N", [1, 128, 300])
+@pytest.mark.parametrize("window_rows", [128, 256])
+def test_windows_cut_into_different_numbers_of_parts(window_rows, N):
+    import torch
+    from paper_2603_08734_amd import Plan, binding
+    rng = np.random.default_rng(23)
+    dense = rng.random((5 * window_rows - 7, 3000)) < np.repeat([0.1, 0.001, 0.02, 0.0002, 0.01], window_rows)[:-7, None]
+    r, c = np.nonzero(dense)
+    A = from_coo(r, c, rng.standard_normal(r.size), dense.shape[0], 3000)
+    print(f"case uneven W={window_rows} N={N}", flush=True)
+    plan = Plan(A.row_ptr, A.col_idx, A.val, A.n_cols, N, window_rows=window_rows, force_path=2, reorder=0)
+    parts = np.bincount(plan.array(binding.RSH_ARR_TILE_ITEM).reshape(-1, 4)[:, 0])
+    assert parts.min() == 1 and len(set(parts)) >= 3
+    B = dense_B(A.n_cols, N, "normal", seed=N)
+    Bd = torch.from_numpy(B.view(np.int16)).cuda().view(torch.float16)
+    C = torch.full((A.n_rows, N), float("nan"), dtype=torch.float32, device="cuda")
+    plan.spmm(Bd, C)
+    torch.cuda.synchronize()
+    C_ref, S, _ = oracle.spmm(A.row_ptr, A.col_idx, A.val, B)
+    got = C.cpu().numpy().astype(np.float64)
+    assert not np.isnan(got).any()
+    assert np.all(np.abs(got - C_ref) <= 1e-4 * S)
+    plan.destroy()
