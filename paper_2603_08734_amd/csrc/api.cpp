@@ -311,6 +311,7 @@ int rsh_plan_create(const rsh_csr_t* csr, int32_t N, const rsh_plan_opts_t* opts
         h.n_rows = csr->n_rows;
         h.n_cols = csr->n_cols;
         h.nnz = csr->nnz;
+        h.n_user = n_user;
         const bool choose_w = o.window_rows == 0;
         if (choose_w) o.window_rows = rsh::kW;   // reordering and the first partition work on 16-row windows
         std::vector<int32_t> col_deg;

@@ -47,6 +47,7 @@ XcdSplit split_by_cost(const std::vector<uint32_t>& cost);
 
 struct HostPlan {
     int64_t n_rows = 0, n_cols = 0, nnz = 0;
+    int n_user = 0;   // features of B and C as the caller has them; geo.N is the run width
     Geometry geo;
     rsh_plan_opts_t opts{};
     std::vector<int32_t> order;  // pi: order[i] = original id of the i-th processed row

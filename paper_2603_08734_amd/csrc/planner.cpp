@@ -657,7 +657,8 @@ static int pack_panel_windows(const rsh_csr_t& a, const Partition& part, HostPla
 }
 
 // Parts that every tall window is cut into, when the caller leaves it open.  The kernel's workgroups (window parts x
-// feature panels) run one per compute unit.  A workgroup takes as long as its fragments plus what its start and end cost (about 10 us, as much as 20
+// feature panels) run one per compute unit for 256 rows, and two for 128 rows, whose four waves take half of the
+// registers.  A workgroup takes as long as its fragments plus what its start and end cost (about 10 us, as much as 20
 // fragments); cut windows leave partial sums: a combine launch (another 10 fragments' time) and 8 bytes a part, row
 // and feature through memory (at 5 TB/s, 0.5 us a fragment).  Item lengths are tried from the longest window whole
 // downwards; a window is cut by its own length into quads of fragments (the kernel runs over whole quads), never below
@@ -665,7 +666,8 @@ static int pack_panel_windows(const rsh_csr_t& a, const Partition& part, HostPla
 // The 20, 10 and 0.5 us come from 256-row windows of one weight, 112 of them with 256 fragments: N = 128 one part
 // 133 us, two 99, four 108; N = 256 164, 189, 221; N = 1024 556, 634, 735 us.  Beside one number of parts for all
 // windows, from their mean length: 256 windows of which 16 are three times longer, N = 512, 219 us, cut by their own
-// length 190; 8 windows of 256 fragments before 118 of 29, N = 128, 98.5 and 86.6 us.
+// length 190; 8 windows of 256 fragments before 118 of 29, N = 128, 98.5 and 86.6 us.  512 places for 128-row windows
+// instead of 256: 28672 x 8192 weight, N = 32, 79.6 and 60.4 us; 14336 x 4096, N = 128, 38.5 and 36.0.
 static std::vector<uint32_t> cut_tall_windows(const HostPlan& plan, int64_t n_win, const std::vector<int64_t>& order) {
     const Geometry& geo = plan.geo;
     std::vector<uint32_t> parts((size_t)n_win, 1u);
@@ -673,8 +675,12 @@ static std::vector<uint32_t> cut_tall_windows(const HostPlan& plan, int64_t n_wi
     int64_t longest = 0, shortest = std::numeric_limits<int64_t>::max();
     for (int64_t w = 0; w < n_win; ++w) longest = std::max(longest, quads(w)), shortest = std::min(shortest, quads(w));
     if (longest == 0) return parts;
-    const int64_t panels = (geo.N + 127) / 128;
-    constexpr size_t places = 256;
+    // features of a panel as the launcher chooses them (launch_panels): rows of B that end inside a 16-byte piece
+    // go in panels of 64 where a workgroup has four waves
+    const bool four = geo.panel_groups == 4;
+    const int panel = four && plan.n_user % 2 == 0 && plan.n_user % 8 != 0 && plan.n_user >= 16 ? 64 : 128;
+    const int64_t panels = (plan.n_user + panel - 1) / panel;
+    const size_t places = four ? 512 : 256;
     const auto parts_of = [](int64_t nq, int64_t length) { return std::max<int64_t>(1, std::min((nq + length - 1) / length, nq / 4)); };
     std::vector<double> free_at;
     const auto cost_of = [&](int64_t length) {

@@ -38,3 +38,18 @@ def test_uneven_tall_windows_are_cut_by_their_own_length(blocks, cols, N):
         assert sum(v) == 0 or all(x % 4 == 0 for x in v[:-1])
         assert len(v) == 1 or (min(v[:-1]) >= 16 and v[-1] >= 13)
     plan.destroy()
+
+
+def test_two_workgroups_of_128_rows_share_a_compute_unit():
+    plan = plan_of([(56 * 128, 205)], 4096, 128, 128)      # 56 windows of 128 fragments
+    lengths = [x for v in item_lengths(plan).values() for x in v]
+    assert plan.stats()["n_windows"] == 56 and 256 < len(lengths) <= 512 and max(lengths) == 16
+    plan.destroy()
+
+
+def test_panels_of_64_features_count_as_workgroups():
+    """Rows of B that end inside a 16-byte piece run in panels of 64 features where the window has 128 rows."""
+    wide, ragged = (plan_of([(56 * 128, 205)], 4096, N, 128) for N in (104, 100))
+    assert ragged.stats()["n_tile_items"] * 2 <= 512 < wide.stats()["n_tile_items"] * 2
+    for p in (wide, ragged):
+        p.destroy()
