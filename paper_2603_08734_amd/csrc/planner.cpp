@@ -5,6 +5,7 @@
 //   validate -> column degrees -> (reorder, reorder.cpp) -> partition rows into
 //   windows / irregular rows / empty rows -> pack windows into bitmap fragments
 //   -> pack irregular rows into team segments -> bounded work items + combine list.
+#include "launch.hpp"
 #include "plan.hpp"
 
 #include <algorithm>
@@ -668,7 +669,8 @@ static int pack_panel_windows(const rsh_csr_t& a, const Partition& part, HostPla
 // windows, from their mean length: 256 windows of which 16 are three times longer, N = 512, 219 us, cut by their own
 // length 190; 8 windows of 256 fragments before 118 of 29, N = 128, 98.5 and 86.6 us.  512 places for 128-row windows
 // instead of 256: 28672 x 8192 weight, N = 32, 79.6 and 60.4 us; 14336 x 4096, N = 128, 38.5 and 36.0.
-static std::vector<uint32_t> cut_tall_windows(const HostPlan& plan, int64_t n_win, const std::vector<int64_t>& order) {
+// `max_slots`: partial rows that may be left.
+static std::vector<uint32_t> cut_tall_windows(const HostPlan& plan, int64_t n_win, const std::vector<int64_t>& order, int64_t max_slots) {
     const Geometry& geo = plan.geo;
     std::vector<uint32_t> parts((size_t)n_win, 1u);
     const auto quads = [&](int64_t w) { return (int64_t)(plan.win_tile_off[(size_t)w + 1] - plan.win_tile_off[(size_t)w] + 3) / 4; };
@@ -683,6 +685,7 @@ static std::vector<uint32_t> cut_tall_windows(const HostPlan& plan, int64_t n_wi
     const size_t places = four ? 512 : 256;
     const auto parts_of = [](int64_t nq, int64_t length) { return std::max<int64_t>(1, std::min((nq + length - 1) / length, nq / 4)); };
     std::vector<double> free_at;
+    // 0 when the partial sums take too much room
     const auto cost_of = [&](int64_t length) {
         int64_t items = 0, slots = 0, work = 0, most = 0;
         for (int64_t w = 0; w < n_win; ++w) {
@@ -692,6 +695,7 @@ static std::vector<uint32_t> cut_tall_windows(const HostPlan& plan, int64_t n_wi
             most = std::max(most, (nq + p - 1) / p);
             work += 20 * p + 4 * nq;
         }
+        if (slots > max_slots) return 0.0;
         double end;
         if (shortest == longest) {   // equal items: whole rounds
             end = (double)((items * panels + (int64_t)places - 1) / (int64_t)places) * (20.0 + 4.0 * (double)most);
@@ -723,7 +727,8 @@ static std::vector<uint32_t> cut_tall_windows(const HostPlan& plan, int64_t n_wi
         if (length == last) continue;
         last = length;
         const double cost = cost_of(length);
-        if (best == 0 || cost < best_cost) best = length, best_cost = cost;
+        if (cost == 0.0 && best > 0) break;
+        if (best == 0 || (cost > 0.0 && cost < best_cost)) best = length, best_cost = cost;
     }
     for (int64_t w = 0; w < n_win; ++w) parts[(size_t)w] = (uint32_t)parts_of(quads(w), best);
     return parts;
@@ -864,6 +869,11 @@ int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int thr
 
     }
 
+    // residual rows: entries of a slice, and from which length on a row is cut by column group (both explained below)
+    const int64_t slice_max = plan.opts.max_nnz_per_slice > 0 ? plan.opts.max_nnz_per_slice : 512;
+    const int64_t xp_auto = std::max<int64_t>(128, 16384 / geo.irr_panel);
+    const int64_t xp_min = plan.opts.xcd_partition_nnz == 0 ? xp_auto : plan.opts.xcd_partition_nnz;
+
     // ---- tile work items (bounded fragments per item, Section 3.3.3) --------------------
     int64_t t_max = plan.opts.max_tiles_per_item;
     const bool choose_parts = geo.panel && t_max <= 0;
@@ -880,7 +890,17 @@ int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int thr
     std::vector<int64_t> spill_slot(element_level ? (size_t)n_win : 0, -1);   // first slot of a window's spilled rows
     const std::vector<int64_t> worder = schedule_windows(a, plan, n_win, &plan.stats.schedule_cols_given, &plan.stats.schedule_cols_found);
     std::vector<uint32_t> panel_parts;
-    if (choose_parts) panel_parts = cut_tall_windows(plan, n_win, worder);
+    if (choose_parts) {
+        // what is chosen leaves room in the library-owned array for the residual rows' partial sums (an upper bound of
+        // them), so that the choice keeps no product from rsh_spmm_noalloc
+        const int64_t room = (int64_t)(kStaticScratchBytes / ((size_t)geo.N * sizeof(float)));
+        int64_t residual = 0;
+        for (int32_t r : part.irregular) {
+            const int64_t len = row_len(a, r), slices = (len + slice_max - 1) / slice_max;
+            if (len > geo.irr_tpr) residual += xp_min > 0 && len >= xp_min ? std::min(len, slices + 8) : slices > 1 ? slices : 0;
+        }
+        panel_parts = cut_tall_windows(plan, n_win, worder, residual < room ? room - residual : std::numeric_limits<int64_t>::max());
+    }
     for (int64_t wi = 0; wi < n_win; ++wi) {
         const int64_t w = worder[(size_t)wi];
         const uint32_t t0 = plan.win_tile_off[w], nt = plan.win_tile_off[w + 1] - t0;
@@ -938,7 +958,6 @@ int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int thr
     // rows grouped by exact length, longest first, so that every wave of the short-row kind
     // runs rows of one length and its teams stay in lock step.
     const int G = geo.irr_teams, TPR = geo.irr_tpr;
-    const int64_t slice_max = plan.opts.max_nnz_per_slice > 0 ? plan.opts.max_nnz_per_slice : 512;
     const int64_t n_irr = (int64_t)part.irregular.size();
     std::vector<std::vector<int32_t>> by_len((size_t)TPR + 1);   // by_len[L] = short rows with L entries
     std::vector<int32_t> long_rows;
@@ -973,8 +992,6 @@ int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int thr
     // threshold keeps the bytes a row gathers per panel at 32 KB or more (128 entries of a
     // 128-column panel, 256 of a 64-column one): below that the fixed cost of eight small
     // waves outweighs the better hit rate (measured at 32, 64 and 128 features).
-    const int64_t xp_auto = std::max<int64_t>(128, 16384 / geo.irr_panel);
-    const int64_t xp_min = plan.opts.xcd_partition_nnz == 0 ? xp_auto : plan.opts.xcd_partition_nnz;
     const int64_t n_long = (int64_t)long_rows.size();
     std::vector<uint8_t> col_group;
     bool any_partitioned = false;

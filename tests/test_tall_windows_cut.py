@@ -53,3 +53,11 @@ def test_panels_of_64_features_count_as_workgroups():
     assert ragged.stats()["n_tile_items"] * 2 <= 512 < wide.stats()["n_tile_items"] * 2
     for p in (wide, ragged):
         p.destroy()
+
+
+def test_chosen_parts_fit_the_library_owned_array():
+    """Parts that the planner chooses by itself keep no product from rsh_spmm_noalloc (64 MiB of partial sums)."""
+    plan = plan_of([(70 * 256, 480)], 32000, 256, 256)
+    st = plan.stats()
+    assert st["n_split_windows"] > 0 and st["n_scratch_slots"] * st["N"] * 4 <= 64 << 20
+    plan.destroy()
