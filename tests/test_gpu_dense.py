@@ -29,9 +29,11 @@ def _guards_hold(buf, n, d, offset=0):
     return (b[:GUARD + offset] == 777.0).all() and (b[GUARD + offset + n * d:] == 777.0).all()
 
 
-# one row; edges of the 16- and 32-row groups; one group more than a round of all waves (512 x 4 groups of 32)
-@pytest.mark.parametrize("n", [1, 17, 33, 2049, 65537 + 32])
-@pytest.mark.parametrize("d_in,d_out", [(8, 64), (9, 31), (16, 16), (32, 33), (33, 8), (50, 50), (63, 57), (64, 64)])
+# one row; edges of the 16- and 32-row groups; one group more than a round of all waves of the backward kernel
+# (512 x 4 groups of 32), and of the forward kernel (1024 x 4), two whole rounds of that and a ragged third
+@pytest.mark.parametrize("n,d_in,d_out", [(n, *d) for n in (1, 17, 33, 2049, 65537 + 32)
+                                          for d in ((8, 64), (9, 31), (16, 16), (32, 33), (33, 8), (50, 50), (63, 57), (64, 64))] +
+                         [(n, *d) for n in (131072 + 33, 300001) for d in ((64, 64), (16, 50), (37, 9))])
 def test_dense_products(n, d_in, d_out):
     import torch
     from paper_2603_08734_amd import binding

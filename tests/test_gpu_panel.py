@@ -182,3 +182,40 @@ def test_windows_cut_into_different_numbers_of_parts(window_rows, N):
     assert not np.isnan(got).any()
     assert np.all(np.abs(got - C_ref) <= 1e-4 * S)
     plan.destroy()
+
+
+# More than 2048 waves of fragments: a narrower last panel of features then takes a launch of its own (fewer go along with
+# the others).  Its panel ends with the row: at 130 and 146 features it begins at an even feature inside the panel before, at
+# 160 behind it; 65 and 257 features run beside a padded copy of B, of which the last panel holds one feature that counts.
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("N", [65, 130, 146, 160, 257])
+@pytest.mark.parametrize("window_rows", [16, 64])
+def test_a_narrower_last_panel_in_a_launch_of_its_own(window_rows, N, fused):
+    import torch
+    from paper_2603_08734_amd import Plan
+    from workloads import stencil27
+    A = stencil27(40)
+    print(f"case last panel W={window_rows} N={N} fused={fused}", flush=True)
+    plan = Plan(A.row_ptr, A.col_idx, A.val, A.n_cols, N, window_rows=window_rows, force_path=2)
+    assert plan.stats()["n_tile_items"] * (window_rows // 16) > 2048
+    B = dense_B(A.n_cols, N, "normal", seed=N)
+    Bd = torch.from_numpy(B.view(np.int16)).cuda().view(torch.float16)
+    C_ref, S, _ = oracle.spmm(A.row_ptr, A.col_idx, A.val, B)
+    dtype, pad = (torch.float16 if fused else torch.float32), 64
+    flat = torch.full((A.n_rows * N + 2 * pad,), float("nan"), dtype=dtype, device="cuda")
+    C = flat[pad:pad + A.n_rows * N].view(A.n_rows, N)
+    if fused:
+        bias = torch.linspace(-1, 1, N, device="cuda")
+        plan.spmm_f16(Bd, C, bias, relu=True)
+        C_ref = np.maximum(C_ref + bias.cpu().numpy().astype(np.float64), 0.0)
+        # the fp32 bound, the addition of the bias, one rounding to binary16
+        bound = 1e-4 * S + 2.0 ** -24 * np.abs(C_ref) + 2.0 ** -11 * np.abs(C_ref) * 1.001 + 2.0 ** -24
+    else:
+        plan.spmm(Bd, C)
+        bound = 1e-4 * S
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(flat[:pad]).all()) and bool(torch.isnan(flat[pad + A.n_rows * N:]).all()), "stores outside C"
+    got = C.cpu().numpy().astype(np.float64)
+    assert not np.isnan(got).any()
+    assert np.all(np.abs(got - C_ref) <= bound)
+    plan.destroy()

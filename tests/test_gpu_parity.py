@@ -199,7 +199,7 @@ FULL_SIZE_CASES = [
     (3, 0, dict(window_rows=128)),                                                    # panel form with gathered (not consecutive) columns
     (4, 208, dict(window_rows=128)),                                                  # panel form: a full feature panel and a masked one
     (2, 160, dict(reorder=0)),                                                        # a full and a partial panel in the irregular kernel
-    (3, 112, {}),                                                                     # tile panels of 64, 32 and 16 columns
+    (3, 112, {}),                                                                     # two tile panels of 64 columns, the second ends with the row
     (4, 0, dict(element_level=1)),                                                    # single-row columns of every window on the residual path
     (3, 0, dict(element_level=1)),
 ]
