@@ -484,15 +484,18 @@ void launch_panel_t(const DevicePlan& d, const void* B, const OUT& out, hipStrea
                        feature0, nv, d.geo.N);
 }
 template <int NCH32, class OUT>
-void launch_panel_g(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st, int nb, int nv, int feature0, int panels) {
+int launch_panel_g(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st, int nb, int nv, int feature0, int panels) {
     if (d.geo.panel_groups == 8) {
         if (nb % 8) launch_panel_t<NCH32, 8, true>(d, B, out, st, nb, nv, feature0, panels);
         else launch_panel_t<NCH32, 8, false>(d, B, out, st, nb, nv, feature0, panels);
     } else if (nb % 8 == 0) {
         launch_panel_t<NCH32, 4, false>(d, B, out, st, nb, nv, feature0, panels);
-    } else if constexpr (NCH32 < 4) {   // see launch_panels
+    } else if constexpr (NCH32 < 4) {
         launch_panel_t<NCH32, 4, true>(d, B, out, st, nb, nv, feature0, panels);
+    } else {
+        return RSH_ERR_UNSUPPORTED_N;   // there is no such kernel (launch_panels)
     }
+    return RSH_OK;
 }
 
 template <class OUT>
@@ -506,12 +509,10 @@ int launch_panels(const DevicePlan& d, const void* B, const OUT& out, hipStream_
     // 38.7; 134 features 89.4 and 55.4; 28672 rows, 70 features 90.4 and 59.6, 602 features 268.6 and 258.6).
     const int rest = nv % wide, least = wide == 64 && nv > 64 ? 1 : wide / 2 + 1;
     const int full = nv / wide + (rest >= least);
-    if (full > 0 && wide == 64) launch_panel_g<2>(d, B, out, st, nb, nv, 0, full);
-    else if (full > 0) launch_panel_g<4>(d, B, out, st, nb, nv, 0, full);
-    if (rest >= least || rest == 0) return RSH_OK;
-    if (rest > 32) launch_panel_g<2>(d, B, out, st, nb, nv, nv - rest, 1);
-    else launch_panel_g<1>(d, B, out, st, nb, nv, nv - rest, 1);
-    return RSH_OK;
+    int rc = RSH_OK;
+    if (full > 0) rc = wide == 64 ? launch_panel_g<2>(d, B, out, st, nb, nv, 0, full) : launch_panel_g<4>(d, B, out, st, nb, nv, 0, full);
+    if (rc != RSH_OK || rest >= least || rest == 0) return rc;
+    return rest > 32 ? launch_panel_g<2>(d, B, out, st, nb, nv, nv - rest, 1) : launch_panel_g<1>(d, B, out, st, nb, nv, nv - rest, 1);
 }
 
 }  // namespace
