@@ -64,6 +64,7 @@ struct HostPlan {
     std::vector<int32_t> panel_col0;  // per window: first column if its condensed columns are one run, else -1
     std::vector<uint32_t> panel_off;  // per 32 x 16 unit: start of its entries, a multiple of 4 (one more at the end)
     std::vector<uint32_t> panel_ent;  // (byte address in the operand tile << 16) | binary16 bits
+    int64_t panel_quads = 0, panel_dwords = 0;   // quads of fragments per row group; dwords of the values as packed on upload (panel.hpp)
     // irregular part
     std::vector<int32_t> irr_col;
     std::vector<uint16_t> irr_val;

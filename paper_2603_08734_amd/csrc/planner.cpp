@@ -593,10 +593,11 @@ static int pack_panel_windows(const rsh_csr_t& a, const Partition& part, HostPla
     plan.tile_colid.assign(n_tiles * K, 0);
     plan.panel_col0.assign((size_t)n_win, -1);
     plan.panel_off.assign(n_units + 1, 0);
-    plan.panel_ent.assign((size_t)win_ent_off[n_win] + 512, 0);   // tail pad: a lane may read the quad after an empty unit
+    plan.panel_ent.assign((size_t)win_ent_off[n_win] + 512, 0);   // tail pad of the exported array: its readers may take whole quads of words
     plan.tile_mask.clear();
     plan.tile_val_off.clear();
     plan.tile_val.clear();
+    std::vector<uint64_t> win_dwords((size_t)n_win, 0);   // of the packed values
     // pass 2: fill
     parallel_dynamic(n_win, threads, 1, [&](int64_t b, int64_t e, int) {
         WindowColumns wc;
@@ -616,14 +617,20 @@ static int pack_panel_windows(const rsh_csr_t& a, const Partition& part, HostPla
             // Entries come row by row, columns ascending; a cell's address orders a unit by (half of
             // the K step, row, column): counting the two halves of every unit apart puts each entry
             // straight into its final place.
+            // Runs of a row's entries within eight columns are a lane's values, padded to whole dwords on upload.
             half.assign(2 * nu, 0);
+            uint64_t dwords = 0;
             for (int r = 0; r < W; ++r) {
                 if (rows[r] < 0) continue;
+                uint32_t run_of = ~0u, run = 0;
                 for (int64_t p = a.row_ptr[rows[r]]; p < a.row_ptr[rows[r] + 1]; ++p) {
                     const uint32_t u = wc.rank[(size_t)a.col_idx[p]];
                     ++half[2 * panel_unit_of((uint32_t)r, u, nt) + ((u % 16) / 8)];
+                    if (u / 8 != run_of) run_of = u / 8, run = 0;
+                    dwords += run++ % 2 == 0;
                 }
             }
+            win_dwords[(size_t)w] = dwords;
             start.assign(nu + 1, 0);
             for (size_t q = 0; q < nu; ++q) {   // start[q] = padded entries of units before q
                 const uint32_t padded = (half[2 * q] + half[2 * q + 1] + 3u) & ~3u;
@@ -654,6 +661,12 @@ static int pack_panel_windows(const rsh_csr_t& a, const Partition& part, HostPla
         }
     });
     plan.panel_off[n_units] = (uint32_t)win_ent_off[n_win];
+    plan.panel_dwords = 0;
+    plan.panel_quads = 0;
+    for (int64_t w = 0; w < n_win; ++w) {
+        plan.panel_dwords += (int64_t)win_dwords[(size_t)w];
+        plan.panel_quads += (int64_t)G * ((plan.win_tile_off[(size_t)w + 1] - plan.win_tile_off[(size_t)w] + 3) / 4);
+    }
     return RSH_OK;
 }
 
@@ -1239,18 +1252,21 @@ int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int thr
     (void)n_tile_combine;
     st.n_scratch_slots = slots;
     st.sum_window_cols = sum_cols;
-    st.plan_bytes = (int64_t)(plan.win_row.size() * 4 + plan.win_tile_off.size() * 4 + plan.tile_colid.size() * 4 +
+    // tall windows: per quad masks and starts of the values (1 KB) and where its first value lies, the values in dwords,
+    // and a window's first quad (panel.hpp; what PANEL_ENT and PANEL_OFF hold is on the device in that form only)
+    const int64_t panel_bytes = geo.panel ? plan.panel_quads * 1028 + plan.panel_dwords * 4 + (n_win + 1) * 4 : 0;
+    st.plan_bytes = panel_bytes +
+                    (int64_t)(plan.win_row.size() * 4 + plan.win_tile_off.size() * 4 + plan.tile_colid.size() * 4 +
                               plan.tile_mask.size() * 8 + plan.tile_val_off.size() * 4 + plan.tile_val.size() * 2 +
-                              plan.tile_item.size() * 4 + plan.panel_col0.size() * 4 + plan.panel_off.size() * 4 +
-                              plan.panel_ent.size() * 4 + plan.irr_col.size() * 4 + plan.irr_val.size() * 2 +
+                              plan.tile_item.size() * 4 + plan.panel_col0.size() * 4 + plan.irr_col.size() * 4 + plan.irr_val.size() * 2 +
                               plan.irr_wave.size() * 4 + plan.irr_row.size() * 4 + plan.combine.size() * 4);
     st.csr_bytes = 6 * a.nnz + 8 * (a.n_rows + 1);
     // What the product has to move under the routing as built (rows are routed whole, Section 3.1):
     // the plan once, a row of B per distinct column of every window and per residual entry, every
     // row of C once, partial rows written and read back.  And under element-level routing, where a
     // window's single-row columns would go to the residual path: their plan bytes change from a
-    // fragment column (column id, a column of bitmap bits, the value: 4 + W/8 + 2, or the 4-byte
-    // entry of the panel form plus its share of a column id) to a residual entry (6), their rows
+    // fragment column (column id, a column of bitmap bits, the value: 4 + W/8 + 2; in the panel form the
+    // column id and a dword for the value) to a residual entry (6), their rows
     // of B are fetched either way, and every row that is then written by both kernels costs one
     // more read and write of its row of C.
     {
@@ -1263,9 +1279,9 @@ int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int thr
         const int64_t per_tile_entry = geo.panel ? 4 + 4 : 4 + geo.win_rows / 8 + 2;
         st.bytes_method_element_level = st.bytes_method - (per_tile_entry - 6) * single_entries + 2 * 4 * Nf * single_rows;
     }
-    st.tile_part_bytes = (int64_t)(plan.win_row.size() * 4 + plan.tile_colid.size() * 4 + plan.tile_mask.size() * 8 +
+    st.tile_part_bytes = panel_bytes + (int64_t)(plan.win_row.size() * 4 + plan.tile_colid.size() * 4 + plan.tile_mask.size() * 8 +
                                    plan.tile_val_off.size() * 4 + plan.tile_val.size() * 2 + plan.tile_item.size() * 4 +
-                                   plan.panel_col0.size() * 4 + plan.panel_off.size() * 4 + plan.panel_ent.size() * 4);
+                                   plan.panel_col0.size() * 4);
     st.irregular_part_bytes = (int64_t)(plan.irr_col.size() * 4 + plan.irr_val.size() * 2 + plan.irr_wave.size() * 4 +
                                         plan.irr_row.size() * 4);
     {
