@@ -333,7 +333,7 @@ int rsh_reorder_knn(const rsh_csr_t *csr, const rsh_plan_opts_t *opts, int32_t *
  *                                               one run of consecutive columns filling whole
  *                                               fragments (column ids are then computed), else -1
  *   RSH_ARR_PANEL_OFF    uint32 [2*G*n_tiles+1] start of each unit's entries in PANEL_ENT, a multiple
- *                                               of 4 (a lane fetches four entries with one load)
+ *                                               of 4 (units are padded to four words)
  *   RSH_ARR_PANEL_ENT    uint32 []              one word per stored entry: bits 0..15 the binary16
  *                                               value, bits 16..31 the byte address of its cell in
  *                                               the operand as the instruction holds it:

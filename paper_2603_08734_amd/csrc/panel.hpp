@@ -23,9 +23,9 @@
 //     cleared), which bounds the fp32 accumulation chain whatever the item length, so windows are cut into
 //     few, long items and few partial sums cross HBM.
 // What bounds it: a fragment of a 256-row window at 128 features takes 1090 cycles of a compute unit, 512 of
-// them of the matrix units; 8 reads of B, 24 vector and 12 scalar instructions share the issue slots of two
-// waves per SIMD with them (a loop of the same multiply-adds, reads and vector instructions alone takes 710
-// cycles), at 2.0-2.2 GHz under that load.  One wave per SIMD with two row groups each (half the reads of B)
+// them of the matrix units.  Beside the 4 multiply-adds of a K step a wave issues 27.5 vector, 15 scalar and 10.7 LDS
+// instructions (counters), 8 of these reads of B, and two waves share a SIMD's issue slots (a loop of the same
+// multiply-adds, reads of B and expansion alone takes 710 cycles), at 2.0-2.2 GHz under that load.  One wave per SIMD with two row groups each (half the reads of B)
 // took 1690 cycles.
 // The product is formed transposed as in the fragment kernel: features along M (operand A, from the
 // staged B rows through the transposing read), window rows along N (operand B, the expanded piece
