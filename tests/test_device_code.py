@@ -62,6 +62,22 @@ def test_rows_of_c_leave_with_the_streaming_hint(kernels_asm):
         assert st and all(want in l and " nt" in l for l in st), f"{name}: {st}"
 
 
+def test_rows_of_even_widths_leave_with_the_streaming_hint(kernels_asm):
+    """The kernels for rows that are not a multiple of 16 features keep the hint as those above do."""
+    seen = {"fragment_even": 0, "residual_even": 0, "sum_even": 0}
+    for name, body in kernels_asm.items():
+        kind = next((k for k in seen if f"rsh_{k}_kernel" in name), None)
+        if kind is None:
+            continue
+        seen[kind] += 1
+        st = [l for l in body.splitlines() if "global_store_dwordx" in l]
+        nt = sum(" nt" in l for l in st)
+        # fragments: partial sums leave with ordinary stores, one per 16-feature chunk
+        ordinary = int(re.search(r"rsh_fragment_even_kernelILi(\d+)E", name).group(1)) if kind == "fragment_even" else 0
+        assert nt > 0 and len(st) - nt == ordinary, f"{name}: {nt} of {len(st)} stores are streaming"
+    assert seen["fragment_even"] >= 60 and seen["residual_even"] == 8 and seen["sum_even"] == 2
+
+
 def test_kernels_keep_their_registers(kernels_asm):
     for name, body in kernels_asm.items():
         m = re.search(r"\.amdhsa_private_segment_fixed_size\s+(\d+)", body)
