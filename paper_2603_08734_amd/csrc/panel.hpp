@@ -504,10 +504,10 @@ int launch_panels(const DevicePlan& d, const void* B, const OUT& out, hipStream_
     // inside a 16-byte piece and the window has 128 rows (a thread then stages two pieces of a 128-feature row
     // and has no registers left to move the broken one).
     const int wide = d.geo.panel_groups == 4 && nb % 8 ? 64 : 128;
-    // A rest of more than half a panel goes along.  Of panels of 64, which leave room for a second workgroup on a compute
-    // unit, any rest does: a launch of its own lasts as long as the other (14336 x 4096 weight, 70 features, 54.9 us and
-    // 38.7; 134 features 89.4 and 55.4; 28672 rows, 70 features 90.4 and 59.6, 602 features 268.6 and 258.6).
-    const int rest = nv % wide, least = wide == 64 && nv > 64 ? 1 : wide / 2 + 1;
+    // Behind a whole panel any rest goes along: a launch of its own lasts nearly as long as the other, whose workgroups seldom
+    // fill the chip to the last.  28672 x 8192 weight, 256-row windows: 130 features 252 us and 151, 300 features 275 and
+    // 239 (with cut_tall_windows' last round); 128-row windows, panels of 64: 70 features 90.4 and 59.6, 602 features 268.6 and 258.6.
+    const int rest = nv % wide, least = nv > wide ? 1 : wide / 2 + 1;
     const int full = nv / wide + (rest >= least);
     int rc = RSH_OK;
     if (full > 0) rc = wide == 64 ? launch_panel_g<2>(d, B, out, st, nb, nv, 0, full) : launch_panel_g<4>(d, B, out, st, nb, nv, 0, full);

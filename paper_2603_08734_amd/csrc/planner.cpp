@@ -695,56 +695,100 @@ static std::vector<uint32_t> cut_tall_windows(const HostPlan& plan, int64_t n_wi
     const bool four = geo.panel_groups == 4;
     const int panel = four && plan.n_user % 2 == 0 && plan.n_user % 8 != 0 && plan.n_user >= 16 ? 64 : 128;
     const int64_t panels = (plan.n_user + panel - 1) / panel;
-    const size_t places = four ? 512 : 256;
-    const auto parts_of = [](int64_t nq, int64_t length) { return std::max<int64_t>(1, std::min((nq + length - 1) / length, nq / 4)); };
+    const int64_t places = four ? 512 : 256;
+    const auto parts_of = [](int64_t nq, int64_t length) { return (uint32_t)std::max<int64_t>(1, std::min((nq + length - 1) / length, nq / 4)); };
     std::vector<double> free_at;
+    std::vector<uint32_t> quads_of, dispatch_cost;
+    XcdSplit split;
     // 0 when the partial sums take too much room
-    const auto cost_of = [&](int64_t length) {
+    const auto cost_of = [&]() {
         int64_t items = 0, slots = 0, work = 0, most = 0;
         for (int64_t w = 0; w < n_win; ++w) {
-            const int64_t nq = quads(w), p = parts_of(nq, length);
+            const int64_t nq = quads(w), p = parts[(size_t)w];
             items += p;
             slots += p > 1 ? p * geo.win_rows : 0;
             most = std::max(most, (nq + p - 1) / p);
             work += 20 * p + 4 * nq;
         }
         if (slots > max_slots) return 0.0;
-        double end;
-        if (shortest == longest) {   // equal items: whole rounds
-            end = (double)((items * panels + (int64_t)places - 1) / (int64_t)places) * (20.0 + 4.0 * (double)most);
-        } else if (items * panels > (int64_t)places * 4) {   // many rounds: every place is busy until the last items
-            end = (double)(work * panels) / (double)places + (20.0 + 4.0 * (double)most) / 2;
-        } else {
-            free_at.assign(places, 0.0);   // heap, earliest first
+        double end = 0.0;
+        if (items * panels > places * 8) {   // many rounds: every place is busy until the last items
+            end = shortest == longest ? (double)((items * panels + places - 1) / places) * (20.0 + 4.0 * (double)most)
+                                      : (double)(work * panels) / (double)places + (20.0 + 4.0 * (double)most) / 2;
+        } else {   // each XCD deals its part of the items (split_by_cost) to whichever of its places is free
+            quads_of.clear();
+            for (int64_t w : order) {
+                const int64_t nq = quads(w), p = parts[(size_t)w];
+                for (int64_t i = 0; i < p; ++i) quads_of.push_back((uint32_t)(nq * (i + 1) / p - nq * i / p));
+            }
+            dispatch_cost.resize(quads_of.size());
+            for (size_t i = 0; i < quads_of.size(); ++i) dispatch_cost[i] = 4 * quads_of[i] + 4;
+            split = split_by_cost(dispatch_cost);
             const auto later = [](double x, double y) { return x > y; };
-            end = 0.0;
-            for (int64_t f = 0; f < panels; ++f)
-                for (int64_t w : order) {
-                    const int64_t nq = quads(w), p = parts_of(nq, length);
-                    for (int64_t i = 0; i < p; ++i) {
-                        std::pop_heap(free_at.begin(), free_at.end(), later);
-                        free_at.back() += 20.0 + 4.0 * (double)(nq * (i + 1) / p - nq * i / p);
-                        end = std::max(end, free_at.back());
-                        std::push_heap(free_at.begin(), free_at.end(), later);
-                    }
-                }
+            for (int x = 0; x < 8; ++x) {
+                free_at.assign((size_t)places / 8, 0.0);   // heap, earliest first
+                const auto deal = [&](uint32_t i) {
+                    std::pop_heap(free_at.begin(), free_at.end(), later);
+                    free_at.back() += 20.0 + 4.0 * (double)quads_of[i];
+                    end = std::max(end, free_at.back());
+                    std::push_heap(free_at.begin(), free_at.end(), later);
+                };
+                for (int64_t f = 0; f < panels; ++f)
+                    for (uint32_t i = split.start[x]; i < split.start[x + 1]; ++i) deal(i);
+            }
         }
         return end + (slots > 0 ? 10.0 + (double)slots * geo.N * 8.0 / 2.5e6 : 0.0);
     };
     // a lane's sums have a second level every 32 fragments, and an item at most 256 additions on it
     const int64_t fewest = (longest + 2047) / 2048;
-    int64_t best = 0, last = 0;
+    int64_t last = 0;
     double best_cost = 0.0;
+    std::vector<uint32_t> best;
     for (int64_t p = fewest; p == fewest || 4 * p <= longest; p += std::max<int64_t>(1, p / 16)) {
         const int64_t length = (longest + p - 1) / p;
         if (length == last) continue;
         last = length;
-        const double cost = cost_of(length);
-        if (cost == 0.0 && best > 0) break;
-        if (best == 0 || (cost > 0.0 && cost < best_cost)) best = length, best_cost = cost;
+        for (int64_t w = 0; w < n_win; ++w) parts[(size_t)w] = parts_of(quads(w), length);
+        const double cost = cost_of();
+        if (cost == 0.0 && !best.empty()) break;
+        if (best.empty() || (cost > 0.0 && cost < best_cost)) best = parts, best_cost = cost;
     }
-    for (int64_t w = 0; w < n_win; ++w) parts[(size_t)w] = (uint32_t)parts_of(quads(w), best);
-    return parts;
+    // The last round of a few is seldom full: then the last windows of every XCD's part are cut further where that ends
+    // sooner (28672 x 8192 weight: 112 windows of 256 fragments at 384 features are 336 workgroups on 256 compute units,
+    // 281 us; with the last six of an XCD's 14 windows in two parts 235).
+    parts = best;
+    int64_t items = 0;
+    for (uint32_t p : best) items += p;
+    const int64_t rounds = items * panels / places;
+    if (best_cost == 0.0 || rounds < 1 || rounds >= 8) return best;
+    (void)cost_of();   // `split` of the chosen parts
+    std::vector<int64_t> behind((size_t)n_win, 0);   // windows that follow this one in its XCD's part
+    {
+        std::vector<int> xcd((size_t)n_win);
+        uint32_t at = 0;
+        int x = 0;
+        for (int64_t w : order) {
+            while (x < 7 && at >= split.start[x + 1]) ++x;
+            xcd[(size_t)w] = x;
+            at += best[(size_t)w];
+        }
+        for (int64_t i = n_win - 2; i >= 0; --i) {
+            const size_t w = (size_t)order[(size_t)i], next = (size_t)order[(size_t)i + 1];
+            behind[w] = xcd[w] == xcd[next] ? behind[next] + 1 : 0;
+        }
+    }
+    const std::vector<uint32_t> even = best;
+    const int64_t deepest = *std::max_element(behind.begin(), behind.end()) + 1;
+    for (int64_t f = 2; f <= 4; ++f)
+        for (int64_t m = 1; m <= deepest; m += std::max<int64_t>(1, deepest / 16)) {
+            for (size_t w = 0; w < (size_t)n_win; ++w) {
+                const int64_t finest = std::max<int64_t>(1, quads((int64_t)w) / 4);
+                parts[w] = behind[w] < m ? (uint32_t)std::max<int64_t>(even[w], std::min(even[w] * f, finest)) : even[w];
+            }
+            const double cost = cost_of();
+            if (cost > 0.0 && cost < best_cost) best = parts, best_cost = cost;
+        }
+    return best;
 }
 
 int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int threads) {

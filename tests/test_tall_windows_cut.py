@@ -61,3 +61,17 @@ def test_chosen_parts_fit_the_library_owned_array():
     st = plan.stats()
     assert st["n_split_windows"] > 0 and st["n_scratch_slots"] * st["N"] * 4 <= 64 << 20
     plan.destroy()
+
+
+# 40 equal windows at seven panels of features are 35 workgroups for every 32 compute units: a second round, which ends
+# sooner when its windows are cut; at one panel all parts run at once
+@pytest.mark.parametrize("N,cut", [(896, True), (770, True), (128, False)])
+def test_the_last_windows_of_a_part_are_cut_further_where_a_round_is_left_nearly_empty(N, cut):
+    plan = plan_of([(40 * 256, 150)], 4096, N, 256)
+    items = item_lengths(plan)
+    counts = {len(v) for v in items.values()}
+    assert (len(counts) > 1) == cut and all(sum(v) == 128 for v in items.values())
+    if cut:      # whole windows first in every eighth of the list
+        parts = [len(items[w]) for w in dict.fromkeys(plan.array(binding.RSH_ARR_TILE_ITEM).reshape(-1, 4)[:, 0].tolist())]
+        assert min(parts) == 1 and all(parts[5 * x] == 1 and parts[5 * x + 4] > 1 for x in range(8))
+    plan.destroy()
