@@ -169,8 +169,11 @@ def main() -> int:
             acc[k] += t[k]
     kernel_ms = {k: v / n_prof for k, v in acc.items()}
     dominant = max(("tile", "irregular"), key=lambda k: kernel_ms[k])
-    # the dense-fragment part runs in the panel kernel for windows of 128 rows and more
-    kernel_name = "rsh_irregular_kernel" if dominant == "irregular" else ("rsh_panel_kernel" if st["window_rows"] >= 128 else "rsh_tile_kernel")
+    # the dense-fragment part runs in the panel kernel for windows of 128 rows and more, with its cells written out beyond
+    # 128 features where one cell in sixteen is stored
+    wide = st["window_rows"] == 256 and N > 128 and st["nnz_tile"] * 16 >= st["n_tiles"] * 32 * 256
+    tile_kernel = "rsh_wide_kernel" if wide else "rsh_panel_kernel" if st["window_rows"] >= 128 else "rsh_tile_kernel"
+    kernel_name = "rsh_irregular_kernel" if dominant == "irregular" else tile_kernel
     if dominant == "irregular":
         alg_bytes = st["irregular_part_bytes"] + 2 * N * st["cols_irregular"] + 4 * N * st["rows_irregular"]
     else:

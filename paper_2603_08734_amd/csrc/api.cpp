@@ -109,7 +109,7 @@ int upload_array(Uploader& up, const std::vector<T>& h, T** d) {
 
 void free_device(rsh::DevicePlan& d) {
     void* ptrs[] = {d.win_row, d.win_tile_off, d.tile_colid, d.tile_mask, d.tile_val_off, d.tile_val,
-                    d.tile_item, d.panel_col0, d.panel_off, d.panel_ent, d.panel_quad0, d.panel_meta, d.panel_qoff, d.panel_val, d.irr_col, d.irr_val, d.irr_wave, d.irr_row, d.combine, d.scratch,
+                    d.tile_item, d.panel_col0, d.panel_off, d.panel_ent, d.panel_quad0, d.panel_meta, d.panel_qoff, d.panel_val, d.panel_cells, d.irr_col, d.irr_val, d.irr_wave, d.irr_row, d.combine, d.scratch,
                     d.b_pad};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
@@ -119,18 +119,11 @@ void free_device(rsh::DevicePlan& d) {
     d = rsh::DevicePlan{};
 }
 
-// The entries of a panel-form plan are turned on the device into the form the kernel reads (panel.hpp);
+// The entries of a panel-form plan are turned on the device into the form the kernel reads (panel.hpp, wide.hpp);
 // what was uploaded for that is given back.
-int upload_panel_units(Uploader& up, const rsh::HostPlan& h, rsh::DevicePlan& d) {
+int upload_panel_units(Uploader& up, rsh::HostPlan& h, rsh::DevicePlan& d) {
     const int64_t n_windows = (int64_t)h.win_tile_off.size() - 1, n_units = (int64_t)h.panel_off.size() - 1;
-    std::vector<uint32_t> quad0((size_t)n_windows + 1, 0);
-    for (int64_t w = 0; w < n_windows; ++w)
-        quad0[(size_t)w + 1] = quad0[(size_t)w] + (uint32_t)h.geo.panel_groups * ((h.win_tile_off[(size_t)w + 1] - h.win_tile_off[(size_t)w] + 3) / 4);
-    const size_t n_quads = quad0[(size_t)n_windows];
     int rc;
-    if ((rc = upload_array(up, quad0, &d.panel_quad0))) return rc;
-    if (!hip_ok(hipMalloc((void**)&d.panel_meta, (n_quads + 1) * 1024))) return RSH_ERR_OOM;
-    if (!hip_ok(hipMalloc((void**)&d.panel_qoff, (n_quads + 1) * 4))) return RSH_ERR_OOM;
     if (n_units <= 0) return RSH_OK;
     uint32_t* counts = nullptr;
     struct Temporary {
@@ -145,6 +138,25 @@ int upload_panel_units(Uploader& up, const rsh::HostPlan& h, rsh::DevicePlan& d)
     } temporary{d, counts};
     if ((rc = upload_array(up, h.panel_off, &d.panel_off))) return rc;
     if ((rc = upload_array(up, h.panel_ent, &d.panel_ent))) return rc;
+    if (h.geo.wide) {
+        d.n_tiles = h.win_tile_off[(size_t)n_windows];
+        if (hip_ok(hipMalloc((void**)&d.panel_cells, (2 * (size_t)d.n_tiles + 1) * rsh::kWideStepBytes))) {
+            if ((rc = rsh::launch_wide_cells(d, n_windows, up.stream))) return rc;
+            return hip_ok(hipStreamSynchronize(up.stream)) ? RSH_OK : RSH_ERR_HIP;
+        }
+        // no room for every cell: the same items run on the packed form
+        const int64_t written_out = rsh::panel_device_bytes(h);
+        h.geo.wide = d.geo.wide = 0;
+        const int64_t less = written_out - rsh::panel_device_bytes(h);
+        for (int64_t* bytes : {&h.stats.plan_bytes, &h.stats.tile_part_bytes, &h.stats.bytes_method, &h.stats.bytes_method_element_level}) *bytes -= less;
+    }
+    std::vector<uint32_t> quad0((size_t)n_windows + 1, 0);
+    for (int64_t w = 0; w < n_windows; ++w)
+        quad0[(size_t)w + 1] = quad0[(size_t)w] + (uint32_t)h.geo.panel_groups * ((h.win_tile_off[(size_t)w + 1] - h.win_tile_off[(size_t)w] + 3) / 4);
+    const size_t n_quads = quad0[(size_t)n_windows];
+    if ((rc = upload_array(up, quad0, &d.panel_quad0))) return rc;
+    if (!hip_ok(hipMalloc((void**)&d.panel_meta, (n_quads + 1) * 1024))) return RSH_ERR_OOM;
+    if (!hip_ok(hipMalloc((void**)&d.panel_qoff, (n_quads + 1) * 4))) return RSH_ERR_OOM;
     if (!hip_ok(hipMalloc((void**)&counts, (size_t)(n_units + 1) * 4))) return RSH_ERR_OOM;
     uint32_t total = 0;
     if (!hip_ok(hipMemsetAsync(d.panel_meta, 0, (n_quads + 1) * 1024, up.stream))) return RSH_ERR_HIP;

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 
+#include <type_traits>
+
 #include "launch.hpp"
 
 namespace rsh {
@@ -159,28 +161,31 @@ __device__ __forceinline__ void tile_store(const OutPlainT<ROWS>& o, size_t row,
     else store_tail(p, nv - f, v);
 }
 
-// Four features of a row of C of `nv` features (even), or its last two; any number of them for kAny.
+// Four features of a row of C of `nv` features, f + 4 <= nv; or what is left of it from f on: its last two (nv is even), for
+// kAny any number.
 template <int ROWS>
-__device__ __forceinline__ void panel_store(const OutPlainT<ROWS>& o, size_t row, int nv, int f, float4_t v) {
+__device__ __forceinline__ void panel_store_whole(const OutPlainT<ROWS>& o, size_t row, int nv, int f, float4_t v) {
+    store_c_streaming(o.C + row * nv + f, v);
+}
+template <int ROWS>
+__device__ __forceinline__ void panel_store_tail(const OutPlainT<ROWS>& o, size_t row, int nv, int f, float4_t v) {
     float* p = o.C + row * nv + f;
-    if (f + 4 <= nv) store_c_streaming(p, v);
-    else if constexpr (ROWS == kRowsAny) store_tail(p, nv - f, v);
+    if constexpr (ROWS == kRowsAny) store_tail(p, nv - f, v);
     else __builtin_nontemporal_store((float2_t){v[0], v[1]}, reinterpret_cast<float2_a4*>(p));
 }
 template <int ROWS>
-__device__ __forceinline__ void panel_store(const OutFusedT<ROWS>& o, size_t row, int nv, int f, float4_t v) {
+__device__ __forceinline__ void panel_store_whole(const OutFusedT<ROWS>& o, size_t row, int nv, int f, float4_t v) {
+    typedef typename std::conditional<ROWS == kRowsAny, uint2_a2, uint2_a4>::type target_t;
+    __builtin_nontemporal_store(finish4(o, f, nv, v), reinterpret_cast<target_t*>(o.C + row * nv + f));
+}
+template <int ROWS>
+__device__ __forceinline__ void panel_store_tail(const OutFusedT<ROWS>& o, size_t row, int nv, int f, float4_t v) {
     _Float16* p = o.C + row * nv + f;
     if constexpr (ROWS == kRowsAny) {
         const uint2_t h = finish4(o, f, nv, v);
-        if (f + 4 <= nv) {
-            __builtin_nontemporal_store(h, reinterpret_cast<uint2_a2*>(p));
-        } else {
 #pragma unroll
-            for (int i = 0; i < 3; ++i)
-                if (f + i < nv) __builtin_nontemporal_store((uint16_t)(h[i / 2] >> (16 * (i & 1))), reinterpret_cast<uint16_t*>(p + i));
-        }
-    } else if (f + 4 <= nv) {
-        __builtin_nontemporal_store(finish4(o, f, nv, v), reinterpret_cast<uint2_a4*>(p));
+        for (int i = 0; i < 3; ++i)
+            if (f + i < nv) __builtin_nontemporal_store((uint16_t)(h[i / 2] >> (16 * (i & 1))), reinterpret_cast<uint16_t*>(p + i));
     } else {
         float2_t t = {v[0], v[1]};
         if (o.bias) t += *reinterpret_cast<const float2_a4*>(o.bias + f);
@@ -189,6 +194,12 @@ __device__ __forceinline__ void panel_store(const OutFusedT<ROWS>& o, size_t row
         const half2_t h = {(_Float16)t[0], (_Float16)t[1]};
         __builtin_nontemporal_store(__builtin_bit_cast(uint32_t, h), reinterpret_cast<uint32_t*>(p));
     }
+}
+// Both, for callers that hold nothing across the store.
+template <class OUT>
+__device__ __forceinline__ void panel_store(const OUT& o, size_t row, int nv, int f, float4_t v) {
+    if (f + 4 <= nv) panel_store_whole(o, row, nv, f, v);
+    else panel_store_tail(o, row, nv, f, v);
 }
 
 }  // namespace rsh

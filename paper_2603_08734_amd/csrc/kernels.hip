@@ -3,6 +3,7 @@
 //   rsh_tile_kernel      dense-fragment path: the MFMA counterpart of the pipelined
 //                        Tensor-Core kernel (paper, Section 3.3.2, Algorithm 2)
 //   rsh_panel_kernel     the same for tall windows (panel.hpp)
+//   rsh_wide_kernel      the same for tall windows and many features (wide.hpp)
 //   rsh_irregular_kernel residual rows (Section 3.3.2, "CUDA path"), teams of lanes own
 //                        feature columns, long rows arrive as bounded slices (Section 3.3.3)
 //   rsh_combine_kernel   fixed-order sum of the partial results of split windows / rows
@@ -23,6 +24,7 @@
 
 #include "device.hpp"
 #include "panel.hpp"
+#include "wide.hpp"
 
 namespace rsh {
 
@@ -929,7 +931,9 @@ static int launch_all(const DevicePlan& d, const void* B, const OUT& out, int nb
             return RSH_ERR_HIP;
     }
     hipStream_t st = forked ? (hipStream_t)d.side : caller;
-    if (d.n_tile_items > 0 && d.geo.panel) {
+    if (d.n_tile_items > 0 && d.geo.wide) {
+        launch_wide(d, B, out.general(), st, nb, nv);
+    } else if (d.n_tile_items > 0 && d.geo.panel) {
         rc = launch_panels(d, B, out.general(), st, nb, nv);
         if (rc != RSH_OK) return rc;
     } else if (d.n_tile_items > 0) {

@@ -26,6 +26,8 @@ struct DevicePlan {
     uint32_t* panel_meta = nullptr;
     uint32_t* panel_qoff = nullptr;
     uint32_t* panel_val = nullptr;
+    uint32_t* panel_cells = nullptr;   // or with every cell written out (wide.hpp)
+    uint32_t n_tiles = 0;
     int32_t* irr_col = nullptr;
     uint16_t* irr_val = nullptr;
     uint32_t* irr_wave = nullptr;
@@ -52,6 +54,10 @@ int launch_spmm(const DevicePlan& d, const void* B_dev, void* C_dev, int nb, int
 // room for their values made, the value stream.  Both read panel_off / panel_ent.
 int launch_panel_masks(const DevicePlan& d, int64_t n_windows, int64_t n_units, uint32_t* unit_dwords, void* stream);
 int launch_panel_values(const DevicePlan& d, int64_t n_windows, const uint32_t* unit_start, void* stream);
+
+// The same for plans whose cells are written out: panel_cells from panel_off / panel_ent.
+int launch_wide_cells(const DevicePlan& d, int64_t n_windows, void* stream);
+constexpr size_t kWideStepBytes = 8192;   // one K step of a window of 256 rows
 
 // Bytes of the library-owned partial-sum array that every GPU holds for rsh_spmm_noalloc, and its
 // address on the current device (looked up on the first call per device; allocates nothing).

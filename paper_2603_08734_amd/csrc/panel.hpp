@@ -36,7 +36,7 @@
 #pragma once
 #include <algorithm>
 
-#include "device.hpp"
+#include "tall.hpp"
 
 namespace rsh {
 
@@ -156,21 +156,13 @@ struct PanelGeom {
     static constexpr int NBUF = 4;                            // staged B tiles (fragment s lives in tile s mod 4)
     static constexpr int LUT_BYTES = 128;
     static constexpr int LOOP_BYTES = LUT_BYTES + NBUF * TILE_HALVES * 2;
-    static constexpr int STAGE_STRIDE = 36;                   // floats per staged output row (32 + pad)
-    static constexpr int STAGE_BYTES = WAVES * 32 * STAGE_STRIDE * 4;
+    static constexpr int STAGE_BYTES = WAVES * 32 * kStageStride * 4;
     static constexpr int SMEM_BYTES = LOOP_BYTES > STAGE_BYTES ? LOOP_BYTES : STAGE_BYTES;
 };
 
 struct __attribute__((packed, aligned(4))) Dwords4 {
     uint32_t d[4];
 };
-
-// Barrier that orders LDS traffic only: global loads stay in flight across it.
-__device__ __forceinline__ void block_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
 
 // The products of one item, fragments [t_begin, t_end) of window `win`, added to acc + acc2.  RUN: the window's
 // condensed columns are one run of columns that fills whole fragments, so its rows of B need no ids.
@@ -444,34 +436,10 @@ __global__ __launch_bounds__(64 * NG) __attribute__((amdgpu_waves_per_eu(2, NCH3
 
     // ---- output: each group's 32 rows x 32 features take a turn through LDS and leave as whole lines ----
     block_barrier();
-    float* const stage = reinterpret_cast<float*>(smem) + wv * (32 * Gm::STAGE_STRIDE);
-    const int n = lane & 31, hh = lane >> 5;
+    float* const stage = reinterpret_cast<float*>(smem) + wv * (32 * kStageStride);
 #pragma unroll
-    for (int c = 0; c < NCH32; ++c) {
-        const float16_t sum = acc2[c] + acc[c];
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            *reinterpret_cast<float4_t*>(stage + n * Gm::STAGE_STRIDE + 8 * q + 4 * hh) =
-                (float4_t){sum[4 * q], sum[4 * q + 1], sum[4 * q + 2], sum[4 * q + 3]};
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int id = i * 64 + lane, pr = id >> 3, fp = id & 7;
-            const float4_t v = *reinterpret_cast<const float4_t*>(stage + pr * Gm::STAGE_STRIDE + 4 * fp);
-            const int f = panel + 32 * c + 4 * fp;
-            const int prow = shfl_i32(row, pr);
-            if (f >= nv) continue;
-            if (dst != kNoDst) {
-                *reinterpret_cast<float4_t*>(scratch + ((size_t)dst + wv * 32 + pr) * ns + f) = v;   // partial sums: ordinary stores
-            } else if (prow >= 0) {
-                panel_store(out, (size_t)prow, nv, f, v);
-                keep_streaming_hint();
-            }
-        }
-    }
+    for (int c = 0; c < NCH32; ++c)
+        store_block(out, scratch, stage, acc2[c] + acc[c], lane, row, dst == kNoDst ? kNoDst : dst + wv * 32, panel + 32 * c, nv, ns);
 }
 
 template <int NCH32, int NG, bool RAGGED, class OUT>

@@ -34,6 +34,7 @@ struct Geometry {
     int tile_k = 16;    // condensed columns per fragment: 16 (v_mfma_f32_16x16x16_f16) or 32 (..._16x16x32_f16)
     int cpl = 4;        // cells per MFMA lane = bitmap words per sub-fragment = tile_k / 4
     int panel = 0;      // 1 = tall windows in the panel form (win_rows == 128 or 256, tile_k == 32)
+    int wide = 0;       // panel form whose cells are written out on the device (wide.hpp); win_rows == 256
     int panel_groups = 0; // panel form: row groups of 32 rows per window = win_rows / 32
 };
 Geometry make_geometry(int N, int window_rows, int tile_k);
@@ -107,6 +108,7 @@ void partition_rows(const rsh_csr_t& a, const rsh_plan_opts_t& o, const std::vec
 // Window height for a partition made with 16-row windows: 16, 32 or 64 (see rsh_plan_opts_t::window_rows).
 int choose_window_rows(const rsh_csr_t& a, const Partition& part16);
 int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int threads);
+int64_t panel_device_bytes(const HostPlan& plan);
 int decode_plan(const HostPlan& p, int64_t* row_ptr, int32_t* col_idx, uint16_t* val, uint8_t* path);
 
 int hardware_threads();

@@ -670,6 +670,13 @@ static int pack_panel_windows(const rsh_csr_t& a, const Partition& part, HostPla
     return RSH_OK;
 }
 
+// Bytes on the device of what PANEL_ENT and PANEL_OFF hold.  Per quad masks and starts of the values (1 KB) and where its
+// first value lies, the values in dwords, and a window's first quad (panel.hpp); or every cell, and a K step of zeros (wide.hpp).
+int64_t panel_device_bytes(const HostPlan& plan) {
+    if (plan.geo.wide) return (2 * (int64_t)plan.win_tile_off.back() + 1) * (int64_t)kWideStepBytes;
+    return plan.geo.panel ? plan.panel_quads * 1028 + plan.panel_dwords * 4 + (int64_t)plan.win_tile_off.size() * 4 : 0;
+}
+
 // Parts that every tall window is cut into, when the caller leaves it open.  The kernel's workgroups (window parts x
 // feature panels) run one per compute unit for 256 rows, and two for 128 rows, whose four waves take half of the
 // registers.  A workgroup takes as long as its fragments plus what its start and end cost (about 10 us, as much as 20
@@ -733,8 +740,9 @@ static std::vector<uint32_t> cut_tall_windows(const HostPlan& plan, int64_t n_wi
                     end = std::max(end, free_at.back());
                     std::push_heap(free_at.begin(), free_at.end(), later);
                 };
-                for (int64_t f = 0; f < panels; ++f)
-                    for (uint32_t i = split.start[x]; i < split.start[x + 1]; ++i) deal(i);
+                // all panels of an item, then the next one's (wide.hpp), or one panel of all items after the other
+                const int64_t n_items = split.start[x + 1] - split.start[x];
+                for (int64_t i = 0; i < n_items * panels; ++i) deal(split.start[x] + (uint32_t)(geo.wide ? i / panels : i % n_items));
             }
         }
         return end + (slots > 0 ? 10.0 + (double)slots * geo.N * 8.0 / 2.5e6 : 0.0);
@@ -809,6 +817,9 @@ int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int thr
         const int rc = pack_panel_windows(a, part, plan, threads, &sum_cols, &nnz_tile);
         if (rc != RSH_OK) return rc;
         n_tiles = plan.win_tile_off[n_win];
+        // Beyond one panel of features the cells are written out (wide.hpp: both kernels' times), as long as one in sixteen
+        // is stored: what the plan then takes of memory is at most 32 bytes per entry.
+        geo.wide = geo.win_rows == 256 && plan.n_user > 128 && n_tiles > 0 && nnz_tile * 16 >= n_tiles * (int64_t)K * W;
     } else {
         // ---- pass 1: fragments and padded value count per window ---------------------------
         // A window of W = 16*NW rows shares one condensed column space; fragment t of the window
@@ -1296,9 +1307,7 @@ int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int thr
     (void)n_tile_combine;
     st.n_scratch_slots = slots;
     st.sum_window_cols = sum_cols;
-    // tall windows: per quad masks and starts of the values (1 KB) and where its first value lies, the values in dwords,
-    // and a window's first quad (panel.hpp; what PANEL_ENT and PANEL_OFF hold is on the device in that form only)
-    const int64_t panel_bytes = geo.panel ? plan.panel_quads * 1028 + plan.panel_dwords * 4 + (n_win + 1) * 4 : 0;
+    const int64_t panel_bytes = panel_device_bytes(plan);
     st.plan_bytes = panel_bytes +
                     (int64_t)(plan.win_row.size() * 4 + plan.win_tile_off.size() * 4 + plan.tile_colid.size() * 4 +
                               plan.tile_mask.size() * 8 + plan.tile_val_off.size() * 4 + plan.tile_val.size() * 2 +

@@ -104,13 +104,42 @@ def test_panel_kernels_use_the_32_row_mfma_and_transposing_reads(kernels_asm):
     """Windows of 128 or 256 rows: the product is formed by v_mfma_f32_32x32x16_f16 with the staged
     B tile read through the transposing LDS load, entries arrive as 16-byte loads, and rows of C
     leave as streaming 16-byte stores (partial sums as ordinary ones)."""
-    panel = {n: b for n, b in kernels_asm.items() if "rsh_panel_kernel" in n}
-    assert panel
+    panel = {n: b for n, b in kernels_asm.items() if "rsh_panel_kernel" in n or "rsh_wide_kernel" in n}
+    assert panel and sum("rsh_wide_kernel" in n for n in panel) == 6
     for name, body in panel.items():
         assert "v_mfma_f32_32x32x16_f16" in body and "ds_read_b64_tr_b16" in body, name
-        assert "global_load_dwordx4" in body and "ds_write_b16" in body, name
+        assert "global_load_dwordx4" in body and ("ds_write_b16" in body or "rsh_wide_kernel" in name), name
         n, nt = _stores(body)   # each kernel holds both ends: rows of C (streaming) and partial sums (ordinary)
         if "OutPlain" in name:
             assert n > 0 and nt * 2 == n, f"{name}: {nt} of {n} stores are streaming"
         else:   # binary16 rows of C are half as wide
             assert any("global_store_dword" in l and " nt" in l for l in body.splitlines()), name
+
+
+def _registers(operand):
+    m = re.match(r"([va])(?:(\d+)|\[(\d+):(\d+)\])$", operand)
+    return {(m.group(1), i) for i in range(int(m.group(2) or m.group(3)), int(m.group(2) or m.group(4)) + 1)} if m else set()
+
+
+def test_no_register_is_restored_for_some_lanes_only(kernels_asm):
+    """A value that is copied away and copied back with fewer lanes running in between is lost in the others; nested
+    conditions that end together have made the compiler do that to the row numbers that lanes take from each other."""
+    copy = re.compile(r"(?:v_mov_b32_e32|v_accvgpr_write_b32|v_accvgpr_read_b32|v_accvgpr_mov_b32) ([va]\d+), ([va]\d+)$")
+    for name, body in kernels_asm.items():
+        if "rsh_wide_kernel" not in name and "rsh_panel_kernel" not in name:
+            continue
+        held = {}      # register: (copied from, conditions opened since)
+        for line in (l.strip() for l in body.splitlines()):
+            if line.startswith(("s_and_b64 exec, exec", "s_and_saveexec")):
+                held = {r: (src, n + 1) for r, (src, n) in held.items()}
+            elif line.startswith(("s_or_b64 exec, exec", "s_mov_b64 exec")):
+                held = {r: (src, max(0, n - 1)) for r, (src, n) in held.items()}
+            m = copy.match(line)
+            if m:
+                kept = held.get(m.group(2))
+                assert not (kept and kept[0] == m.group(1) and kept[1] > 0), f"{name}: {line}"
+            if line.startswith("v_") or "_load" in line or line.startswith("ds_read") or line.startswith("ds_bpermute"):
+                for kind, i in _registers(line.split(None, 1)[1].split(",")[0]) if " " in line else ():
+                    held.pop(f"{kind}{i}", None)
+            if m:
+                held[m.group(1)] = (m.group(2), 0)

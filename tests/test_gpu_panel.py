@@ -43,6 +43,44 @@ def test_units_quads_and_parts(N, density, cols, window_rows, parts):
     plan.destroy()
 
 
+# Beyond 128 features windows of 256 rows run on cells written out (at 1 / 16 of them and more).  Fragments per window: 1 and
+# 3 (fewer than a turn of the loop), 5, 33 (one past the second level of sums), 36; the last one full or with one column; parts
+# of 3 and 7 fragments begin anywhere; gathered columns and runs.  Widths: one feature into the second panel, rows of B that
+# end at every place inside a 16-byte piece, odd ones beside the padded copy, a whole last panel.  Canaries around C.
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("N", [129, 130, 132, 134, 136, 160, 255, 256, 300])
+@pytest.mark.parametrize("rows,cols,parts,density", [(256, 32, 0, 0.5), (300, 65, 0, 0.3), (520, 160, 3, 1.0), (257, 1025, 0, 0.15), (256, 1152, 7, 0.08)])
+def test_cells_written_out(rows, cols, parts, density, N, fused):
+    import torch
+    from paper_2603_08734_amd import Plan
+    A = random_matrix(rows, cols, density, 7)
+    print(f"case wide rows={rows} cols={cols} parts={parts} N={N} fused={fused}", flush=True)
+    plan = Plan(A.row_ptr, A.col_idx, A.val, A.n_cols, N, window_rows=256, force_path=2, max_tiles_per_item=parts)
+    st = plan.stats()
+    assert st["nnz_tile"] * 16 >= st["n_tiles"] * 32 * 256 and st["tile_part_bytes"] >= 8192 * (2 * st["n_tiles"] + 1)
+    B = dense_B(A.n_cols, N, "normal", seed=N)
+    Bd = torch.from_numpy(B.view(np.int16)).cuda().view(torch.float16)
+    C_ref, S, _ = oracle.spmm(A.row_ptr, A.col_idx, A.val, B)
+    pad = 64
+    flat = torch.full((A.n_rows * N + 2 * pad,), float("nan"), dtype=torch.float16 if fused else torch.float32, device="cuda")
+    C = flat[pad:pad + A.n_rows * N].view(A.n_rows, N)
+    bound = 1e-4 * S
+    if fused:
+        bias = torch.linspace(-1, 1, N, device="cuda")
+        plan.spmm_f16(Bd, C, bias, relu=True)
+        C_ref = np.maximum(C_ref + bias.cpu().numpy().astype(np.float64), 0.0)
+        # the fp32 bound, the addition of the bias, one rounding to binary16
+        bound = bound + 2.0 ** -24 * np.abs(C_ref) + 2.0 ** -11 * np.abs(C_ref) * 1.001 + 2.0 ** -24
+    else:
+        plan.spmm(Bd, C)
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(flat[:pad]).all()) and bool(torch.isnan(flat[pad + A.n_rows * N:]).all()), "stores outside C"
+    got = C.cpu().numpy().astype(np.float64)
+    assert not np.isnan(got).any()
+    assert np.all(np.abs(got - C_ref) <= bound)
+    plan.destroy()
+
+
 # Even widths that are not multiples of 16 run without copies of the operands: rows end inside 16-byte pieces of
 # B (8 features) and of C (4 features), inside a feature panel, and one or two pieces into one.  Every kernel takes
 # them: windows of 16 rows, tall windows (128-row ones in panels of their own), residual rows of all kinds with

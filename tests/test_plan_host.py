@@ -611,3 +611,16 @@ def test_plan_bytes_of_tall_windows_are_those_of_the_packed_form(window_rows):
     assert st["tile_part_bytes"] == tile + packed
     rest = sum(p.array(getattr(B_, "RSH_ARR_" + n)).nbytes for n in ("WIN_TILE_OFF", "IRR_COL", "IRR_VAL", "IRR_WAVE", "IRR_ROW", "COMBINE"))
     assert st["plan_bytes"] == tile + packed + rest
+
+
+# cells are written out beyond one panel of 128 features where one in sixteen of a fragment's is stored
+@pytest.mark.parametrize("N,window_rows,density,wide", [(128, 256, 0.2, False), (129, 256, 0.2, True), (1024, 256, 0.1, True), (256, 256, 0.05, False),
+                                                        (256, 128, 0.2, False)])
+def test_plan_bytes_of_tall_windows_with_cells_written_out(N, window_rows, density, wide):
+    rng = np.random.default_rng(3)
+    r, c = np.nonzero(rng.random((600, 512)) < density)
+    p = host_plan(from_coo(r, c, rng.standard_normal(r.size), 600, 512), N, window_rows=window_rows, force_path=2)
+    st = p.stats()
+    tile = sum(p.array(getattr(B_, "RSH_ARR_" + n)).nbytes for n in ("WIN_ROW", "TILE_COLID", "TILE_ITEM", "PANEL_COL0"))
+    cells = 8192 * (2 * st["n_tiles"] + 1)     # 256 rows x 16 columns a K step, and one of zeros
+    assert (st["tile_part_bytes"] == tile + cells) == wide
