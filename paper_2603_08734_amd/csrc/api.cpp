@@ -109,7 +109,7 @@ int upload_array(Uploader& up, const std::vector<T>& h, T** d) {
 
 void free_device(rsh::DevicePlan& d) {
     void* ptrs[] = {d.win_row, d.win_tile_off, d.tile_colid, d.tile_mask, d.tile_val_off, d.tile_val,
-                    d.tile_item, d.panel_col0, d.panel_off, d.panel_ent, d.panel_quad0, d.panel_meta, d.panel_qoff, d.panel_val, d.panel_cells, d.irr_col, d.irr_val, d.irr_wave, d.irr_row, d.combine, d.scratch,
+                    d.tile_item, d.panel_col0, d.panel_off, d.panel_ent, d.panel_quad0, d.panel_meta, d.panel_qoff, d.panel_val, d.panel_cells, d.irr_col, d.irr_val, d.irr_wave, d.irr_row, d.narrow_seg, d.combine, d.scratch,
                     d.b_pad};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
@@ -173,12 +173,12 @@ int upload_plan(rsh_plan& p) {
     rsh::DevicePlan& d = p.dev;
     d.geo = h.geo;
     d.n_tile_items = (int64_t)h.tile_item.size() / 4;
-    d.n_irr_waves = (int64_t)h.irr_wave.size() / 4;
+    d.n_irr_waves = (int64_t)(h.geo.narrow ? h.narrow_wave : h.irr_wave).size() / 4;
     d.n_combine = (int64_t)h.combine.size() / 4;
     d.n_scratch_slots = h.n_scratch_slots;
     d.n_split_rows = h.stats.n_split_rows;
     d.tile_split = h.tile_split;
-    d.irr_split = h.irr_split;
+    d.irr_split = h.geo.narrow ? h.narrow_split : h.irr_split;
     Uploader up;
     struct Closer {
         Uploader& u;
@@ -195,10 +195,17 @@ int upload_plan(rsh_plan& p) {
     if ((rc = upload_array(up, h.tile_item, &d.tile_item))) return rc;
     if ((rc = upload_array(up, h.panel_col0, &d.panel_col0))) return rc;
     if (h.geo.panel && (rc = upload_panel_units(up, h, d))) return rc;
-    if ((rc = upload_array(up, h.irr_col, &d.irr_col))) return rc;
-    if ((rc = upload_array(up, h.irr_val, &d.irr_val))) return rc;
-    if ((rc = upload_array(up, h.irr_wave, &d.irr_wave))) return rc;
-    if ((rc = upload_array(up, h.irr_row, &d.irr_row))) return rc;
+    if (h.geo.narrow) {
+        if ((rc = upload_array(up, h.narrow_col, &d.irr_col))) return rc;
+        if ((rc = upload_array(up, h.narrow_val, &d.irr_val))) return rc;
+        if ((rc = upload_array(up, h.narrow_wave, &d.irr_wave))) return rc;
+        if ((rc = upload_array(up, h.narrow_seg, &d.narrow_seg))) return rc;
+    } else {
+        if ((rc = upload_array(up, h.irr_col, &d.irr_col))) return rc;
+        if ((rc = upload_array(up, h.irr_val, &d.irr_val))) return rc;
+        if ((rc = upload_array(up, h.irr_wave, &d.irr_wave))) return rc;
+        if ((rc = upload_array(up, h.irr_row, &d.irr_row))) return rc;
+    }
     if ((rc = upload_array(up, h.combine, &d.combine))) return rc;
     const size_t sbytes = (size_t)std::max<int64_t>(1, h.n_scratch_slots) * (size_t)h.geo.N * sizeof(float);
     if (!hip_ok(hipMalloc((void**)&d.scratch, sbytes))) return RSH_ERR_OOM;
@@ -214,6 +221,9 @@ int upload_plan(rsh_plan& p) {
         d.ev_join = join;
     }
     if ((rc = up.close())) return rc;   // every copy has landed
+    for (auto* v : {&h.narrow_wave, &h.narrow_seg}) std::vector<uint32_t>().swap(*v);
+    std::vector<int32_t>().swap(h.narrow_col);
+    std::vector<uint16_t>().swap(h.narrow_val);
     if (!hip_ok(hipGetDevice(&p.device))) return RSH_ERR_HIP;
     p.uploaded = true;
     return RSH_OK;
@@ -359,7 +369,17 @@ int rsh_plan_create(const rsh_csr_t* csr, int32_t N, const rsh_plan_opts_t* opts
             o.window_rows = rsh::choose_window_rows(*csr, part);
             if (o.window_rows != rsh::kW) rsh::partition_rows(*csr, o, h.order, tau_nnz, tau_inc, part, threads);
         }
-        if (o.tile_k == 0 || o.window_rows >= rsh::kPanelMinRows) o.tile_k = o.window_rows == rsh::kW ? 16 : 32;
+        // 16-row windows of up to 8 features join the residual rows where that pays, in the order in which the windows had them
+        if (choose_w && o.window_rows == rsh::kW && o.force_path == 0 && !o.element_level && N <= rsh::kNarrow && rsh::narrow_pays(*csr, part, n_user)) {
+            rsh_plan_opts_t residual = o;
+            residual.force_path = 1;
+            rsh::partition_rows(*csr, residual, h.order, tau_nnz, tau_inc, part, threads);
+            h.narrow_in_order = true;
+        }
+        // Fragments of 16 columns in 16-row windows, of 32 where rows of B are two 16-byte pieces: a wave's one load per
+        // fragment then names 32 rows and not 16 twice (27-point stencil on 80^3, 16 features, 42.7 us and 31.5; on 24^3 8.4 and
+        // 7.5; 524288 rows of communities 55.2 and 53.5; at 128 features the stencil takes 160.1 and 162.3).
+        if (o.tile_k == 0 || o.window_rows >= rsh::kPanelMinRows) o.tile_k = o.window_rows == rsh::kW && N > rsh::kNarrow ? 16 : 32;
         h.geo = rsh::make_geometry(N, o.window_rows, o.tile_k);
         h.opts = o;
         const double ms_partition = ms_since(t0);
@@ -426,13 +446,20 @@ int check_launch(const rsh_plan_t* plan, const void* B, const void* C, const voi
         *padded = false;
         *width = n;
     }
+    // Without windows rows of up to 16 features are read at the next power of two (narrow.hpp): as they are where that is
+    // their width and they are aligned to it
+    if (n < rsh::kNarrow && plan->dev.geo.narrow && plan->dev.n_tile_items == 0) {
+        const int wide = rsh::narrow_width(n);
+        *padded = wide != n || ((uintptr_t)B & (uintptr_t)(2 * std::min(wide, 8) - 1));
+        *width = *padded ? std::max(4, wide) : n;
+    }
     return RSH_OK;
 }
 
 // The rows of B that the kernels read: the caller's, or the plan's padded copy of them.
-int readable_rows(const rsh::DevicePlan& d, int64_t n_cols, bool padded, const void** B, void* stream) {
+int readable_rows(const rsh::DevicePlan& d, int64_t n_cols, bool padded, int width, const void** B, void* stream) {
     if (!padded) return RSH_OK;
-    const int rc = rsh::launch_widen_rows(*B, d.b_pad, n_cols, d.n_user, d.geo.N, stream);
+    const int rc = rsh::launch_widen_rows(*B, d.b_pad, n_cols, d.n_user, width, stream);
     *B = d.b_pad;
     return rc;
 }
@@ -445,7 +472,7 @@ int rsh_spmm(const rsh_plan_t* plan, const void* B_dev, void* C_dev, void* hip_s
     int rc = check_launch(plan, B_dev, C_dev, nullptr, 4, &padded, &width);
     if (rc != RSH_OK || plan->host.n_rows == 0) return rc;
     const rsh::DevicePlan& d = plan->dev;
-    rc = readable_rows(d, plan->host.n_cols, padded, &B_dev, hip_stream);
+    rc = readable_rows(d, plan->host.n_cols, padded, width, &B_dev, hip_stream);
     if (rc == RSH_OK) rc = rsh::launch_spmm(d, B_dev, C_dev, width, padded ? d.n_user : width, hip_stream, nullptr);
     if (rc == RSH_ERR_HIP) g_hip_error = "kernel launch failed";
     return rc;
@@ -468,7 +495,7 @@ int rsh_spmm_noalloc(const rsh_plan_t* plan, const void* B_dev, void* C_dev, voi
         g_hip_error = "hipGetSymbolAddress failed for the library-owned scratch array";
         return rc;
     }
-    rc = readable_rows(d, plan->host.n_cols, padded, &B_dev, hip_stream);
+    rc = readable_rows(d, plan->host.n_cols, padded, width, &B_dev, hip_stream);
     if (rc == RSH_OK) rc = rsh::launch_spmm(d, B_dev, C_dev, width, padded ? d.n_user : width, hip_stream, nullptr);
     if (rc == RSH_ERR_HIP) g_hip_error = "kernel launch failed";
     return rc;
@@ -482,7 +509,7 @@ int rsh_spmm_f16(const rsh_plan_t* plan, const void* B_dev, void* C16_dev, const
     int rc = check_launch(plan, B_dev, C16_dev, bias_dev, 2, &padded, &width);
     if (rc != RSH_OK || plan->host.n_rows == 0) return rc;
     const rsh::DevicePlan& d = plan->dev;
-    rc = readable_rows(d, plan->host.n_cols, padded, &B_dev, hip_stream);
+    rc = readable_rows(d, plan->host.n_cols, padded, width, &B_dev, hip_stream);
     if (rc == RSH_OK) rc = rsh::launch_spmm_f16(d, B_dev, C16_dev, bias_dev, relu, width, padded ? d.n_user : width, hip_stream, nullptr);
     if (rc == RSH_ERR_HIP) g_hip_error = "kernel launch failed";
     return rc;
@@ -502,7 +529,7 @@ int rsh_spmm_profile(const rsh_plan_t* plan, const void* B_dev, void* C_dev, voi
     if (rc == RSH_OK) {
         void* evp[4] = {ev[0], ev[1], ev[2], ev[3]};
         // the copy to the padded width lies outside the three timed kernels
-        rc = readable_rows(d, plan->host.n_cols, padded, &B_dev, hip_stream);
+        rc = readable_rows(d, plan->host.n_cols, padded, width, &B_dev, hip_stream);
         if (rc == RSH_OK) rc = rsh::launch_spmm(d, B_dev, C_dev, width, padded ? d.n_user : width, hip_stream, evp);
         if (!hip_ok(hipStreamSynchronize((hipStream_t)hip_stream))) rc = RSH_ERR_HIP;
         if (rc == RSH_OK) {

@@ -99,6 +99,7 @@ struct OutPlainT {
     float* C;
     // the same rows for a kernel that makes no use of their being whole
     OutPlainT<kAny ? kRowsAny : kRowsEven> general() const { return {C}; }
+    OutPlainT<kRowsAny> any() const { return {C}; }
 };
 template <int ROWS>
 struct OutFusedT {
@@ -108,6 +109,7 @@ struct OutFusedT {
     const float* bias;
     int relu;
     OutFusedT<kAny ? kRowsAny : kRowsEven> general() const { return {C, bias, relu}; }
+    OutFusedT<kRowsAny> any() const { return {C, bias, relu}; }
 };
 
 // `end`: one past the last feature of the row (kAny).

@@ -6,13 +6,14 @@
 //   rsh_wide_kernel      the same for tall windows and many features (wide.hpp)
 //   rsh_irregular_kernel residual rows (Section 3.3.2, "CUDA path"), teams of lanes own
 //                        feature columns, long rows arrive as bounded slices (Section 3.3.3)
+//   rsh_narrow_kernel    residual rows of at most 16 features (narrow.hpp)
 //   rsh_combine_kernel   fixed-order sum of the partial results of split windows / rows
 //   rsh_sum_narrow_kernel   the same for rows of up to 16 features, several rows per wave
 //   rsh_fragment_even_kernel, rsh_residual_even_kernel, rsh_sum_even_kernel   the first, third (its partial panel) and
 //                        fourth for rows of an even number of features (device.hpp, Rows)
 //   rsh_fragment_any_kernel, rsh_residual_any_kernel, rsh_sum_any_kernel   the first, third and fourth
 //                        for rows of C of any length and alignment beside a padded copy of B
-//   rsh_widen_rows_kernel   copies B to the run width where its rows cannot be read as they are
+//   rsh_widen_rows_kernel, rsh_widen_four_kernel   copy B to a width at which its rows can be read
 // Each of the first three exists for two outputs: the fp32 sums (OutPlain) and binary16 of
 // act(sum + bias) (OutFused, the GCN layer of Section 4.4).
 #include <hip/hip_runtime.h>
@@ -25,6 +26,7 @@
 #include "device.hpp"
 #include "panel.hpp"
 #include "wide.hpp"
+#include "narrow.hpp"
 
 namespace rsh {
 
@@ -758,8 +760,25 @@ __global__ __launch_bounds__(256) void rsh_widen_rows_kernel(const uint16_t* __r
     dst[i] = v;
 }
 
+// Rows of up to four features: a thread a row.
+__global__ __launch_bounds__(256) void rsh_widen_four_kernel(const uint16_t* __restrict__ src, uint2_t* __restrict__ dst, uint32_t rows, uint32_t n) {
+    const uint32_t r = blockIdx.x * 256u + threadIdx.x;
+    if (r >= rows) return;
+    const uint16_t* from = src + (size_t)r * n;
+    uint2_t v = {0, 0};
+#pragma unroll
+    for (uint32_t k = 0; k < 4; ++k)
+        if (k < n) v[k / 2] |= (uint32_t)from[k] << (16 * (k & 1));
+    dst[r] = v;
+}
+
 int launch_widen_rows(const void* src, void* dst, int64_t rows, int n, int n_wide, void* stream) {
     if (rows <= 0) return RSH_OK;
+    if (n_wide == 4) {
+        hipLaunchKernelGGL(rsh_widen_four_kernel, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, (hipStream_t)stream, (const uint16_t*)src, (uint2_t*)dst,
+                           (uint32_t)rows, (uint32_t)n);
+        return hipGetLastError() == hipSuccess ? RSH_OK : RSH_ERR_HIP;
+    }
     const uint32_t ppr = (uint32_t)n_wide / 8u, pieces = (uint32_t)rows * ppr;   // rows * 2 n_wide < 2^32
     hipLaunchKernelGGL(rsh_widen_rows_kernel, dim3((pieces + 255) / 256), dim3(256), 0, (hipStream_t)stream, (const uint16_t*)src, (uint4_t*)dst,
                        pieces, (uint32_t)n, ppr);
@@ -967,9 +986,10 @@ static int launch_all(const DevicePlan& d, const void* B, const OUT& out, int nb
     if (forked && hipEventRecord((hipEvent_t)d.ev_join, (hipStream_t)d.side) != hipSuccess) return RSH_ERR_HIP;
     st = caller;
     mark(1);
-    if (d.n_irr_waves > 0) {
+    if (d.n_irr_waves > 0 && d.geo.narrow) {
+        launch_narrow(d, B, out.any(), st, nb, nv);
+    } else if (d.n_irr_waves > 0) {
         switch (d.geo.irr_tpr) {
-            case 2: launch_irregular_t<2>(d, B, out, st, nb, nv); break;
             case 4: launch_irregular_t<4>(d, B, out, st, nb, nv); break;
             case 8: launch_irregular_t<8>(d, B, out, st, nb, nv); break;
             case 16: launch_irregular_t<16>(d, B, out, st, nb, nv); break;
@@ -1000,7 +1020,7 @@ static int launch_all(const DevicePlan& d, const void* B, const OUT& out, int nb
 }
 
 int launch_spmm(const DevicePlan& d, const void* B, void* C, int nb, int nv, void* stream, void* const* events) {
-    if (nb != nv) return launch_all(d, B, OutPlainT<kRowsAny>{(float*)C}, nb, nv, stream, events);
+    if (nb != nv || nv < 16) return launch_all(d, B, OutPlainT<kRowsAny>{(float*)C}, nb, nv, stream, events);
     if (nb == d.geo.N) return launch_all(d, B, OutPlainT<kRowsWhole>{(float*)C}, nb, nv, stream, events);
     return launch_all(d, B, OutPlainT<kRowsEven>{(float*)C}, nb, nv, stream, events);
 }
@@ -1033,7 +1053,7 @@ int static_scratch(float** ptr) {
 
 int launch_spmm_f16(const DevicePlan& d, const void* B, void* C16, const float* bias, int relu, int nb, int nv, void* stream,
                     void* const* events) {
-    if (nb != nv) return launch_all(d, B, OutFusedT<kRowsAny>{(_Float16*)C16, bias, relu}, nb, nv, stream, events);
+    if (nb != nv || nv < 16) return launch_all(d, B, OutFusedT<kRowsAny>{(_Float16*)C16, bias, relu}, nb, nv, stream, events);
     if (nb == d.geo.N) return launch_all(d, B, OutFusedT<kRowsWhole>{(_Float16*)C16, bias, relu}, nb, nv, stream, events);
     return launch_all(d, B, OutFusedT<kRowsEven>{(_Float16*)C16, bias, relu}, nb, nv, stream, events);
 }

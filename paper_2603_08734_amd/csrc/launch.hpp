@@ -32,6 +32,7 @@ struct DevicePlan {
     uint16_t* irr_val = nullptr;
     uint32_t* irr_wave = nullptr;
     int32_t* irr_row = nullptr;
+    uint32_t* narrow_seg = nullptr;    // geo.narrow: irr_col, irr_val and irr_wave are those of narrow.hpp, which has no irr_row
     uint32_t* combine = nullptr;
     float* scratch = nullptr;
     // rows of B that the kernels cannot read as they are pass through this plan-owned buffer of the run width
@@ -69,7 +70,7 @@ int static_scratch(float** ptr);
 int launch_spmm_f16(const DevicePlan& d, const void* B_dev, void* C16_dev, const float* bias_dev, int relu, int nb,
                     int nv, void* stream, void* const* events);
 
-// Row-wise copy of a binary16 matrix of `n` columns into one of n_wide >= n columns, a multiple of 8, at a 16-byte
+// Row-wise copy of a binary16 matrix of `n` columns into one of n_wide >= n columns, 4 or a multiple of 8, at a 16-byte
 // aligned address; the columns from n on become zero.
 int launch_widen_rows(const void* src, void* dst, int64_t rows, int n, int n_wide, void* stream);
 

@@ -1,0 +1,182 @@
+// Residual rows of at most 16 features: lanes own rows.  Included by kernels.hip.
+//
+// The residual kernel gives a row of B to a team of lanes, eight features each; of rows this short two lanes do, and what
+// they gather, 32 bytes, is less than what tells them where (a wave's 32 teams fetch their column ids two at a time from 32
+// places).  Here a lane takes an entry's whole row of B and adds it to sums of its own:
+//   * T = 1 .. 64 lanes share a row (or a slice of a long one) and are added up once at its end; rows of up to 24 entries,
+//     in a large matrix, have a lane each and need no addition across lanes at all.
+//   * Column ids and values lie in the order in which the lanes take them (pack_narrow in planner.cpp), in pairs of
+//     entries: one 8-byte and one 4-byte load per lane for two entries, whole lines per wave.
+//   * Rows of B are read at the next power of two of their width NP: one load per entry up to 8 features.  Rows of
+//     that width are read where they lie, so that a row of one feature takes 2 bytes of cache and not 32.
+//   * Rows of C leave by ordinary stores (524288 rows of communities, 8 features: 87 us with streaming ones, 79 so).
+// What bounds it: a gather is a request of its own to the L2, 32.4 M of them for the power-law graph of 2^20 vertices, whose
+// product takes 152 us at one feature (the 194 MB of ids and values alone would take 40) and 222 at 8, 13 us more in the
+// combine pass.  Teams of two lanes and this kernel, us: that graph, 1 feature 338 and 168, 8 343 and 236, 16 329 and 313; of
+// 2^17 vertices 45.2 and 19.9, 45.1 and 26.3, 40.8 and 34.5; 150000 rows of 12 entries 47.1 and 12.8, 46.1 and 13.3, 41.4 and 23.5.
+// A lane that takes up to twice 16 entries is better than one that is helped from 24 on (stencil 80^3, 8 features, 27.8 and 31.2).
+#pragma once
+#include "device.hpp"
+
+namespace rsh {
+
+namespace {
+
+template <int NP>
+struct NarrowRow {
+    static constexpr int WORDS = NP < 2 ? 1 : NP / 2;
+    uint32_t w[WORDS];
+};
+template <int NP>
+__device__ __forceinline__ NarrowRow<NP> load_narrow(const char* p) {
+    NarrowRow<NP> r;
+    if constexpr (NP == 1) {
+        r.w[0] = *reinterpret_cast<const uint16_t*>(p);
+    } else if constexpr (NP == 2) {
+        r.w[0] = *reinterpret_cast<const uint32_t*>(p);
+    } else if constexpr (NP == 4) {
+        const uint2_t v = *reinterpret_cast<const uint2_t*>(p);
+        r.w[0] = v[0], r.w[1] = v[1];
+    } else {
+#pragma unroll
+        for (int i = 0; i < NP / 8; ++i) {
+            const uint4_t v = *reinterpret_cast<const uint4_t*>(p + 16 * i);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) r.w[4 * i + k] = v[k];
+        }
+    }
+    return r;
+}
+template <int NP>
+__device__ __forceinline__ void add_narrow(float v, const NarrowRow<NP>& b, float (&acc)[NP]) {
+#pragma unroll
+    for (int i = 0; i < NP; ++i) {
+        const __half2 h = __builtin_bit_cast(__half2, b.w[i / 2]);
+        acc[i] = fmaf(v, i % 2 ? __high2float(h) : __low2float(h), acc[i]);
+    }
+}
+
+// Ordinary stores: a row is a part of a line, which the L2 puts together from the stores of neighbouring rows.
+template <int ROWS>
+__device__ __forceinline__ void store_narrow4(const OutPlainT<ROWS>& o, size_t row, int nv, int f, float4_t v) {
+    float* p = o.C + row * nv + f;
+    if (f + 4 <= nv) {
+        *reinterpret_cast<float4_a4*>(p) = v;
+    } else {
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            if (f + i < nv) p[i] = v[i];
+    }
+}
+template <int ROWS>
+__device__ __forceinline__ void store_narrow4(const OutFusedT<ROWS>& o, size_t row, int nv, int f, float4_t v) {
+    _Float16* p = o.C + row * nv + f;
+    if (f >= nv) return;
+    const uint2_t h = finish4(o, f, nv, v);
+    if (f + 4 <= nv) {
+        *reinterpret_cast<uint2_a2*>(p) = h;
+    } else {
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            if (f + i < nv) reinterpret_cast<uint16_t*>(p)[i] = (uint16_t)(h[i / 2] >> (16 * (i & 1)));
+    }
+}
+
+// waves {first pair of entries (in lanes), steps, log2 T | segments << 8 | steps that every lane takes << 16, first segment};
+// segments {row of C or of scratch, entries | kSegmentToScratch}.
+template <int NP, class OUT>
+__global__ __launch_bounds__(64 * kWavesPerBlock) void rsh_narrow_kernel(const uint4* __restrict__ waves, XcdSplit xs, const uint2_t* __restrict__ segments,
+                                                                         const uint2_t* __restrict__ col, const uint32_t* __restrict__ val,
+                                                                         const __half* __restrict__ B, const OUT out, float* __restrict__ scratch, int nb,
+                                                                         int nv, int ns) {
+    constexpr int PAIRS = NP >= 8 ? 2 : kNarrowAhead;   // pairs of entries in flight
+    const int lane = threadIdx.x & 63;
+    uint32_t wave;
+    if (!xcd_work_item(xs, &wave)) return;
+    const uint4 d = waves[wave];
+    const uint32_t first = __builtin_amdgcn_readfirstlane(d.x), steps = __builtin_amdgcn_readfirstlane(d.y);
+    const uint32_t info = __builtin_amdgcn_readfirstlane(d.z), seg0 = __builtin_amdgcn_readfirstlane(d.w);
+    const uint32_t t = info & 0xffu, n_seg = (info >> 8) & 0xffu, full = info >> 16;
+    const uint32_t seg = (uint32_t)lane >> t, in_seg = (uint32_t)lane & ((1u << t) - 1u);
+    const bool live = seg < n_seg;
+    uint2_t s = {0, 0};
+    if (live) s = segments[seg0 + seg];
+    const uint32_t len = s[1] & ~kSegmentToScratch;
+    const uint32_t mine = len > in_seg ? (len - in_seg + (1u << t) - 1u) >> t : 0u;   // entries of this lane
+    const uint2_t* pc = col + first + lane;
+    const uint32_t* pv = val + first + lane;
+    const char* const Bb = reinterpret_cast<const char*>(B);
+    const uint32_t row_bytes = 2u * (uint32_t)nb;
+    float acc[NP];
+#pragma unroll
+    for (int i = 0; i < NP; ++i) acc[i] = 0.f;
+
+    uint2_t c[PAIRS];
+    uint32_t v[PAIRS];
+#pragma unroll
+    for (int u = 0; u < PAIRS; ++u) c[u] = pc[64 * u], v[u] = pv[64 * u];
+    for (uint32_t j = 0; j < steps; j += 2 * PAIRS) {
+        NarrowRow<NP> b[2 * PAIRS];
+        uint32_t w[PAIRS];
+#pragma unroll
+        for (int u = 0; u < PAIRS; ++u) {
+            b[2 * u] = load_narrow<NP>(Bb + c[u][0] * row_bytes);
+            b[2 * u + 1] = load_narrow<NP>(Bb + c[u][1] * row_bytes);
+            w[u] = v[u];
+        }
+        // the next turn's (behind the last wave the arrays go on for kNarrowAhead pairs)
+        const uint32_t next = min(j + 2 * PAIRS, (steps + 1) & ~1u);
+#pragma unroll
+        for (int u = 0; u < PAIRS; ++u) c[u] = pc[32 * next + 64 * u], v[u] = pv[32 * next + 64 * u];
+        if (j + 2 * PAIRS > full) {   // some lane ends: nothing of what it reads past its end may count, infinities neither
+#pragma unroll
+            for (int u = 0; u < 2 * PAIRS; ++u) {
+                const bool on = j + u < mine;
+#pragma unroll
+                for (int i = 0; i < NarrowRow<NP>::WORDS; ++i) b[u].w[i] = on ? b[u].w[i] : 0u;
+                w[u / 2] &= on ? ~0u : u % 2 ? 0x0000ffffu : 0xffff0000u;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < PAIRS; ++u) {
+            const __half2 h = __builtin_bit_cast(__half2, w[u]);
+            add_narrow<NP>(__low2float(h), b[2 * u], acc);
+            add_narrow<NP>(__high2float(h), b[2 * u + 1], acc);
+        }
+    }
+    for (uint32_t k = 0; k < t; ++k) {
+#pragma unroll
+        for (int i = 0; i < NP; ++i) acc[i] += shfl_f32(acc[i], lane ^ (1 << k));
+    }
+    if (!live || in_seg != 0) return;
+    constexpr int QUADS = NP < 4 ? 1 : NP / 4;
+#pragma unroll
+    for (int q = 0; q < QUADS; ++q) {
+        float4_t x = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (4 * q + i < NP) x[i] = acc[(4 * q + i) % NP];
+        if (s[1] & kSegmentToScratch) *reinterpret_cast<float4_t*>(scratch + (size_t)s[0] * ns + 4 * q) = x;
+        else store_narrow4(out, (size_t)s[0], nv, 4 * q, x);
+    }
+}
+
+template <class OUT>
+void launch_narrow(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st, int nb, int nv) {
+    uint32_t longest = 0;
+    for (int x = 0; x < 8; ++x) longest = std::max(longest, d.irr_split.start[x + 1] - d.irr_split.start[x]);
+    const auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(8u * ((longest + kWavesPerBlock - 1) / kWavesPerBlock)), dim3(64 * kWavesPerBlock), 0, st, (const uint4*)d.irr_wave,
+                           d.irr_split, (const uint2_t*)d.narrow_seg, (const uint2_t*)d.irr_col, (const uint32_t*)d.irr_val, (const __half*)B, out, d.scratch,
+                           nb, nv, d.geo.N);
+    };
+    if (nv == 1) launch(rsh_narrow_kernel<1, OUT>);
+    else if (nv == 2) launch(rsh_narrow_kernel<2, OUT>);
+    else if (nv <= 4) launch(rsh_narrow_kernel<4, OUT>);
+    else if (nv <= 8) launch(rsh_narrow_kernel<8, OUT>);
+    else launch(rsh_narrow_kernel<16, OUT>);
+}
+
+}  // namespace
+
+}  // namespace rsh

@@ -20,6 +20,10 @@ constexpr uint32_t kWaveSlice = 1u;      // `count` consecutive entries of one r
 constexpr uint32_t kWaveZeroRows = 2u;   // `count` rows of irr_row (from dst) receive zeros
 constexpr uint32_t kWaveKindMask = 3u;
 constexpr uint32_t kWaveToScratch = 4u;  // slice result goes to a scratch slot
+// Rows of at most kNarrow features run on lanes that own a row, or a share of one, each (narrow.hpp)
+constexpr int kNarrow = 16;
+constexpr uint32_t kSegmentToScratch = 0x80000000u;
+constexpr int kNarrowAhead = 4;   // pairs of entries per lane behind the last wave's that the kernel may read
 
 // Feature-panel geometry derived from N (both kernels walk N in panels).
 struct Geometry {
@@ -35,6 +39,7 @@ struct Geometry {
     int cpl = 4;        // cells per MFMA lane = bitmap words per sub-fragment = tile_k / 4
     int panel = 0;      // 1 = tall windows in the panel form (win_rows == 128 or 256, tile_k == 32)
     int wide = 0;       // panel form whose cells are written out on the device (wide.hpp); win_rows == 256
+    int narrow = 0;     // residual rows in the form of narrow.hpp: rows of at most 16 features
     int panel_groups = 0; // panel form: row groups of 32 rows per window = win_rows / 32
 };
 Geometry make_geometry(int N, int window_rows, int tile_k);
@@ -71,6 +76,12 @@ struct HostPlan {
     std::vector<uint16_t> irr_val;
     std::vector<uint32_t> irr_wave;  // 4 per wave
     std::vector<int32_t> irr_row;    // row ids named by short-row and zero-row waves
+    // the same work as narrow.hpp reads it (geo.narrow); what the device holds instead of the arrays above
+    std::vector<int32_t> narrow_col;
+    std::vector<uint16_t> narrow_val;
+    std::vector<uint32_t> narrow_wave, narrow_seg;   // 4 per wave, 2 per segment
+    XcdSplit narrow_split;
+    bool narrow_in_order = false;   // rows run in the processing order, not by id
     // combine
     XcdSplit tile_split, irr_split;
     std::vector<uint32_t> combine;  // 4 per entry
@@ -109,6 +120,15 @@ void partition_rows(const rsh_csr_t& a, const rsh_plan_opts_t& o, const std::vec
 int choose_window_rows(const rsh_csr_t& a, const Partition& part16);
 int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int threads);
 int64_t panel_device_bytes(const HostPlan& plan);
+void pack_narrow(HostPlan& plan, int threads);
+// Whether the 16-row windows of `part` are better off as residual rows at n features (narrow.hpp).
+bool narrow_pays(const rsh_csr_t& a, const Partition& part, int n);
+// Features of a row of B as narrow.hpp reads it.
+inline int narrow_width(int n) {
+    int w = 1;
+    while (w < n) w *= 2;
+    return w;
+}
 int decode_plan(const HostPlan& p, int64_t* row_ptr, int32_t* col_idx, uint16_t* val, uint8_t* path);
 
 int hardware_threads();

@@ -44,6 +44,7 @@ Geometry make_geometry(int N, int window_rows, int tile_k) {
     g.tile_nch = g.tile_panel / 16;
     g.panel = window_rows >= kPanelMinRows ? 1 : 0;
     g.panel_groups = g.panel ? window_rows / 32 : 0;
+    g.narrow = N <= kNarrow ? 1 : 0;
     return g;
 }
 
@@ -1281,6 +1282,7 @@ int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int thr
     }
 
     plan.n_scratch_slots = slots;
+    if (geo.narrow) pack_narrow(plan, threads);
 
     // ---- statistics -----------------------------------------------------------------------
     rsh_plan_stats_t& st = plan.stats;
@@ -1308,11 +1310,12 @@ int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int thr
     st.n_scratch_slots = slots;
     st.sum_window_cols = sum_cols;
     const int64_t panel_bytes = panel_device_bytes(plan);
+    const int64_t residual_bytes = geo.narrow ? (int64_t)(plan.narrow_col.size() * 4 + plan.narrow_val.size() * 2 + plan.narrow_wave.size() * 4 + plan.narrow_seg.size() * 4)
+                                              : (int64_t)(plan.irr_col.size() * 4 + plan.irr_val.size() * 2 + plan.irr_wave.size() * 4 + plan.irr_row.size() * 4);
     st.plan_bytes = panel_bytes +
                     (int64_t)(plan.win_row.size() * 4 + plan.win_tile_off.size() * 4 + plan.tile_colid.size() * 4 +
                               plan.tile_mask.size() * 8 + plan.tile_val_off.size() * 4 + plan.tile_val.size() * 2 +
-                              plan.tile_item.size() * 4 + plan.panel_col0.size() * 4 + plan.irr_col.size() * 4 + plan.irr_val.size() * 2 +
-                              plan.irr_wave.size() * 4 + plan.irr_row.size() * 4 + plan.combine.size() * 4);
+                              plan.tile_item.size() * 4 + plan.panel_col0.size() * 4 + plan.combine.size() * 4) + residual_bytes;
     st.csr_bytes = 6 * a.nnz + 8 * (a.n_rows + 1);
     // What the product has to move under the routing as built (rows are routed whole, Section 3.1):
     // the plan once, a row of B per distinct column of every window and per residual entry, every
@@ -1335,8 +1338,7 @@ int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int thr
     st.tile_part_bytes = panel_bytes + (int64_t)(plan.win_row.size() * 4 + plan.tile_colid.size() * 4 + plan.tile_mask.size() * 8 +
                                    plan.tile_val_off.size() * 4 + plan.tile_val.size() * 2 + plan.tile_item.size() * 4 +
                                    plan.panel_col0.size() * 4);
-    st.irregular_part_bytes = (int64_t)(plan.irr_col.size() * 4 + plan.irr_val.size() * 2 + plan.irr_wave.size() * 4 +
-                                        plan.irr_row.size() * 4);
+    st.irregular_part_bytes = residual_bytes;
     {
         // distinct columns referenced by each part (the B rows each kernel must fetch at least once)
         std::vector<uint8_t> seen((size_t)a.n_cols, 0);
@@ -1359,6 +1361,150 @@ int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int thr
         st.rows_irregular = n_irr + (int64_t)part.empty.size();
     }
     return RSH_OK;
+}
+
+// A window fetches a row of B once for all its entries; the lanes of narrow.hpp fetch it for every entry, which costs
+// little where the line is at hand: where all of B stays in an XCD's L2 (up to 3 of its 4 MB, the rest for what streams
+// through), or where a window's columns lie next to each other, several to a line.  27-point stencil on 80^3, B of 8 MB at 8
+// features, 5.6 columns to a line: windows 48.0 us, lanes 27.8.  Communities, whose columns lie anywhere: 128000 rows, B of 2 MB,
+// 17.5 and 15.4; 524288 rows, 8 MB, 63.1 and 78.6, and 4 MB at 3 features 67.2 and 76.9, 1 MB at 1 feature 60.5 and 56.5.
+// From 9 features on windows are faster in both (stencil 12 features 46.5 and 57; communities 53.4 and more than 80).
+bool narrow_pays(const rsh_csr_t& a, const Partition& part, int n) {
+    if (n > kNarrow / 2 || part.win_row.empty()) return false;
+    const int64_t row_bytes = 2 * narrow_width(n);
+    if (a.n_cols * row_bytes <= (int64_t)3 << 20) return true;
+    const int64_t n_win = (int64_t)part.win_row.size() / kW, step = std::max<int64_t>(1, n_win / 512);
+    int64_t columns = 0, lines = 0;
+    std::vector<int32_t> cols;
+    for (int64_t w = 0; w < n_win; w += step) {
+        cols.clear();
+        for (int r = 0; r < kW; ++r) {
+            const int32_t row = part.win_row[(size_t)(w * kW + r)];
+            if (row >= 0) cols.insert(cols.end(), a.col_idx + a.row_ptr[row], a.col_idx + a.row_ptr[row + 1]);
+        }
+        std::sort(cols.begin(), cols.end());
+        int64_t last_line = -1;
+        int32_t last = -1;
+        for (int32_t c : cols) {
+            columns += c != last;
+            lines += c * row_bytes / 128 != last_line;
+            last = c;
+            last_line = c * row_bytes / 128;
+        }
+    }
+    return 2 * lines <= columns;
+}
+
+// ---------------------------------------------------------------------------
+// Residual rows of at most kNarrow features (narrow.hpp).  The waves of IRR_WAVE are taken apart into segments -- a row, or
+// a slice of one -- and these dealt to lanes: T = 1, 2, .. 64 lanes take a segment, entry e being lane e % T's, 64 / T
+// segments make a wave.  A lane takes up to twice `per_lane` entries: 16, or fewer where the plan would have too few waves
+// to fill the chip.  Segments that write C are dealt to the XCDs in contiguous runs of rows of equal cost, so that lines of C
+// that hold several short rows are written by one L2; partial sums stay on the XCD that the plan chose for their columns.
+// Inside a run they are ordered by length within blocks of rows, so that the lanes of a wave end together: 8192 rows, or, for
+// rows whose order puts those with the same columns next to each other, 128 (128000 rows of communities, 8 features: 15.6 us, 18.9
+// with 512).
+// Entries lie in pairs: entry pair q of lane l at 2 * (first + 64 q + l), a wave's lanes next to each other.
+// ---------------------------------------------------------------------------
+void pack_narrow(HostPlan& plan, int threads) {
+    struct Segment {
+        uint32_t dst, len, start;   // len with kSegmentToScratch
+    };
+    const int64_t block_rows = plan.narrow_in_order ? 128 : 8192;
+    constexpr uint64_t kShare = 6;   // cost of a segment beside its entries
+    std::vector<Segment> partial[8], direct;
+    const auto len_of = [](const Segment& s) { return s.len & ~kSegmentToScratch; };
+    uint64_t entries = 0;
+    for (int x = 0; x < 8; ++x)
+        for (uint32_t w = plan.irr_split.start[x]; w < plan.irr_split.start[x + 1]; ++w) {
+            const uint32_t* d = &plan.irr_wave[4 * (size_t)w];
+            const uint32_t kind = d[3] & kWaveKindMask, L = (d[3] >> 8) & 0xffu;
+            if (kind == kWaveSlice) {
+                const bool to_scratch = (d[3] & kWaveToScratch) != 0;
+                (to_scratch ? partial[x] : direct).push_back({d[2], d[1] | (to_scratch ? kSegmentToScratch : 0u), d[0]});
+                entries += d[1];
+            } else {   // rows of L entries, or of none
+                for (uint32_t i = 0; i < d[1]; ++i)
+                    direct.push_back({(uint32_t)plan.irr_row[(size_t)d[2] + i], kind == kWaveShortRows ? L : 0u, d[0] + i * (kind == kWaveShortRows ? L : 0u)});
+                if (kind == kWaveShortRows) entries += (uint64_t)d[1] * L;
+            }
+        }
+    if (plan.narrow_in_order) {
+        std::vector<uint32_t> place((size_t)plan.n_rows);
+        for (size_t i = 0; i < plan.order.size(); ++i) place[(size_t)plan.order[i]] = (uint32_t)i;
+        parallel_sort(direct.begin(), direct.end(), threads, [&](const Segment& a, const Segment& b) { return place[a.dst] < place[b.dst]; });
+    } else {
+        parallel_sort(direct.begin(), direct.end(), threads, [](const Segment& a, const Segment& b) { return a.dst < b.dst; });
+    }
+    const uint32_t per_lane = (uint32_t)std::min<uint64_t>(16, std::max<uint64_t>(2, entries / (64 * 4096)));
+    const auto log_lanes = [per_lane](uint32_t len) {
+        uint32_t t = 0;
+        while (t < 6 && len > 2 * (per_lane << t)) ++t;
+        return t;
+    };
+    // contiguous eighths of the rows, by cost
+    uint64_t cost = 0, run = 0;
+    for (const Segment& s : direct) cost += len_of(s) + kShare;
+    for (int x = 0; x < 8; ++x)
+        for (const Segment& s : partial[x]) cost += len_of(s) + kShare;
+    std::vector<Segment> order;
+    order.reserve(direct.size());
+    plan.narrow_wave.clear();
+    plan.narrow_seg.clear();
+    std::vector<uint32_t> wave_seg;   // first segment of every wave, in `order`
+    uint64_t first = 0;
+    const auto emit = [&](size_t b, size_t e) {   // segments [b, e) of `order`: by lanes, then length, descending
+        std::stable_sort(order.begin() + (int64_t)b, order.begin() + (int64_t)e, [&](const Segment& p, const Segment& q) { return len_of(p) > len_of(q); });
+        for (size_t i = b; i < e;) {
+            const uint32_t t = log_lanes(len_of(order[i])), T = 1u << t;
+            size_t j = i;
+            uint32_t shortest = ~0u;
+            while (j < e && j - i < (64u >> t) && log_lanes(len_of(order[j])) == t) shortest = std::min(shortest, len_of(order[j])), ++j;
+            const uint32_t steps = (len_of(order[i]) + T - 1) >> t, pairs = (steps + 1) / 2, full = std::min<uint32_t>(shortest >> t, 0xffffu);
+            wave_seg.push_back((uint32_t)i);
+            plan.narrow_wave.insert(plan.narrow_wave.end(), {(uint32_t)first, steps, t | (uint32_t)(j - i) << 8 | full << 16, (uint32_t)i});
+            first += (uint64_t)pairs * 64;
+            i = j;
+        }
+    };
+    size_t at = 0;
+    for (int x = 0; x < 8; ++x) {
+        plan.narrow_split.start[x] = (uint32_t)(plan.narrow_wave.size() / 4);
+        const size_t b = order.size();
+        order.insert(order.end(), partial[x].begin(), partial[x].end());
+        for (const Segment& s : partial[x]) run += len_of(s) + kShare;
+        emit(b, order.size());
+        while (at < direct.size() && (x == 7 || run * 8 < cost * (uint64_t)(x + 1))) {
+            const size_t block = order.size();
+            while (at < direct.size() && (int64_t)(order.size() - block) < block_rows && (x == 7 || run * 8 < cost * (uint64_t)(x + 1))) {
+                run += len_of(direct[at]) + kShare;
+                order.push_back(direct[at++]);
+            }
+            emit(block, order.size());
+        }
+    }
+    plan.narrow_split.start[8] = (uint32_t)(plan.narrow_wave.size() / 4);
+    plan.narrow_seg.resize(2 * order.size());
+    const size_t slots = 2 * ((size_t)first + 64 * (size_t)kNarrowAhead);
+    plan.narrow_col.assign(slots, 0);
+    plan.narrow_val.assign(slots, 0);
+    parallel_dynamic((int64_t)wave_seg.size(), threads, 256, [&](int64_t b, int64_t e, int) {
+        for (int64_t w = b; w < e; ++w) {
+            const uint32_t* d = &plan.narrow_wave[4 * (size_t)w];
+            const uint32_t t = d[2] & 0xffu, n = (d[2] >> 8) & 0xffu;
+            for (uint32_t k = 0; k < n; ++k) {
+                const Segment& s = order[(size_t)d[3] + k];
+                plan.narrow_seg[2 * ((size_t)d[3] + k)] = s.dst;
+                plan.narrow_seg[2 * ((size_t)d[3] + k) + 1] = s.len;
+                for (uint32_t i = 0, len = len_of(s); i < len; ++i) {
+                    const uint32_t j = i >> t, lane = (k << t) + (i & ((1u << t) - 1u));
+                    const size_t to = 2 * ((size_t)d[0] + 64 * (size_t)(j / 2) + lane) + (j & 1);
+                    plan.narrow_col[to] = plan.irr_col[(size_t)s.start + i];
+                    plan.narrow_val[to] = plan.irr_val[(size_t)s.start + i];
+                }
+            }
+        }
+    });
 }
 
 // ---------------------------------------------------------------------------

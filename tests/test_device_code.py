@@ -42,8 +42,8 @@ def test_rows_of_c_leave_with_the_streaming_hint(kernels_asm):
     irregular = {n: b for n, b in kernels_asm.items() if "rsh_irregular_kernel" in n}
     combine = {n: b for n, b in kernels_asm.items() if "rsh_combine_kernel" in n}
     # every kernel exists twice: fp32 sums (OutPlain) and the fused binary16 epilogue (OutFused);
-    # the irregular kernel once more for a partial last feature panel
-    assert len(tile) >= 60 and len(irregular) == 16 and len(combine) == 2
+    # the irregular kernel, for teams of four, eight and sixteen lanes, once more for a partial last feature panel
+    assert len(tile) >= 60 and len(irregular) == 12 and len(combine) == 2
     for name, body in tile.items():
         n, nt = _stores(body)
         if "OutFused" in name:
@@ -75,7 +75,7 @@ def test_rows_of_even_widths_leave_with_the_streaming_hint(kernels_asm):
         # fragments: partial sums leave with ordinary stores, one per 16-feature chunk
         ordinary = int(re.search(r"rsh_fragment_even_kernelILi(\d+)E", name).group(1)) if kind == "fragment_even" else 0
         assert nt > 0 and len(st) - nt == ordinary, f"{name}: {nt} of {len(st)} stores are streaming"
-    assert seen["fragment_even"] >= 60 and seen["residual_even"] == 8 and seen["sum_even"] == 2
+    assert seen["fragment_even"] >= 60 and seen["residual_even"] == 6 and seen["sum_even"] == 2
 
 
 def test_kernels_keep_their_registers(kernels_asm):

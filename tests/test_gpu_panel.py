@@ -257,3 +257,50 @@ def test_a_narrower_last_panel_in_a_launch_of_its_own(window_rows, N, fused):
     assert not np.isnan(got).any()
     assert np.all(np.abs(got - C_ref) <= bound)
     plan.destroy()
+
+
+# Rows of up to 16 features (lanes own rows).  Rows of 0 .. 2000 entries: empty, one to a lane with an odd and an even number of
+# entries, at both sides of every doubling of the lanes that share one, sliced with partial sums; few rows (a lane takes two
+# entries) and many (16); column groups; beside windows that read a copy of 16 features.  B and C begin one element past a
+# 16-byte boundary in `odd`: then widths that are a power of two go through the copy too.
+@pytest.mark.parametrize("fused,odd", [(False, 0), (False, 1), (True, 0)])
+@pytest.mark.parametrize("N", [1, 2, 3, 4, 5, 8, 9, 16])
+@pytest.mark.parametrize("rows,opts", [(90, {}), (90, dict(max_nnz_per_slice=40)), (90, dict(xcd_partition_nnz=32)), (90, dict(window_rows=16, min_reuse=0.0)),
+                                       (70000, {})], ids=["few", "slices", "groups", "windows", "many"])
+def test_narrow_rows(rows, opts, N, fused, odd):
+    import torch
+    from paper_2603_08734_amd import Plan
+    rng = np.random.default_rng(13)
+    lengths = np.array([0, 1, 2, 3, 4, 5, 8, 9, 16, 17, 31, 32, 33, 63, 64, 65, 128, 129, 500, 2000])
+    if rows > 100:
+        lengths = lengths[lengths <= 65]
+    per_row = rng.permutation(np.resize(lengths, rows))
+    r = np.repeat(np.arange(rows), per_row)
+    c = np.concatenate([rng.choice(3000, k, replace=False) if k > 100 else (rng.integers(0, 2900) + rng.permutation(100)[:k]) for k in per_row])
+    A = from_coo(r, c, rng.standard_normal(r.size), rows, 3000)
+    if N == 16 and odd:
+        pytest.skip("rows of 16 features have to be 16-byte aligned")
+    print(f"case narrow rows={rows} {opts} N={N} fused={fused} odd={odd}", flush=True)
+    plan = Plan(A.row_ptr, A.col_idx, A.val, A.n_cols, N, **opts)
+    B = dense_B(A.n_cols, N, "normal", seed=N)
+    Bd = torch.empty(B.size + odd, dtype=torch.float16, device="cuda")[odd:].view(A.n_cols, N)
+    Bd.copy_(torch.from_numpy(B.view(np.float16) if B.dtype != np.float16 else B))
+    C_ref, S, _ = oracle.spmm(A.row_ptr, A.col_idx, A.val, B)
+    pad = 64
+    flat = torch.full((rows * N + 2 * pad,), float("nan"), dtype=torch.float16 if fused else torch.float32, device="cuda")
+    C = flat[pad + odd:pad + odd + rows * N].view(rows, N)
+    bound = 1e-4 * S
+    if fused:
+        bias = torch.linspace(-1, 1, N, device="cuda")
+        plan.spmm_f16(Bd, C, bias, relu=True)
+        C_ref = np.maximum(C_ref + bias.cpu().numpy().astype(np.float64), 0.0)
+        # the fp32 bound, the addition of the bias, one rounding to binary16
+        bound = bound + 2.0 ** -24 * np.abs(C_ref) + 2.0 ** -11 * np.abs(C_ref) * 1.001 + 2.0 ** -24
+    else:
+        plan.spmm(Bd, C)
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(flat[:pad + odd]).all()) and bool(torch.isnan(flat[pad + odd + rows * N:]).all()), "stores outside C"
+    got = C.cpu().numpy().astype(np.float64)
+    assert not np.isnan(got).any()
+    assert np.all(np.abs(got - C_ref) <= bound)
+    plan.destroy()

@@ -624,3 +624,24 @@ def test_plan_bytes_of_tall_windows_with_cells_written_out(N, window_rows, densi
     tile = sum(p.array(getattr(B_, "RSH_ARR_" + n)).nbytes for n in ("WIN_ROW", "TILE_COLID", "TILE_ITEM", "PANEL_COL0"))
     cells = 8192 * (2 * st["n_tiles"] + 1)     # 256 rows x 16 columns a K step, and one of zeros
     assert (st["tile_part_bytes"] == tile + cells) == wide
+
+
+# 16-row windows of up to 8 features join the residual rows where B stays in an L2 or columns share lines
+@pytest.mark.parametrize("N,n_cols,neighbours,windows", [(8, 4000, False, False), (8, 400000, False, True), (8, 400000, True, False), (1, 400000, False, False),
+                                                         (9, 4000, False, True), (16, 400000, True, True)])
+def test_windows_of_narrow_rows(N, n_cols, neighbours, windows):
+    rng = np.random.default_rng(2)
+    r, c = [], []
+    for w in range(100):     # groups of 16 rows with 24 columns, of which each row holds 16
+        cols = np.sort(rng.integers(0, n_cols - 24)) + np.arange(24) if neighbours else rng.choice(n_cols, 24, replace=False)
+        for i in range(16):
+            r.append(np.full(16, 16 * w + i))
+            c.append(rng.choice(cols, 16, replace=False))
+    r, c = np.concatenate(r), np.concatenate(c)
+    A = from_coo(r, c, rng.standard_normal(r.size), 1600, n_cols)
+    p = host_plan(A, N, reorder=0)
+    assert (p.stats()["nnz_tile"] == A.nnz) == windows and p.stats()["nnz_tile"] in (0, A.nnz)
+    assert p.stats()["tile_k"] == 32
+    row_ptr, col_idx, val, _ = p.decode()
+    assert np.array_equal(row_ptr, A.row_ptr) and np.array_equal(col_idx, A.col_idx) and np.array_equal(val, A.val.view(np.uint16))
+    assert host_plan(A, 8, window_rows=16, reorder=0).stats()["nnz_tile"] > 0      # windows that the caller asks for stay
