@@ -26,7 +26,6 @@
 #include "device.hpp"
 #include "panel.hpp"
 #include "wide.hpp"
-#include "narrow.hpp"
 
 namespace rsh {
 
@@ -85,6 +84,10 @@ __device__ __forceinline__ void emit_row(const OutFusedT<ROWS>& o, size_t row, i
     const uint2_t hi = finish4(o, f + 4, end, (float4_t){acc[4], acc[5], acc[6], acc[7]});
     store_halves(o, row, nv, f, end, (uint4_t){lo[0], lo[1], hi[0], hi[1]});
 }
+
+}  // namespace rsh
+#include "narrow.hpp"
+namespace rsh {
 
 // ---------------------------------------------------------------------------
 // Irregular rows.  A wave is G = 64/TPR teams of TPR lanes; lane t of a team owns
@@ -987,7 +990,7 @@ static int launch_all(const DevicePlan& d, const void* B, const OUT& out, int nb
     st = caller;
     mark(1);
     if (d.n_irr_waves > 0 && d.geo.narrow) {
-        launch_narrow(d, B, out.any(), st, nb, nv);
+        launch_narrow(d, B, out, st, nb, nv);
     } else if (d.n_irr_waves > 0) {
         switch (d.geo.irr_tpr) {
             case 4: launch_irregular_t<4>(d, B, out, st, nb, nv); break;

@@ -1,4 +1,4 @@
-// Residual rows of at most 16 features: lanes own rows.  Included by kernels.hip.
+// Residual rows of few features: lanes own rows, or share them in fours or eights.  Included by kernels.hip.
 //
 // The residual kernel gives a row of B to a team of lanes, eight features each; of rows this short two lanes do, and what
 // they gather, 32 bytes, is less than what tells them where (a wave's 32 teams fetch their column ids two at a time from 32
@@ -161,20 +161,113 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void rsh_narrow_kernel(const u
     }
 }
 
+// The same with F lanes to a row of B of up to 8 F features, eight features each: a wave has 64 / F places for rows.  Teams that
+// share one row of C (rsh_irregular_kernel) add up 64 / F sums at its end, for rows of a dozen entries as much work as the
+// entries, and fetch ids F at a time; the times of both are at lanes_per_row in planner.cpp.  Rows of C leave like theirs, by
+// streaming stores of whole lines after a turn through LDS (ordinary stores of 16-byte pieces: 80 us instead of 60 for the
+// power-law graph of 2^18 vertices at 32 features).  Four rows of B in flight per lane; with eight 64 features take 112 us
+// instead of 98.
+template <int F, bool PARTIAL, class OUT>
+__global__ __launch_bounds__(64 * kWavesPerBlock) void rsh_shared_kernel(const uint4* __restrict__ waves, XcdSplit xs, const uint2_t* __restrict__ segments,
+                                                                         const uint2_t* __restrict__ col, const uint32_t* __restrict__ val,
+                                                                         const __half* __restrict__ B, const OUT out, float* __restrict__ scratch, int nb,
+                                                                         int nv, int ns) {
+    constexpr int PAIRS = 2, S = 64 / F;
+    const int lane = threadIdx.x & 63, slot = lane / F, tl = lane % F, lane_f = lane_features<PARTIAL, OUT::kRows>(nb, tl);
+    __shared__ __attribute__((aligned(16))) float lds_stage[kWavesPerBlock][64 * 8];
+    uint32_t wave;
+    if (!xcd_work_item(xs, &wave)) return;
+    const uint4 d = waves[wave];
+    const uint32_t first = __builtin_amdgcn_readfirstlane(d.x), steps = __builtin_amdgcn_readfirstlane(d.y);
+    const uint32_t info = __builtin_amdgcn_readfirstlane(d.z), seg0 = __builtin_amdgcn_readfirstlane(d.w);
+    const uint32_t t = info & 0xffu, n_seg = (info >> 8) & 0xffu, full = info >> 16;
+    const uint32_t seg = (uint32_t)slot >> t, in_seg = (uint32_t)slot & ((1u << t) - 1u);
+    const bool live = seg < n_seg;
+    uint2_t s = {0, 0};
+    if (live) s = segments[seg0 + seg];
+    const uint32_t len = s[1] & ~kSegmentToScratch;
+    const uint32_t mine = len > in_seg ? (len - in_seg + (1u << t) - 1u) >> t : 0u;
+    const uint2_t* pc = col + first + slot;
+    const uint32_t* pv = val + first + slot;
+    const char* const Bb = reinterpret_cast<const char*>(B);
+    const uint32_t row_bytes = 2u * (uint32_t)nb, lane_byte = 2u * (uint32_t)lane_f;
+    float acc[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[i] = 0.f;
+    uint2_t c[PAIRS];
+    uint32_t v[PAIRS];
+#pragma unroll
+    for (int u = 0; u < PAIRS; ++u) c[u] = pc[S * u], v[u] = pv[S * u];
+    for (uint32_t j = 0; j < steps; j += 2 * PAIRS) {
+        uint4_t b[2 * PAIRS];
+        uint32_t w[PAIRS];
+#pragma unroll
+        for (int u = 0; u < PAIRS; ++u) {
+            b[2 * u] = *reinterpret_cast<const uint4_a4*>(Bb + (c[u][0] * row_bytes + lane_byte));
+            b[2 * u + 1] = *reinterpret_cast<const uint4_a4*>(Bb + (c[u][1] * row_bytes + lane_byte));
+            w[u] = v[u];
+        }
+        const uint32_t next = min(j + 2 * PAIRS, (steps + 1) & ~1u);
+#pragma unroll
+        for (int u = 0; u < PAIRS; ++u) c[u] = pc[(S / 2) * next + S * u], v[u] = pv[(S / 2) * next + S * u];
+        if (j + 2 * PAIRS > full) {
+#pragma unroll
+            for (int u = 0; u < 2 * PAIRS; ++u) {
+                const bool on = j + u < mine;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) b[u][i] = on ? b[u][i] : 0u;
+                w[u / 2] &= on ? ~0u : u % 2 ? 0x0000ffffu : 0xffff0000u;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < 2 * PAIRS; ++u) {
+            const __half2 h = __builtin_bit_cast(__half2, w[u / 2]);
+            const float x = u % 2 ? __high2float(h) : __low2float(h);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t q = b[u][i];
+                const __half2 p = __builtin_bit_cast(__half2, q);
+                acc[2 * i] = fmaf(x, __low2float(p), acc[2 * i]);
+                acc[2 * i + 1] = fmaf(x, __high2float(p), acc[2 * i + 1]);
+            }
+        }
+    }
+    for (uint32_t k = 0; k < t; ++k) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[i] += shfl_f32(acc[i], lane ^ (F << k));
+    }
+    if (!live || in_seg != 0) return;
+    float* const stage = lds_stage[threadIdx.x >> 6] + slot * (8 * F);
+    if (s[1] & kSegmentToScratch) store_row_streaming<F, PARTIAL, kRowsEven>(scratch + (size_t)s[0] * ns, acc, stage, tl, lane_f, nb);
+    else emit_row<F, PARTIAL>(out, (size_t)s[0], nv, 0, acc, stage, tl, lane_f);
+}
+
 template <class OUT>
 void launch_narrow(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st, int nb, int nv) {
     uint32_t longest = 0;
     for (int x = 0; x < 8; ++x) longest = std::max(longest, d.irr_split.start[x + 1] - d.irr_split.start[x]);
-    const auto launch = [&](auto kernel) {
+    const auto launch = [&](auto kernel, const auto& to) {
         hipLaunchKernelGGL(kernel, dim3(8u * ((longest + kWavesPerBlock - 1) / kWavesPerBlock)), dim3(64 * kWavesPerBlock), 0, st, (const uint4*)d.irr_wave,
-                           d.irr_split, (const uint2_t*)d.narrow_seg, (const uint2_t*)d.irr_col, (const uint32_t*)d.irr_val, (const __half*)B, out, d.scratch,
+                           d.irr_split, (const uint2_t*)d.narrow_seg, (const uint2_t*)d.irr_col, (const uint32_t*)d.irr_val, (const __half*)B, to, d.scratch,
                            nb, nv, d.geo.N);
     };
-    if (nv == 1) launch(rsh_narrow_kernel<1, OUT>);
-    else if (nv == 2) launch(rsh_narrow_kernel<2, OUT>);
-    else if (nv <= 4) launch(rsh_narrow_kernel<4, OUT>);
-    else if (nv <= 8) launch(rsh_narrow_kernel<8, OUT>);
-    else launch(rsh_narrow_kernel<16, OUT>);
+    if (d.geo.narrow == 1) {
+        const auto any = out.any();
+        using Any = std::decay_t<decltype(any)>;
+        if (nv == 1) launch(rsh_narrow_kernel<1, Any>, any);
+        else if (nv == 2) launch(rsh_narrow_kernel<2, Any>, any);
+        else if (nv <= 4) launch(rsh_narrow_kernel<4, Any>, any);
+        else if (nv <= 8) launch(rsh_narrow_kernel<8, Any>, any);
+        else launch(rsh_narrow_kernel<16, Any>, any);
+        return;
+    }
+    const auto rows = out.general();
+    using Rows = std::decay_t<decltype(rows)>;
+    if constexpr (!Rows::kAny) {
+        if (nv == 8 * d.geo.narrow) return d.geo.narrow == 4 ? launch(rsh_shared_kernel<4, false, Rows>, rows) : launch(rsh_shared_kernel<8, false, Rows>, rows);
+    }
+    if (d.geo.narrow == 4) launch(rsh_shared_kernel<4, true, Rows>, rows);
+    else launch(rsh_shared_kernel<8, true, Rows>, rows);
 }
 
 }  // namespace

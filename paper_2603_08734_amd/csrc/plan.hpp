@@ -39,7 +39,7 @@ struct Geometry {
     int cpl = 4;        // cells per MFMA lane = bitmap words per sub-fragment = tile_k / 4
     int panel = 0;      // 1 = tall windows in the panel form (win_rows == 128 or 256, tile_k == 32)
     int wide = 0;       // panel form whose cells are written out on the device (wide.hpp); win_rows == 256
-    int narrow = 0;     // residual rows in the form of narrow.hpp: rows of at most 16 features
+    int narrow = 0;     // residual rows in the form of narrow.hpp: lanes that share a row of B (1, 4 or 8), 0 = teams
     int panel_groups = 0; // panel form: row groups of 32 rows per window = win_rows / 32
 };
 Geometry make_geometry(int N, int window_rows, int tile_k);

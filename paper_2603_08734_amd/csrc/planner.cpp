@@ -44,7 +44,6 @@ Geometry make_geometry(int N, int window_rows, int tile_k) {
     g.tile_nch = g.tile_panel / 16;
     g.panel = window_rows >= kPanelMinRows ? 1 : 0;
     g.panel_groups = g.panel ? window_rows / 32 : 0;
-    g.narrow = N <= kNarrow ? 1 : 0;
     return g;
 }
 
@@ -800,6 +799,8 @@ static std::vector<uint32_t> cut_tall_windows(const HostPlan& plan, int64_t n_wi
     return best;
 }
 
+static int lanes_per_row(const HostPlan& plan, const rsh_csr_t& a, const std::vector<int32_t>& rows, int64_t entries);
+
 int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int threads) {
     Geometry& geo = plan.geo;
     const int W = geo.win_rows, NW = geo.nw;
@@ -1282,6 +1283,7 @@ int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int thr
     }
 
     plan.n_scratch_slots = slots;
+    geo.narrow = lanes_per_row(plan, a, part.irregular, nnz_irr);
     if (geo.narrow) pack_narrow(plan, threads);
 
     // ---- statistics -----------------------------------------------------------------------
@@ -1395,16 +1397,34 @@ bool narrow_pays(const rsh_csr_t& a, const Partition& part, int n) {
     return 2 * lines <= columns;
 }
 
+// Lanes that share a row of B in the residual part (narrow.hpp), or none for teams that share a wave (rsh_irregular_kernel).
+// Up to 16 features always one.  Beyond that from 2^18 entries on: below, a launch is over before it matters (65536 entries, 32
+// features, 7.5 .. 8.4 us both).  Not from 49 to 63 features, where rows of B end inside their last line: power-law
+// graph of 2^18 vertices, us with teams and with shared lanes, 24 features 80 and 67, 32 72 and 60, 40 90 and 90, 48 106 and 105,
+// 50 104 and 112, 60 112 and 123, 64 107 and 96 (binary16 111 and 94); of 2^20 vertices 32 340 and 332, 64 445 and 409; of
+// 2^16 32 23.9 and 19.9, 64 32.8 and 24.9; 150000 rows of 12 entries 43.7 and 21.9, 47.9 and 32.4.  What is saved is a wave for
+// each row of medium length: a tenth of the rows has to be longer than the teams of a wave take several of (100000 rows of 5
+// entries, 64 features, 13.6 and 15.2) and short enough to need no sum over places (60000 rows of 36 entries, 48 features
+// 50.5 and 55, 64 40.0 and 41.8).  In these graphs it is a seventh to a quarter.
+static int lanes_per_row(const HostPlan& plan, const rsh_csr_t& a, const std::vector<int32_t>& rows, int64_t entries) {
+    if (plan.geo.N <= kNarrow) return 1;
+    if (entries < (1 << 18) || (plan.n_user > 48 && plan.n_user != 64)) return 0;
+    const int lanes = plan.n_user <= 32 ? 4 : 8;
+    const int64_t medium = std::count_if(rows.begin(), rows.end(), [&](int32_t r) { return row_len(a, r) > lanes && row_len(a, r) <= 32; });
+    return 10 * medium >= (int64_t)rows.size() ? lanes : 0;
+}
+
 // ---------------------------------------------------------------------------
-// Residual rows of at most kNarrow features (narrow.hpp).  The waves of IRR_WAVE are taken apart into segments -- a row, or
-// a slice of one -- and these dealt to lanes: T = 1, 2, .. 64 lanes take a segment, entry e being lane e % T's, 64 / T
-// segments make a wave.  A lane takes up to twice `per_lane` entries: 16, or fewer where the plan would have too few waves
-// to fill the chip.  Segments that write C are dealt to the XCDs in contiguous runs of rows of equal cost, so that lines of C
-// that hold several short rows are written by one L2; partial sums stay on the XCD that the plan chose for their columns.
-// Inside a run they are ordered by length within blocks of rows, so that the lanes of a wave end together: 8192 rows, or, for
+// Residual rows in the form of narrow.hpp.  The waves of IRR_WAVE are taken apart into segments -- a row, or a slice of one --
+// and these dealt to the S places of a wave (its lanes, or groups of geo.narrow lanes that share a row of B): T = 1, 2, .. S
+// places take a segment, entry e being place e % T's, S / T segments make a wave.  A place takes up to twice `per_lane`
+// entries: 16, or fewer where the plan would have too few waves to fill the chip.  Segments that write C are dealt to the
+// XCDs in contiguous runs of rows of equal cost, so that lines of C that hold several short rows are written by one L2 (dealt
+// in runs of 64 to 2048 rows nothing changes); partial sums stay on the XCD that the plan chose for their columns.
+// Inside a run they are ordered by length within blocks of rows, so that the places of a wave end together: 8192 rows, or, for
 // rows whose order puts those with the same columns next to each other, 128 (128000 rows of communities, 8 features: 15.6 us, 18.9
 // with 512).
-// Entries lie in pairs: entry pair q of lane l at 2 * (first + 64 q + l), a wave's lanes next to each other.
+// Entries lie in pairs: entry pair q of place l at 2 * (first + S q + l), a wave's places next to each other.
 // ---------------------------------------------------------------------------
 void pack_narrow(HostPlan& plan, int threads) {
     struct Segment {
@@ -1436,10 +1456,11 @@ void pack_narrow(HostPlan& plan, int threads) {
     } else {
         parallel_sort(direct.begin(), direct.end(), threads, [](const Segment& a, const Segment& b) { return a.dst < b.dst; });
     }
-    const uint32_t per_lane = (uint32_t)std::min<uint64_t>(16, std::max<uint64_t>(2, entries / (64 * 4096)));
-    const auto log_lanes = [per_lane](uint32_t len) {
+    const uint32_t S = 64u / (uint32_t)plan.geo.narrow;   // rows of B that a wave takes at a time
+    const uint32_t per_lane = (uint32_t)std::min<uint64_t>(16, std::max<uint64_t>(2, entries / (S * 4096)));
+    const auto log_lanes = [per_lane, S](uint32_t len) {
         uint32_t t = 0;
-        while (t < 6 && len > 2 * (per_lane << t)) ++t;
+        while ((1u << t) < S && len > 2 * (per_lane << t)) ++t;
         return t;
     };
     // contiguous eighths of the rows, by cost
@@ -1459,11 +1480,11 @@ void pack_narrow(HostPlan& plan, int threads) {
             const uint32_t t = log_lanes(len_of(order[i])), T = 1u << t;
             size_t j = i;
             uint32_t shortest = ~0u;
-            while (j < e && j - i < (64u >> t) && log_lanes(len_of(order[j])) == t) shortest = std::min(shortest, len_of(order[j])), ++j;
+            while (j < e && j - i < (S >> t) && log_lanes(len_of(order[j])) == t) shortest = std::min(shortest, len_of(order[j])), ++j;
             const uint32_t steps = (len_of(order[i]) + T - 1) >> t, pairs = (steps + 1) / 2, full = std::min<uint32_t>(shortest >> t, 0xffffu);
             wave_seg.push_back((uint32_t)i);
             plan.narrow_wave.insert(plan.narrow_wave.end(), {(uint32_t)first, steps, t | (uint32_t)(j - i) << 8 | full << 16, (uint32_t)i});
-            first += (uint64_t)pairs * 64;
+            first += (uint64_t)pairs * S;
             i = j;
         }
     };
@@ -1498,7 +1519,7 @@ void pack_narrow(HostPlan& plan, int threads) {
                 plan.narrow_seg[2 * ((size_t)d[3] + k) + 1] = s.len;
                 for (uint32_t i = 0, len = len_of(s); i < len; ++i) {
                     const uint32_t j = i >> t, lane = (k << t) + (i & ((1u << t) - 1u));
-                    const size_t to = 2 * ((size_t)d[0] + 64 * (size_t)(j / 2) + lane) + (j & 1);
+                    const size_t to = 2 * ((size_t)d[0] + S * (size_t)(j / 2) + lane) + (j & 1);
                     plan.narrow_col[to] = plan.irr_col[(size_t)s.start + i];
                     plan.narrow_val[to] = plan.irr_val[(size_t)s.start + i];
                 }

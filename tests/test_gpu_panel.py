@@ -263,10 +263,15 @@ def test_a_narrower_last_panel_in_a_launch_of_its_own(window_rows, N, fused):
 # entries, at both sides of every doubling of the lanes that share one, sliced with partial sums; few rows (a lane takes two
 # entries) and many (16); column groups; beside windows that read a copy of 16 features.  B and C begin one element past a
 # 16-byte boundary in `odd`: then widths that are a power of two go through the copy too.
+# From 17 features on four or eight lanes share a row, in plans of 2^18 entries and more: widths that fill the lanes, end at
+# every place inside the last one's eight features, and odd ones beside the padded copy.
+FEW = [(90, {}), (90, dict(max_nnz_per_slice=40)), (90, dict(xcd_partition_nnz=32)), (90, dict(window_rows=16, min_reuse=0.0))]
+MANY = [(20000, {}), (20000, dict(max_nnz_per_slice=20)), (20000, dict(xcd_partition_nnz=32))]
+
+
 @pytest.mark.parametrize("fused,odd", [(False, 0), (False, 1), (True, 0)])
-@pytest.mark.parametrize("N", [1, 2, 3, 4, 5, 8, 9, 16])
-@pytest.mark.parametrize("rows,opts", [(90, {}), (90, dict(max_nnz_per_slice=40)), (90, dict(xcd_partition_nnz=32)), (90, dict(window_rows=16, min_reuse=0.0)),
-                                       (70000, {})], ids=["few", "slices", "groups", "windows", "many"])
+@pytest.mark.parametrize("rows,opts,N", [(*p, n) for p in FEW + MANY[:1] for n in (1, 2, 3, 4, 5, 8, 9, 16)] +
+                         [(*p, n) for p in MANY for n in (17, 18, 24, 30, 31, 32, 34, 47, 48, 64)])
 def test_narrow_rows(rows, opts, N, fused, odd):
     import torch
     from paper_2603_08734_amd import Plan
@@ -278,8 +283,8 @@ def test_narrow_rows(rows, opts, N, fused, odd):
     r = np.repeat(np.arange(rows), per_row)
     c = np.concatenate([rng.choice(3000, k, replace=False) if k > 100 else (rng.integers(0, 2900) + rng.permutation(100)[:k]) for k in per_row])
     A = from_coo(r, c, rng.standard_normal(r.size), rows, 3000)
-    if N == 16 and odd:
-        pytest.skip("rows of 16 features have to be 16-byte aligned")
+    if N % 16 == 0 and odd:
+        pytest.skip("rows of a multiple of 16 features have to be 16-byte aligned")
     print(f"case narrow rows={rows} {opts} N={N} fused={fused} odd={odd}", flush=True)
     plan = Plan(A.row_ptr, A.col_idx, A.val, A.n_cols, N, **opts)
     B = dense_B(A.n_cols, N, "normal", seed=N)
