@@ -398,6 +398,7 @@ int rsh_plan_create(const rsh_csr_t* csr, int32_t N, const rsh_plan_opts_t* opts
 
         t0 = std::chrono::steady_clock::now();
         p->dev.n_user = n_user;
+        p->dev.n_cols = h.n_cols;
         if (o.upload) {
             rc = upload_plan(*p);
             if (rc) throw rc;
@@ -443,6 +444,15 @@ int check_launch(const rsh_plan_t* plan, const void* B, const void* C, const voi
     const uintptr_t mb = *padded ? 1u : 15u, mc = *padded ? (uintptr_t)c_elem - 1u : 15u, mbias = *padded ? 3u : 15u;
     if (((uintptr_t)B & mb) || ((uintptr_t)C & mc) || ((uintptr_t)bias & mbias)) return RSH_ERR_BAD_OPTION;
     if (*padded && n >= 16 && n % 2 == 0 && plan->dev.geo.N == auto_run_width(n) && !(((uintptr_t)B | (uintptr_t)C) & 3u)) {
+        *padded = false;
+        *width = n;
+    }
+    // Tall windows without residual rows beside them read rows of fewer than 16 features where they lie (panel.hpp).  That
+    // saves a launch and costs the loop 0.08 us per fragment of a workgroup, so not beyond 32 fragments per compute unit: weights
+    // of 1024 x 1024, 5 features, 15.4 us with the copy and 13.9, 5000 x 3000 16.9 and 15.1, 17000 x 2000 (16 fragments) 20.3
+    // and 19.1; 28672 x 8192 (112) 59.9 and 65.1.
+    if (n < 16 && plan->dev.geo.panel && plan->dev.geo.N <= 16 && plan->dev.n_irr_waves == 0 && plan->host.n_cols * n >= 8 &&
+        (int64_t)plan->host.win_tile_off.back() * plan->dev.geo.win_rows <= 32 * 256 * 256) {
         *padded = false;
         *width = n;
     }

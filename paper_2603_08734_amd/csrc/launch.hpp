@@ -38,6 +38,7 @@ struct DevicePlan {
     // rows of B that the kernels cannot read as they are pass through this plan-owned buffer of the run width
     // (made where n_user != geo.N)
     int n_user = 0;
+    int64_t n_cols = 0;
     void* b_pad = nullptr;      // binary16 [n_cols][geo.N]
     // optional second stream for the dense-fragment kernel (rsh_plan_opts_t::side_stream)
     void* side = nullptr;       // hipStream_t

@@ -166,12 +166,13 @@ struct __attribute__((packed, aligned(4))) Dwords4 {
 
 // The products of one item, fragments [t_begin, t_end) of window `win`, added to acc + acc2.  RUN: the window's
 // condensed columns are one run of columns that fills whole fragments, so its rows of B need no ids.
-template <int NCH32, int NG, bool RUN, bool RAGGED>
+// NARROW: rows of B of fewer than 16 features, read where they lie; `b_last` is the byte at which the last 16 of B begin.
+template <int NCH32, int NG, bool RUN, bool RAGGED, bool NARROW>
 __device__ __forceinline__ void panel_item(unsigned char* smem, uint32_t win, uint32_t t_begin, uint32_t t_end, uint32_t t0, uint32_t nt,
                                             int32_t col0, const int32_t* __restrict__ tile_colid, const uint32_t* __restrict__ quad0,
                                             const uint4_t* __restrict__ meta, const uint32_t* __restrict__ qoff,
                                             const uint32_t* __restrict__ val, const __half* __restrict__ B, int N, int panel,
-                                            float16_t (&acc)[NCH32], float16_t (&acc2)[NCH32]) {
+                                            uint32_t b_last, float16_t (&acc)[NCH32], float16_t (&acc2)[NCH32]) {
     using Gm = PanelGeom<NCH32, NG>;
     // fragments ahead at which rows of B are requested, and how much earlier their column ids; where a thread
     // holds two pieces of each row (128-row windows at 128 features) more would spill registers
@@ -197,6 +198,8 @@ __device__ __forceinline__ void panel_item(unsigned char* smem, uint32_t win, ui
     // ends with the row, so that nothing behind B is touched, and moved down by whole dwords when it is staged.
     const int f_piece = panel + 8 * piece, over = f_piece < N && f_piece + 8 > N ? (f_piece + 8 - N) / 2 : 0;
     [[maybe_unused]] const bool over1 = over == 1, over2 = over == 2, over3 = over == 3;
+    // NARROW: a piece goes on into the next row, whose features land where none is stored; the last of B are read where they
+    // end with it, and moved down when they are staged.
     const uint32_t ld_byte = (f_piece + 8 <= N ? 2u * (uint32_t)f_piece : RAGGED && over ? 2u * (uint32_t)(N - 8) : 0u) + (RUN ? (uint32_t)row0 * row_bytes : 0u);
     // RUN: the window's columns are one run, a fragment's rows of B follow each other
     const char* Bbytes = reinterpret_cast<const char*>(B) + (RUN ? (size_t)(uint32_t)col0 * row_bytes : 0);
@@ -210,6 +213,7 @@ __device__ __forceinline__ void panel_item(unsigned char* smem, uint32_t win, ui
     uint4_t m_cur, m_nxt, m_req;
     Dwords4 vals[4][2];
     uint4_t breg[4][NLD];
+    [[maybe_unused]] uint32_t moved[4];   // halves that a piece was read too early
     int cid_ring[RUN ? 1 : 4][NLD];
     struct Operands {
         half8_t b[NCH32];
@@ -255,16 +259,36 @@ __device__ __forceinline__ void panel_item(unsigned char* smem, uint32_t win, ui
             for (int j = 0; j < NLD; ++j) cid[j] = tile_colid[(size_t)(t0 + min(f0 + step, last)) * KT + row0 + j * kRowStep];
         }
     };
-    auto issue_b = [&](uint32_t step, const int (&cid)[NLD], uint4_t (&b)[NLD]) {
+    auto issue_b = [&](uint32_t step, const int (&cid)[NLD], uint4_t (&b)[NLD], [[maybe_unused]] int slot) {
+        if constexpr (NARROW) {
+            // threads without a piece that counts all read the first 16 bytes of B: a load at 2-byte alignment takes the
+            // vector memory path nearly four times as long as another
+            static_assert(NLD == 1);
+            const uint32_t row = RUN ? (uint32_t)(col0 + row0) + min(f0 + step, last) * KT : (uint32_t)cid[0];
+            const uint32_t at = tix < Gm::PIECES && f_piece < N ? row * row_bytes + 2u * (uint32_t)f_piece : 0u, from = min(at, b_last);
+            moved[slot] = (at - from) / 2u;
+            b[0] = *reinterpret_cast<const uint4_a2*>(reinterpret_cast<const char*>(B) + from);
+            return;
+        }
         const char* from = RUN ? Bbytes + (size_t)min(f0 + step, last) * (KT * row_bytes) : Bbytes;
 #pragma unroll
         for (int j = 0; j < NLD; ++j) b[j] = *reinterpret_cast<const uint4_a4*>(RUN ? from + (size_t)j * kRowStep * row_bytes + ld_byte : from + ((uint32_t)cid[j] * row_bytes + ld_byte));
     };
-    auto stage_b = [&](const uint4_t (&b)[NLD], int buf) {
+    auto stage_b = [&](const uint4_t (&b)[NLD], int buf, [[maybe_unused]] int slot) {
         _Float16* sb = lds_b + buf * Gm::TILE_HALVES;
 #pragma unroll
         for (int j = 0; j < NLD; ++j) {
             uint4_t x = b[j];
+            if constexpr (NARROW) {
+                const uint32_t by = moved[slot];
+                if (by) {
+                    const uint64_t lo = (uint64_t)x[1] << 32 | x[0], hi = (uint64_t)x[3] << 32 | x[2];
+                    const uint64_t a = by >= 4 ? hi : lo, z = by >= 4 ? 0u : hi;
+                    const uint32_t k = 16u * (by & 3u);
+                    const uint64_t l = k ? a >> k | z << (64u - k) : a, h = z >> k;
+                    x = (uint4_t){(uint32_t)l, (uint32_t)(l >> 32), (uint32_t)h, (uint32_t)(h >> 32)};
+                }
+            }
             if constexpr (RAGGED) {
                 x[0] = over1 ? x[1] : over2 ? x[2] : over3 ? x[3] : x[0];
                 x[1] = over1 ? x[2] : over2 ? x[3] : x[1];
@@ -318,17 +342,17 @@ __device__ __forceinline__ void panel_item(unsigned char* smem, uint32_t win, ui
 #pragma unroll
     for (int d = 0; d < 4; ++d) fetch_colids((uint32_t)d, cid_ring[RUN ? 0 : d]);
 #pragma unroll
-    for (int d = 0; d < (LB < 4 ? LB : 4); ++d) issue_b((uint32_t)d, cid_ring[RUN ? 0 : d], breg[d]);
+    for (int d = 0; d < (LB < 4 ? LB : 4); ++d) issue_b((uint32_t)d, cid_ring[RUN ? 0 : d], breg[d], d);
 #pragma unroll
     for (int d = 0; d < 4; ++d) issue_values(m_cur, d, vals[d]);
     clip_quads(1, m_nxt);
     clip_fragments(0, m_cur);
 #pragma unroll
     for (int d = 4; d < (LB + LC < 8 ? LB + LC : 8); ++d) fetch_colids((uint32_t)d, cid_ring[RUN ? 0 : d & 3]);
-    stage_b(breg[0], 0);
-    stage_b(breg[1], 1);
+    stage_b(breg[0], 0, 0);
+    stage_b(breg[1], 1, 1);
     if constexpr (LB == 5) {
-        issue_b(4, cid_ring[0], breg[0]);
+        issue_b(4, cid_ring[0], breg[0], 0);
         fetch_colids(8, cid_ring[0]);
     }
     block_barrier();
@@ -359,11 +383,11 @@ __device__ __forceinline__ void panel_item(unsigned char* smem, uint32_t win, ui
             } else look_up(m_cur, (k2 / 2) & 3, k2 & 1, sel[k & 1]);
             expand(m_cur, (k1 / 2) & 3, k1 & 1, vals[(k1 / 2) & 3], sel[k1 & 1], op[k1 & 1]);
             if (h == 0) {   // the fragment's values are used up: request those of fragment s + u + 4, and a fragment of B
-                issue_b(s + u + LB, cid_ring[RUN ? 0 : (u + LB) & 3], breg[(u + LB) & 3]);
+                issue_b(s + u + LB, cid_ring[RUN ? 0 : (u + LB) & 3], breg[(u + LB) & 3], (u + LB) & 3);
                 fetch_colids(s + u + LB + LC, cid_ring[RUN ? 0 : (u + LB + LC) & 3]);
                 issue_values(m_nxt, u, vals[u]);
             }
-            if ((k & 3) == 1 || (k & 3) == 2) stage_b(breg[(2 * (k / 4) + 1 + (k & 3)) & 3], (2 * (k / 4) + 1 + (k & 3)) & 3);
+            if ((k & 3) == 1 || (k & 3) == 2) stage_b(breg[(2 * (k / 4) + 1 + (k & 3)) & 3], (2 * (k / 4) + 1 + (k & 3)) & 3, (2 * (k / 4) + 1 + (k & 3)) & 3);
             multiply(op[h]);
             if ((k & 3) == 2) block_barrier();
             __builtin_amdgcn_sched_barrier(0);
@@ -384,13 +408,13 @@ __device__ __forceinline__ void panel_item(unsigned char* smem, uint32_t win, ui
 
 // RAGGED: rows of B end inside a 16-byte piece (N is not a multiple of 8).  Moving the broken piece costs 3 % of
 // the kernel at 128 features, so the other widths have a kernel without it.
-template <int NCH32, int NG, bool RAGGED, class OUT>
+template <int NCH32, int NG, bool RAGGED, class OUT, bool NARROW = false>
 __global__ __launch_bounds__(64 * NG) __attribute__((amdgpu_waves_per_eu(2, NCH32 == 4 ? 2 : 4))) void rsh_panel_kernel(
     const uint4* __restrict__ items, XcdSplit xs, const int32_t* __restrict__ win_row,
     const uint32_t* __restrict__ win_tile_off, const int32_t* __restrict__ win_col0,
     const int32_t* __restrict__ tile_colid, const uint32_t* __restrict__ quad0, const uint4_t* __restrict__ meta,
     const uint32_t* __restrict__ qoff, const uint32_t* __restrict__ val, const __half* __restrict__ B, const OUT out,
-    float* __restrict__ scratch, int N, int feature0, int nv, int ns) {
+    float* __restrict__ scratch, int N, int feature0, int nv, int ns, uint32_t b_last) {
     using Gm = PanelGeom<NCH32, NG>;
     constexpr int P = Gm::P;
     if constexpr (!OUT::kAny) nv = N;
@@ -429,9 +453,9 @@ __global__ __launch_bounds__(64 * NG) __attribute__((amdgpu_waves_per_eu(2, NCH3
     if (t_begin < t_end) {
         const int32_t col0 = win_col0[win];
         if (col0 >= 0)
-            panel_item<NCH32, NG, true, RAGGED>(smem, win, t_begin, t_end, t0, nt, col0, tile_colid, quad0, meta, qoff, val, B, N, panel, acc, acc2);
+            panel_item<NCH32, NG, true, RAGGED, NARROW>(smem, win, t_begin, t_end, t0, nt, col0, tile_colid, quad0, meta, qoff, val, B, N, panel, b_last, acc, acc2);
         else
-            panel_item<NCH32, NG, false, RAGGED>(smem, win, t_begin, t_end, t0, nt, col0, tile_colid, quad0, meta, qoff, val, B, N, panel, acc, acc2);
+            panel_item<NCH32, NG, false, RAGGED, NARROW>(smem, win, t_begin, t_end, t0, nt, col0, tile_colid, quad0, meta, qoff, val, B, N, panel, b_last, acc, acc2);
     }
 
     // ---- output: each group's 32 rows x 32 features take a turn through LDS and leave as whole lines ----
@@ -442,14 +466,14 @@ __global__ __launch_bounds__(64 * NG) __attribute__((amdgpu_waves_per_eu(2, NCH3
         store_block(out, scratch, stage, acc2[c] + acc[c], lane, row, dst == kNoDst ? kNoDst : dst + wv * 32, panel + 32 * c, nv, ns);
 }
 
-template <int NCH32, int NG, bool RAGGED, class OUT>
+template <int NCH32, int NG, bool RAGGED, bool NARROW = false, class OUT>
 void launch_panel_t(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st, int nb, int nv, int feature0, int panels) {
     uint32_t longest = 0;
     for (int x = 0; x < 8; ++x) longest = std::max(longest, d.tile_split.start[x + 1] - d.tile_split.start[x]);
-    hipLaunchKernelGGL((rsh_panel_kernel<NCH32, NG, RAGGED, OUT>), dim3(8u * longest, (unsigned)panels), dim3(64 * NG), 0, st,
+    hipLaunchKernelGGL((rsh_panel_kernel<NCH32, NG, RAGGED, OUT, NARROW>), dim3(8u * longest, (unsigned)panels), dim3(64 * NG), 0, st,
                        (const uint4*)d.tile_item, d.tile_split, d.win_row, d.win_tile_off, d.panel_col0, d.tile_colid,
                        d.panel_quad0, (const uint4_t*)d.panel_meta, d.panel_qoff, d.panel_val, (const __half*)B, out, d.scratch, nb,
-                       feature0, nv, d.geo.N);
+                       feature0, nv, d.geo.N, NARROW ? 2u * ((uint32_t)d.n_cols * (uint32_t)nb - 8u) : 0u);
 }
 template <int NCH32, class OUT>
 int launch_panel_g(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st, int nb, int nv, int feature0, int panels) {
@@ -477,6 +501,13 @@ int launch_panels(const DevicePlan& d, const void* B, const OUT& out, hipStream_
     // 239 (with cut_tall_windows' last round); 128-row windows, panels of 64: 70 features 90.4 and 59.6, 602 features 268.6 and 258.6.
     const int rest = nv % wide, least = nv > wide ? 1 : wide / 2 + 1;
     const int full = nv / wide + (rest >= least);
+    if constexpr (OUT::kAny) {
+        if (nb < 16) {   // rows of B as they lie (check_launch)
+            if (d.geo.panel_groups == 8) launch_panel_t<1, 8, false, true>(d, B, out, st, nb, nv, 0, 1);
+            else launch_panel_t<1, 4, false, true>(d, B, out, st, nb, nv, 0, 1);
+            return RSH_OK;
+        }
+    }
     int rc = RSH_OK;
     if (full > 0) rc = wide == 64 ? launch_panel_g<2>(d, B, out, st, nb, nv, 0, full) : launch_panel_g<4>(d, B, out, st, nb, nv, 0, full);
     if (rc != RSH_OK || rest >= least || rest == 0) return rc;

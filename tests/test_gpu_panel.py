@@ -309,3 +309,46 @@ def test_narrow_rows(rows, opts, N, fused, odd):
     assert not np.isnan(got).any()
     assert np.all(np.abs(got - C_ref) <= bound)
     plan.destroy()
+
+
+# Tall windows read rows of fewer than 16 features where they lie: runs of columns and gathered ones, up to the last row of B,
+# whose eight features are read where they end with it; 9 columns of 1 feature are hardly more than one piece, 7 less.  An empty
+# row makes a residual part, beside which B is copied.
+@pytest.mark.parametrize("fused,odd", [(False, 0), (False, 1), (True, 1)])
+@pytest.mark.parametrize("N", [1, 2, 3, 7, 8, 9, 11, 15])
+@pytest.mark.parametrize("window_rows", [128, 256])
+@pytest.mark.parametrize("cols,density,empty", [(400, 0.3, False), (1500, 0.02, False), (9, 1.0, False), (7, 1.0, False), (130, 0.3, True)])
+def test_tall_windows_of_narrow_rows(cols, density, empty, window_rows, N, fused, odd):
+    import torch
+    from paper_2603_08734_amd import Plan
+    rng = np.random.default_rng(9)
+    cells = rng.random((300, cols)) < density
+    cells[:, -1] = True
+    if empty:
+        cells[17] = False
+    r, c = np.nonzero(cells)
+    A = from_coo(r, c, rng.standard_normal(r.size), 300, cols)
+    print(f"case tall narrow cols={cols} W={window_rows} N={N} fused={fused} odd={odd}", flush=True)
+    plan = Plan(A.row_ptr, A.col_idx, A.val, A.n_cols, N, window_rows=window_rows, force_path=2)
+    B = dense_B(A.n_cols, N, "normal", seed=N)
+    Bd = torch.empty(B.size + odd, dtype=torch.float16, device="cuda")[odd:].view(A.n_cols, N)
+    Bd.copy_(torch.from_numpy(B.view(np.float16) if B.dtype != np.float16 else B))
+    C_ref, S, _ = oracle.spmm(A.row_ptr, A.col_idx, A.val, B)
+    pad = 64
+    flat = torch.full((300 * N + 2 * pad,), float("nan"), dtype=torch.float16 if fused else torch.float32, device="cuda")
+    C = flat[pad + odd:pad + odd + 300 * N].view(300, N)
+    bound = 1e-4 * S
+    if fused:
+        bias = torch.linspace(-1, 1, N, device="cuda")
+        plan.spmm_f16(Bd, C, bias, relu=True)
+        C_ref = np.maximum(C_ref + bias.cpu().numpy().astype(np.float64), 0.0)
+        # the fp32 bound, the addition of the bias, one rounding to binary16
+        bound = bound + 2.0 ** -24 * np.abs(C_ref) + 2.0 ** -11 * np.abs(C_ref) * 1.001 + 2.0 ** -24
+    else:
+        plan.spmm(Bd, C)
+    torch.cuda.synchronize()
+    assert bool(torch.isnan(flat[:pad + odd]).all()) and bool(torch.isnan(flat[pad + odd + 300 * N:]).all()), "stores outside C"
+    got = C.cpu().numpy().astype(np.float64)
+    assert not np.isnan(got).any()
+    assert np.all(np.abs(got - C_ref) <= bound)
+    plan.destroy()
