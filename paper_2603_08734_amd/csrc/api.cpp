@@ -100,11 +100,14 @@ struct Uploader {
 };
 
 template <class T>
-int upload_array(Uploader& up, const std::vector<T>& h, T** d) {
+int upload_array(Uploader& up, const T* h, size_t n, T** d) {
     *d = nullptr;
-    const size_t bytes = (h.size() ? h.size() : 1) * sizeof(T);
-    if (!hip_ok(hipMalloc((void**)d, bytes))) return RSH_ERR_OOM;
-    return h.empty() ? RSH_OK : up.copy(*d, h.data(), h.size() * sizeof(T));
+    if (!hip_ok(hipMalloc((void**)d, (n ? n : 1) * sizeof(T)))) return RSH_ERR_OOM;
+    return n == 0 ? RSH_OK : up.copy(*d, h, n * sizeof(T));
+}
+template <class T>
+int upload_array(Uploader& up, const std::vector<T>& h, T** d) {
+    return upload_array(up, h.data(), h.size(), d);
 }
 
 void free_device(rsh::DevicePlan& d) {
@@ -196,8 +199,8 @@ int upload_plan(rsh_plan& p) {
     if ((rc = upload_array(up, h.panel_col0, &d.panel_col0))) return rc;
     if (h.geo.panel && (rc = upload_panel_units(up, h, d))) return rc;
     if (h.geo.narrow) {
-        if ((rc = upload_array(up, h.narrow_col, &d.irr_col))) return rc;
-        if ((rc = upload_array(up, h.narrow_val, &d.irr_val))) return rc;
+        if ((rc = upload_array(up, h.narrow_col.get(), h.narrow_slots, &d.irr_col))) return rc;
+        if ((rc = upload_array(up, h.narrow_val.get(), h.narrow_slots, &d.irr_val))) return rc;
         if ((rc = upload_array(up, h.narrow_wave, &d.irr_wave))) return rc;
         if ((rc = upload_array(up, h.narrow_seg, &d.narrow_seg))) return rc;
     } else {
@@ -222,8 +225,8 @@ int upload_plan(rsh_plan& p) {
     }
     if ((rc = up.close())) return rc;   // every copy has landed
     for (auto* v : {&h.narrow_wave, &h.narrow_seg}) std::vector<uint32_t>().swap(*v);
-    std::vector<int32_t>().swap(h.narrow_col);
-    std::vector<uint16_t>().swap(h.narrow_val);
+    h.narrow_col.reset();
+    h.narrow_val.reset();
     if (!hip_ok(hipGetDevice(&p.device))) return RSH_ERR_HIP;
     p.uploaded = true;
     return RSH_OK;

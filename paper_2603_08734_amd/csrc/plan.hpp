@@ -1,6 +1,7 @@
 // Internal plan structures shared by the host planner, the C ABI and the launchers.
 #pragma once
 #include <cstdint>
+#include <memory>
 #include <vector>
 
 #include "../../include/rsh_spmm.h"
@@ -77,8 +78,9 @@ struct HostPlan {
     std::vector<uint32_t> irr_wave;  // 4 per wave
     std::vector<int32_t> irr_row;    // row ids named by short-row and zero-row waves
     // the same work as narrow.hpp reads it (geo.narrow); what the device holds instead of the arrays above
-    std::vector<int32_t> narrow_col;
-    std::vector<uint16_t> narrow_val;
+    std::unique_ptr<int32_t[]> narrow_col;
+    std::unique_ptr<uint16_t[]> narrow_val;
+    size_t narrow_slots = 0;          // of both
     std::vector<uint32_t> narrow_wave, narrow_seg;   // 4 per wave, 2 per segment
     XcdSplit narrow_split;
     bool narrow_in_order = false;   // rows run in the processing order, not by id

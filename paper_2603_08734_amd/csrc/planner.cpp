@@ -1312,7 +1312,7 @@ int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int thr
     st.n_scratch_slots = slots;
     st.sum_window_cols = sum_cols;
     const int64_t panel_bytes = panel_device_bytes(plan);
-    const int64_t residual_bytes = geo.narrow ? (int64_t)(plan.narrow_col.size() * 4 + plan.narrow_val.size() * 2 + plan.narrow_wave.size() * 4 + plan.narrow_seg.size() * 4)
+    const int64_t residual_bytes = geo.narrow ? (int64_t)(plan.narrow_slots * 6 + plan.narrow_wave.size() * 4 + plan.narrow_seg.size() * 4)
                                               : (int64_t)(plan.irr_col.size() * 4 + plan.irr_val.size() * 2 + plan.irr_wave.size() * 4 + plan.irr_row.size() * 4);
     st.plan_bytes = panel_bytes +
                     (int64_t)(plan.win_row.size() * 4 + plan.win_tile_off.size() * 4 + plan.tile_colid.size() * 4 +
@@ -1472,47 +1472,62 @@ void pack_narrow(HostPlan& plan, int threads) {
     order.reserve(direct.size());
     plan.narrow_wave.clear();
     plan.narrow_seg.clear();
-    std::vector<uint32_t> wave_seg;   // first segment of every wave, in `order`
-    uint64_t first = 0;
-    const auto emit = [&](size_t b, size_t e) {   // segments [b, e) of `order`: by lanes, then length, descending
-        std::stable_sort(order.begin() + (int64_t)b, order.begin() + (int64_t)e, [&](const Segment& p, const Segment& q) { return len_of(p) > len_of(q); });
-        for (size_t i = b; i < e;) {
-            const uint32_t t = log_lanes(len_of(order[i])), T = 1u << t;
-            size_t j = i;
-            uint32_t shortest = ~0u;
-            while (j < e && j - i < (S >> t) && log_lanes(len_of(order[j])) == t) shortest = std::min(shortest, len_of(order[j])), ++j;
-            const uint32_t steps = (len_of(order[i]) + T - 1) >> t, pairs = (steps + 1) / 2, full = std::min<uint32_t>(shortest >> t, 0xffffu);
-            wave_seg.push_back((uint32_t)i);
-            plan.narrow_wave.insert(plan.narrow_wave.end(), {(uint32_t)first, steps, t | (uint32_t)(j - i) << 8 | full << 16, (uint32_t)i});
-            first += (uint64_t)pairs * S;
-            i = j;
-        }
-    };
+    // blocks of segments: the partial sums of an XCD, then its run of rows in pieces of block_rows
+    std::vector<size_t> block_at{0};
+    size_t xcd_block[9];
     size_t at = 0;
     for (int x = 0; x < 8; ++x) {
-        plan.narrow_split.start[x] = (uint32_t)(plan.narrow_wave.size() / 4);
-        const size_t b = order.size();
+        xcd_block[x] = block_at.size() - 1;
         order.insert(order.end(), partial[x].begin(), partial[x].end());
         for (const Segment& s : partial[x]) run += len_of(s) + kShare;
-        emit(b, order.size());
+        block_at.push_back(order.size());
         while (at < direct.size() && (x == 7 || run * 8 < cost * (uint64_t)(x + 1))) {
             const size_t block = order.size();
             while (at < direct.size() && (int64_t)(order.size() - block) < block_rows && (x == 7 || run * 8 < cost * (uint64_t)(x + 1))) {
                 run += len_of(direct[at]) + kShare;
                 order.push_back(direct[at++]);
             }
-            emit(block, order.size());
+            block_at.push_back(order.size());
         }
+    }
+    xcd_block[8] = block_at.size() - 1;
+    parallel_dynamic((int64_t)xcd_block[8], threads, 16, [&](int64_t b, int64_t e, int) {
+        for (int64_t i = b; i < e; ++i)
+            std::stable_sort(order.begin() + (int64_t)block_at[(size_t)i], order.begin() + (int64_t)block_at[(size_t)i + 1],
+                             [&](const Segment& p, const Segment& q) { return len_of(p) > len_of(q); });
+    });
+    uint64_t first = 0;
+    for (int x = 0; x < 8; ++x) {
+        plan.narrow_split.start[x] = (uint32_t)(plan.narrow_wave.size() / 4);
+        for (size_t block = xcd_block[x]; block < xcd_block[x + 1]; ++block)
+            for (size_t i = block_at[block], e = block_at[block + 1]; i < e;) {
+                const uint32_t t = log_lanes(len_of(order[i])), T = 1u << t;
+                size_t j = i;
+                uint32_t shortest = ~0u;
+                while (j < e && j - i < (S >> t) && log_lanes(len_of(order[j])) == t) shortest = std::min(shortest, len_of(order[j])), ++j;
+                const uint32_t steps = (len_of(order[i]) + T - 1) >> t, pairs = (steps + 1) / 2, full = std::min<uint32_t>(shortest >> t, 0xffffu);
+                plan.narrow_wave.insert(plan.narrow_wave.end(), {(uint32_t)first, steps, t | (uint32_t)(j - i) << 8 | full << 16, (uint32_t)i});
+                first += (uint64_t)pairs * S;
+                i = j;
+            }
     }
     plan.narrow_split.start[8] = (uint32_t)(plan.narrow_wave.size() / 4);
     plan.narrow_seg.resize(2 * order.size());
-    const size_t slots = 2 * ((size_t)first + 64 * (size_t)kNarrowAhead);
-    plan.narrow_col.assign(slots, 0);
-    plan.narrow_val.assign(slots, 0);
-    parallel_dynamic((int64_t)wave_seg.size(), threads, 256, [&](int64_t b, int64_t e, int) {
+    // every wave clears and fills its own slots: of memory that is touched first here, most of the time goes into that
+    const size_t used = 2 * (size_t)first;
+    plan.narrow_slots = used + 2 * 64 * (size_t)kNarrowAhead;
+    plan.narrow_col.reset(new int32_t[plan.narrow_slots]);
+    plan.narrow_val.reset(new uint16_t[plan.narrow_slots]);
+    std::fill(&plan.narrow_col[used], &plan.narrow_col[0] + plan.narrow_slots, 0);
+    std::fill(&plan.narrow_val[used], &plan.narrow_val[0] + plan.narrow_slots, (uint16_t)0);
+    const int64_t n_waves = (int64_t)plan.narrow_wave.size() / 4;
+    parallel_dynamic(n_waves, threads, 256, [&](int64_t b, int64_t e, int) {
         for (int64_t w = b; w < e; ++w) {
             const uint32_t* d = &plan.narrow_wave[4 * (size_t)w];
             const uint32_t t = d[2] & 0xffu, n = (d[2] >> 8) & 0xffu;
+            const size_t mine = 2 * (size_t)d[0], slots = 2 * (size_t)S * ((d[1] + 1) / 2);
+            std::fill(&plan.narrow_col[mine], &plan.narrow_col[0] + mine + slots, 0);
+            std::fill(&plan.narrow_val[mine], &plan.narrow_val[0] + mine + slots, (uint16_t)0);
             for (uint32_t k = 0; k < n; ++k) {
                 const Segment& s = order[(size_t)d[3] + k];
                 plan.narrow_seg[2 * ((size_t)d[3] + k)] = s.dst;
