@@ -173,7 +173,10 @@ def main() -> int:
     # 128 features where one cell in sixteen is stored
     wide = st["window_rows"] == 256 and N > 128 and st["nnz_tile"] * 16 >= st["n_tiles"] * 32 * 256
     tile_kernel = "rsh_wide_kernel" if wide else "rsh_panel_kernel" if st["window_rows"] >= 128 else "rsh_tile_kernel"
-    kernel_name = "rsh_irregular_kernel" if dominant == "irregular" else tile_kernel
+    # residual rows of few features: lanes own or share rows of B (power-law rows of medium length in plans of 2^18 entries)
+    shared = (N <= 48 or N == 64) and st["nnz_irregular"] >= 1 << 18
+    residual_kernel = "rsh_narrow_kernel" if N <= 16 else "rsh_shared_kernel" if shared else "rsh_irregular_kernel"
+    kernel_name = residual_kernel if dominant == "irregular" else tile_kernel
     if dominant == "irregular":
         alg_bytes = st["irregular_part_bytes"] + 2 * N * st["cols_irregular"] + 4 * N * st["rows_irregular"]
     else:

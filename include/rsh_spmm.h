@@ -62,7 +62,8 @@ typedef struct {
                              windows (a sample of them) keeps the merged windows' distinct columns within
                              0.6 of the sum                                                           */
     int32_t tile_k;       /* K, condensed columns per fragment: 16 (v_mfma_f32_16x16x16_f16) or 32
-                             (v_mfma_f32_16x16x32_f16); 0 (default) = 16 for 16-row windows, else 32;
+                             (v_mfma_f32_16x16x32_f16); 0 (default) = 16 for 16-row windows of a run width above 16,
+                             else 32;
                              windows of 128 or 256 rows always take 32 (two K steps of
                              v_mfma_f32_32x32x16_f16)                                                 */
     int32_t tau_nnz;      /* Algorithm 1 row-length threshold; -1 = estimate from the matrix     */
