@@ -375,6 +375,15 @@ int rsh_plan_array(const rsh_plan_t *plan, int32_t which, const void **ptr, int6
 /* Number of lane teams in one wave of the irregular kernel for this plan's N (64 / lanes per team). */
 int rsh_plan_teams_per_wave(const rsh_plan_t *plan, int32_t *teams);
 
+/* Which kernels a product of this plan runs.  cells_written: 1 = the windows (of 256 rows) run on cells written out on the
+ * device, 0 = on their packed entries.  row_lanes: lanes that share a row of B in the residual part: 1 (up to 16 features),
+ * 4 or 8; 0 = teams of lanes share the rows of a wave (rsh_plan_teams_per_wave). */
+int rsh_plan_kernels(const rsh_plan_t *plan, int32_t *cells_written, int32_t *row_lanes);
+
+/* How a product with operands at these addresses reads B (nothing is read or launched; host-only plans answer too):
+ * copied = 1: through the plan's buffer, else in place; width: features of the rows that the kernels read. */
+int rsh_plan_operand(const rsh_plan_t *plan, const void *B_dev, const void *C_dev, int32_t *copied, int32_t *width);
+
 /* sizeof(rsh_plan_opts_t), sizeof(rsh_plan_stats_t) as compiled into the library, so that a
  * binding can check its own struct declarations. */
 int rsh_struct_sizes(int32_t *opts_bytes, int32_t *stats_bytes);

@@ -35,6 +35,7 @@ EXPORTED_SYMBOLS = [
     "rsh_plan_opts_default", "rsh_plan_create", "rsh_spmm", "rsh_spmm_noalloc", "rsh_spmm_f16", "rsh_spmm_profile",
     "rsh_dense_forward", "rsh_dense_backward", "rsh_act_backward", "rsh_copy_probe", "rsh_plan_destroy", "rsh_plan_stats",
     "rsh_plan_decode", "rsh_plan_row_order", "rsh_reorder_knn", "rsh_plan_array", "rsh_plan_teams_per_wave",
+    "rsh_plan_kernels", "rsh_plan_operand",
     "rsh_struct_sizes", "rsh_status_string", "rsh_last_hip_error",
 ]
 
@@ -125,6 +126,8 @@ def lib() -> ctypes.CDLL:
         L.rsh_reorder_knn.argtypes = [ctypes.POINTER(rsh_csr_t), ctypes.POINTER(rsh_plan_opts_t), vp, vp]
         L.rsh_plan_array.argtypes = [vp, i32, ctypes.POINTER(vp), i64p]
         L.rsh_plan_teams_per_wave.argtypes = [vp, ctypes.POINTER(i32)]
+        L.rsh_plan_kernels.argtypes = [vp, ctypes.POINTER(i32), ctypes.POINTER(i32)]
+        L.rsh_plan_operand.argtypes = [vp, vp, vp, ctypes.POINTER(i32), ctypes.POINTER(i32)]
         L.rsh_struct_sizes.argtypes = [ctypes.POINTER(i32), ctypes.POINTER(i32)]
         L.rsh_status_string.argtypes = [ctypes.c_int]
         L.rsh_status_string.restype = ctypes.c_char_p
@@ -333,6 +336,19 @@ class Plan:
         t = ctypes.c_int32()
         _check(lib().rsh_plan_teams_per_wave(self._h, ctypes.byref(t)))
         return t.value
+
+    def kernels(self) -> dict:
+        """Which kernels the plan's products run (rsh_plan_kernels)."""
+        cells, lanes = ctypes.c_int32(), ctypes.c_int32()
+        _check(lib().rsh_plan_kernels(self._h, ctypes.byref(cells), ctypes.byref(lanes)))
+        return {"cells_written": bool(cells.value), "row_lanes": lanes.value}
+
+    def operand(self, b_address: int, c_address: int):
+        """(B is copied first, features of the rows that the kernels read) of a product with operands at these addresses
+        (rsh_plan_operand)."""
+        copied, width = ctypes.c_int32(), ctypes.c_int32()
+        _check(lib().rsh_plan_operand(self._h, ctypes.c_void_p(b_address), ctypes.c_void_p(c_address), ctypes.byref(copied), ctypes.byref(width)))
+        return bool(copied.value), width.value
 
     def destroy(self) -> None:
         if getattr(self, "_h", None) is not None and self._h.value:

@@ -427,10 +427,39 @@ int rsh_plan_create(const rsh_csr_t* csr, int32_t N, const rsh_plan_opts_t* opts
 
 namespace {
 
-// Common checks of the launch entry points; *padded tells whether B passes through the plan's buffer of the run
-// width (then B, C and bias need their element's alignment only), *width the features of the rows the kernels read.
-// The kernels read rows of any even number of features from 16 on at 4-byte aligned addresses; what is left for
-// the copy is odd widths, widths below 16, a run width the caller chose and operands aligned to less.
+// Whether a product on operands at these addresses copies B into the plan's buffer first (then B, C and bias need their
+// element's alignment only), and *width, the features of the rows that the kernels read.  The kernels read rows of any even
+// number of features from 16 on at 4-byte aligned addresses, and some plans of fewer; what is left for the copy is odd widths,
+// other widths below 16, a run width the caller chose and operands aligned to less.
+bool copies_operand(const rsh::HostPlan& h, uintptr_t B, uintptr_t C, int* width) {
+    const int n = h.n_user;
+    bool padded = n != h.geo.N;
+    *width = h.geo.N;
+    if (padded && n >= 16 && n % 2 == 0 && h.geo.N == auto_run_width(n) && !((B | C) & 3u)) {
+        padded = false;
+        *width = n;
+    }
+    // Tall windows without residual rows beside them read rows of fewer than 16 features where they lie (panel.hpp).  That
+    // saves a launch and costs the loop 0.08 us per fragment of a workgroup, so not beyond 32 fragments per compute unit: weights
+    // of 1024 x 1024, 5 features, 15.4 us with the copy and 13.9, 5000 x 3000 16.9 and 15.1, 17000 x 2000 (16 fragments) 20.3
+    // and 19.1; 28672 x 8192 (112) 59.9 and 65.1.
+    if (n < 16 && h.geo.panel && h.geo.N <= 16 && h.irr_wave.empty() && h.n_cols * n >= 8 &&
+        (int64_t)h.win_tile_off.back() * h.geo.win_rows <= 32 * 256 * 256) {
+        padded = false;
+        *width = n;
+    }
+    // Without windows rows whose lanes own them (narrow.hpp) are read at the next power of two: as they are where that is
+    // their width and they are aligned to it.  Lanes that share a row, as at a chosen run width above 16, read eight features
+    // each and need the whole of it.
+    if (n < rsh::kNarrow && h.geo.narrow == 1 && h.tile_item.empty()) {
+        const int wide = rsh::narrow_width(n);
+        padded = wide != n || (B & (uintptr_t)(2 * std::min(wide, 8) - 1));
+        *width = padded ? std::max(4, wide) : n;
+    }
+    return padded;
+}
+
+// Common checks of the launch entry points; *padded and *width as copies_operand has them.
 int check_launch(const rsh_plan_t* plan, const void* B, const void* C, const void* bias, int c_elem, bool* padded, int* width) {
     if (!plan) return RSH_ERR_NULL;
     if (!plan->uploaded) return RSH_ERR_NOT_UPLOADED;
@@ -446,26 +475,7 @@ int check_launch(const rsh_plan_t* plan, const void* B, const void* C, const voi
     if (!C || (!B && (plan->host.nnz > 0 || (*padded && plan->host.n_cols > 0)))) return RSH_ERR_NULL;
     const uintptr_t mb = *padded ? 1u : 15u, mc = *padded ? (uintptr_t)c_elem - 1u : 15u, mbias = *padded ? 3u : 15u;
     if (((uintptr_t)B & mb) || ((uintptr_t)C & mc) || ((uintptr_t)bias & mbias)) return RSH_ERR_BAD_OPTION;
-    if (*padded && n >= 16 && n % 2 == 0 && plan->dev.geo.N == auto_run_width(n) && !(((uintptr_t)B | (uintptr_t)C) & 3u)) {
-        *padded = false;
-        *width = n;
-    }
-    // Tall windows without residual rows beside them read rows of fewer than 16 features where they lie (panel.hpp).  That
-    // saves a launch and costs the loop 0.08 us per fragment of a workgroup, so not beyond 32 fragments per compute unit: weights
-    // of 1024 x 1024, 5 features, 15.4 us with the copy and 13.9, 5000 x 3000 16.9 and 15.1, 17000 x 2000 (16 fragments) 20.3
-    // and 19.1; 28672 x 8192 (112) 59.9 and 65.1.
-    if (n < 16 && plan->dev.geo.panel && plan->dev.geo.N <= 16 && plan->dev.n_irr_waves == 0 && plan->host.n_cols * n >= 8 &&
-        (int64_t)plan->host.win_tile_off.back() * plan->dev.geo.win_rows <= 32 * 256 * 256) {
-        *padded = false;
-        *width = n;
-    }
-    // Without windows rows of up to 16 features are read at the next power of two (narrow.hpp): as they are where that is
-    // their width and they are aligned to it
-    if (n < rsh::kNarrow && plan->dev.geo.narrow && plan->dev.n_tile_items == 0) {
-        const int wide = rsh::narrow_width(n);
-        *padded = wide != n || ((uintptr_t)B & (uintptr_t)(2 * std::min(wide, 8) - 1));
-        *width = *padded ? std::max(4, wide) : n;
-    }
+    *padded = copies_operand(plan->host, (uintptr_t)B, (uintptr_t)C, width);
     return RSH_OK;
 }
 
@@ -698,6 +708,19 @@ int rsh_plan_array(const rsh_plan_t* plan, int32_t which, const void** ptr, int6
         default: return RSH_ERR_BAD_OPTION;
     }
 #undef RSH_CASE
+}
+
+int rsh_plan_kernels(const rsh_plan_t* plan, int32_t* cells_written, int32_t* row_lanes) {
+    if (!plan || !cells_written || !row_lanes) return RSH_ERR_NULL;
+    *cells_written = plan->host.geo.wide;
+    *row_lanes = plan->host.geo.narrow;
+    return RSH_OK;
+}
+
+int rsh_plan_operand(const rsh_plan_t* plan, const void* B_dev, const void* C_dev, int32_t* copied, int32_t* width) {
+    if (!plan || !copied || !width) return RSH_ERR_NULL;
+    *copied = copies_operand(plan->host, (uintptr_t)B_dev, (uintptr_t)C_dev, width) ? 1 : 0;
+    return RSH_OK;
 }
 
 int rsh_plan_teams_per_wave(const rsh_plan_t* plan, int32_t* teams) {

@@ -352,3 +352,30 @@ def test_tall_windows_of_narrow_rows(cols, density, empty, window_rows, N, fused
     assert not np.isnan(got).any()
     assert np.all(np.abs(got - C_ref) <= bound)
     plan.destroy()
+
+
+# A chosen run width above 16 beside few features: B is copied to it, and lanes that share a row read the copy.
+@pytest.mark.parametrize("run_width", [32, 64])
+@pytest.mark.parametrize("N", [1, 2, 3, 4, 7])
+def test_chosen_run_width_of_few_features(N, run_width):
+    import torch
+    from paper_2603_08734_amd import Plan
+    rng = np.random.default_rng(4)
+    rows, cols = 24000, 20000
+    r = np.repeat(np.arange(rows), 12)
+    A = from_coo(r, 1600 * np.tile(np.arange(12), rows) + rng.integers(0, 1600, r.size), rng.standard_normal(r.size), rows, cols)
+    print(f"case run width {run_width} N={N}", flush=True)
+    plan = Plan(A.row_ptr, A.col_idx, A.val, cols, N, run_width=run_width, force_path=1)
+    assert plan.kernels()["row_lanes"] == 4
+    B = dense_B(cols, N, "normal", seed=N)
+    Bd = torch.from_numpy(B.view(np.int16)).cuda().view(torch.float16)
+    assert plan.operand(Bd.data_ptr(), 4096) == (True, run_width)
+    pad = 64
+    flat = torch.full((rows * N + 2 * pad,), float("nan"), dtype=torch.float32, device="cuda")
+    C = flat[pad:pad + rows * N].view(rows, N)
+    plan.spmm(Bd, C)
+    torch.cuda.synchronize()
+    C_ref, S, _ = oracle.spmm(A.row_ptr, A.col_idx, A.val, B)
+    assert bool(torch.isnan(flat[:pad]).all()) and bool(torch.isnan(flat[pad + rows * N:]).all()), "stores outside C"
+    assert np.all(np.abs(C.cpu().numpy().astype(np.float64) - C_ref) <= 1e-4 * S)
+    plan.destroy()

@@ -645,3 +645,37 @@ def test_windows_of_narrow_rows(N, n_cols, neighbours, windows):
     row_ptr, col_idx, val, _ = p.decode()
     assert np.array_equal(row_ptr, A.row_ptr) and np.array_equal(col_idx, A.col_idx) and np.array_equal(val, A.val.view(np.uint16))
     assert host_plan(A, 8, window_rows=16, reorder=0).stats()["nnz_tile"] > 0      # windows that the caller asks for stay
+
+
+# Rows of medium length without windows, enough of them for lanes that share a row of B (narrow.hpp).  Whatever run width the
+# caller chose, a lane's eight features lie inside the row that the kernels read; lanes that own rows read a power of two of
+# features, in place only where B is aligned to that.
+@pytest.mark.parametrize("run_width", [0, 16, 32, 48, 64])
+def test_lanes_read_inside_the_rows_of_b(run_width):
+    rng = np.random.default_rng(4)
+    rows = 24000
+    r = np.repeat(np.arange(rows), 12)
+    c = 1600 * np.tile(np.arange(12), rows) + rng.integers(0, 1600, r.size)     # one column out of each of 12 ranges
+    A = from_coo(r, c, rng.standard_normal(r.size), rows, 20000)
+    lanes_seen = set()
+    for N in range(1, 17):
+        p = host_plan(A, N, run_width=run_width, force_path=1, reorder=0)
+        lanes = p.kernels()["row_lanes"]
+        lanes_seen.add(lanes)
+        for offset in (0, 2, 4, 8) if N < 16 else (0,):     # rows of 16 features have to be aligned unless they are copied
+            copied, width = p.operand(4096 + offset, 8192)
+            assert width >= N and (copied or width == N)
+            if lanes == 1:
+                assert width & (width - 1) == 0 and (copied or offset % min(2 * width, 16) == 0)
+            else:
+                assert lanes and A.nnz >= 1 << 18
+                first = [min(8 * t, width - 8) for t in range(lanes)]
+                assert min(first) >= 0 and max(first) + 8 <= width and copied == (N != run_width)
+        p.destroy()
+    assert lanes_seen == ({1} if run_width <= 16 else {4})
+
+
+def test_operand_of_an_empty_plan():
+    A = from_coo(np.zeros(0, int), np.zeros(0, int), np.zeros(0), 0, 40)
+    for N in (3, 16):
+        assert host_plan(A, N, window_rows=256).operand(4096, 4096)[1] >= N
