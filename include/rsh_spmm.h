@@ -376,8 +376,8 @@ int rsh_plan_array(const rsh_plan_t *plan, int32_t which, const void **ptr, int6
 int rsh_plan_teams_per_wave(const rsh_plan_t *plan, int32_t *teams);
 
 /* Which kernels a product of this plan runs.  cells_written: 1 = the windows (of 256 rows) run on cells written out on the
- * device, 0 = on their packed entries.  row_lanes: lanes that share a row of B in the residual part: 1 (up to 16 features),
- * 4 or 8; 0 = teams of lanes share the rows of a wave (rsh_plan_teams_per_wave). */
+ * device, 0 = on their packed entries.  row_lanes: lanes that share a row of B in the residual part: 1 (up to 8 features),
+ * 2 (up to 16), 4 or 8; 0 = teams of lanes share the rows of a wave (rsh_plan_teams_per_wave). */
 int rsh_plan_kernels(const rsh_plan_t *plan, int32_t *cells_written, int32_t *row_lanes);
 
 /* How a product with operands at these addresses reads B (nothing is read or launched; host-only plans answer too):

@@ -44,6 +44,10 @@ __device__ __forceinline__ int shfl_i32(int v, int src_lane) { return __builtin_
 __device__ __forceinline__ float shfl_f32(float v, int src_lane) {
     return __int_as_float(__builtin_amdgcn_ds_bpermute(src_lane << 2, __float_as_int(v)));
 }
+__device__ __forceinline__ double shfl_f64(double v, int src_lane) {
+    const uint2_t w = __builtin_bit_cast(uint2_t, v);
+    return __builtin_bit_cast(double, (uint2_t){(uint32_t)shfl_i32((int)w[0], src_lane), (uint32_t)shfl_i32((int)w[1], src_lane)});
+}
 
 // Value held by lane (l ^ 8): rotation by 8 inside each row of 16 lanes.
 __device__ __forceinline__ int swap_lane8(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x128, 0xf, 0xf, false); }

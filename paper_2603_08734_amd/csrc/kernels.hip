@@ -6,7 +6,8 @@
 //   rsh_wide_kernel      the same for tall windows and many features (wide.hpp)
 //   rsh_irregular_kernel residual rows (Section 3.3.2, "CUDA path"), teams of lanes own
 //                        feature columns, long rows arrive as bounded slices (Section 3.3.3)
-//   rsh_narrow_kernel    residual rows of at most 16 features (narrow.hpp)
+//   rsh_narrow_kernel, rsh_shared_kernel   residual rows of at most 8 features, and of more where lanes_per_row says so
+//                        (narrow.hpp)
 //   rsh_combine_kernel   fixed-order sum of the partial results of split windows / rows
 //   rsh_sum_narrow_kernel   the same for rows of up to 16 features, several rows per wave
 //   rsh_fragment_even_kernel, rsh_residual_even_kernel, rsh_sum_even_kernel   the first, third (its partial panel) and

@@ -1,19 +1,22 @@
-// Residual rows of few features: lanes own rows, or share them in fours or eights.  Included by kernels.hip.
+// Residual rows of few features: lanes own rows, or share them in pairs, fours or eights.  Included by kernels.hip.
 //
 // The residual kernel gives a row of B to a team of lanes, eight features each; of rows this short two lanes do, and what
 // they gather, 32 bytes, is less than what tells them where (a wave's 32 teams fetch their column ids two at a time from 32
-// places).  Here a lane takes an entry's whole row of B and adds it to sums of its own:
-//   * T = 1 .. 64 lanes share a row (or a slice of a long one) and are added up once at its end; rows of up to 24 entries,
-//     in a large matrix, have a lane each and need no addition across lanes at all.
+// places).  Here, up to 8 features, a lane takes an entry's whole row of B and adds it to sums of its own; of more features
+// two, four or eight lanes share it (rsh_shared_kernel):
+//   * T = 1 .. 64 places (lanes, or groups of lanes that share a row of B) share a row (or a slice of a long one) and are added
+//     up once at its end; rows of up to 32 entries, in a large matrix, have a place each and need no addition across lanes at all.
 //   * Column ids and values lie in the order in which the lanes take them (pack_narrow in planner.cpp), in pairs of
 //     entries: one 8-byte and one 4-byte load per lane for two entries, whole lines per wave.
-//   * Rows of B are read at the next power of two of their width NP: one load per entry up to 8 features.  Rows of
+//   * Rows of B of up to 8 features are read at the next power of two of their width NP: one load per entry.  Rows of
 //     that width are read where they lie, so that a row of one feature takes 2 bytes of cache and not 32.
-//   * Rows of C leave by ordinary stores (524288 rows of communities, 8 features: 87 us with streaming ones, 79 so).
+//   * Rows of C of up to 8 features leave by ordinary stores (524288 rows of communities, 8 features: 87 us with streaming ones,
+//     79 so).
 // What bounds it: a gather is a request of its own to the L2, 32.4 M of them for the power-law graph of 2^20 vertices, whose
 // product takes 152 us at one feature (the 194 MB of ids and values alone would take 40) and 222 at 8, 13 us more in the
-// combine pass.  Teams of two lanes and this kernel, us: that graph, 1 feature 338 and 168, 8 343 and 236, 16 329 and 313; of
-// 2^17 vertices 45.2 and 19.9, 45.1 and 26.3, 40.8 and 34.5; 150000 rows of 12 entries 47.1 and 12.8, 46.1 and 13.3, 41.4 and 23.5.
+// combine pass.  Teams of two lanes and this kernel, us: that graph, 1 feature 338 and 168, 8 343 and 236; of 2^19 vertices 16 145
+// and 109 (133 with a lane to a row of 16 features); of 2^17 1 45.2 and 19.9, 8 45.1 and 26.3; 150000 rows of 12 entries 1
+// 53.9 and 12.9, 8 53.4 and 14.3, 16 44.6 and 16.4 (22.4).
 // A lane that takes up to twice 16 entries is better than one that is helped from 24 on (stencil 80^3, 8 features, 27.8 and 31.2).
 #pragma once
 #include "device.hpp"
@@ -38,22 +41,37 @@ __device__ __forceinline__ NarrowRow<NP> load_narrow(const char* p) {
         const uint2_t v = *reinterpret_cast<const uint2_t*>(p);
         r.w[0] = v[0], r.w[1] = v[1];
     } else {
+        static_assert(NP == 8);
+        const uint4_t v = *reinterpret_cast<const uint4_t*>(p);
 #pragma unroll
-        for (int i = 0; i < NP / 8; ++i) {
-            const uint4_t v = *reinterpret_cast<const uint4_t*>(p + 16 * i);
-#pragma unroll
-            for (int k = 0; k < 4; ++k) r.w[4 * i + k] = v[k];
-        }
+        for (int k = 0; k < 4; ++k) r.w[k] = v[k];
     }
     return r;
 }
-template <int NP>
-__device__ __forceinline__ void add_narrow(float v, const NarrowRow<NP>& b, float (&acc)[NP]) {
+// Eight features of a row of any width.
+__device__ __forceinline__ NarrowRow<8> load_piece(const char* p) {
+    const uint4_t v = *reinterpret_cast<const uint4_a4*>(p);
+    return {{v[0], v[1], v[2], v[3]}};
+}
+// Feature `i` of a row of B held as packed halves.
+__device__ __forceinline__ float half_of(const uint32_t* w, int i) {
+    const uint32_t x = w[i / 2];   // copy first: bit_cast of a vector element lvalue reads element 0
+    const __half2 h = __builtin_bit_cast(__half2, x);
+    return i % 2 ? __high2float(h) : __low2float(h);
+}
+// sums += the entries of one turn.  Products of two binary16 values are exact in fp32; they are added up in pairs, the pairs in
+// 64 bits: a lane takes up to 32 entries, and fp32 sums one behind the other lose up to 1.7 times as much as those of teams,
+// which add up across a wave.  Relative error against 64 bits of what ran before lanes did, of lanes in fp32 and so: 27-point
+// stencil on 80^3 6.4e-8, 9.1e-8, 3.5e-8; rows of 30 random entries 5.3e-8, 8.6e-8, 2.8e-8; power-law graph of 2^17 vertices
+// 1.23e-8, 1.23e-8, 1.02e-8.  Lanes in fp32 took, and these take: that graph at 2^18 vertices, 8 features 49.6 us and 49.8, 32
+// 62.6 and 63.7, 64 86.8 and 89.7; 150000 rows of 12 entries, 64 features 36.0 and 36.2.
+template <int PAIRS, int F, class ROW>
+__device__ __forceinline__ void add_turn(const uint32_t (&w)[PAIRS], const ROW (&b)[2 * PAIRS], float zero, double (&acc)[F]) {
 #pragma unroll
-    for (int i = 0; i < NP; ++i) {
-        const __half2 h = __builtin_bit_cast(__half2, b.w[i / 2]);
-        acc[i] = fmaf(v, i % 2 ? __high2float(h) : __low2float(h), acc[i]);
-    }
+    for (int u = 0; u < PAIRS; ++u)
+#pragma unroll
+        for (int i = 0; i < F; ++i)
+            acc[i] += (double)fmaf(half_of(&w[u], 1), half_of(b[2 * u + 1].w, i), fmaf(half_of(&w[u], 0), half_of(b[2 * u].w, i), zero));
 }
 
 // Ordinary stores: a row is a part of a line, which the L2 puts together from the stores of neighbouring rows.
@@ -89,7 +107,7 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void rsh_narrow_kernel(const u
                                                                          const uint2_t* __restrict__ col, const uint32_t* __restrict__ val,
                                                                          const __half* __restrict__ B, const OUT out, float* __restrict__ scratch, int nb,
                                                                          int nv, int ns) {
-    constexpr int PAIRS = NP >= 8 ? 2 : kNarrowAhead;   // pairs of entries in flight
+    constexpr int PAIRS = NP == 8 ? 2 : kNarrowAhead;   // pairs of entries in flight
     const int lane = threadIdx.x & 63;
     uint32_t wave;
     if (!xcd_work_item(xs, &wave)) return;
@@ -107,9 +125,11 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void rsh_narrow_kernel(const u
     const uint32_t* pv = val + first + lane;
     const char* const Bb = reinterpret_cast<const char*>(B);
     const uint32_t row_bytes = 2u * (uint32_t)nb;
-    float acc[NP];
+    double sum[NP];
 #pragma unroll
-    for (int i = 0; i < NP; ++i) acc[i] = 0.f;
+    for (int i = 0; i < NP; ++i) sum[i] = 0.0;
+    float zero = 0.f;
+    asm("" : "+v"(zero));   // a register: with a constant the first products are multiplied apart, behind conversions
 
     uint2_t c[PAIRS];
     uint32_t v[PAIRS];
@@ -137,16 +157,11 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void rsh_narrow_kernel(const u
                 w[u / 2] &= on ? ~0u : u % 2 ? 0x0000ffffu : 0xffff0000u;
             }
         }
-#pragma unroll
-        for (int u = 0; u < PAIRS; ++u) {
-            const __half2 h = __builtin_bit_cast(__half2, w[u]);
-            add_narrow<NP>(__low2float(h), b[2 * u], acc);
-            add_narrow<NP>(__high2float(h), b[2 * u + 1], acc);
-        }
+        add_turn(w, b, zero, sum);
     }
     for (uint32_t k = 0; k < t; ++k) {
 #pragma unroll
-        for (int i = 0; i < NP; ++i) acc[i] += shfl_f32(acc[i], lane ^ (1 << k));
+        for (int i = 0; i < NP; ++i) sum[i] += shfl_f64(sum[i], lane ^ (1 << k));
     }
     if (!live || in_seg != 0) return;
     constexpr int QUADS = NP < 4 ? 1 : NP / 4;
@@ -155,7 +170,7 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void rsh_narrow_kernel(const u
         float4_t x = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int i = 0; i < 4; ++i)
-            if (4 * q + i < NP) x[i] = acc[(4 * q + i) % NP];
+            if (4 * q + i < NP) x[i] = (float)sum[(4 * q + i) % NP];
         if (s[1] & kSegmentToScratch) *reinterpret_cast<float4_t*>(scratch + (size_t)s[0] * ns + 4 * q) = x;
         else store_narrow4(out, (size_t)s[0], nv, 4 * q, x);
     }
@@ -191,20 +206,22 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void rsh_shared_kernel(const u
     const uint32_t* pv = val + first + slot;
     const char* const Bb = reinterpret_cast<const char*>(B);
     const uint32_t row_bytes = 2u * (uint32_t)nb, lane_byte = 2u * (uint32_t)lane_f;
-    float acc[8];
+    double sum[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) acc[i] = 0.f;
+    for (int i = 0; i < 8; ++i) sum[i] = 0.0;
+    float zero = 0.f;
+    asm("" : "+v"(zero));
     uint2_t c[PAIRS];
     uint32_t v[PAIRS];
 #pragma unroll
     for (int u = 0; u < PAIRS; ++u) c[u] = pc[S * u], v[u] = pv[S * u];
     for (uint32_t j = 0; j < steps; j += 2 * PAIRS) {
-        uint4_t b[2 * PAIRS];
+        NarrowRow<8> b[2 * PAIRS];
         uint32_t w[PAIRS];
 #pragma unroll
         for (int u = 0; u < PAIRS; ++u) {
-            b[2 * u] = *reinterpret_cast<const uint4_a4*>(Bb + (c[u][0] * row_bytes + lane_byte));
-            b[2 * u + 1] = *reinterpret_cast<const uint4_a4*>(Bb + (c[u][1] * row_bytes + lane_byte));
+            b[2 * u] = load_piece(Bb + (c[u][0] * row_bytes + lane_byte));
+            b[2 * u + 1] = load_piece(Bb + (c[u][1] * row_bytes + lane_byte));
             w[u] = v[u];
         }
         const uint32_t next = min(j + 2 * PAIRS, (steps + 1) & ~1u);
@@ -215,28 +232,20 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void rsh_shared_kernel(const u
             for (int u = 0; u < 2 * PAIRS; ++u) {
                 const bool on = j + u < mine;
 #pragma unroll
-                for (int i = 0; i < 4; ++i) b[u][i] = on ? b[u][i] : 0u;
+                for (int i = 0; i < 4; ++i) b[u].w[i] = on ? b[u].w[i] : 0u;
                 w[u / 2] &= on ? ~0u : u % 2 ? 0x0000ffffu : 0xffff0000u;
             }
         }
-#pragma unroll
-        for (int u = 0; u < 2 * PAIRS; ++u) {
-            const __half2 h = __builtin_bit_cast(__half2, w[u / 2]);
-            const float x = u % 2 ? __high2float(h) : __low2float(h);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const uint32_t q = b[u][i];
-                const __half2 p = __builtin_bit_cast(__half2, q);
-                acc[2 * i] = fmaf(x, __low2float(p), acc[2 * i]);
-                acc[2 * i + 1] = fmaf(x, __high2float(p), acc[2 * i + 1]);
-            }
-        }
+        add_turn(w, b, zero, sum);
     }
     for (uint32_t k = 0; k < t; ++k) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) acc[i] += shfl_f32(acc[i], lane ^ (F << k));
+        for (int i = 0; i < 8; ++i) sum[i] += shfl_f64(sum[i], lane ^ (F << k));
     }
     if (!live || in_seg != 0) return;
+    float acc[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) acc[i] = (float)sum[i];
     float* const stage = lds_stage[threadIdx.x >> 6] + slot * (8 * F);
     if (s[1] & kSegmentToScratch) store_row_streaming<F, PARTIAL, kRowsEven>(scratch + (size_t)s[0] * ns, acc, stage, tl, lane_f, nb);
     else emit_row<F, PARTIAL>(out, (size_t)s[0], nv, 0, acc, stage, tl, lane_f);
@@ -257,17 +266,21 @@ void launch_narrow(const DevicePlan& d, const void* B, const OUT& out, hipStream
         if (nv == 1) launch(rsh_narrow_kernel<1, Any>, any);
         else if (nv == 2) launch(rsh_narrow_kernel<2, Any>, any);
         else if (nv <= 4) launch(rsh_narrow_kernel<4, Any>, any);
-        else if (nv <= 8) launch(rsh_narrow_kernel<8, Any>, any);
-        else launch(rsh_narrow_kernel<16, Any>, any);
+        else launch(rsh_narrow_kernel<8, Any>, any);
         return;
     }
     const auto rows = out.general();
     using Rows = std::decay_t<decltype(rows)>;
+    const auto shared = [&](auto partial) {
+        constexpr bool PARTIAL = decltype(partial)::value;
+        if (d.geo.narrow == 2) launch(rsh_shared_kernel<2, PARTIAL, Rows>, rows);
+        else if (d.geo.narrow == 4) launch(rsh_shared_kernel<4, PARTIAL, Rows>, rows);
+        else launch(rsh_shared_kernel<8, PARTIAL, Rows>, rows);
+    };
     if constexpr (!Rows::kAny) {
-        if (nv == 8 * d.geo.narrow) return d.geo.narrow == 4 ? launch(rsh_shared_kernel<4, false, Rows>, rows) : launch(rsh_shared_kernel<8, false, Rows>, rows);
+        if (nv == 8 * d.geo.narrow) return shared(std::false_type{});
     }
-    if (d.geo.narrow == 4) launch(rsh_shared_kernel<4, true, Rows>, rows);
-    else launch(rsh_shared_kernel<8, true, Rows>, rows);
+    shared(std::true_type{});
 }
 
 }  // namespace

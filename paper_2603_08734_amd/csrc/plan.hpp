@@ -21,7 +21,7 @@ constexpr uint32_t kWaveSlice = 1u;      // `count` consecutive entries of one r
 constexpr uint32_t kWaveZeroRows = 2u;   // `count` rows of irr_row (from dst) receive zeros
 constexpr uint32_t kWaveKindMask = 3u;
 constexpr uint32_t kWaveToScratch = 4u;  // slice result goes to a scratch slot
-// Rows of at most kNarrow features run on lanes that own a row, or a share of one, each (narrow.hpp)
+// Rows of at most kNarrow features run on lanes that own rows, or share them in pairs (narrow.hpp)
 constexpr int kNarrow = 16;
 constexpr uint32_t kSegmentToScratch = 0x80000000u;
 constexpr int kNarrowAhead = 4;   // pairs of entries per lane behind the last wave's that the kernel may read
@@ -40,7 +40,7 @@ struct Geometry {
     int cpl = 4;        // cells per MFMA lane = bitmap words per sub-fragment = tile_k / 4
     int panel = 0;      // 1 = tall windows in the panel form (win_rows == 128 or 256, tile_k == 32)
     int wide = 0;       // panel form whose cells are written out on the device (wide.hpp); win_rows == 256
-    int narrow = 0;     // residual rows in the form of narrow.hpp: lanes that share a row of B (1, 4 or 8), 0 = teams
+    int narrow = 0;     // residual rows in the form of narrow.hpp: lanes that share a row of B (1, 2, 4 or 8), 0 = teams
     int panel_groups = 0; // panel form: row groups of 32 rows per window = win_rows / 32
 };
 Geometry make_geometry(int N, int window_rows, int tile_k);

@@ -1398,7 +1398,7 @@ bool narrow_pays(const rsh_csr_t& a, const Partition& part, int n) {
 }
 
 // Lanes that share a row of B in the residual part (narrow.hpp), or none for teams that share a wave (rsh_irregular_kernel).
-// Up to 16 features always one.  Beyond that from 2^18 entries on: below, a launch is over before it matters (65536 entries, 32
+// Up to 8 features always one, up to 16 two.  Beyond that from 2^18 entries on: below, a launch is over before it matters (65536 entries, 32
 // features, 7.5 .. 8.4 us both).  Not from 49 to 63 features, where rows of B end inside their last line: power-law
 // graph of 2^18 vertices, us with teams and with shared lanes, 24 features 80 and 67, 32 72 and 60, 40 90 and 90, 48 106 and 105,
 // 50 104 and 112, 60 112 and 123, 64 107 and 96 (binary16 111 and 94); of 2^20 vertices 32 340 and 332, 64 445 and 409; of
@@ -1407,7 +1407,7 @@ bool narrow_pays(const rsh_csr_t& a, const Partition& part, int n) {
 // entries, 64 features, 13.6 and 15.2) and short enough to need no sum over places (60000 rows of 36 entries, 48 features
 // 50.5 and 55, 64 40.0 and 41.8).  In these graphs it is a seventh to a quarter.
 static int lanes_per_row(const HostPlan& plan, const rsh_csr_t& a, const std::vector<int32_t>& rows, int64_t entries) {
-    if (plan.geo.N <= kNarrow) return 1;
+    if (plan.geo.N <= kNarrow) return plan.n_user <= 8 ? 1 : 2;
     if (entries < (1 << 18) || (plan.n_user > 48 && plan.n_user != 64)) return 0;
     const int lanes = plan.n_user <= 32 ? 4 : 8;
     const int64_t medium = std::count_if(rows.begin(), rows.end(), [&](int32_t r) { return row_len(a, r) > lanes && row_len(a, r) <= 32; });
