@@ -180,7 +180,8 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void rsh_narrow_kernel(const u
 // share one row of C (rsh_irregular_kernel) add up 64 / F sums at its end, for rows of a dozen entries as much work as the
 // entries, and fetch ids F at a time; the times of both are at lanes_per_row in planner.cpp.  Rows of C leave like theirs, by
 // streaming stores of whole lines after a turn through LDS (ordinary stores of 16-byte pieces: 80 us instead of 60 for the
-// power-law graph of 2^18 vertices at 32 features).  Four rows of B in flight per lane; with eight 64 features take 112 us
+// power-law graph of 2^18 vertices at 32 features; of 2^20 vertices at 16 267 and 243), except rows of 9 to 15 features, whose last
+// pieces end inside 16 bytes (2^18 vertices, 9 features 65.3 streaming and 63.4, 15 86.8 and 66.8).  Four rows of B in flight per lane; with eight 64 features take 112 us
 // instead of 98.
 template <int F, bool PARTIAL, class OUT>
 __global__ __launch_bounds__(64 * kWavesPerBlock) void rsh_shared_kernel(const uint4* __restrict__ waves, XcdSplit xs, const uint2_t* __restrict__ segments,
@@ -246,6 +247,16 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void rsh_shared_kernel(const u
     float acc[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] = (float)sum[i];
+    if constexpr (F == 2 && OUT::kAny) {   // 9 to 15 features: less than half a line, ordinary stores as above
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int f = 8 * tl + 4 * q;
+            const float4_t x = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+            if (s[1] & kSegmentToScratch) *reinterpret_cast<float4_t*>(scratch + (size_t)s[0] * ns + f) = x;
+            else store_narrow4(out, (size_t)s[0], nv, f, x);
+        }
+        return;
+    }
     float* const stage = lds_stage[threadIdx.x >> 6] + slot * (8 * F);
     if (s[1] & kSegmentToScratch) store_row_streaming<F, PARTIAL, kRowsEven>(scratch + (size_t)s[0] * ns, acc, stage, tl, lane_f, nb);
     else emit_row<F, PARTIAL>(out, (size_t)s[0], nv, 0, acc, stage, tl, lane_f);
