@@ -1398,20 +1398,37 @@ bool narrow_pays(const rsh_csr_t& a, const Partition& part, int n) {
 }
 
 // Lanes that share a row of B in the residual part (narrow.hpp), or none for teams that share a wave (rsh_irregular_kernel).
-// Up to 8 features always one, up to 16 two.  Beyond that from 2^18 entries on: below, a launch is over before it matters (65536 entries, 32
-// features, 7.5 .. 8.4 us both).  Not from 49 to 63 features, where rows of B end inside their last line: power-law
-// graph of 2^18 vertices, us with teams and with shared lanes, 24 features 80 and 67, 32 72 and 60, 40 90 and 90, 48 106 and 105,
-// 50 104 and 112, 60 112 and 123, 64 107 and 96 (binary16 111 and 94); of 2^20 vertices 32 340 and 332, 64 445 and 409; of
-// 2^16 32 23.9 and 19.9, 64 32.8 and 24.9; 150000 rows of 12 entries 43.7 and 21.9, 47.9 and 32.4.  What is saved is a wave for
-// each row of medium length: a tenth of the rows has to be longer than the teams of a wave take several of (100000 rows of 5
-// entries, 64 features, 13.6 and 15.2) and short enough to need no sum over places (60000 rows of 36 entries, 48 features
-// 50.5 and 55, 64 40.0 and 41.8).  In these graphs it is a seventh to a quarter.
+// Up to 8 features always one, up to 16 two.  Beyond that from 2^18 entries on: below, a launch is over before it matters
+// (65536 entries, 32 features, 7.5 .. 8.4 us both).  What is saved is a wave for each row of medium length, longer than the teams
+// of a wave take several of and short enough to need no sum over places.  Times with teams and with lanes, us:
+//   * A tenth of the rows has to be such: power-law graphs of 2^16 vertices, 32 features 24.4 and 20.2, 64 33.5 and 27.1; 2^18 76.5
+//     and 63.9, 101 and 89.7; 2^20 334 and 328, 445 and 412 (a seventh to a quarter of their rows); 150000 rows of 12 entries 46.4
+//     and 26.7, 50.7 and 36.2; 60000 rows of 36 entries, 48 features 50.5 and 55, 64 40.0 and 41.8.
+//   * At 33 to 63 features, where rows of B lie across lines, except 48: half of the rows.  Power-law graphs of 2^18 vertices, 40
+//     features 92.8 and 94.5, 56 101.7 and 103, of 2^20 438 and 465, 491 and 519; 48 104.5 and 93, 469 and 457; 150000 rows of
+//     12 entries 40 55.0 and 39.6, 56 59.3 and 50.7; rows of 31 50.1 and 49.0, 68.4 and 67.3.  Up to 47 features a tenth where B takes
+//     no more than 16 MB, half of what the XCDs' caches hold: 40 features, 2^16 vertices 28.5 and 27.6, 2^17 51.2 and 50.0.
+//   * Entries in rows of 65 to 512, which take places from each other: up to twelve times those of medium rows (40000 rows,
+//     88 % of 100 entries and 12 % of 30, 20 features 28.2 and 30.4, 48 37.9 and 40.5; 75 % and 25 % of 25 27.4 and 26.3, 36.5 and
+//     36.7).
+//   * Eight lanes: rows of 5 to 8 entries, which eight teams take one each, up to five times the medium ones (200000 rows, 90 %
+//     of 5 entries and 10 % of 20, 64 features 31.7 and 32.7; 75 % of 8 and 25 % of 20 48.1 and 46.4).
+// Entries that element-level routing takes out of windows are no rows here: lanes (4000 communities, 48 features 170 and 136; stencil
+// 96^3, 64 features 409 and 395).
 static int lanes_per_row(const HostPlan& plan, const rsh_csr_t& a, const std::vector<int32_t>& rows, int64_t entries) {
-    if (plan.geo.N <= kNarrow) return plan.n_user <= 8 ? 1 : 2;
-    if (entries < (1 << 18) || (plan.n_user > 48 && plan.n_user != 64)) return 0;
-    const int lanes = plan.n_user <= 32 ? 4 : 8;
-    const int64_t medium = std::count_if(rows.begin(), rows.end(), [&](int32_t r) { return row_len(a, r) > lanes && row_len(a, r) <= 32; });
-    return 10 * medium >= (int64_t)rows.size() ? lanes : 0;
+    const int n = plan.n_user;
+    if (plan.geo.N <= kNarrow) return n <= 8 ? 1 : 2;
+    if (entries < (1 << 18) || n > 64) return 0;
+    const int lanes = n <= 32 ? 4 : 8;
+    int64_t medium = 0, medium_entries = 0, long_entries = 0, just_short = 0;
+    for (int32_t r : rows) {
+        const int64_t len = row_len(a, r);
+        if (len > lanes && len <= 32) ++medium, medium_entries += len;
+        if (len > 64 && len <= 512) long_entries += len;
+        if (lanes == 8 && len > 4 && len <= 8) ++just_short;
+    }
+    const bool tenth = n <= 32 || n % 16 == 0 || (n < 48 && 2 * n * a.n_cols <= (int64_t)16 << 20);
+    return (tenth ? 10 : 2) * medium >= (int64_t)rows.size() && 12 * medium_entries >= long_entries && 5 * medium >= just_short ? lanes : 0;
 }
 
 // ---------------------------------------------------------------------------

@@ -679,3 +679,43 @@ def test_operand_of_an_empty_plan():
     A = from_coo(np.zeros(0, int), np.zeros(0, int), np.zeros(0), 0, 40)
     for N in (3, 16):
         assert host_plan(A, N, window_rows=256).operand(4096, 4096)[1] >= N
+
+
+# Lanes share rows of B where enough rows are of medium length, and not where rows that other kernels take better outweigh them
+# (lanes_per_row): {entries: rows}, {features: lanes}
+@pytest.mark.parametrize("lengths,lanes", [
+    ({12: 30000}, {20: 4, 32: 4, 33: 8, 40: 8, 48: 8, 56: 8, 64: 8, 65: 0, 128: 0}),
+    ({12: 20000}, {32: 0, 64: 0}),                                       # fewer than 2^18 entries
+    ({20: 17000, 2: 83000}, {17: 4, 32: 4, 40: 8, 47: 8, 48: 8, 49: 0, 56: 0, 64: 8}),
+    ({20: 5000, 40: 55000}, {32: 0, 64: 0}),
+    ({30: 1200, 100: 8800}, {20: 0, 48: 0}),
+    ({25: 2500, 100: 2500}, {20: 4, 48: 8}),
+    ({20: 10000, 5: 90000}, {32: 4, 48: 0}),
+])
+def test_lanes_that_share_rows(lengths, lanes):
+    rng = np.random.default_rng(8)
+    per_row = rng.permutation(np.repeat(list(lengths), list(lengths.values())))
+    r = np.repeat(np.arange(per_row.size), per_row)
+    c = np.concatenate([np.arange(k) for k in per_row]) * 40 + rng.integers(0, 40, r.size)
+    A = from_coo(r, c, rng.standard_normal(r.size), per_row.size, 4000)
+    for N, want in lanes.items():
+        p = host_plan(A, N, force_path=1, reorder=0)
+        assert p.kernels()["row_lanes"] == want, N
+        p.destroy()
+    if 2 in lengths:     # as many columns as make B larger than 16 MB
+        A = from_coo(r, 75 * c, rng.standard_normal(r.size), per_row.size, 300000)
+        for N, want in ((32, 4), (40, 0), (48, 8), (64, 8)):
+            assert host_plan(A, N, force_path=1, reorder=0).kernels()["row_lanes"] == want, N
+
+
+def test_lanes_share_rows_of_entries_that_windows_gave_up():
+    rng = np.random.default_rng(9)
+    rows, cols = 68000, 400000
+    window = np.arange(rows)[:, None] // 16 * 16 % (cols - 16)
+    c = np.concatenate([window + rng.permuted(np.tile(np.arange(16), (rows, 1)), axis=1)[:, :8],
+                        window[:, :1] * 0 + 50000 * (np.arange(4) + 4) + rng.integers(0, 50000, (rows, 4))], axis=1)
+    c[:, :8] %= 190000
+    A = from_coo(np.repeat(np.arange(rows), 12), c.ravel(), rng.standard_normal(c.size), rows, cols)
+    p = host_plan(A, 48, element_level=1, reorder=0, window_rows=16, force_path=2)
+    assert p.stats()["n_irregular_rows"] == 0 and p.stats()["nnz_irregular"] >= 1 << 18
+    assert p.kernels()["row_lanes"] == 8
