@@ -1,5 +1,5 @@
-"""Residual rows whose lanes own rows of B or share them (rsh_narrow_kernel, rsh_shared_kernel): what a sum may lose, and what
-lanes read past the end of their rows."""
+"""Residual rows whose lanes own rows of B or share them (rsh_narrow_kernel, rsh_shared_kernel): what a sum may lose, what lanes
+read past the end of their rows, widths where only plans of rows of medium length take them, and windows beside them."""
 import numpy as np
 import pytest
 
@@ -9,18 +9,28 @@ from workloads import from_coo
 pytestmark = pytest.mark.gpu
 
 
-def product(A, B, lanes, **opts):
+def product(A, B, lanes, windows=False, **opts):
     import torch
     from paper_2603_08734_amd import Plan
     N = B.shape[1]
-    plan = Plan(A.row_ptr, A.col_idx, A.val, A.n_cols, N, force_path=1, **opts)
-    assert plan.kernels()["row_lanes"] == lanes
+    plan = Plan(A.row_ptr, A.col_idx, A.val, A.n_cols, N, **opts)
+    assert plan.kernels()["row_lanes"] == lanes and (plan.stats()["n_tile_items"] > 0) == windows
     Bd = torch.from_numpy(B).cuda()
     C = torch.full((A.n_rows, N), float("nan"), dtype=torch.float32, device="cuda")
     plan.spmm(Bd, C)
     torch.cuda.synchronize()
     plan.destroy()
     return C.cpu().numpy().astype(np.float64)
+
+
+def rows_of(per_row, cols, seed):
+    """Rows of the given numbers of entries, in random columns of 1 .. cols - 1."""
+    rng = np.random.default_rng(seed)
+    per_row = np.asarray(per_row)
+    r = np.repeat(np.arange(per_row.size), per_row)
+    step = (cols - 1) // per_row.max()
+    c = 1 + np.concatenate([np.arange(k) for k in per_row]) * step + rng.integers(0, step, r.size)
+    return r, c, rng.standard_normal(r.size)
 
 
 # 32 entries, as many as one lane takes, the first product 1 and the others 2^-25: one behind the other in fp32 none of them would
@@ -34,6 +44,59 @@ def test_entries_of_a_lane_keep_small_products(N, lanes):
     B = np.full((length, N), 2.0 ** -13, dtype=np.float16)
     B[0] = 1.0
     print(f"case small products N={N}", flush=True)
-    got = product(A, B, lanes)
+    got = product(A, B, lanes, force_path=1)
     exact = 1.0 + 31 * 2.0 ** -25
     assert np.abs(got - exact).max() <= 2 * 2.0 ** -24 * exact
+
+
+# A lane goes on past its row's last entry, through slots that name column 0 and through other rows' entries: rows of B that its
+# own row does not name, infinite or not a number, must not count.  Every fiftieth row names them.
+@pytest.mark.parametrize("N,lanes", [(1, 1), (3, 1), (4, 1), (8, 1), (11, 2), (16, 2), (32, 4), (31, 4), (48, 8), (64, 8)])
+def test_rows_of_b_that_are_not_finite(N, lanes):
+    rng = np.random.default_rng(N)
+    rows, cols = 24000, 3000
+    per_row = np.resize([1, 2, 3, 7, 8, 12, 15, 16, 17, 30, 31, 32, 33, 40], rows)
+    r, c, v = rows_of(rng.permutation(per_row), cols, N)
+    bad = rng.permutation(np.arange(0, rows, 50))
+    r, c, v = np.concatenate([r, bad]), np.concatenate([c, np.zeros(bad.size, int)]), np.concatenate([v, np.ones(bad.size)])
+    A = from_coo(r, c, v, rows, cols)
+    B = rng.standard_normal((cols, N)).astype(np.float16)
+    B[0, ::2], B[0, 1::2] = np.inf, np.nan
+    print(f"case not finite N={N}", flush=True)
+    got = product(A, B, lanes, force_path=1)
+    B[0] = 0
+    want, S, _ = oracle.spmm(A.row_ptr, A.col_idx, A.val, B)
+    names = np.zeros(rows, bool)
+    names[bad] = True
+    assert np.all(np.abs(got[~names] - want[~names]) <= 1e-4 * S[~names])
+    assert np.isposinf(got[names][:, ::2]).all() and np.isnan(got[names][:, 1::2]).all()
+
+
+# From 33 to 63 features, except 48, eight lanes share rows where half of them are of medium length: rows of C and B that end at
+# every even place inside the last lane's eight features, and odd ones beside the padded copy.
+@pytest.mark.parametrize("N", [33, 38, 49, 50, 52, 54, 56, 62, 63])
+def test_widths_where_half_of_the_rows_are_medium(N):
+    rows, cols = 28000, 5000
+    A = from_coo(*rows_of(np.resize([12, 9, 20, 0], rows), cols, N), rows, cols)
+    B = np.random.default_rng(N).standard_normal((cols, N)).astype(np.float16)
+    print(f"case medium rows N={N}", flush=True)
+    got = product(A, B, 8, force_path=1)
+    want, S, _ = oracle.spmm(A.row_ptr, A.col_idx, A.val, B)
+    assert np.all(np.abs(got - want) <= 1e-4 * S)
+
+
+# Windows and lanes in one plan, one after the other and on two streams.
+@pytest.mark.parametrize("side_stream", [0, 1])
+@pytest.mark.parametrize("N,lanes", [(5, 1), (12, 2), (16, 2), (20, 4), (32, 4), (48, 8), (64, 8)])
+def test_windows_beside_lanes(N, lanes, side_stream):
+    rng = np.random.default_rng(3)
+    rows, cols = 34000, 40000
+    r, c, v = rows_of(np.resize([12, 9, 20, 0, 2], rows), cols, 4)
+    w = np.nonzero(rng.random((320, 48)) < 0.6)     # windows: 320 further rows, 16 to 48 columns
+    r, c = np.concatenate([r, rows + w[0]]), np.concatenate([c, w[0] // 16 * 50 + w[1]])
+    A = from_coo(r, c, np.concatenate([v, rng.standard_normal(w[0].size)]), rows + 320, cols)
+    B = rng.standard_normal((cols, N)).astype(np.float16)
+    print(f"case windows beside lanes N={N} side_stream={side_stream}", flush=True)
+    got = product(A, B, lanes, windows=True, side_stream=side_stream, window_rows=16)
+    want, S, _ = oracle.spmm(A.row_ptr, A.col_idx, A.val, B)
+    assert np.all(np.abs(got - want) <= 1e-4 * S)

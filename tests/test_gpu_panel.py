@@ -259,14 +259,14 @@ def test_a_narrower_last_panel_in_a_launch_of_its_own(window_rows, N, fused):
     plan.destroy()
 
 
-# Rows of up to 16 features (lanes own rows).  Rows of 0 .. 2000 entries: empty, one to a lane with an odd and an even number of
-# entries, at both sides of every doubling of the lanes that share one, sliced with partial sums; few rows (a lane takes two
-# entries) and many (16); column groups; beside windows that read a copy of 16 features.  B and C begin one element past a
-# 16-byte boundary in `odd`: then widths that are a power of two go through the copy too.
+# Rows of up to 16 features (lanes own rows, or share them in pairs).  Rows of 0 .. 2000 entries: empty, one to a lane with an odd
+# and an even number of entries, at both sides of every doubling of the lanes that share one, sliced with partial sums; few rows (a
+# lane takes two entries) and many (16); column groups; beside windows that read a copy of 16 features.  B and C begin one element
+# past a 16-byte boundary in `odd`: then widths that are a power of two go through the copy too.
 # From 17 features on four or eight lanes share a row, in plans of 2^18 entries and more: widths that fill the lanes, end at
 # every place inside the last one's eight features, and odd ones beside the padded copy.
 FEW = [(90, {}), (90, dict(max_nnz_per_slice=40)), (90, dict(xcd_partition_nnz=32)), (90, dict(window_rows=16, min_reuse=0.0))]
-MANY = [(20000, {}), (20000, dict(max_nnz_per_slice=20)), (20000, dict(xcd_partition_nnz=32))]
+MANY = [(20000, dict(force_path=1)), (20000, dict(force_path=1, max_nnz_per_slice=20)), (20000, dict(force_path=1, xcd_partition_nnz=32))]
 
 
 @pytest.mark.parametrize("fused,odd", [(False, 0), (False, 1), (True, 0)])
@@ -287,6 +287,9 @@ def test_narrow_rows(rows, opts, N, fused, odd):
         pytest.skip("rows of a multiple of 16 features have to be 16-byte aligned")
     print(f"case narrow rows={rows} {opts} N={N} fused={fused} odd={odd}", flush=True)
     plan = Plan(A.row_ptr, A.col_idx, A.val, A.n_cols, N, **opts)
+    assert plan.kernels()["row_lanes"] == (1 if N <= 8 else 2 if N <= 16 else 4 if N <= 32 else 8)
+    assert plan.stats()["nnz_irregular"] == A.nnz or rows < 100
+    assert plan.stats()["n_scratch_slots"] > 0 or "max_nnz_per_slice" not in opts and "xcd_partition_nnz" not in opts
     B = dense_B(A.n_cols, N, "normal", seed=N)
     Bd = torch.empty(B.size + odd, dtype=torch.float16, device="cuda")[odd:].view(A.n_cols, N)
     Bd.copy_(torch.from_numpy(B.view(np.float16) if B.dtype != np.float16 else B))
