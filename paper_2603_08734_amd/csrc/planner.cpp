@@ -1370,13 +1370,17 @@ int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int thr
 // through), or where a window's columns lie next to each other, several to a line.  27-point stencil on 80^3, B of 8 MB at 8
 // features, 5.6 columns to a line: windows 48.0 us, lanes 27.8.  Communities, whose columns lie anywhere: 128000 rows, B of 2 MB,
 // 17.5 and 15.4; 524288 rows, 8 MB, 63.1 and 78.6, and 4 MB at 3 features 67.2 and 76.9, 1 MB at 1 feature 60.5 and 56.5.
-// From 9 features on windows are faster in both (stencil 12 features 46.5 and 57; communities 53.4 and more than 80).
+// Windows that are nearly full take 2 bytes an entry and lanes 6, which decides where a launch less (of the copy of B) no
+// longer does: beyond ten entries to a column from 2^22 entries on.  Windows and lanes at 1, 3, 4, 6 and 8 features, us: 20000
+// windows of 64 columns, 0.7 full, 14 M entries 21.2 21.9 22.2 23.4 21.6 and 25.8 25.8 21.4 28.8 24.1; 200 windows of 2048, 0.9 full,
+// 5.9 M 16.0 16.4 17.4 16.6 16.8 and 16.6 24.4 21.6 31.4 27.6; 4000 of 64, 0.9 full, 3.7 M 10 to 11 and 9.4 11.8 8.6 11.7 9.3;
+// 2000 of 400, 0.5 full (eight to a column), 6.4 M 19.7 20.3 20.5 21.1 20.3 and 11.1 14.2 10.9 16.5 11.7.
+// From 9 features on windows are faster (stencil 12 features 46.5 and 57; communities 53.4 and more than 80).
 bool narrow_pays(const rsh_csr_t& a, const Partition& part, int n) {
     if (n > kNarrow / 2 || part.win_row.empty()) return false;
     const int64_t row_bytes = 2 * narrow_width(n);
-    if (a.n_cols * row_bytes <= (int64_t)3 << 20) return true;
     const int64_t n_win = (int64_t)part.win_row.size() / kW, step = std::max<int64_t>(1, n_win / 512);
-    int64_t columns = 0, lines = 0;
+    int64_t windows = 0, entries = 0, columns = 0, lines = 0;   // of the sample
     std::vector<int32_t> cols;
     for (int64_t w = 0; w < n_win; w += step) {
         cols.clear();
@@ -1393,8 +1397,11 @@ bool narrow_pays(const rsh_csr_t& a, const Partition& part, int n) {
             last = c;
             last_line = c * row_bytes / 128;
         }
+        ++windows;
+        entries += (int64_t)cols.size();
     }
-    return 2 * lines <= columns;
+    if (entries > 10 * columns && entries * n_win >= windows << 22) return false;
+    return a.n_cols * row_bytes <= (int64_t)3 << 20 || 2 * lines <= columns;
 }
 
 // Lanes that share a row of B in the residual part (narrow.hpp), or none for teams that share a wave (rsh_irregular_kernel).

@@ -719,3 +719,13 @@ def test_lanes_share_rows_of_entries_that_windows_gave_up():
     p = host_plan(A, 48, element_level=1, reorder=0, window_rows=16, force_path=2)
     assert p.stats()["n_irregular_rows"] == 0 and p.stats()["nnz_irregular"] >= 1 << 18
     assert p.kernels()["row_lanes"] == 8
+
+
+# Windows that are nearly full stay windows once there are 2^22 entries; half full ones of as many entries do not.
+@pytest.mark.parametrize("rows,full,windows", [(48000, 0.9, True), (24000, 0.9, False), (48000, 0.5, False)])
+def test_full_windows_of_narrow_rows(rows, full, windows):
+    rng = np.random.default_rng(6)
+    hit = np.nonzero(rng.random((rows, 100)) < full)
+    A = from_coo(hit[0], hit[0] // 16 * 137 % 20000 + hit[1], rng.standard_normal(hit[0].size), rows, 20100)
+    st = host_plan(A, 4, reorder=0).stats()
+    assert st["window_rows"] == 16 and (st["nnz_tile"] == A.nnz) == windows and st["nnz_tile"] in (0, A.nnz)
