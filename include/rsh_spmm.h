@@ -277,8 +277,8 @@ int rsh_plan_destroy(rsh_plan_t *plan); /* NULL is a no-op */
 int rsh_plan_stats(const rsh_plan_t *plan, rsh_plan_stats_t *out);
 
 /*
- * Reconstruct the CSR matrix from the plan's own arrays (the host mirrors of
- * what the kernels read).  Outputs are caller-allocated: row_ptr [n_rows+1],
+ * Reconstruct the CSR matrix from the plan's own arrays, read as the kernels read them (entries of tall windows
+ * in the form that is packed on the device; residual entries in the order of the lanes, see RSH_ARR_NARROW_COL).  Outputs are caller-allocated: row_ptr [n_rows+1],
  * col_idx [nnz], val_f16 [nnz], path [nnz] (0 = dense-fragment path, 1 =
  * irregular path; may be NULL).  Fails with RSH_ERR_INVALID_CSR if some stored
  * entry is covered zero times or more than once.
@@ -304,8 +304,9 @@ int rsh_plan_row_order(const rsh_plan_t *plan, int32_t *order);
 int rsh_reorder_knn(const rsh_csr_t *csr, const rsh_plan_opts_t *opts, int32_t *nbr, float *nbr_sim);
 
 /*
- * Read-only access to the host mirror of one plan array (exactly the bytes the
- * device holds).  *count is the number of elements.
+ * Read-only access to one plan array on the host.  *count is the number of elements.  The device holds the same bytes, but for
+ * PANEL_OFF and PANEL_ENT, which are packed into another form there, and, where rsh_plan_kernels reports row_lanes > 0, the
+ * IRR_* arrays, in whose place it holds the NARROW_* ones.
  *
  * Dense-fragment part (RS-Tile "TC block part", Section 3.2).  W = window_rows, NW = W/16,
  * K = tile_k (both as reported by rsh_plan_stats), Q = K/4; a fragment is K condensed columns;
@@ -358,17 +359,29 @@ int rsh_reorder_knn(const rsh_csr_t *csr, const rsh_plan_opts_t *opts, int32_t *
  *                                                 kind 2 (zero rows): rows IRR_ROW[dst .. dst+count) of C
  *                                                   are set to 0
  *   RSH_ARR_IRR_ROW      int32  []              row ids named by kind-0 and kind-2 waves
+ * The same entries for lanes that own or share rows of B (row_lanes F > 0; a wave has S = 64 / F places).  A segment is a row or
+ * a slice of one; T = 2^t places of a wave take it, entry e being entry e / T of place e mod T.  Host-only plans have these
+ * arrays; those of uploaded ones are on the device alone and empty here:
+ *   RSH_ARR_NARROW_SEG   uint32 [n_segments*2]  {row of C, or with bit 31 of the second word scratch slot; entries}
+ *   RSH_ARR_NARROW_WAVE  uint32 [n_waves*4]     {first, steps, info, first segment}; info = t | segments << 8 | full << 16: the
+ *                                               most entries that a place takes, and the number that every place of a segment
+ *                                               has at least; segment k has places k*T .. k*T + T-1
+ *   RSH_ARR_NARROW_COL   int32  []              column ids: entry j of place p at 2 * (first + S * (j / 2) + p) + j % 2; unused
+ *                                               places name column 0; 512 such behind the last wave
+ *   RSH_ARR_NARROW_VAL   uint16 []              binary16 values likewise, unused ones 0
  * Combine:
  *   RSH_ARR_COMBINE      uint32 [n_combine*4]   {row, first slot, parts, slot stride}
  * Work split over the eight XCDs (workgroup b serves XCD b mod 8):
  *   RSH_ARR_TILE_XCD     uint32 [9]             XCD x runs tile items [v[x], v[x+1])
  *   RSH_ARR_IRR_XCD      uint32 [9]             XCD x runs irregular waves [v[x], v[x+1])
+ *   RSH_ARR_NARROW_XCD   uint32 [9]             likewise of NARROW_WAVE
  */
 enum {
     RSH_ARR_WIN_ROW = 0, RSH_ARR_WIN_TILE_OFF, RSH_ARR_TILE_COLID, RSH_ARR_TILE_MASK,
     RSH_ARR_TILE_VAL_OFF, RSH_ARR_TILE_VAL, RSH_ARR_TILE_ITEM, RSH_ARR_IRR_COL, RSH_ARR_IRR_VAL,
     RSH_ARR_IRR_WAVE, RSH_ARR_IRR_ROW, RSH_ARR_COMBINE, RSH_ARR_TILE_XCD, RSH_ARR_IRR_XCD,
-    RSH_ARR_PANEL_COL0, RSH_ARR_PANEL_OFF, RSH_ARR_PANEL_ENT, RSH_ARR_COUNT
+    RSH_ARR_PANEL_COL0, RSH_ARR_PANEL_OFF, RSH_ARR_PANEL_ENT, RSH_ARR_NARROW_COL, RSH_ARR_NARROW_VAL,
+    RSH_ARR_NARROW_WAVE, RSH_ARR_NARROW_SEG, RSH_ARR_NARROW_XCD, RSH_ARR_COUNT
 };
 int rsh_plan_array(const rsh_plan_t *plan, int32_t which, const void **ptr, int64_t *count);
 

@@ -176,12 +176,12 @@ int upload_plan(rsh_plan& p) {
     rsh::DevicePlan& d = p.dev;
     d.geo = h.geo;
     d.n_tile_items = (int64_t)h.tile_item.size() / 4;
-    d.n_irr_waves = (int64_t)(h.geo.narrow ? h.narrow_wave : h.irr_wave).size() / 4;
+    d.n_irr_waves = (int64_t)(h.geo.narrow ? h.narrow.wave : h.irr_wave).size() / 4;
     d.n_combine = (int64_t)h.combine.size() / 4;
     d.n_scratch_slots = h.n_scratch_slots;
     d.n_split_rows = h.stats.n_split_rows;
     d.tile_split = h.tile_split;
-    d.irr_split = h.geo.narrow ? h.narrow_split : h.irr_split;
+    d.irr_split = h.geo.narrow ? h.narrow.split : h.irr_split;
     Uploader up;
     struct Closer {
         Uploader& u;
@@ -199,10 +199,10 @@ int upload_plan(rsh_plan& p) {
     if ((rc = upload_array(up, h.panel_col0, &d.panel_col0))) return rc;
     if (h.geo.panel && (rc = upload_panel_units(up, h, d))) return rc;
     if (h.geo.narrow) {
-        if ((rc = upload_array(up, h.narrow_col.get(), h.narrow_slots, &d.irr_col))) return rc;
-        if ((rc = upload_array(up, h.narrow_val.get(), h.narrow_slots, &d.irr_val))) return rc;
-        if ((rc = upload_array(up, h.narrow_wave, &d.irr_wave))) return rc;
-        if ((rc = upload_array(up, h.narrow_seg, &d.narrow_seg))) return rc;
+        if ((rc = upload_array(up, h.narrow.col.get(), h.narrow.slots, &d.irr_col))) return rc;
+        if ((rc = upload_array(up, h.narrow.val.get(), h.narrow.slots, &d.irr_val))) return rc;
+        if ((rc = upload_array(up, h.narrow.wave, &d.irr_wave))) return rc;
+        if ((rc = upload_array(up, h.narrow.seg, &d.narrow_seg))) return rc;
     } else {
         if ((rc = upload_array(up, h.irr_col, &d.irr_col))) return rc;
         if ((rc = upload_array(up, h.irr_val, &d.irr_val))) return rc;
@@ -224,9 +224,7 @@ int upload_plan(rsh_plan& p) {
         d.ev_join = join;
     }
     if ((rc = up.close())) return rc;   // every copy has landed
-    for (auto* v : {&h.narrow_wave, &h.narrow_seg}) std::vector<uint32_t>().swap(*v);
-    h.narrow_col.reset();
-    h.narrow_val.reset();
+    h.narrow = rsh::NarrowPart{};
     if (!hip_ok(hipGetDevice(&p.device))) return RSH_ERR_HIP;
     p.uploaded = true;
     return RSH_OK;
@@ -697,6 +695,20 @@ int rsh_plan_array(const rsh_plan_t* plan, int32_t which, const void** ptr, int6
         RSH_CASE(RSH_ARR_PANEL_COL0, h.panel_col0)
         RSH_CASE(RSH_ARR_PANEL_OFF, h.panel_off)
         RSH_CASE(RSH_ARR_PANEL_ENT, h.panel_ent)
+        RSH_CASE(RSH_ARR_NARROW_WAVE, h.narrow.wave)
+        RSH_CASE(RSH_ARR_NARROW_SEG, h.narrow.seg)
+        case RSH_ARR_NARROW_COL:
+            *ptr = h.narrow.col.get();
+            *count = (int64_t)h.narrow.slots;
+            return RSH_OK;
+        case RSH_ARR_NARROW_VAL:
+            *ptr = h.narrow.val.get();
+            *count = (int64_t)h.narrow.slots;
+            return RSH_OK;
+        case RSH_ARR_NARROW_XCD:
+            *ptr = h.narrow.split.start;
+            *count = 9;
+            return RSH_OK;
         case RSH_ARR_TILE_XCD:
             *ptr = h.tile_split.start;
             *count = 9;

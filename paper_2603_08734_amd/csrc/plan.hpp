@@ -52,6 +52,15 @@ struct XcdSplit {
 };
 XcdSplit split_by_cost(const std::vector<uint32_t>& cost);
 
+// Residual work in the order in which lanes take it (pack_narrow): what the device holds instead of HostPlan's irr_* arrays.
+struct NarrowPart {
+    std::unique_ptr<int32_t[]> col;
+    std::unique_ptr<uint16_t[]> val;
+    size_t slots = 0;                  // of both
+    std::vector<uint32_t> wave, seg;   // 4 per wave, 2 per segment
+    XcdSplit split;
+};
+
 struct HostPlan {
     int64_t n_rows = 0, n_cols = 0, nnz = 0;
     int n_user = 0;   // features of B and C as the caller has them; geo.N is the run width
@@ -77,12 +86,7 @@ struct HostPlan {
     std::vector<uint16_t> irr_val;
     std::vector<uint32_t> irr_wave;  // 4 per wave
     std::vector<int32_t> irr_row;    // row ids named by short-row and zero-row waves
-    // the same work as narrow.hpp reads it (geo.narrow); what the device holds instead of the arrays above
-    std::unique_ptr<int32_t[]> narrow_col;
-    std::unique_ptr<uint16_t[]> narrow_val;
-    size_t narrow_slots = 0;          // of both
-    std::vector<uint32_t> narrow_wave, narrow_seg;   // 4 per wave, 2 per segment
-    XcdSplit narrow_split;
+    NarrowPart narrow;              // geo.narrow: the same work as narrow.hpp reads it, until it is uploaded
     bool narrow_in_order = false;   // rows run in the processing order, not by id
     // combine
     XcdSplit tile_split, irr_split;
@@ -122,7 +126,7 @@ void partition_rows(const rsh_csr_t& a, const rsh_plan_opts_t& o, const std::vec
 int choose_window_rows(const rsh_csr_t& a, const Partition& part16);
 int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int threads);
 int64_t panel_device_bytes(const HostPlan& plan);
-void pack_narrow(HostPlan& plan, int threads);
+NarrowPart pack_narrow(const HostPlan& plan, int threads);
 // Whether the 16-row windows of `part` are better off as residual rows at n features (narrow.hpp).
 bool narrow_pays(const rsh_csr_t& a, const Partition& part, int n);
 // Features of a row of B as narrow.hpp reads it.

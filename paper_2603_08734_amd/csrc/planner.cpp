@@ -1284,7 +1284,7 @@ int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int thr
 
     plan.n_scratch_slots = slots;
     geo.narrow = lanes_per_row(plan, a, part.irregular, nnz_irr);
-    if (geo.narrow) pack_narrow(plan, threads);
+    if (geo.narrow) plan.narrow = pack_narrow(plan, threads);
 
     // ---- statistics -----------------------------------------------------------------------
     rsh_plan_stats_t& st = plan.stats;
@@ -1312,7 +1312,7 @@ int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int thr
     st.n_scratch_slots = slots;
     st.sum_window_cols = sum_cols;
     const int64_t panel_bytes = panel_device_bytes(plan);
-    const int64_t residual_bytes = geo.narrow ? (int64_t)(plan.narrow_slots * 6 + plan.narrow_wave.size() * 4 + plan.narrow_seg.size() * 4)
+    const int64_t residual_bytes = geo.narrow ? (int64_t)(plan.narrow.slots * 6 + plan.narrow.wave.size() * 4 + plan.narrow.seg.size() * 4)
                                               : (int64_t)(plan.irr_col.size() * 4 + plan.irr_val.size() * 2 + plan.irr_wave.size() * 4 + plan.irr_row.size() * 4);
     st.plan_bytes = panel_bytes +
                     (int64_t)(plan.win_row.size() * 4 + plan.win_tile_off.size() * 4 + plan.tile_colid.size() * 4 +
@@ -1450,7 +1450,8 @@ static int lanes_per_row(const HostPlan& plan, const rsh_csr_t& a, const std::ve
 // with 512).
 // Entries lie in pairs: entry pair q of place l at 2 * (first + S q + l), a wave's places next to each other.
 // ---------------------------------------------------------------------------
-void pack_narrow(HostPlan& plan, int threads) {
+NarrowPart pack_narrow(const HostPlan& plan, int threads) {
+    NarrowPart out;
     struct Segment {
         uint32_t dst, len, start;   // len with kSegmentToScratch
     };
@@ -1494,8 +1495,6 @@ void pack_narrow(HostPlan& plan, int threads) {
         for (const Segment& s : partial[x]) cost += len_of(s) + kShare;
     std::vector<Segment> order;
     order.reserve(direct.size());
-    plan.narrow_wave.clear();
-    plan.narrow_seg.clear();
     // blocks of segments: the partial sums of an XCD, then its run of rows in pieces of block_rows
     std::vector<size_t> block_at{0};
     size_t xcd_block[9];
@@ -1522,7 +1521,7 @@ void pack_narrow(HostPlan& plan, int threads) {
     });
     uint64_t first = 0;
     for (int x = 0; x < 8; ++x) {
-        plan.narrow_split.start[x] = (uint32_t)(plan.narrow_wave.size() / 4);
+        out.split.start[x] = (uint32_t)(out.wave.size() / 4);
         for (size_t block = xcd_block[x]; block < xcd_block[x + 1]; ++block)
             for (size_t i = block_at[block], e = block_at[block + 1]; i < e;) {
                 const uint32_t t = log_lanes(len_of(order[i])), T = 1u << t;
@@ -1530,41 +1529,42 @@ void pack_narrow(HostPlan& plan, int threads) {
                 uint32_t shortest = ~0u;
                 while (j < e && j - i < (S >> t) && log_lanes(len_of(order[j])) == t) shortest = std::min(shortest, len_of(order[j])), ++j;
                 const uint32_t steps = (len_of(order[i]) + T - 1) >> t, pairs = (steps + 1) / 2, full = std::min<uint32_t>(shortest >> t, 0xffffu);
-                plan.narrow_wave.insert(plan.narrow_wave.end(), {(uint32_t)first, steps, t | (uint32_t)(j - i) << 8 | full << 16, (uint32_t)i});
+                out.wave.insert(out.wave.end(), {(uint32_t)first, steps, t | (uint32_t)(j - i) << 8 | full << 16, (uint32_t)i});
                 first += (uint64_t)pairs * S;
                 i = j;
             }
     }
-    plan.narrow_split.start[8] = (uint32_t)(plan.narrow_wave.size() / 4);
-    plan.narrow_seg.resize(2 * order.size());
+    out.split.start[8] = (uint32_t)(out.wave.size() / 4);
+    out.seg.resize(2 * order.size());
     // every wave clears and fills its own slots: of memory that is touched first here, most of the time goes into that
     const size_t used = 2 * (size_t)first;
-    plan.narrow_slots = used + 2 * 64 * (size_t)kNarrowAhead;
-    plan.narrow_col.reset(new int32_t[plan.narrow_slots]);
-    plan.narrow_val.reset(new uint16_t[plan.narrow_slots]);
-    std::fill(&plan.narrow_col[used], &plan.narrow_col[0] + plan.narrow_slots, 0);
-    std::fill(&plan.narrow_val[used], &plan.narrow_val[0] + plan.narrow_slots, (uint16_t)0);
-    const int64_t n_waves = (int64_t)plan.narrow_wave.size() / 4;
+    out.slots = used + 2 * 64 * (size_t)kNarrowAhead;
+    out.col.reset(new int32_t[out.slots]);
+    out.val.reset(new uint16_t[out.slots]);
+    std::fill(&out.col[used], &out.col[0] + out.slots, 0);
+    std::fill(&out.val[used], &out.val[0] + out.slots, (uint16_t)0);
+    const int64_t n_waves = (int64_t)out.wave.size() / 4;
     parallel_dynamic(n_waves, threads, 256, [&](int64_t b, int64_t e, int) {
         for (int64_t w = b; w < e; ++w) {
-            const uint32_t* d = &plan.narrow_wave[4 * (size_t)w];
+            const uint32_t* d = &out.wave[4 * (size_t)w];
             const uint32_t t = d[2] & 0xffu, n = (d[2] >> 8) & 0xffu;
             const size_t mine = 2 * (size_t)d[0], slots = 2 * (size_t)S * ((d[1] + 1) / 2);
-            std::fill(&plan.narrow_col[mine], &plan.narrow_col[0] + mine + slots, 0);
-            std::fill(&plan.narrow_val[mine], &plan.narrow_val[0] + mine + slots, (uint16_t)0);
+            std::fill(&out.col[mine], &out.col[0] + mine + slots, 0);
+            std::fill(&out.val[mine], &out.val[0] + mine + slots, (uint16_t)0);
             for (uint32_t k = 0; k < n; ++k) {
                 const Segment& s = order[(size_t)d[3] + k];
-                plan.narrow_seg[2 * ((size_t)d[3] + k)] = s.dst;
-                plan.narrow_seg[2 * ((size_t)d[3] + k) + 1] = s.len;
+                out.seg[2 * ((size_t)d[3] + k)] = s.dst;
+                out.seg[2 * ((size_t)d[3] + k) + 1] = s.len;
                 for (uint32_t i = 0, len = len_of(s); i < len; ++i) {
                     const uint32_t j = i >> t, lane = (k << t) + (i & ((1u << t) - 1u));
                     const size_t to = 2 * ((size_t)d[0] + S * (size_t)(j / 2) + lane) + (j & 1);
-                    plan.narrow_col[to] = plan.irr_col[(size_t)s.start + i];
-                    plan.narrow_val[to] = plan.irr_val[(size_t)s.start + i];
+                    out.col[to] = plan.irr_col[(size_t)s.start + i];
+                    out.val[to] = plan.irr_val[(size_t)s.start + i];
                 }
             }
         }
     });
+    return out;
 }
 
 // ---------------------------------------------------------------------------
@@ -1615,7 +1615,35 @@ int decode_plan(const HostPlan& p, int64_t* row_ptr, int32_t* col_idx, uint16_t*
     std::vector<int32_t> slot_row((size_t)p.n_scratch_slots, -1);
     for (size_t c = 0; c + 3 < p.combine.size(); c += 4)
         for (uint32_t q = 0; q < p.combine[c + 2]; ++q) slot_row[p.combine[c + 1] + (size_t)q * p.combine[c + 3]] = (int32_t)p.combine[c];
-    for (size_t s = 0; s + 3 < p.irr_wave.size(); s += 4) {
+    if (p.geo.narrow) {   // as narrow.hpp takes them; what the device holds has left the plan and is made again
+        const NarrowPart again = p.narrow.wave.empty() ? pack_narrow(p, p.opts.threads > 0 ? p.opts.threads : hardware_threads()) : NarrowPart{};
+        const NarrowPart& part = p.narrow.wave.empty() ? again : p.narrow;
+        const uint32_t S = 64u / (uint32_t)p.geo.narrow;
+        std::vector<uint8_t> written((size_t)p.n_rows, 0);   // every row by its window, the combine pass or one segment
+        for (int32_t row : p.win_row)
+            if (row >= 0) written[(size_t)row] = 2;
+        for (size_t c = 0; c + 3 < p.combine.size(); c += 4) written[p.combine[c]] = 2;
+        for (uint32_t w = 0; w < part.split.start[8]; ++w) {
+            const uint32_t* d = &part.wave[4 * (size_t)w];
+            const uint32_t t = d[2] & 0xffu, n = (d[2] >> 8) & 0xffu, full = d[2] >> 16, T = 1u << t;
+            for (uint32_t k = 0; k < n; ++k) {
+                const uint32_t dst = part.seg[2 * ((size_t)d[3] + k)], len = part.seg[2 * ((size_t)d[3] + k) + 1];
+                const uint32_t entries = len & ~kSegmentToScratch;
+                const int32_t row = (len & kSegmentToScratch) ? slot_row[dst] : (int32_t)dst;
+                if (row < 0 || row >= p.n_rows || (!(len & kSegmentToScratch) && written[(size_t)row]++)) return RSH_ERR_INVALID_CSR;
+                for (uint32_t lane = 0; lane < T; ++lane) {
+                    const uint32_t mine = entries > lane ? (entries - lane + T - 1) >> t : 0u;
+                    if (mine > d[1] || mine < full || (k << t) + lane >= S) return RSH_ERR_INVALID_CSR;
+                    for (uint32_t j = 0; j < mine; ++j) {
+                        const size_t at = 2 * ((size_t)d[0] + S * (size_t)(j / 2) + (k << t) + lane) + (j & 1);
+                        ent.push_back({row, part.col[at], part.val[at], 1});
+                    }
+                }
+            }
+        }
+        if (std::count(written.begin(), written.end(), (uint8_t)0) != 0) return RSH_ERR_INVALID_CSR;
+    }
+    for (size_t s = 0; s + 3 < p.irr_wave.size() && !p.geo.narrow; s += 4) {
         const uint32_t start = p.irr_wave[s], count = p.irr_wave[s + 1], dst = p.irr_wave[s + 2], info = p.irr_wave[s + 3];
         const uint32_t kind = info & kWaveKindMask;
         if (kind == kWaveShortRows) {

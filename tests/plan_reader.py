@@ -23,6 +23,10 @@ are the words panel_ent[panel_off[u] .. panel_off[u+1]) with u = 2 * G * t0 + (g
 (t0 = win_tile_off[w], nt = the window's fragment count); a word is value bits | address << 16 with
 address = ((r + 32 * (k // 8)) * 8 + k % 8) * 2 for row r of the group and column k of the K step;
 units start at multiples of four words and are padded with words whose address is >= 1024.
+
+Lanes that own or share rows of B (F of them to a row): a wave (first, steps, info, first segment) has S = 64 / F
+places; segment k of it (destination, entries; bit 31 of the second word: a scratch slot) has places k T .. k T + T - 1,
+T = 2^(info & 255), entry e being entry j = e // T of place p = k T + e % T, at 2 (first + S (j // 2) + p) + j % 2.
 """
 from __future__ import annotations
 
@@ -123,3 +127,37 @@ def csr_from_entries(rows, cols, vals, paths, n_rows, n_cols):
     row_ptr = np.zeros(n_rows + 1, dtype=np.int64)
     np.cumsum(np.bincount(rows, minlength=n_rows), out=row_ptr[1:])
     return row_ptr, cols[order].astype(np.int32), vals[order], paths[order]
+
+
+def lane_entries(col, val, wave, seg, xcd, combine, row_lanes, n_scratch_slots, ahead=4):
+    """(rows, columns, value bits) of the residual part as lanes take it, and the rows of C that segments write.  Checks what the
+    kernel relies on: bounds of a wave's steps, segments and reads ahead of them, unused places, every segment in one wave."""
+    S = 64 // row_lanes
+    slot_row = np.full(max(1, n_scratch_slots), -1, dtype=np.int64)
+    for row, first, parts, stride in np.asarray(combine, dtype=np.int64).reshape(-1, 4):
+        slot_row[first + stride * np.arange(parts)] = row
+    wave, seg = np.asarray(wave, dtype=np.int64).reshape(-1, 4), np.asarray(seg, dtype=np.int64).reshape(-1, 2)
+    assert xcd[0] == 0 and xcd[8] == len(wave) and np.all(np.diff(xcd.astype(np.int64)) >= 0)
+    used, taken = np.zeros(col.size, dtype=bool), np.zeros(len(seg), dtype=int)
+    rows, at, written = [], [], []
+    for first, steps, info, seg0 in wave:
+        T, n, full = 1 << (info & 0xff), (info >> 8) & 0xff, info >> 16
+        assert 1 <= n and n * T <= S
+        assert 2 * (first + S * ((steps + 1) // 2) + 64 * ahead) <= col.size     # what the last turn reads ahead
+        taken[seg0:seg0 + n] += 1
+        for k in range(n):
+            dst, length = seg[seg0 + k, 0], seg[seg0 + k, 1] & 0x7fffffff
+            e = np.arange(length)
+            j, p = e // T, k * T + e % T
+            assert length <= steps * T and length // T >= full
+            to_scratch = seg[seg0 + k, 1] >> 31
+            rows.append(np.full(length, slot_row[dst] if to_scratch else dst))
+            at.append(2 * (first + S * (j // 2) + p) + j % 2)
+            if not to_scratch:
+                written.append(dst)
+    assert np.all(taken == 1)
+    rows, at = np.concatenate(rows), np.concatenate(at)
+    assert np.unique(at).size == at.size
+    used[at] = True
+    assert not col[~used].any() and not val[~used].any()
+    return rows, col[at], val[at], np.array(written, dtype=np.int64)

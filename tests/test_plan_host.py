@@ -729,3 +729,37 @@ def test_full_windows_of_narrow_rows(rows, full, windows):
     A = from_coo(hit[0], hit[0] // 16 * 137 % 20000 + hit[1], rng.standard_normal(hit[0].size), rows, 20100)
     st = host_plan(A, 4, reorder=0).stats()
     assert st["window_rows"] == 16 and (st["nnz_tile"] == A.nnz) == windows and st["nnz_tile"] in (0, A.nnz)
+
+
+# What the device holds for lanes, read as the kernel reads it: every entry once, every row written once.  Rows of 0 to 2000 entries,
+# few and many, sliced, cut by column group, the rows of windows that joined, entries that windows gave up.
+@pytest.mark.parametrize("N,rows,opts,lanes", [
+    (1, 90, {}, 1), (3, 90, dict(max_nnz_per_slice=40), 1), (8, 90, dict(xcd_partition_nnz=32), 1), (5, 90, dict(window_rows=16, min_reuse=0.0), 1),
+    (9, 90, dict(xcd_partition_nnz=32), 2), (16, 90, dict(window_rows=16, min_reuse=0.0), 2), (3, 20000, {}, 1), (12, 20000, {}, 2),
+    (24, 20000, dict(force_path=1), 4), (24, 20000, dict(force_path=1, max_nnz_per_slice=20), 4), (32, 20000, dict(force_path=1, xcd_partition_nnz=32), 4),
+    (48, 20000, dict(force_path=1), 8), (48, 20000, dict(force_path=1, max_nnz_per_slice=20), 8), (64, 20000, dict(force_path=1, xcd_partition_nnz=32), 8),
+    (12, 20000, dict(window_rows=16, force_path=2, element_level=1), 2)])
+def test_lanes_hold_every_entry_once(N, rows, opts, lanes):
+    rng = np.random.default_rng(13)
+    lengths = np.array([0, 1, 2, 3, 4, 5, 8, 9, 16, 17, 31, 32, 33, 63, 64, 65, 128, 129, 500, 2000])
+    if rows > 100:
+        lengths = lengths[lengths <= 65]
+    per_row = rng.permutation(np.resize(lengths, rows))
+    c = np.concatenate([rng.choice(3000, k, replace=False) if k > 100 else (rng.integers(0, 2900) + rng.permutation(100)[:k]) for k in per_row])
+    A = from_coo(np.repeat(np.arange(rows), per_row), c, rng.standard_normal(c.size), rows, 3000)
+    p = host_plan(A, N, **opts)
+    st = p.stats()
+    assert p.kernels()["row_lanes"] == lanes and st["nnz_irregular"] > 0
+    a = {n: p.array(getattr(B_, "RSH_ARR_NARROW_" + n)) for n in ("COL", "VAL", "WAVE", "SEG", "XCD")}
+    combine = p.array(B_.RSH_ARR_COMBINE)
+    r, c, v, written = rstile.lane_entries(a["COL"], a["VAL"], a["WAVE"], a["SEG"], a["XCD"], combine, lanes, st["n_scratch_slots"])
+    row_ptr, col_idx, val, path = p.decode()
+    order = np.lexsort((c, r))
+    of_lanes = path == 1
+    assert np.array_equal(np.repeat(np.arange(rows), np.diff(row_ptr))[of_lanes], r[order])
+    assert np.array_equal(col_idx[of_lanes], c[order]) and np.array_equal(val[of_lanes], v[order])
+    assert np.array_equal(row_ptr, A.row_ptr) and np.array_equal(col_idx, A.col_idx) and np.array_equal(val, A.val.view(np.uint16))
+    windows = p.array(B_.RSH_ARR_WIN_ROW)
+    everywhere = np.concatenate([written, np.unique(np.concatenate([windows[windows >= 0], combine[0::4]]))])
+    assert np.array_equal(np.sort(everywhere), np.arange(rows))
+    assert st["irregular_part_bytes"] == sum(a[n].nbytes for n in ("COL", "VAL", "WAVE", "SEG"))
