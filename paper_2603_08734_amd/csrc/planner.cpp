@@ -1457,30 +1457,41 @@ NarrowPart pack_narrow(const HostPlan& plan, int threads) {
     };
     const int64_t block_rows = plan.narrow_in_order ? 128 : 8192;
     constexpr uint64_t kShare = 6;   // cost of a segment beside its entries
-    std::vector<Segment> partial[8], direct;
+    constexpr uint32_t kNone = 0xffffffffu;
     const auto len_of = [](const Segment& s) { return s.len & ~kSegmentToScratch; };
-    uint64_t entries = 0;
-    for (int x = 0; x < 8; ++x)
-        for (uint32_t w = plan.irr_split.start[x]; w < plan.irr_split.start[x + 1]; ++w) {
-            const uint32_t* d = &plan.irr_wave[4 * (size_t)w];
-            const uint32_t kind = d[3] & kWaveKindMask, L = (d[3] >> 8) & 0xffu;
-            if (kind == kWaveSlice) {
-                const bool to_scratch = (d[3] & kWaveToScratch) != 0;
-                (to_scratch ? partial[x] : direct).push_back({d[2], d[1] | (to_scratch ? kSegmentToScratch : 0u), d[0]});
-                entries += d[1];
-            } else {   // rows of L entries, or of none
-                for (uint32_t i = 0; i < d[1]; ++i)
-                    direct.push_back({(uint32_t)plan.irr_row[(size_t)d[2] + i], kind == kWaveShortRows ? L : 0u, d[0] + i * (kind == kWaveShortRows ? L : 0u)});
-                if (kind == kWaveShortRows) entries += (uint64_t)d[1] * L;
+    // segments that write C by their row, which only one of them does, the others by XCD
+    std::unique_ptr<Segment[]> direct(new Segment[(size_t)plan.n_rows]);
+    parallel_chunks(plan.n_rows, threads, [&](int64_t b, int64_t e, int) {
+        for (int64_t r = b; r < e; ++r) direct[(size_t)r].len = kNone;
+    });
+    std::vector<Segment> partial[8];
+    uint64_t entries_of[8], costs[8];
+    parallel_chunks(8, std::min(threads, 8), [&](int64_t xb, int64_t xe, int) {
+        for (int64_t x = xb; x < xe; ++x) {
+            uint64_t n = 0, segments = 0;
+            for (uint32_t w = plan.irr_split.start[x]; w < plan.irr_split.start[x + 1]; ++w) {
+                const uint32_t* d = &plan.irr_wave[4 * (size_t)w];
+                const uint32_t kind = d[3] & kWaveKindMask, L = kind == kWaveShortRows ? (d[3] >> 8) & 0xffu : 0u;
+                if (kind == kWaveSlice) {
+                    if (d[3] & kWaveToScratch) partial[x].push_back({d[2], d[1] | kSegmentToScratch, d[0]});
+                    else direct[d[2]] = {d[2], d[1], d[0]};
+                    n += d[1];
+                    ++segments;
+                } else {   // rows of L entries, or of none
+                    for (uint32_t i = 0; i < d[1]; ++i) {
+                        const uint32_t row = (uint32_t)plan.irr_row[(size_t)d[2] + i];
+                        direct[row] = {row, L, d[0] + i * L};
+                    }
+                    n += (uint64_t)d[1] * L;
+                    segments += d[1];
+                }
             }
+            entries_of[x] = n;
+            costs[x] = n + kShare * segments;
         }
-    if (plan.narrow_in_order) {
-        std::vector<uint32_t> place((size_t)plan.n_rows);
-        for (size_t i = 0; i < plan.order.size(); ++i) place[(size_t)plan.order[i]] = (uint32_t)i;
-        parallel_sort(direct.begin(), direct.end(), threads, [&](const Segment& a, const Segment& b) { return place[a.dst] < place[b.dst]; });
-    } else {
-        parallel_sort(direct.begin(), direct.end(), threads, [](const Segment& a, const Segment& b) { return a.dst < b.dst; });
-    }
+    });
+    uint64_t entries = 0, cost = 0, run = 0;
+    for (int x = 0; x < 8; ++x) entries += entries_of[x], cost += costs[x];
     const uint32_t S = 64u / (uint32_t)plan.geo.narrow;   // rows of B that a wave takes at a time
     const uint32_t per_lane = (uint32_t)std::min<uint64_t>(16, std::max<uint64_t>(2, entries / (S * 4096)));
     const auto log_lanes = [per_lane, S](uint32_t len) {
@@ -1488,36 +1499,53 @@ NarrowPart pack_narrow(const HostPlan& plan, int threads) {
         while ((1u << t) < S && len > 2 * (per_lane << t)) ++t;
         return t;
     };
-    // contiguous eighths of the rows, by cost
-    uint64_t cost = 0, run = 0;
-    for (const Segment& s : direct) cost += len_of(s) + kShare;
-    for (int x = 0; x < 8; ++x)
-        for (const Segment& s : partial[x]) cost += len_of(s) + kShare;
     std::vector<Segment> order;
-    order.reserve(direct.size());
-    // blocks of segments: the partial sums of an XCD, then its run of rows in pieces of block_rows
+    order.reserve((size_t)plan.n_rows);
+    // blocks of segments: the partial sums of an XCD, then its run of rows, a contiguous eighth by cost, in pieces of block_rows
     std::vector<size_t> block_at{0};
     size_t xcd_block[9];
-    size_t at = 0;
+    int64_t at = 0;
+    const auto next_row = [&]() {   // of direct, from `at` on; nullptr behind the last
+        for (; at < plan.n_rows; ++at) {
+            const Segment& s = direct[plan.narrow_in_order ? (size_t)plan.order[(size_t)at] : (size_t)at];
+            if (s.len != kNone) return &s;
+        }
+        return (const Segment*)nullptr;
+    };
     for (int x = 0; x < 8; ++x) {
         xcd_block[x] = block_at.size() - 1;
         order.insert(order.end(), partial[x].begin(), partial[x].end());
         for (const Segment& s : partial[x]) run += len_of(s) + kShare;
         block_at.push_back(order.size());
-        while (at < direct.size() && (x == 7 || run * 8 < cost * (uint64_t)(x + 1))) {
-            const size_t block = order.size();
-            while (at < direct.size() && (int64_t)(order.size() - block) < block_rows && (x == 7 || run * 8 < cost * (uint64_t)(x + 1))) {
-                run += len_of(direct[at]) + kShare;
-                order.push_back(direct[at++]);
-            }
-            block_at.push_back(order.size());
+        const Segment* s;
+        while ((x == 7 || run * 8 < cost * (uint64_t)(x + 1)) && (s = next_row()) != nullptr) {
+            if ((int64_t)(order.size() - block_at.back()) == block_rows) block_at.push_back(order.size());
+            run += len_of(*s) + kShare;
+            order.push_back(*s);
+            ++at;
         }
+        block_at.push_back(order.size());
     }
     xcd_block[8] = block_at.size() - 1;
-    parallel_dynamic((int64_t)xcd_block[8], threads, 16, [&](int64_t b, int64_t e, int) {
-        for (int64_t i = b; i < e; ++i)
-            std::stable_sort(order.begin() + (int64_t)block_at[(size_t)i], order.begin() + (int64_t)block_at[(size_t)i + 1],
-                             [&](const Segment& p, const Segment& q) { return len_of(p) > len_of(q); });
+    // longest first, equal ones as they were
+    parallel_dynamic((int64_t)xcd_block[8], threads, 4, [&](int64_t b, int64_t e, int) {
+        std::vector<uint32_t> place;
+        std::vector<Segment> sorted;
+        for (int64_t i = b; i < e; ++i) {
+            const size_t lo = block_at[(size_t)i], hi = block_at[(size_t)i + 1];
+            uint32_t longest = 0;
+            for (size_t k = lo; k < hi; ++k) longest = std::max(longest, len_of(order[k]));
+            if (longest > 4096) {   // more places to count than it saves
+                std::stable_sort(order.begin() + (int64_t)lo, order.begin() + (int64_t)hi, [&](const Segment& p, const Segment& q) { return len_of(p) > len_of(q); });
+                continue;
+            }
+            place.assign((size_t)longest + 2, 0);
+            for (size_t k = lo; k < hi; ++k) ++place[longest - len_of(order[k]) + 1];
+            for (uint32_t k = 1; k <= longest; ++k) place[k] += place[k - 1];
+            sorted.resize(hi - lo);
+            for (size_t k = lo; k < hi; ++k) sorted[place[longest - len_of(order[k])]++] = order[k];
+            std::copy(sorted.begin(), sorted.end(), order.begin() + (int64_t)lo);
+        }
     });
     uint64_t first = 0;
     for (int x = 0; x < 8; ++x) {
