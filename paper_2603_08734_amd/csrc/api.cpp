@@ -289,7 +289,13 @@ int rsh_plan_create(const rsh_csr_t* csr, int32_t N, const rsh_plan_opts_t* opts
 
     const auto t_all = std::chrono::steady_clock::now();
     auto t0 = t_all;
-    int rc = rsh::validate_csr(*csr);
+    const int threads = o.threads > 0 ? o.threads : rsh::hardware_threads();
+    int rc;
+    try {
+        rc = rsh::validate_csr(*csr, threads);
+    } catch (...) {   // no room for a thread
+        return RSH_ERR_OOM;
+    }
     if (rc) return rc;
     // A^T: counting sort by column; rows are visited in ascending order, so the columns of every
     // row of A^T come out ascending and the result is canonical CSR again
@@ -330,7 +336,6 @@ int rsh_plan_create(const rsh_csr_t* csr, int32_t N, const rsh_plan_opts_t* opts
     if (!p) return RSH_ERR_OOM;
     try {
         rsh::HostPlan& h = p->host;
-        const int threads = o.threads > 0 ? o.threads : rsh::hardware_threads();
         h.n_rows = csr->n_rows;
         h.n_cols = csr->n_cols;
         h.nnz = csr->nnz;
@@ -636,11 +641,16 @@ int rsh_reorder_knn(const rsh_csr_t* csr, const rsh_plan_opts_t* opts, int32_t* 
     if (o.knn_k < 1 || o.knn_k > 64 || !(o.alpha > 0.f) || o.threads < 0 || o.device_scoring < 0 || o.device_scoring > 2 ||
         o.partition < 0 || o.partition > 1 || o.force_path < 0 || o.force_path > 2 || o.long_row_nnz < 0)
         return RSH_ERR_BAD_OPTION;
-    int rc = rsh::validate_csr(*csr);
+    const int threads = o.threads > 0 ? o.threads : rsh::hardware_threads();
+    int rc;
+    try {
+        rc = rsh::validate_csr(*csr, threads);
+    } catch (...) {
+        return RSH_ERR_OOM;
+    }
     if (rc) return rc;
     if (csr->nnz >= (1ll << 31) || csr->n_rows >= (1ll << 31) - 1 || csr->n_cols >= (1ll << 31)) return RSH_ERR_TOO_LARGE;
     try {
-        const int threads = o.threads > 0 ? o.threads : rsh::hardware_threads();
         if (o.device_scoring == 2) o.device_scoring = csr->n_rows >= kDeviceScoringRows ? 1 : 0;
         if (o.window_rows == 0) o.window_rows = rsh::kW;
         std::vector<int32_t> col_deg, order;

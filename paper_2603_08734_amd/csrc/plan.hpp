@@ -106,7 +106,7 @@ struct Partition {
 };
 
 // Stages (planner.cpp / reorder.cpp).  All return an RSH_* status.
-int validate_csr(const rsh_csr_t& a);
+int validate_csr(const rsh_csr_t& a, int threads);
 void column_degrees(const rsh_csr_t& a, std::vector<int32_t>& deg, int threads);
 void estimate_threshold(int64_t n_rows, int64_t nnz, int32_t* tau_nnz, int32_t* tau_inc);
 // Keeps the text of the HIP runtime's last error for rsh_last_hip_error (calling thread) and clears it.

@@ -50,27 +50,48 @@ Geometry make_geometry(int N, int window_rows, int tile_k) {
 // ---------------------------------------------------------------------------
 // validation and column degrees (d_j of Section 3.4)
 // ---------------------------------------------------------------------------
-int validate_csr(const rsh_csr_t& a) {
+int validate_csr(const rsh_csr_t& a, int threads) {
     if (a.n_rows < 0 || a.n_cols < 0 || a.nnz < 0) return RSH_ERR_INVALID_CSR;
     if (!a.row_ptr) return RSH_ERR_NULL;
     if (a.nnz > 0 && (!a.col_idx || !a.val_f16)) return RSH_ERR_NULL;
     if (a.row_ptr[0] != 0 || a.row_ptr[a.n_rows] != a.nnz) return RSH_ERR_INVALID_CSR;
-    for (int64_t i = 0; i < a.n_rows; ++i) {
-        const int64_t b = a.row_ptr[i], e = a.row_ptr[i + 1];
-        if (e < b || e > a.nnz) return RSH_ERR_INVALID_CSR;
-        int64_t prev = -1;
-        for (int64_t p = b; p < e; ++p) {
-            const int64_t c = a.col_idx[p];
-            if (c <= prev || c >= a.n_cols) return RSH_ERR_INVALID_CSR;
-            prev = c;
+    std::atomic<bool> valid{true};
+    parallel_dynamic(a.n_rows, a.n_rows + a.nnz < 65536 ? 1 : threads, 4096, [&](int64_t first, int64_t last, int) {
+        for (int64_t i = first; i < last; ++i) {
+            const int64_t b = a.row_ptr[i], e = a.row_ptr[i + 1];
+            bool ok = b >= 0 && e >= b && e <= a.nnz;   // a row is read only where it lies in the arrays
+            int64_t prev = -1;
+            for (int64_t p = b; ok && p < e; ++p) {
+                const int64_t c = a.col_idx[p];
+                ok = c > prev && c < a.n_cols;
+                prev = c;
+            }
+            if (!ok) {
+                valid = false;
+                return;
+            }
         }
-    }
-    return RSH_OK;
+    });
+    return valid ? RSH_OK : RSH_ERR_INVALID_CSR;
 }
 
-void column_degrees(const rsh_csr_t& a, std::vector<int32_t>& deg, int) {
+void column_degrees(const rsh_csr_t& a, std::vector<int32_t>& deg, int threads) {
     deg.assign((size_t)a.n_cols, 0);
-    for (int64_t p = 0; p < a.nnz; ++p) ++deg[a.col_idx[p]];
+    // a table of its own for every thread but the first, as long as clearing and adding them costs less than the counting
+    const int64_t parts = a.nnz < 65536 ? 1 : std::max<int64_t>(1, std::min<int64_t>(threads, a.nnz / (4 * a.n_cols)));
+    std::vector<std::vector<int32_t>> more((size_t)parts - 1);
+    parallel_chunks(parts, (int)parts, [&](int64_t b, int64_t e, int) {
+        for (int64_t t = b; t < e; ++t) {
+            if (t > 0) more[(size_t)t - 1].assign((size_t)a.n_cols, 0);
+            int32_t* count = t > 0 ? more[(size_t)t - 1].data() : deg.data();
+            for (int64_t p = a.nnz * t / parts; p < a.nnz * (t + 1) / parts; ++p) ++count[a.col_idx[p]];
+        }
+    });
+    if (parts > 1)
+        parallel_chunks(a.n_cols, threads, [&](int64_t b, int64_t e, int) {
+            for (const auto& m : more)
+                for (int64_t c = b; c < e; ++c) deg[(size_t)c] += m[(size_t)c];
+        });
 }
 
 // The paper names an estimator but does not define it; it only says the row-length

@@ -763,3 +763,29 @@ def test_lanes_hold_every_entry_once(N, rows, opts, lanes):
     everywhere = np.concatenate([written, np.unique(np.concatenate([windows[windows >= 0], combine[0::4]]))])
     assert np.array_equal(np.sort(everywhere), np.arange(rows))
     assert st["irregular_part_bytes"] == sum(a[n].nbytes for n in ("COL", "VAL", "WAVE", "SEG"))
+
+
+# Large enough for several threads: a fault in any of their pieces is found, row starts outside the arrays are not followed.
+@pytest.mark.parametrize("row", [0, 4095, 4096, 30000, 49999])
+@pytest.mark.parametrize("threads", [1, 5])
+def test_invalid_rows_of_a_large_matrix(row, threads):
+    rows, cols = 50000, 1000
+    rng = np.random.default_rng(1)
+    c = np.sort(rng.permuted(np.tile(np.arange(20), (rows, 1)), axis=1)[:, :4] * 50, axis=1)
+    A = from_coo(np.repeat(np.arange(rows), 4), c.ravel(), np.ones(4 * rows), rows, cols)
+
+    def status(row_ptr, col_idx):
+        try:
+            Plan(row_ptr, col_idx, A.val, cols, 16, upload=0, threads=threads, reorder=0).destroy()
+        except RshError as e:
+            return e.status
+        return B_.RSH_OK
+    assert status(A.row_ptr, A.col_idx) == B_.RSH_OK
+    for at, bad in ((4 * row + 3, cols), (4 * row, -1), (4 * row + 1, A.col_idx[4 * row])):
+        col_idx = A.col_idx.copy()
+        col_idx[at] = bad
+        assert status(A.row_ptr, col_idx) == B_.RSH_ERR_INVALID_CSR
+    for bad in (-(1 << 40), A.nnz + 1, 1 << 40):
+        row_ptr = A.row_ptr.copy()
+        row_ptr[min(row + 1, rows - 1)] = bad
+        assert status(row_ptr, A.col_idx) == B_.RSH_ERR_INVALID_CSR
