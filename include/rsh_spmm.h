@@ -167,6 +167,10 @@ int rsh_plan_opts_default(rsh_plan_opts_t *opts);
  * it needs; the CSR arrays may be freed after the call.  With opts->upload != 0
  * the device arrays and the plan's private scratch are allocated on the current
  * HIP device.  opts == NULL means defaults.
+ * Windows of 256 rows (chosen or asked for) at N > 128 with at least one cell in sixteen stored are written out cell by cell on
+ * the device, 512 bytes per row and 256 columns of a window (rsh_plan_stats' tile_part_bytes counts them; 470 MB for a
+ * 28672 x 8192 weight, 2.6 times the packed entries; at one cell in sixteen 32 bytes an entry).  A device without room for
+ * them and the plan's other arrays gets the packed entries; window_rows = 128 asks for those.
  * Limits: nnz and n_rows must be below 2^31, n_cols * (2 NR) below 2^32 (NR = the run width,
  * below); otherwise RSH_ERR_TOO_LARGE.
  * Feature width: the kernels take rows of any even number of features from 16 on, in feature panels of

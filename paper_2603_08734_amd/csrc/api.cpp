@@ -124,7 +124,7 @@ void free_device(rsh::DevicePlan& d) {
 
 // The entries of a panel-form plan are turned on the device into the form the kernel reads (panel.hpp, wide.hpp);
 // what was uploaded for that is given back.
-int upload_panel_units(Uploader& up, rsh::HostPlan& h, rsh::DevicePlan& d) {
+int upload_panel_units(Uploader& up, const rsh::HostPlan& h, rsh::DevicePlan& d) {
     const int64_t n_windows = (int64_t)h.win_tile_off.size() - 1, n_units = (int64_t)h.panel_off.size() - 1;
     int rc;
     if (n_units <= 0) return RSH_OK;
@@ -143,15 +143,9 @@ int upload_panel_units(Uploader& up, rsh::HostPlan& h, rsh::DevicePlan& d) {
     if ((rc = upload_array(up, h.panel_ent, &d.panel_ent))) return rc;
     if (h.geo.wide) {
         d.n_tiles = h.win_tile_off[(size_t)n_windows];
-        if (hip_ok(hipMalloc((void**)&d.panel_cells, (2 * (size_t)d.n_tiles + 1) * rsh::kWideStepBytes))) {
-            if ((rc = rsh::launch_wide_cells(d, n_windows, up.stream))) return rc;
-            return hip_ok(hipStreamSynchronize(up.stream)) ? RSH_OK : RSH_ERR_HIP;
-        }
-        // no room for every cell: the same items run on the packed form
-        const int64_t written_out = rsh::panel_device_bytes(h);
-        h.geo.wide = d.geo.wide = 0;
-        const int64_t less = written_out - rsh::panel_device_bytes(h);
-        for (int64_t* bytes : {&h.stats.plan_bytes, &h.stats.tile_part_bytes, &h.stats.bytes_method, &h.stats.bytes_method_element_level}) *bytes -= less;
+        if (!hip_ok(hipMalloc((void**)&d.panel_cells, (2 * (size_t)d.n_tiles + 1) * rsh::kWideStepBytes))) return RSH_ERR_OOM;
+        if ((rc = rsh::launch_wide_cells(d, n_windows, up.stream))) return rc;
+        return hip_ok(hipStreamSynchronize(up.stream)) ? RSH_OK : RSH_ERR_HIP;
     }
     std::vector<uint32_t> quad0((size_t)n_windows + 1, 0);
     for (int64_t w = 0; w < n_windows; ++w)
@@ -171,10 +165,12 @@ int upload_panel_units(Uploader& up, rsh::HostPlan& h, rsh::DevicePlan& d) {
     return hip_ok(hipStreamSynchronize(up.stream)) ? RSH_OK : RSH_ERR_HIP;
 }
 
-int upload_plan(rsh_plan& p) {
+int upload_arrays(rsh_plan& p) {
     rsh::HostPlan& h = p.host;
     rsh::DevicePlan& d = p.dev;
     d.geo = h.geo;
+    d.n_user = h.n_user;
+    d.n_cols = h.n_cols;
     d.n_tile_items = (int64_t)h.tile_item.size() / 4;
     d.n_irr_waves = (int64_t)(h.geo.narrow ? h.narrow.wave : h.irr_wave).size() / 4;
     d.n_combine = (int64_t)h.combine.size() / 4;
@@ -228,6 +224,19 @@ int upload_plan(rsh_plan& p) {
     if (!hip_ok(hipGetDevice(&p.device))) return RSH_ERR_HIP;
     p.uploaded = true;
     return RSH_OK;
+}
+
+int upload_plan(rsh_plan& p) {
+    int rc = upload_arrays(p);
+    rsh::HostPlan& h = p.host;
+    if (rc != RSH_ERR_OOM || !h.geo.wide) return rc;
+    // no room beside cells written out: the same items run on the packed form
+    free_device(p.dev);
+    const int64_t written_out = rsh::panel_device_bytes(h);
+    h.geo.wide = 0;
+    const int64_t less = written_out - rsh::panel_device_bytes(h);
+    for (int64_t* bytes : {&h.stats.plan_bytes, &h.stats.tile_part_bytes, &h.stats.bytes_method, &h.stats.bytes_method_element_level}) *bytes -= less;
+    return upload_arrays(p);
 }
 
 // The width the kernels run at when the caller leaves the choice open: the next multiple of 16.
@@ -403,8 +412,6 @@ int rsh_plan_create(const rsh_csr_t* csr, int32_t N, const rsh_plan_opts_t* opts
         h.stats.tau_inc = tau_inc;
 
         t0 = std::chrono::steady_clock::now();
-        p->dev.n_user = n_user;
-        p->dev.n_cols = h.n_cols;
         if (o.upload) {
             rc = upload_plan(*p);
             if (rc) throw rc;
