@@ -32,6 +32,13 @@ ABLATIONS = {
 }
 
 
+def kernel_names(plan):
+    """The kernels that a plan's dense-fragment part and its residual part run in."""
+    runs = plan.kernels()
+    tile = "rsh_wide_kernel" if runs["cells_written"] else "rsh_panel_kernel" if plan.stats()["window_rows"] >= 128 else "rsh_tile_kernel"
+    return tile, {0: "rsh_irregular_kernel", 1: "rsh_narrow_kernel"}.get(runs["row_lanes"], "rsh_shared_kernel")
+
+
 def ablation(args, A, N, B_np) -> int:
     """One plan + timed SpMM per setting; everything else at its default."""
     import numpy as np
@@ -169,13 +176,7 @@ def main() -> int:
             acc[k] += t[k]
     kernel_ms = {k: v / n_prof for k, v in acc.items()}
     dominant = max(("tile", "irregular"), key=lambda k: kernel_ms[k])
-    # the dense-fragment part runs in the panel kernel for windows of 128 rows and more, with its cells written out beyond
-    # 128 features where one cell in sixteen is stored
-    wide = st["window_rows"] == 256 and N > 128 and st["nnz_tile"] * 16 >= st["n_tiles"] * 32 * 256
-    tile_kernel = "rsh_wide_kernel" if wide else "rsh_panel_kernel" if st["window_rows"] >= 128 else "rsh_tile_kernel"
-    # residual rows of few features: lanes own or share rows of B (power-law rows of medium length in plans of 2^18 entries)
-    shared = (N <= 48 or N == 64) and st["nnz_irregular"] >= 1 << 18
-    residual_kernel = "rsh_narrow_kernel" if N <= 16 else "rsh_shared_kernel" if shared else "rsh_irregular_kernel"
+    tile_kernel, residual_kernel = kernel_names(plan)
     kernel_name = residual_kernel if dominant == "irregular" else tile_kernel
     if dominant == "irregular":
         alg_bytes = st["irregular_part_bytes"] + 2 * N * st["cols_irregular"] + 4 * N * st["rows_irregular"]

@@ -2,7 +2,12 @@
 feature width, plan options and library sources it is timing (paper_2603_08734_amd/profiles.py)."""
 import json
 
-from paper_2603_08734_amd import build, profiles
+import numpy as np
+import pytest
+
+import bench
+from paper_2603_08734_amd import Plan, build, profiles
+from workloads import from_coo
 
 
 def _write(dirname, name, **over):
@@ -49,3 +54,22 @@ def test_kernel_names_keep_what_follows_an_anonymous_namespace():
     assert profiles._short("void rsh::(anonymous namespace)::rsh_panel_kernel<4, 8, false, rsh::OutPlainT<false> >(uint4 const*, int)") == \
         "rsh::rsh_panel_kernel<4, 8, false, rsh::OutPlainT<false> >"
     assert profiles._short("rsh::rsh_copy_probe_kernel(uint4 const*)") == "rsh::rsh_copy_probe_kernel"
+
+
+@pytest.mark.parametrize("lengths,N,opts,names", [
+    ({5: 60000}, 48, dict(force_path=1), ("rsh_tile_kernel", "rsh_irregular_kernel")),      # 2^18 entries, no row of medium length
+    ({12: 30000}, 56, dict(force_path=1), ("rsh_tile_kernel", "rsh_shared_kernel")),
+    ({12: 300}, 12, dict(force_path=1), ("rsh_tile_kernel", "rsh_shared_kernel")),
+    ({12: 300}, 8, dict(force_path=1), ("rsh_tile_kernel", "rsh_narrow_kernel")),
+    ({300: 512}, 256, dict(window_rows=256, force_path=2), ("rsh_wide_kernel", "rsh_irregular_kernel")),
+    ({300: 512}, 256, dict(window_rows=128, force_path=2), ("rsh_panel_kernel", "rsh_irregular_kernel")),
+])
+def test_bench_names_the_kernels_that_the_plan_runs(lengths, N, opts, names):
+    rng = np.random.default_rng(1)
+    per_row = np.repeat(list(lengths), list(lengths.values()))
+    r = np.repeat(np.arange(per_row.size), per_row)
+    c = np.concatenate([np.arange(k) for k in per_row]) * 4 + rng.integers(0, 4, r.size)
+    A = from_coo(r, c, rng.standard_normal(r.size), per_row.size, 2000)
+    plan = Plan(A.row_ptr, A.col_idx, A.val, A.n_cols, N, upload=0, reorder=0, **opts)
+    assert bench.kernel_names(plan) == names
+    plan.destroy()
