@@ -178,8 +178,9 @@ int rsh_plan_opts_default(rsh_plan_opts_t *opts);
  * columns (tile kernel; the last panel ends with the row), one pass over the matrix per panel.  B, C and
  * bias then need 16-byte alignment where N is a multiple of 16, else 4-byte alignment.  For other widths
  * (odd ones, those below 16, a run_width the caller chose, operands with less alignment) the kernels run at
- * a width NR > N (plans of up to 16 features without windows: the next power of two, and where N is one and B is aligned to
- * its rows, N): whenever N is not a multiple of 16 (or opts->run_width asks for it) the plan owns a
+ * a width NR > N (plans of up to 8 features without windows at a run width of 16: the next power of two, and where N is one
+ * and B is aligned to its rows, N; small plans of tall windows alone read rows of fewer than 16 features where they lie;
+ * rsh_plan_operand answers for a plan): whenever N is not a multiple of 16 (or opts->run_width asks for it) the plan owns a
  * binary16 buffer [n_cols][NR] on the device, and such a product first copies B into it (pad columns zero);
  * the kernels then store the N columns of the result into C themselves.  B, C and bias then only need the
  * alignment of their element type.  Results are the same, column for column; the cost is one more pass over B.

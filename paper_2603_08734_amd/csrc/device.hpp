@@ -52,7 +52,7 @@ __device__ __forceinline__ double shfl_f64(double v, int src_lane) {
 // Value held by lane (l ^ 8): rotation by 8 inside each row of 16 lanes.
 __device__ __forceinline__ int swap_lane8(int v) { return __builtin_amdgcn_update_dpp(0, v, 0x128, 0xf, 0xf, false); }
 
-// Sum of v over the lanes that differ from this one by a multiple of TPR (TPR = 2, 4, 8, 16):
+// Sum of v over the lanes that differ from this one by a multiple of TPR (TPR = 4, 8, 16):
 // after the call every lane holds the sum of its counterparts in all 64 / TPR teams.  Inside a
 // row of 16 lanes v += v rotated by 8, 4, ... TPR lanes (DPP row_ror); across rows a cross-lane
 // read of lane ^ 16 and lane ^ 32.  (v_permlane16_swap / v_permlane32_swap do the second part in
@@ -60,8 +60,8 @@ __device__ __forceinline__ int swap_lane8(int v) { return __builtin_amdgcn_updat
 template <int TPR>
 __device__ __forceinline__ float sum_over_teams(float v, int lane) {
     if constexpr (TPR <= 8) v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x128, 0xf, 0xf, false));
+    static_assert(TPR >= 4);
     if constexpr (TPR <= 4) v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x124, 0xf, 0xf, false));
-    if constexpr (TPR <= 2) v += __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x122, 0xf, 0xf, false));
     v += shfl_f32(v, lane ^ 16);
     v += shfl_f32(v, lane ^ 32);
     return v;

@@ -735,9 +735,8 @@ __global__ __launch_bounds__(256) void rsh_copy_probe_kernel(const uint4* __rest
 }
 
 // ---------------------------------------------------------------------------
-// Rows of B that the kernels do not read as they are (an odd number of features, fewer than 16, a run width the
-// caller chose, or an address that is not a multiple of 4) are copied into the plan's buffer of the run width; the
-// result needs no copy, whatever its width.  One thread makes one 16-byte piece of a wide row, from one load at
+// Rows of B that the kernels do not read as they are (copies_operand in api.cpp) are copied into the plan's buffer, at
+// the run width or, where lanes own rows, at the next power of two from 4 on; the result needs no copy, whatever its width.  One thread makes one 16-byte piece of a wide row, from one load at
 // whatever alignment the narrow row has (2 bytes: 59 cycles of the vector memory path per wave instead of 16,
 // which is still twice what memory delivers); only the piece that holds the row's end is put together from
 // single elements.  One thread per element, with a 64-bit division each, took 12.6 us for 512000 rows of 3 -> 16.

@@ -35,11 +35,11 @@ struct DevicePlan {
     uint32_t* narrow_seg = nullptr;    // geo.narrow: irr_col, irr_val and irr_wave are those of narrow.hpp, which has no irr_row
     uint32_t* combine = nullptr;
     float* scratch = nullptr;
-    // rows of B that the kernels cannot read as they are pass through this plan-owned buffer of the run width
-    // (made where n_user != geo.N)
+    // rows of B that the kernels cannot read as they are pass through this plan-owned buffer, at the run width or, for lanes
+    // that own rows, at 4 or 8 features (made where n_user != geo.N)
     int n_user = 0;
     int64_t n_cols = 0;
-    void* b_pad = nullptr;      // binary16 [n_cols][geo.N]
+    void* b_pad = nullptr;      // binary16, room for [n_cols][geo.N]
     // optional second stream for the dense-fragment kernel (rsh_plan_opts_t::side_stream)
     void* side = nullptr;       // hipStream_t
     void* ev_fork = nullptr;    // hipEvent_t: caller's stream -> side stream

@@ -1,4 +1,4 @@
-// What the kernels of tall windows (panel.hpp, wide.hip) share.
+// What the kernels of tall windows (panel.hpp, wide.hpp) share.
 #pragma once
 #include "device.hpp"
 

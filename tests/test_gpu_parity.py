@@ -375,8 +375,7 @@ def test_transposed_product(k):
 def test_feature_widths_that_the_kernels_do_not_run_at(N, run_width, mode):
     """Any width runs at a multiple of 16 (chosen by the planner or given) through the plan's padded
     buffers: plain and fused entry points against the oracle, on tensors whose rows are not 16-byte
-    aligned.  The pairs with run_width == N keep the narrow-panel kernels (two or four lanes per row,
-    several panels) under test, which the planner's own choice avoids."""
+    aligned.  The pairs with run_width == N need no copy."""
     from oracle import gcn as oracle_gcn
     torch = _torch()
     from paper_2603_08734_amd import Plan
