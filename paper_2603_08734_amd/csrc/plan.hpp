@@ -167,8 +167,8 @@ inline int64_t long_row_threshold(const rsh_csr_t& a, const rsh_plan_opts_t& o) 
 #include <mutex>
 #include <thread>
 namespace rsh {
-// Runs body(t) for t = 0 .. threads-1 on as many threads and joins them.  An exception thrown by a
-// body (std::bad_alloc from a worker's own buffers) is kept and rethrown on the calling thread
+// Runs body(t) for t = 0 .. threads-1 on as many threads, or on those that could be started and the calling one, and joins
+// them.  An exception thrown by a body (std::bad_alloc from a worker's own buffers) is kept and rethrown on the calling thread
 // after the join, so that it reaches the caller's handlers instead of ending the process.
 template <class Body>
 void run_workers(int threads, Body body) {
@@ -176,15 +176,20 @@ void run_workers(int threads, Body body) {
     std::mutex guard;
     std::vector<std::thread> pool;
     pool.reserve((size_t)threads);
-    for (int t = 0; t < threads; ++t)
-        pool.emplace_back([&, t]() {
-            try {
-                body(t);
-            } catch (...) {
-                std::lock_guard<std::mutex> lock(guard);
-                if (!first) first = std::current_exception();
-            }
-        });
+    const auto run = [&](int t) {
+        try {
+            body(t);
+        } catch (...) {
+            std::lock_guard<std::mutex> lock(guard);
+            if (!first) first = std::current_exception();
+        }
+    };
+    int started = 0;
+    try {
+        for (; started < threads; ++started) pool.emplace_back(run, started);
+    } catch (...) {   // no room for another thread: the rest runs here
+    }
+    for (int t = started; t < threads; ++t) run(t);
     for (auto& th : pool) th.join();
     if (first) std::rethrow_exception(first);
 }

@@ -2,6 +2,7 @@
 import ctypes
 import os
 import subprocess
+import sys
 
 import numpy as np
 import pytest
@@ -789,3 +790,37 @@ def test_invalid_rows_of_a_large_matrix(row, threads):
         row_ptr = A.row_ptr.copy()
         row_ptr[min(row + 1, rows - 1)] = bad
         assert status(row_ptr, A.col_idx) == B_.RSH_ERR_INVALID_CSR
+
+
+# Threads that cannot be started: the plan is made by those that are there, or refused for lack of memory; the process goes on.
+FEW_THREADS = r"""
+import resource, sys
+import numpy as np
+sys.path.insert(0, sys.argv[1])
+from paper_2603_08734_amd import Plan, RshError, binding
+from workloads import from_coo
+rng = np.random.default_rng(0)
+r = np.repeat(np.arange(20000), 12)
+A = from_coo(r, 1000 * np.tile(np.arange(12), 20000) + rng.integers(0, 1000, r.size), rng.standard_normal(r.size), 20000, 12000)
+make = lambda threads: Plan(A.row_ptr, A.col_idx, A.val, A.n_cols, 32, upload=0, reorder=0, threads=threads)
+make(1).destroy()
+with open("/proc/self/statm") as f:
+    used = int(f.read().split()[0]) * resource.getpagesize()
+resource.setrlimit(resource.RLIMIT_AS, (used + (int(sys.argv[2]) << 20),) * 2)
+try:
+    p = make(256)
+    row_ptr, col_idx, val, _ = p.decode()
+    assert np.array_equal(row_ptr, A.row_ptr) and np.array_equal(col_idx, A.col_idx) and np.array_equal(val, A.val.view(np.uint16))
+    print("made")
+except RshError as e:
+    assert e.status == binding.RSH_ERR_OOM, e
+    print("refused")
+"""
+
+
+@pytest.mark.parametrize("room", [1, 48, 400])     # MB: of stacks of 8 MB none, a few, some of 256
+def test_threads_that_cannot_be_started(room):
+    root = os.path.join(os.path.dirname(os.path.abspath(__file__)), "..")
+    done = subprocess.run([sys.executable, "-c", FEW_THREADS, root, str(room)], capture_output=True, text=True, timeout=120)
+    assert done.returncode == 0 and done.stdout.strip() in ("made", "refused"), done.stderr[-2000:]
+    assert room < 400 or done.stdout.strip() == "made"
