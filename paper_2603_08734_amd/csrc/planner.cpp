@@ -56,7 +56,7 @@ int validate_csr(const rsh_csr_t& a, int threads) {
     if (a.nnz > 0 && (!a.col_idx || !a.val_f16)) return RSH_ERR_NULL;
     if (a.row_ptr[0] != 0 || a.row_ptr[a.n_rows] != a.nnz) return RSH_ERR_INVALID_CSR;
     std::atomic<bool> valid{true};
-    parallel_dynamic(a.n_rows, a.n_rows + a.nnz < 65536 ? 1 : threads, 4096, [&](int64_t first, int64_t last, int) {
+    parallel_dynamic(a.n_rows, threads_for(a.n_rows + a.nnz, threads), 4096, [&](int64_t first, int64_t last, int) {
         for (int64_t i = first; i < last; ++i) {
             const int64_t b = a.row_ptr[i], e = a.row_ptr[i + 1];
             bool ok = b >= 0 && e >= b && e <= a.nnz;   // a row is read only where it lies in the arrays
@@ -78,7 +78,7 @@ int validate_csr(const rsh_csr_t& a, int threads) {
 void column_degrees(const rsh_csr_t& a, std::vector<int32_t>& deg, int threads) {
     deg.assign((size_t)a.n_cols, 0);
     // a table of its own for every thread but the first, as long as clearing and adding them costs less than the counting
-    const int64_t parts = a.nnz < 65536 ? 1 : std::max<int64_t>(1, std::min<int64_t>(threads, a.nnz / (4 * a.n_cols)));
+    const int64_t parts = a.nnz < 2 * 65536 ? 1 : std::max<int64_t>(1, std::min<int64_t>(threads_for(a.nnz, threads), a.nnz / (4 * a.n_cols)));
     std::vector<std::vector<int32_t>> more((size_t)parts - 1);
     parallel_chunks(parts, (int)parts, [&](int64_t b, int64_t e, int) {
         for (int64_t t = b; t < e; ++t) {
@@ -88,7 +88,7 @@ void column_degrees(const rsh_csr_t& a, std::vector<int32_t>& deg, int threads) 
         }
     });
     if (parts > 1)
-        parallel_chunks(a.n_cols, threads, [&](int64_t b, int64_t e, int) {
+        parallel_chunks(a.n_cols, threads_for(a.n_cols * parts, threads), [&](int64_t b, int64_t e, int) {
             for (const auto& m : more)
                 for (int64_t c = b; c < e; ++c) deg[(size_t)c] += m[(size_t)c];
         });
@@ -1400,6 +1400,7 @@ int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int thr
 bool narrow_pays(const rsh_csr_t& a, const Partition& part, int n) {
     if (n > kNarrow / 2 || part.win_row.empty()) return false;
     const int64_t row_bytes = 2 * narrow_width(n);
+    if (a.nnz < (1 << 22) && a.n_cols * row_bytes <= (int64_t)3 << 20) return true;   // whatever is in the windows (4 ms for 512 of them)
     const int64_t n_win = (int64_t)part.win_row.size() / kW, step = std::max<int64_t>(1, n_win / 512);
     int64_t windows = 0, entries = 0, columns = 0, lines = 0;   // of the sample
     std::vector<int32_t> cols;
@@ -1482,12 +1483,12 @@ NarrowPart pack_narrow(const HostPlan& plan, int threads) {
     const auto len_of = [](const Segment& s) { return s.len & ~kSegmentToScratch; };
     // segments that write C by their row, which only one of them does, the others by XCD
     std::unique_ptr<Segment[]> direct(new Segment[(size_t)plan.n_rows]);
-    parallel_chunks(plan.n_rows, threads, [&](int64_t b, int64_t e, int) {
+    parallel_chunks(plan.n_rows, threads_for(2 * plan.n_rows, threads), [&](int64_t b, int64_t e, int) {
         for (int64_t r = b; r < e; ++r) direct[(size_t)r].len = kNone;
     });
     std::vector<Segment> partial[8];
     uint64_t entries_of[8], costs[8];
-    parallel_chunks(8, std::min(threads, 8), [&](int64_t xb, int64_t xe, int) {
+    parallel_chunks(8, threads_for(4 * plan.n_rows, std::min(threads, 8)), [&](int64_t xb, int64_t xe, int) {
         for (int64_t x = xb; x < xe; ++x) {
             uint64_t n = 0, segments = 0;
             for (uint32_t w = plan.irr_split.start[x]; w < plan.irr_split.start[x + 1]; ++w) {
@@ -1549,7 +1550,7 @@ NarrowPart pack_narrow(const HostPlan& plan, int threads) {
     }
     xcd_block[8] = block_at.size() - 1;
     // longest first, equal ones as they were
-    parallel_dynamic((int64_t)xcd_block[8], threads, 4, [&](int64_t b, int64_t e, int) {
+    parallel_dynamic((int64_t)xcd_block[8], threads_for(8 * (int64_t)order.size(), threads), 4, [&](int64_t b, int64_t e, int) {
         std::vector<uint32_t> place;
         std::vector<Segment> sorted;
         for (int64_t i = b; i < e; ++i) {
@@ -1593,7 +1594,7 @@ NarrowPart pack_narrow(const HostPlan& plan, int threads) {
     std::fill(&out.col[used], &out.col[0] + out.slots, 0);
     std::fill(&out.val[used], &out.val[0] + out.slots, (uint16_t)0);
     const int64_t n_waves = (int64_t)out.wave.size() / 4;
-    parallel_dynamic(n_waves, threads, 256, [&](int64_t b, int64_t e, int) {
+    parallel_dynamic(n_waves, threads_for(2 * (int64_t)out.slots, threads), 256, [&](int64_t b, int64_t e, int) {
         for (int64_t w = b; w < e; ++w) {
             const uint32_t* d = &out.wave[4 * (size_t)w];
             const uint32_t t = d[2] & 0xffu, n = (d[2] >> 8) & 0xffu;
