@@ -35,7 +35,7 @@ ABLATIONS = {
 def kernel_names(plan):
     """The kernels that a plan's dense-fragment part and its residual part run in."""
     runs = plan.kernels()
-    tile = "rsh_wide_kernel" if runs["cells_written"] else "rsh_panel_kernel" if plan.stats()["window_rows"] >= 128 else "rsh_tile_kernel"
+    tile = "rsh_wide_kernel" if runs["cells_written"] else "rsh_strip_kernel" if plan.strip() else "rsh_panel_kernel" if plan.stats()["window_rows"] >= 128 else "rsh_tile_kernel"
     return tile, {0: "rsh_irregular_kernel", 1: "rsh_narrow_kernel"}.get(runs["row_lanes"], "rsh_shared_kernel")
 
 

@@ -398,6 +398,10 @@ int rsh_plan_teams_per_wave(const rsh_plan_t *plan, int32_t *teams);
  * 2 (up to 16), 4 or 8; 0 = teams of lanes share the rows of a wave (rsh_plan_teams_per_wave). */
 int rsh_plan_kernels(const rsh_plan_t *plan, int32_t *cells_written, int32_t *row_lanes);
 
+/* The form in which a plan's tall windows run where waves divide their columns (small products): features of a panel (32 or 64),
+ * row groups of 32 rows (1 or 2) and waves (4 or 8) of a workgroup; all 0 where whole windows or no tall ones run. */
+int rsh_plan_strip(const rsh_plan_t *plan, int32_t *features, int32_t *row_groups, int32_t *waves);
+
 /* How a product with operands at these addresses reads B (nothing is read or launched; host-only plans answer too):
  * copied = 1: through the plan's buffer, else in place; width: features of the rows that the kernels read. */
 int rsh_plan_operand(const rsh_plan_t *plan, const void *B_dev, const void *C_dev, int32_t *copied, int32_t *width);

@@ -37,7 +37,7 @@ EXPORTED_SYMBOLS = [
     "rsh_plan_opts_default", "rsh_plan_create", "rsh_spmm", "rsh_spmm_noalloc", "rsh_spmm_f16", "rsh_spmm_profile",
     "rsh_dense_forward", "rsh_dense_backward", "rsh_act_backward", "rsh_copy_probe", "rsh_plan_destroy", "rsh_plan_stats",
     "rsh_plan_decode", "rsh_plan_row_order", "rsh_reorder_knn", "rsh_plan_array", "rsh_plan_teams_per_wave",
-    "rsh_plan_kernels", "rsh_plan_operand",
+    "rsh_plan_kernels", "rsh_plan_strip", "rsh_plan_operand",
     "rsh_struct_sizes", "rsh_status_string", "rsh_last_hip_error",
 ]
 
@@ -129,6 +129,7 @@ def lib() -> ctypes.CDLL:
         L.rsh_plan_array.argtypes = [vp, i32, ctypes.POINTER(vp), i64p]
         L.rsh_plan_teams_per_wave.argtypes = [vp, ctypes.POINTER(i32)]
         L.rsh_plan_kernels.argtypes = [vp, ctypes.POINTER(i32), ctypes.POINTER(i32)]
+        L.rsh_plan_strip.argtypes = [vp, ctypes.POINTER(i32), ctypes.POINTER(i32), ctypes.POINTER(i32)]
         L.rsh_plan_operand.argtypes = [vp, vp, vp, ctypes.POINTER(i32), ctypes.POINTER(i32)]
         L.rsh_struct_sizes.argtypes = [ctypes.POINTER(i32), ctypes.POINTER(i32)]
         L.rsh_status_string.argtypes = [ctypes.c_int]
@@ -344,6 +345,12 @@ class Plan:
         cells, lanes = ctypes.c_int32(), ctypes.c_int32()
         _check(lib().rsh_plan_kernels(self._h, ctypes.byref(cells), ctypes.byref(lanes)))
         return {"cells_written": bool(cells.value), "row_lanes": lanes.value}
+
+    def strip(self):
+        """(features, row groups, waves) of a workgroup where waves divide the columns of tall windows, else None (rsh_plan_strip)."""
+        form = [ctypes.c_int32() for _ in range(3)]
+        _check(lib().rsh_plan_strip(self._h, *(ctypes.byref(x) for x in form)))
+        return tuple(x.value for x in form) if form[0].value else None
 
     def operand(self, b_address: int, c_address: int):
         """(B is copied first, features of the rows that the kernels read) of a product with operands at these addresses

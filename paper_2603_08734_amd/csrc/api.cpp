@@ -112,7 +112,7 @@ int upload_array(Uploader& up, const std::vector<T>& h, T** d) {
 
 void free_device(rsh::DevicePlan& d) {
     void* ptrs[] = {d.win_row, d.win_tile_off, d.tile_colid, d.tile_mask, d.tile_val_off, d.tile_val,
-                    d.tile_item, d.panel_col0, d.panel_off, d.panel_ent, d.panel_quad0, d.panel_meta, d.panel_qoff, d.panel_val, d.panel_cells, d.irr_col, d.irr_val, d.irr_wave, d.irr_row, d.narrow_seg, d.combine, d.scratch,
+                    d.tile_item, d.panel_col0, d.panel_off, d.panel_ent, d.panel_quad0, d.panel_meta, d.panel_qoff, d.panel_val, d.panel_cells, d.win_run, d.irr_col, d.irr_val, d.irr_wave, d.irr_row, d.narrow_seg, d.combine, d.scratch,
                     d.b_pad};
     for (void* p : ptrs)
         if (p) (void)hipFree(p);
@@ -141,6 +141,18 @@ int upload_panel_units(Uploader& up, const rsh::HostPlan& h, rsh::DevicePlan& d)
     } temporary{d, counts};
     if ((rc = upload_array(up, h.panel_off, &d.panel_off))) return rc;
     if ((rc = upload_array(up, h.panel_ent, &d.panel_ent))) return rc;
+    if (h.geo.strip) {
+        std::vector<int32_t> run(2 * (size_t)n_windows);
+        for (int64_t w = 0; w < n_windows; ++w) {
+            const size_t b = (size_t)h.win_tile_off[(size_t)w] * rsh::kPanelK, e = (size_t)h.win_tile_off[(size_t)w + 1] * rsh::kPanelK;
+            const int32_t first = e > b ? h.tile_colid[b] : -1, last = e > b ? h.tile_colid[e - 1] : -1;
+            bool one = e > b;
+            for (size_t k = b; one && k < e; ++k) one = h.tile_colid[k] == std::min(first + (int32_t)(k - b), last);
+            run[2 * (size_t)w] = one ? first : -1;
+            run[2 * (size_t)w + 1] = one ? last : -1;
+        }
+        if ((rc = upload_array(up, run, &d.win_run))) return rc;
+    }
     if (h.geo.wide) {
         d.n_tiles = h.win_tile_off[(size_t)n_windows];
         if (!hip_ok(hipMalloc((void**)&d.panel_cells, (2 * (size_t)d.n_tiles + 1) * rsh::kWideStepBytes))) return RSH_ERR_OOM;
@@ -233,7 +245,7 @@ int upload_plan(rsh_plan& p) {
     // no room beside cells written out: the same items run on the packed form
     free_device(p.dev);
     const int64_t written_out = rsh::panel_device_bytes(h);
-    h.geo.wide = 0;
+    h.geo.wide = h.geo.strip = 0;
     const int64_t less = written_out - rsh::panel_device_bytes(h);
     for (int64_t* bytes : {&h.stats.plan_bytes, &h.stats.tile_part_bytes, &h.stats.bytes_method, &h.stats.bytes_method_element_level}) *bytes -= less;
     return upload_arrays(p);
@@ -380,6 +392,7 @@ int rsh_plan_create(const rsh_csr_t* csr, int32_t N, const rsh_plan_opts_t* opts
         if (o.tau_inc >= 0) tau_inc = o.tau_inc;
         rsh::Partition part;
         rsh::partition_rows(*csr, o, h.order, tau_nnz, tau_inc, part, threads);
+        h.height_chosen = choose_w;
         if (choose_w) {
             o.window_rows = rsh::choose_window_rows(*csr, part);
             if (o.window_rows != rsh::kW) rsh::partition_rows(*csr, o, h.order, tau_nnz, tau_inc, part, threads);
@@ -449,11 +462,11 @@ bool copies_operand(const rsh::HostPlan& h, uintptr_t B, uintptr_t C, int* width
         padded = false;
         *width = n;
     }
-    // Tall windows without residual rows beside them read rows of fewer than 16 features where they lie (panel.hpp).  That
-    // saves a launch and costs the loop 0.08 us per fragment of a workgroup, so not beyond 32 fragments per compute unit: weights
-    // of 1024 x 1024, 5 features, 15.4 us with the copy and 13.9, 5000 x 3000 16.9 and 15.1, 17000 x 2000 (16 fragments) 20.3
-    // and 19.1; 28672 x 8192 (112) 59.9 and 65.1.
-    if (n < 16 && h.geo.panel && h.geo.N <= 16 && h.irr_wave.empty() && h.n_cols * n >= 8 &&
+    // Tall windows without residual rows beside them read rows of fewer than 16 features where they lie (panel.hpp), and where
+    // waves divide the columns (strip.hpp) rows of any width.  That saves a launch and costs the loop 0.08 us per fragment of a
+    // workgroup, so not beyond 32 fragments per compute unit: weights of 1024 x 1024, 5 features, 15.4 us with the copy and
+    // 13.9, 5000 x 3000 16.9 and 15.1, 17000 x 2000 (16 fragments) 20.3 and 19.1; 28672 x 8192 (112) 59.9 and 65.1.
+    if ((h.geo.strip ? n < 16 || n % 2 != 0 : n < 16 && h.geo.panel) && h.geo.N == auto_run_width(n) && h.irr_wave.empty() && h.n_cols * n >= 8 &&
         (int64_t)h.win_tile_off.back() * h.geo.win_rows <= 32 * 256 * 256) {
         padded = false;
         *width = n;
@@ -743,6 +756,15 @@ int rsh_plan_kernels(const rsh_plan_t* plan, int32_t* cells_written, int32_t* ro
     if (!plan || !cells_written || !row_lanes) return RSH_ERR_NULL;
     *cells_written = plan->host.geo.wide;
     *row_lanes = plan->host.geo.narrow;
+    return RSH_OK;
+}
+
+int rsh_plan_strip(const rsh_plan_t* plan, int32_t* features, int32_t* row_groups, int32_t* waves) {
+    if (!plan || !features || !row_groups || !waves) return RSH_ERR_NULL;
+    const int code = plan->host.geo.strip;
+    *features = code & 0xff;
+    *row_groups = (code >> 8) & 0xff;
+    *waves = code >> 16;
     return RSH_OK;
 }
 

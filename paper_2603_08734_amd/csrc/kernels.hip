@@ -4,6 +4,7 @@
 //                        Tensor-Core kernel (paper, Section 3.3.2, Algorithm 2)
 //   rsh_panel_kernel     the same for tall windows (panel.hpp)
 //   rsh_wide_kernel      the same for tall windows and many features (wide.hpp)
+//   rsh_strip_kernel     the same for tall windows of small products (strip.hpp)
 //   rsh_irregular_kernel residual rows (Section 3.3.2, "CUDA path"), teams of lanes own
 //                        feature columns, long rows arrive as bounded slices (Section 3.3.3)
 //   rsh_narrow_kernel, rsh_shared_kernel   residual rows of at most 8 features, and of more where lanes_per_row says so
@@ -26,6 +27,7 @@
 
 #include "device.hpp"
 #include "panel.hpp"
+#include "strip.hpp"
 #include "wide.hpp"
 
 namespace rsh {
@@ -953,7 +955,10 @@ static int launch_all(const DevicePlan& d, const void* B, const OUT& out, int nb
             return RSH_ERR_HIP;
     }
     hipStream_t st = forked ? (hipStream_t)d.side : caller;
-    if (d.n_tile_items > 0 && d.geo.wide) {
+    if (d.n_tile_items > 0 && d.geo.strip) {
+        rc = launch_strip(d, B, out.general(), st, nb, nv);
+        if (rc != RSH_OK) return rc;
+    } else if (d.n_tile_items > 0 && d.geo.wide) {
         launch_wide(d, B, out.general(), st, nb, nv);
     } else if (d.n_tile_items > 0 && d.geo.panel) {
         rc = launch_panels(d, B, out.general(), st, nb, nv);
@@ -1023,7 +1028,7 @@ static int launch_all(const DevicePlan& d, const void* B, const OUT& out, int nb
 }
 
 int launch_spmm(const DevicePlan& d, const void* B, void* C, int nb, int nv, void* stream, void* const* events) {
-    if (nb != nv || nv < 16) return launch_all(d, B, OutPlainT<kRowsAny>{(float*)C}, nb, nv, stream, events);
+    if (nb != nv || nv < 16 || nv % 2) return launch_all(d, B, OutPlainT<kRowsAny>{(float*)C}, nb, nv, stream, events);
     if (nb == d.geo.N) return launch_all(d, B, OutPlainT<kRowsWhole>{(float*)C}, nb, nv, stream, events);
     return launch_all(d, B, OutPlainT<kRowsEven>{(float*)C}, nb, nv, stream, events);
 }
@@ -1056,7 +1061,7 @@ int static_scratch(float** ptr) {
 
 int launch_spmm_f16(const DevicePlan& d, const void* B, void* C16, const float* bias, int relu, int nb, int nv, void* stream,
                     void* const* events) {
-    if (nb != nv || nv < 16) return launch_all(d, B, OutFusedT<kRowsAny>{(_Float16*)C16, bias, relu}, nb, nv, stream, events);
+    if (nb != nv || nv < 16 || nv % 2) return launch_all(d, B, OutFusedT<kRowsAny>{(_Float16*)C16, bias, relu}, nb, nv, stream, events);
     if (nb == d.geo.N) return launch_all(d, B, OutFusedT<kRowsWhole>{(_Float16*)C16, bias, relu}, nb, nv, stream, events);
     return launch_all(d, B, OutFusedT<kRowsEven>{(_Float16*)C16, bias, relu}, nb, nv, stream, events);
 }

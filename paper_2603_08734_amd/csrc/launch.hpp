@@ -28,6 +28,7 @@ struct DevicePlan {
     uint32_t* panel_val = nullptr;
     uint32_t* panel_cells = nullptr;   // or with every cell written out (wide.hpp)
     uint32_t n_tiles = 0;
+    int32_t* win_run = nullptr;        // geo.strip: first and last column of a window whose columns are one run, else -1
     int32_t* irr_col = nullptr;
     uint16_t* irr_val = nullptr;
     uint32_t* irr_wave = nullptr;

@@ -142,6 +142,69 @@ __global__ __launch_bounds__(256) void rsh_panel_values_kernel(const uint32_t* _
 // ---------------------------------------------------------------------------
 // The product.  NG row groups of 32 rows per window, panels of 32 * NCH32 features.
 // ---------------------------------------------------------------------------
+struct __attribute__((packed, aligned(4))) Dwords4 {
+    uint32_t d[4];
+};
+struct Selectors {
+    uint2_t lo, hi;
+};
+constexpr int kSelectorBytes = 128;
+
+// Selector table, by a wave: entry m (a 4-cell mask) holds for each cell which of the next four values it takes (bytes
+// 2i, 2i + 1 of the pair of registers that holds them), or zero (selector 0x0c).
+__device__ __forceinline__ void write_selectors(unsigned char* table, int lane) {
+    const uint32_t m = (uint32_t)lane >> 2, c = (uint32_t)lane & 3;
+    const uint32_t i = (uint32_t)__builtin_popcount(m & ((1u << c) - 1u));
+    reinterpret_cast<uint16_t*>(table)[lane] = (uint16_t)((m >> c) & 1u ? 0x0100u + 0x0202u * i : 0x0c0cu);
+}
+// Selectors of the lane's 8 cells of K step h of a fragment (w: its word of meta).
+__device__ __forceinline__ void look_up_selectors(const unsigned char* table, uint32_t w, int h, Selectors& y) {
+    y.lo = *reinterpret_cast<const uint2_t*>(table + ((h ? w >> 21 : w >> 5) & 0x78u));
+    y.hi = *reinterpret_cast<const uint2_t*>(table + ((h ? w >> 25 : w >> 9) & 0x78u));
+}
+// Values of a fragment's two units: one 16-byte load per lane and unit, at the lane's dword offset from the
+// unit's start; the next unit starts behind the last lane's values.  vbase: wave-uniform, moves on.
+__device__ __forceinline__ void issue_unit_values(uint32_t w, const uint32_t*& vbase, Dwords4 (&v)[2]) {
+    const uint32_t w63 = (uint32_t)__builtin_amdgcn_readlane((int)w, 63);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const uint32_t off = (w >> (16 * h)) & 0xffu;
+        v[h] = *reinterpret_cast<const Dwords4*>(reinterpret_cast<const char*>(vbase) + 4u * off);
+        const uint32_t e = w63 >> (16 * h);
+        vbase += (e & 0xffu) + ((uint32_t)__builtin_popcount(e & 0xff00u) + 1u) / 2u;
+    }
+}
+// The lane's 8 cells of K step h: the values of cells 0-3 start at the first register, those of cells
+// 4-7 behind them, i.e. at a half that depends on the lane: the registers are funnelled down by it.
+__device__ __forceinline__ half8_t expand_cells(uint32_t w, int h, const Dwords4& v, const Selectors& y) {
+    const uint32_t n = (uint32_t)__builtin_popcount(w & (h ? 0x0f000000u : 0x0f00u));   // values of cells 0-3
+    const uint32_t* d = v.d;
+    const bool two = n >= 2, four = n >= 4;
+    uint32_t a0 = two ? d[1] : d[0], a1 = two ? d[2] : d[1];
+    const uint32_t a2 = two ? d[3] : d[2];
+    a0 = four ? d[2] : a0;
+    a1 = four ? d[3] : a1;
+    const uint32_t w0 = __builtin_amdgcn_alignbit(a1, a0, n << 4), w1 = __builtin_amdgcn_alignbit(a2, a1, n << 4);   // shift mod 32
+    const uint4_t r = {__builtin_amdgcn_perm(d[1], d[0], y.lo[0]), __builtin_amdgcn_perm(d[1], d[0], y.lo[1]),
+                       __builtin_amdgcn_perm(w1, w0, y.hi[0]), __builtin_amdgcn_perm(w1, w0, y.hi[1])};
+    return __builtin_bit_cast(half8_t, r);
+}
+// Sixteen bytes moved down by `by` halves (1 .. 7), zeros behind.
+__device__ __forceinline__ uint4_t halves_down(uint4_t x, uint32_t by) {
+    const uint64_t lo = (uint64_t)x[1] << 32 | x[0], hi = (uint64_t)x[3] << 32 | x[2];
+    const uint64_t a = by >= 4 ? hi : lo, z = by >= 4 ? 0u : hi;
+    const uint32_t k = 16u * (by & 3u);
+    const uint64_t l = k ? a >> k | z << (64u - k) : a, h = z >> k;
+    return (uint4_t){(uint32_t)l, (uint32_t)(l >> 32), (uint32_t)h, (uint32_t)(h >> 32)};
+}
+// Eight staged rows of 32 features from `from` on as the instruction's operand: two transposing reads, four rows apart.
+template <int LDB>
+__device__ __forceinline__ half8_t read_transposed(const _Float16* from) {
+    const half4_t l = __builtin_bit_cast(half4_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((short4_t __attribute__((address_space(3)))*)from));
+    const half4_t u = __builtin_bit_cast(half4_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16((short4_t __attribute__((address_space(3)))*)(from + 4 * LDB)));
+    return (half8_t){l[0], l[1], l[2], l[3], u[0], u[1], u[2], u[3]};
+}
+
 template <int NCH32, int NG>
 struct PanelGeom {
     static constexpr int P = 32 * NCH32;
@@ -154,14 +217,10 @@ struct PanelGeom {
     static constexpr int IDLE = NLD * THREADS - PIECES;       // threads without a piece stage into spare space
     static constexpr int TILE_HALVES = kPanelK * LDB + 8 * IDLE;
     static constexpr int NBUF = 4;                            // staged B tiles (fragment s lives in tile s mod 4)
-    static constexpr int LUT_BYTES = 128;
+    static constexpr int LUT_BYTES = kSelectorBytes;
     static constexpr int LOOP_BYTES = LUT_BYTES + NBUF * TILE_HALVES * 2;
     static constexpr int STAGE_BYTES = WAVES * 32 * kStageStride * 4;
     static constexpr int SMEM_BYTES = LOOP_BYTES > STAGE_BYTES ? LOOP_BYTES : STAGE_BYTES;
-};
-
-struct __attribute__((packed, aligned(4))) Dwords4 {
-    uint32_t d[4];
 };
 
 // The products of one item, fragments [t_begin, t_end) of window `win`, added to acc + acc2.  RUN: the window's
@@ -219,9 +278,6 @@ __device__ __forceinline__ void panel_item(unsigned char* smem, uint32_t win, ui
         half8_t b[NCH32];
         half8_t a;
     };
-    struct Selectors {
-        uint2_t lo, hi;
-    };
     Operands op[2];
     Selectors sel[2];
 
@@ -241,18 +297,7 @@ __device__ __forceinline__ void panel_item(unsigned char* smem, uint32_t win, ui
             m[i] &= keep;
         }
     };
-    // Values of a fragment's units: one 16-byte load per lane and unit, at the lane's dword offset from the
-    // unit's start; the next unit starts behind the last lane's values.
-    auto issue_values = [&](const uint4_t& m, int i, Dwords4 (&v)[2]) {
-        const uint32_t w = m[i], w63 = (uint32_t)__builtin_amdgcn_readlane((int)w, 63);
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const uint32_t off = (w >> (16 * h)) & 0xffu;
-            v[h] = *reinterpret_cast<const Dwords4*>(reinterpret_cast<const char*>(vbase) + 4u * off);
-            const uint32_t e = w63 >> (16 * h);
-            vbase += (e & 0xffu) + ((uint32_t)__builtin_popcount(e & 0xff00u) + 1u) / 2u;
-        }
-    };
+    auto issue_values = [&](const uint4_t& m, int i, Dwords4 (&v)[2]) { issue_unit_values(m[i], vbase, v); };
     auto fetch_colids = [&](uint32_t step, int (&cid)[NLD]) {
         if constexpr (!RUN) {
 #pragma unroll
@@ -280,14 +325,7 @@ __device__ __forceinline__ void panel_item(unsigned char* smem, uint32_t win, ui
         for (int j = 0; j < NLD; ++j) {
             uint4_t x = b[j];
             if constexpr (NARROW) {
-                const uint32_t by = moved[slot];
-                if (by) {
-                    const uint64_t lo = (uint64_t)x[1] << 32 | x[0], hi = (uint64_t)x[3] << 32 | x[2];
-                    const uint64_t a = by >= 4 ? hi : lo, z = by >= 4 ? 0u : hi;
-                    const uint32_t k = 16u * (by & 3u);
-                    const uint64_t l = k ? a >> k | z << (64u - k) : a, h = z >> k;
-                    x = (uint4_t){(uint32_t)l, (uint32_t)(l >> 32), (uint32_t)h, (uint32_t)(h >> 32)};
-                }
+                if (moved[slot]) x = halves_down(x, moved[slot]);
             }
             if constexpr (RAGGED) {
                 x[0] = over1 ? x[1] : over2 ? x[2] : over3 ? x[3] : x[0];
@@ -300,34 +338,10 @@ __device__ __forceinline__ void panel_item(unsigned char* smem, uint32_t win, ui
     auto read_b = [&](int buf, int h, Operands& x) {
         const _Float16* sb = lds_b + buf * Gm::TILE_HALVES + tr_off + (16 * h) * LDB;
 #pragma unroll
-        for (int c = 0; c < NCH32; ++c) {
-            const half4_t l = __builtin_bit_cast(half4_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                (short4_t __attribute__((address_space(3)))*)(sb + 32 * c)));
-            const half4_t u = __builtin_bit_cast(half4_t, __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                (short4_t __attribute__((address_space(3)))*)(sb + 4 * LDB + 32 * c)));
-            x.b[c] = (half8_t){l[0], l[1], l[2], l[3], u[0], u[1], u[2], u[3]};
-        }
+        for (int c = 0; c < NCH32; ++c) x.b[c] = read_transposed<LDB>(sb + 32 * c);
     };
-    auto look_up = [&](const uint4_t& m, int i, int h, Selectors& y) {
-        const uint32_t w = m[i];
-        y.lo = *reinterpret_cast<const uint2_t*>(smem + ((h ? w >> 21 : w >> 5) & 0x78u));
-        y.hi = *reinterpret_cast<const uint2_t*>(smem + ((h ? w >> 25 : w >> 9) & 0x78u));
-    };
-    // The lane's 8 cells of K step h: the values of cells 0-3 start at the first register, those of cells
-    // 4-7 behind them, i.e. at a half that depends on the lane: the registers are funnelled down by it.
-    auto expand = [&](const uint4_t& m, int i, int h, const Dwords4 (&v)[2], const Selectors& y, Operands& x) {
-        const uint32_t n = (uint32_t)__builtin_popcount(m[i] & (h ? 0x0f000000u : 0x0f00u));   // values of cells 0-3
-        const uint32_t* d = v[h].d;
-        const bool two = n >= 2, four = n >= 4;
-        uint32_t a0 = two ? d[1] : d[0], a1 = two ? d[2] : d[1];
-        const uint32_t a2 = two ? d[3] : d[2];
-        a0 = four ? d[2] : a0;
-        a1 = four ? d[3] : a1;
-        const uint32_t w0 = __builtin_amdgcn_alignbit(a1, a0, n << 4), w1 = __builtin_amdgcn_alignbit(a2, a1, n << 4);   // shift mod 32
-        const uint4_t r = {__builtin_amdgcn_perm(d[1], d[0], y.lo[0]), __builtin_amdgcn_perm(d[1], d[0], y.lo[1]),
-                           __builtin_amdgcn_perm(w1, w0, y.hi[0]), __builtin_amdgcn_perm(w1, w0, y.hi[1])};
-        x.a = __builtin_bit_cast(half8_t, r);
-    };
+    auto look_up = [&](const uint4_t& m, int i, int h, Selectors& y) { look_up_selectors(smem, m[i], h, y); };
+    auto expand = [&](const uint4_t& m, int i, int h, const Dwords4 (&v)[2], const Selectors& y, Operands& x) { x.a = expand_cells(m[i], h, v[h], y); };
     auto multiply = [&](const Operands& x) {
 #pragma unroll
         for (int c = 0; c < NCH32; ++c)
@@ -436,13 +450,7 @@ __global__ __launch_bounds__(64 * NG) __attribute__((amdgpu_waves_per_eu(2, NCH3
     const int panel = feature0 + blockIdx.y * P;
     const int row = win_row[(size_t)win * (32 * NG) + wv * 32 + (lane & 31)];
 
-    // Selector table: entry m (a 4-cell mask) holds for each cell which of the next four values it takes (bytes
-    // 2i, 2i + 1 of the pair of registers that holds them), or zero (selector 0x0c).
-    if (threadIdx.x < 64) {
-        const uint32_t m = threadIdx.x >> 2, c = threadIdx.x & 3;
-        const uint32_t i = (uint32_t)__builtin_popcount(m & ((1u << c) - 1u));
-        reinterpret_cast<uint16_t*>(smem)[threadIdx.x] = (uint16_t)((m >> c) & 1u ? 0x0100u + 0x0202u * i : 0x0c0cu);
-    }
+    if (threadIdx.x < 64) write_selectors(smem, lane);
 
     float16_t acc[NCH32], acc2[NCH32];
 #pragma unroll

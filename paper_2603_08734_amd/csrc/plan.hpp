@@ -26,6 +26,9 @@ constexpr int kNarrow = 16;
 constexpr uint32_t kSegmentToScratch = 0x80000000u;
 constexpr int kNarrowAhead = 4;   // pairs of entries per lane behind the last wave's that the kernel may read
 
+// A form of strip.hpp: features of a panel, row groups of a workgroup, its waves.
+constexpr int strip_code(int features, int row_groups, int waves) { return features | row_groups << 8 | waves << 16; }
+
 // Feature-panel geometry derived from N (both kernels walk N in panels).
 struct Geometry {
     int N = 0;
@@ -40,6 +43,7 @@ struct Geometry {
     int cpl = 4;        // cells per MFMA lane = bitmap words per sub-fragment = tile_k / 4
     int panel = 0;      // 1 = tall windows in the panel form (win_rows == 128 or 256, tile_k == 32)
     int wide = 0;       // panel form whose cells are written out on the device (wide.hpp); win_rows == 256
+    int strip = 0;      // panel form of small products, whose waves share rows and divide the columns (strip.hpp): strip_code; windows are not cut
     int narrow = 0;     // residual rows in the form of narrow.hpp: lanes that share a row of B (1, 2, 4 or 8), 0 = teams
     int panel_groups = 0; // panel form: row groups of 32 rows per window = win_rows / 32
 };
@@ -66,6 +70,7 @@ struct HostPlan {
     int n_user = 0;   // features of B and C as the caller has them; geo.N is the run width
     Geometry geo;
     rsh_plan_opts_t opts{};
+    bool height_chosen = false;    // the planner, not the caller, chose the window height
     std::vector<int32_t> order;  // pi: order[i] = original id of the i-th processed row
 
     // dense-fragment part

@@ -822,6 +822,43 @@ static std::vector<uint32_t> cut_tall_windows(const HostPlan& plan, int64_t n_wi
 
 static int lanes_per_row(const HostPlan& plan, const rsh_csr_t& a, const std::vector<int32_t>& rows, int64_t entries);
 
+// Form of strip.hpp in which a plan of tall windows runs, 0 for the kernels of whole windows (panel.hpp, wide.hpp).  A
+// compute unit holds two workgroups of 32 rows x 32 features, three of 64 x 32, one of 32 x 64 (or 64 x 64 in eight waves) and
+// two of 64 x 64 in four; the smallest that fill the chip once are taken, and no strip where 64 x 64 would run more than one
+// round.  Weights at densities of 0.1 to 0.35, us, kernels of whole windows and, in this order, 32 x 32 (eight waves), 64 x 32
+// (four), 32 x 64, 64 x 64 in eight waves and in four:
+//   rows x columns  features
+//    4736 x 1871       2    16.0    9.1  11.5   9.2  12.1  14.3
+//    5000 x 4000      16    14.5   10.5  18.8  12.6  17.2  22.2
+//   12985 x 1028      32    17.7    9.4   9.8  13.3  10.4  10.8
+//   28672 x 2000      16    22.4   19.9  15.4  28.0  21.9  17.9
+//    1848 x 3452      48    17.1    9.9  16.2  11.3  15.7  19.6
+//    5000 x 4000      64    17.5   19.1  18.9  12.7  17.4  22.7
+//   14000 x 4000      64    27.3   34.5  24.3  24.0  19.0  23.1
+//   28672 x 2000      64    30.2   39.0  26.1  30.1  24.0  19.2
+//   28672 x 8192      64    81.3  142   105    98.8  70.5  66.6
+//    2143 x 2545     200    18.5   17.4  16.4  20.9  15.2  16.1
+//   14000 x 4000     128    35.3   55.9  42.4  45.1  35.1  30.8
+//   15764 x 6465     200    80.5  205   134   169   117   103
+//   28672 x 8192     128    99.4  230   158   156   129   117
+// A wave's share has at most 32 fragments, so four waves take windows of up to 128.
+static int strip_form(const HostPlan& plan, int64_t n_win) {
+    if (!plan.height_chosen || plan.opts.max_tiles_per_item > 0) return 0;
+    uint32_t longest = 0;
+    for (int64_t w = 0; w < n_win; ++w) longest = std::max(longest, plan.win_tile_off[(size_t)w + 1] - plan.win_tile_off[(size_t)w]);
+    // column ids and bytes of a row of B are multiplied as 24-bit numbers
+    if (longest == 0 || longest > 256 || plan.n_cols >= (1 << 24) || plan.n_cols * plan.n_user < 8) return 0;
+    const int n = plan.n_user;
+    const int64_t groups = n_win * plan.geo.panel_groups, small = groups * ((n + 31) / 32), blocks = groups * ((n + 63) / 64);
+    const bool four = longest <= 128;
+    if (small <= 256 || (n <= 32 && small <= 512)) return strip_code(32, 1, 8);
+    if (n <= 32) return strip_code(32, 2, four ? 4 : 8);
+    if (blocks <= 256) return strip_code(64, 1, 8);
+    if (blocks <= 512) return strip_code(64, 2, 8);
+    if (blocks <= 1024 && (four || n <= 64)) return strip_code(64, 2, four ? 4 : 8);
+    return 0;
+}
+
 int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int threads) {
     Geometry& geo = plan.geo;
     const int W = geo.win_rows, NW = geo.nw;
@@ -843,6 +880,8 @@ int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int thr
         // Beyond one panel of features the cells are written out (wide.hpp: both kernels' times), as long as one in sixteen
         // is stored: what the plan then takes of memory is at most 32 bytes per entry.
         geo.wide = geo.win_rows == 256 && plan.n_user > 128 && n_tiles > 0 && nnz_tile * 16 >= n_tiles * (int64_t)K * W;
+        geo.strip = strip_form(plan, n_win);
+        if (geo.strip) geo.wide = 0;
     } else {
         // ---- pass 1: fragments and padded value count per window ---------------------------
         // A window of W = 16*NW rows shares one condensed column space; fragment t of the window
@@ -981,7 +1020,8 @@ int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int thr
     std::vector<int64_t> spill_slot(element_level ? (size_t)n_win : 0, -1);   // first slot of a window's spilled rows
     const std::vector<int64_t> worder = schedule_windows(a, plan, n_win, &plan.stats.schedule_cols_given, &plan.stats.schedule_cols_found);
     std::vector<uint32_t> panel_parts;
-    if (choose_parts) {
+    if (choose_parts && geo.strip) panel_parts.assign((size_t)n_win, 1u);
+    else if (choose_parts) {
         // what is chosen leaves room in the library-owned array for the residual rows' partial sums (an upper bound of
         // them), so that the choice keeps no product from rsh_spmm_noalloc
         const int64_t room = (int64_t)(kStaticScratchBytes / ((size_t)geo.N * sizeof(float)));
