@@ -462,11 +462,11 @@ bool copies_operand(const rsh::HostPlan& h, uintptr_t B, uintptr_t C, int* width
         padded = false;
         *width = n;
     }
-    // Tall windows without residual rows beside them read rows of fewer than 16 features where they lie (panel.hpp), and where
-    // waves divide the columns (strip.hpp) rows of any width.  That saves a launch and costs the loop 0.08 us per fragment of a
-    // workgroup, so not beyond 32 fragments per compute unit: weights of 1024 x 1024, 5 features, 15.4 us with the copy and
-    // 13.9, 5000 x 3000 16.9 and 15.1, 17000 x 2000 (16 fragments) 20.3 and 19.1; 28672 x 8192 (112) 59.9 and 65.1.
-    if ((h.geo.strip ? n < 16 || n % 2 != 0 : n < 16 && h.geo.panel) && h.geo.N == auto_run_width(n) && h.irr_wave.empty() && h.n_cols * n >= 8 &&
+    // Tall windows without residual rows beside them read rows of fewer than 16 features where they lie (panel.hpp).  That
+    // saves a launch and costs the loop 0.08 us per fragment of a workgroup, so not beyond 32 fragments per compute unit: weights
+    // of 1024 x 1024, 5 features, 15.4 us with the copy and 13.9, 5000 x 3000 16.9 and 15.1, 17000 x 2000 (16 fragments) 20.3
+    // and 19.1; 28672 x 8192 (112) 59.9 and 65.1.  Where waves divide the columns (strip.hpp) so are rows of odd widths: strip_form.
+    if (h.geo.strip ? h.strip_in_place && h.irr_wave.empty() : n < 16 && h.geo.panel && h.geo.N <= 16 && h.irr_wave.empty() && h.n_cols * n >= 8 &&
         (int64_t)h.win_tile_off.back() * h.geo.win_rows <= 32 * 256 * 256) {
         padded = false;
         *width = n;
@@ -478,6 +478,15 @@ bool copies_operand(const rsh::HostPlan& h, uintptr_t B, uintptr_t C, int* width
         const int wide = rsh::narrow_width(n);
         padded = wide != n || (B & (uintptr_t)(2 * std::min(wide, 8) - 1));
         *width = padded ? std::max(4, wide) : n;
+    }
+    // Plans of fewer than 2^18 entries take rows of 3, 5 to 7 and 9 to 15 features from where they lie: there the launch of the copy is
+    // a good part of the product.  With the copy and without, us: 6000 rows of 13 entries, 3 features 12.3 and 9.5, 7 11.7 and
+    // 9.1, 9 12.1 and 8.8, 15 12.0 and 9.0; power-law graph of 2^12 vertices 12.0 8.9, 10.9 8.1, 10.7 8.1, 11.0 7.9; 27-point stencil
+    // on 24^3, 3 features 10.4 and 7.8.  In large ones the loads of odd widths, at 2-byte boundaries, cost more than the copy: 2^18
+    // vertices 48.5 49.4, 53.9 64.7, 57.5 61.6, 62.2 69.7.
+    if (n < rsh::kNarrow && n > 2 && n != 4 && n != 8 && h.nnz < (1 << 18) && h.geo.N == rsh::kNarrow && h.geo.narrow && h.tile_item.empty()) {
+        padded = false;
+        *width = n;
     }
     return padded;
 }
@@ -762,9 +771,9 @@ int rsh_plan_kernels(const rsh_plan_t* plan, int32_t* cells_written, int32_t* ro
 int rsh_plan_strip(const rsh_plan_t* plan, int32_t* features, int32_t* row_groups, int32_t* waves) {
     if (!plan || !features || !row_groups || !waves) return RSH_ERR_NULL;
     const int code = plan->host.geo.strip;
-    *features = code & 0xff;
-    *row_groups = (code >> 8) & 0xff;
-    *waves = code >> 16;
+    *features = rsh::strip_features(code);
+    *row_groups = rsh::strip_row_groups(code);
+    *waves = rsh::strip_waves(code);
     return RSH_OK;
 }
 

@@ -24,6 +24,9 @@ typedef unsigned int uint4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef unsigned int uint2_a4 __attribute__((ext_vector_type(2), aligned(4)));
 typedef unsigned int uint4_a2 __attribute__((ext_vector_type(4), aligned(2)));   // rows of an odd number of halves
 typedef unsigned int uint2_a2 __attribute__((ext_vector_type(2), aligned(2)));
+typedef unsigned int uint3_t __attribute__((ext_vector_type(3)));
+typedef unsigned int uint3_a2 __attribute__((ext_vector_type(3), aligned(2)));
+typedef unsigned int uint1_a2 __attribute__((aligned(2)));
 typedef float float4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 typedef float float2_a4 __attribute__((ext_vector_type(2), aligned(4)));
 

@@ -48,9 +48,25 @@ __device__ __forceinline__ NarrowRow<NP> load_narrow(const char* p) {
     }
     return r;
 }
-// Eight features of a row of any width.
+// A row of E features, as the next power of two: no byte behind it is read.
+template <int NP, int E>
+__device__ __forceinline__ NarrowRow<NP> load_exact(const char* p) {
+    if constexpr (E == NP) {
+        return load_narrow<NP>(p);
+    } else if constexpr (E == 3) {
+        return {{*reinterpret_cast<const uint1_a2*>(p), *reinterpret_cast<const uint16_t*>(p + 4)}};
+    } else if constexpr (E == 5) {
+        const uint2_t v = *reinterpret_cast<const uint2_a2*>(p);
+        return {{v[0], v[1], *reinterpret_cast<const uint16_t*>(p + 8), 0u}};
+    } else {
+        static_assert(E == 6 || E == 7);
+        const uint3_t v = *reinterpret_cast<const uint3_a2*>(p);
+        return {{v[0], v[1], v[2], E == 7 ? (uint32_t)*reinterpret_cast<const uint16_t*>(p + 12) : 0u}};
+    }
+}
+// Eight features of a row of any width and alignment.
 __device__ __forceinline__ NarrowRow<8> load_piece(const char* p) {
-    const uint4_t v = *reinterpret_cast<const uint4_a4*>(p);
+    const uint4_t v = *reinterpret_cast<const uint4_a2*>(p);
     return {{v[0], v[1], v[2], v[3]}};
 }
 // Feature `i` of a row of B held as packed halves.
@@ -102,7 +118,8 @@ __device__ __forceinline__ void store_narrow4(const OutFusedT<ROWS>& o, size_t r
 
 // waves {first pair of entries (in lanes), steps, log2 T | segments << 8 | steps that every lane takes << 16, first segment};
 // segments {row of C or of scratch, entries | kSegmentToScratch}.
-template <int NP, class OUT>
+// E: features of a row of B, NP or, where rows lie as the caller has them, fewer.
+template <int NP, class OUT, int E = NP>
 __global__ __launch_bounds__(64 * kWavesPerBlock) void rsh_narrow_kernel(const uint4* __restrict__ waves, XcdSplit xs, const uint2_t* __restrict__ segments,
                                                                          const uint2_t* __restrict__ col, const uint32_t* __restrict__ val,
                                                                          const __half* __restrict__ B, const OUT out, float* __restrict__ scratch, int nb,
@@ -140,8 +157,8 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void rsh_narrow_kernel(const u
         uint32_t w[PAIRS];
 #pragma unroll
         for (int u = 0; u < PAIRS; ++u) {
-            b[2 * u] = load_narrow<NP>(Bb + c[u][0] * row_bytes);
-            b[2 * u + 1] = load_narrow<NP>(Bb + c[u][1] * row_bytes);
+            b[2 * u] = load_exact<NP, E>(Bb + c[u][0] * row_bytes);
+            b[2 * u + 1] = load_exact<NP, E>(Bb + c[u][1] * row_bytes);
             w[u] = v[u];
         }
         // the next turn's (behind the last wave the arrays go on for kNarrowAhead pairs)
@@ -250,9 +267,10 @@ __global__ __launch_bounds__(64 * kWavesPerBlock) void rsh_shared_kernel(const u
     if constexpr (F == 2 && OUT::kAny) {   // 9 to 15 features: less than half a line, ordinary stores as above
 #pragma unroll
         for (int q = 0; q < 2; ++q) {
-            const int f = 8 * tl + 4 * q;
+            // where rows of B lie as the caller has them the second lane takes the eight features that end with the row
+            const int f = lane_f + 4 * q;
             const float4_t x = {acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
-            if (s[1] & kSegmentToScratch) *reinterpret_cast<float4_t*>(scratch + (size_t)s[0] * ns + f) = x;
+            if (s[1] & kSegmentToScratch) *reinterpret_cast<float4_a4*>(scratch + (size_t)s[0] * ns + f) = x;
             else store_narrow4(out, (size_t)s[0], nv, f, x);
         }
         return;
@@ -276,7 +294,11 @@ void launch_narrow(const DevicePlan& d, const void* B, const OUT& out, hipStream
         using Any = std::decay_t<decltype(any)>;
         if (nv == 1) launch(rsh_narrow_kernel<1, Any>, any);
         else if (nv == 2) launch(rsh_narrow_kernel<2, Any>, any);
+        else if (nb == 3) launch(rsh_narrow_kernel<4, Any, 3>, any);
         else if (nv <= 4) launch(rsh_narrow_kernel<4, Any>, any);
+        else if (nb == 5) launch(rsh_narrow_kernel<8, Any, 5>, any);
+        else if (nb == 6) launch(rsh_narrow_kernel<8, Any, 6>, any);
+        else if (nb == 7) launch(rsh_narrow_kernel<8, Any, 7>, any);
         else launch(rsh_narrow_kernel<8, Any>, any);
         return;
     }

@@ -29,6 +29,10 @@ constexpr int kNarrowAhead = 4;   // pairs of entries per lane behind the last w
 // A form of strip.hpp: features of a panel, row groups of a workgroup, its waves.
 constexpr int strip_code(int features, int row_groups, int waves) { return features | row_groups << 8 | waves << 16; }
 
+constexpr int strip_features(int code) { return code & 0xff; }
+constexpr int strip_row_groups(int code) { return (code >> 8) & 0xff; }
+constexpr int strip_waves(int code) { return code >> 16; }
+
 // Feature-panel geometry derived from N (both kernels walk N in panels).
 struct Geometry {
     int N = 0;
@@ -71,6 +75,7 @@ struct HostPlan {
     Geometry geo;
     rsh_plan_opts_t opts{};
     bool height_chosen = false;    // the planner, not the caller, chose the window height
+    bool strip_in_place = false;   // geo.strip: rows of B of odd widths and of fewer than 16 features are read where they lie
     std::vector<int32_t> order;  // pi: order[i] = original id of the i-th processed row
 
     // dense-fragment part

@@ -842,10 +842,8 @@ static int lanes_per_row(const HostPlan& plan, const rsh_csr_t& a, const std::ve
 //   15764 x 6465     200    80.5  205   134   169   117   103
 //   28672 x 8192     128    99.4  230   158   156   129   117
 // A wave's share has at most 32 fragments, so four waves take windows of up to 128.
-static int strip_form(const HostPlan& plan, int64_t n_win) {
+static int strip_form(const HostPlan& plan, int64_t n_win, uint32_t longest) {
     if (!plan.height_chosen || plan.opts.max_tiles_per_item > 0) return 0;
-    uint32_t longest = 0;
-    for (int64_t w = 0; w < n_win; ++w) longest = std::max(longest, plan.win_tile_off[(size_t)w + 1] - plan.win_tile_off[(size_t)w]);
     // column ids and bytes of a row of B are multiplied as 24-bit numbers
     if (longest == 0 || longest > 256 || plan.n_cols >= (1 << 24) || plan.n_cols * plan.n_user < 8) return 0;
     const int n = plan.n_user;
@@ -857,6 +855,17 @@ static int strip_form(const HostPlan& plan, int64_t n_win) {
     if (blocks <= 512) return strip_code(64, 2, 8);
     if (blocks <= 1024 && (four || n <= 64)) return strip_code(64, 2, four ? 4 : 8);
     return 0;
+}
+
+// Rows of B of odd widths and of fewer than 16 features are read where they lie while that costs a compute unit's loads less than
+// the 3 us of a copy's launch: a load at 2-byte boundaries takes 59 cycles of the vector memory path instead of 16, however few of its
+// lanes have a piece of a row.  In place and with the copy, us: 1300 x 1500 weight (94 loads) 9.2 and 12; 6000 x 2500 (158) 12.4 both;
+// 4444 x 5903 (370) 19.1 and 15.8, 85 features (1480) 34.4 and 27.4.
+static bool strip_reads_in_place(const HostPlan& plan, int64_t n_win, uint32_t longest) {
+    const int n = plan.n_user, features = strip_features(plan.geo.strip);
+    if ((n >= 16 && n % 2 == 0) || plan.geo.N != (n + 15) / 16 * 16) return false;
+    const int64_t blocks = n_win * plan.geo.panel_groups / strip_row_groups(plan.geo.strip) * ((n + features - 1) / features);
+    return (int64_t)longest * (features / 16) * ((blocks + 255) / 256) <= 150;
 }
 
 int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int threads) {
@@ -880,7 +889,10 @@ int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int thr
         // Beyond one panel of features the cells are written out (wide.hpp: both kernels' times), as long as one in sixteen
         // is stored: what the plan then takes of memory is at most 32 bytes per entry.
         geo.wide = geo.win_rows == 256 && plan.n_user > 128 && n_tiles > 0 && nnz_tile * 16 >= n_tiles * (int64_t)K * W;
-        geo.strip = strip_form(plan, n_win);
+        uint32_t longest = 0;
+        for (int64_t w = 0; w < n_win; ++w) longest = std::max(longest, plan.win_tile_off[(size_t)w + 1] - plan.win_tile_off[(size_t)w]);
+        geo.strip = strip_form(plan, n_win, longest);
+        plan.strip_in_place = geo.strip && strip_reads_in_place(plan, n_win, longest);
         if (geo.strip) geo.wide = 0;
     } else {
         // ---- pass 1: fragments and padded value count per window ---------------------------

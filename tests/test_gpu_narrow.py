@@ -100,3 +100,42 @@ def test_windows_beside_lanes(N, lanes, side_stream):
     got = product(A, B, lanes, windows=True, side_stream=side_stream, window_rows=16)
     want, S, _ = oracle.spmm(A.row_ptr, A.col_idx, A.val, B)
     assert np.all(np.abs(got - want) <= 1e-4 * S)
+
+
+# Plans of fewer than 2^18 entries read rows of 3, 5 to 7 and 9 to 15 features where they lie, at their element's alignment: the
+# last row ends with the allocation and every entry list names it.  Rows of every length, whole and in slices that leave partial
+# sums; fp32 and binary16; canaries around C.
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("N", [3, 5, 6, 7, 9, 10, 11, 12, 13, 14, 15])
+@pytest.mark.parametrize("opts", [{}, dict(max_nnz_per_slice=20), dict(xcd_partition_nnz=24)], ids=["whole", "slices", "xcd"])
+def test_small_plans_read_rows_of_any_width_where_they_lie(opts, N, fused):
+    import torch
+    from paper_2603_08734_amd import Plan
+    rng = np.random.default_rng(N)
+    rows, cols = 3000, 701
+    per_row = rng.permutation(np.resize([0, 1, 2, 3, 7, 16, 31, 33, 64, 65, 130], rows))
+    r, c, v = rows_of(per_row, cols - 1, N)
+    full = np.flatnonzero(per_row)
+    r, c, v = np.concatenate([r, full]), np.concatenate([c, np.full(full.size, cols - 1)]), np.concatenate([v, rng.standard_normal(full.size)])
+    A = from_coo(r, c, v, rows, cols)
+    print(f"case rows in place N={N} opts={opts} fused={fused}", flush=True)
+    plan = Plan(A.row_ptr, A.col_idx, A.val, cols, N, force_path=1, **opts)
+    B = rng.standard_normal((cols, N)).astype(np.float16)
+    flat = torch.full((rows * N + 129,), float("nan"), dtype=torch.float16 if fused else torch.float32, device="cuda")
+    C = flat[65:65 + rows * N].view(rows, N)
+    Bd = torch.empty(cols * N + 1, dtype=torch.float16, device="cuda")[1:].view(cols, N)
+    Bd.copy_(torch.from_numpy(B))
+    assert plan.operand(Bd.data_ptr(), C.data_ptr()) == (False, N)
+    want, S, _ = oracle.spmm(A.row_ptr, A.col_idx, A.val, B)
+    bound = 1e-4 * S
+    if fused:
+        bias = torch.linspace(-1, 1, N, device="cuda")
+        plan.spmm_f16(Bd, C, bias, relu=True)
+        want = np.maximum(want + bias.cpu().numpy().astype(np.float64), 0.0)
+        bound = bound + 2.0 ** -24 * np.abs(want) + 2.0 ** -11 * np.abs(want) * 1.001 + 2.0 ** -24   # the bias, one rounding to binary16
+    else:
+        plan.spmm(Bd, C)
+    torch.cuda.synchronize()
+    plan.destroy()
+    assert bool(torch.isnan(flat[:65]).all()) and bool(torch.isnan(flat[65 + rows * N:]).all()), "stores outside C"
+    assert np.all(np.abs(C.cpu().numpy().astype(np.float64) - want) <= bound)
