@@ -397,12 +397,19 @@ int rsh_plan_create(const rsh_csr_t* csr, int32_t N, const rsh_plan_opts_t* opts
             o.window_rows = rsh::choose_window_rows(*csr, part);
             if (o.window_rows != rsh::kW) rsh::partition_rows(*csr, o, h.order, tau_nnz, tau_inc, part, threads);
         }
-        // 16-row windows of up to 8 features join the residual rows where that pays, in the order in which the windows had them
-        if (choose_w && o.window_rows == rsh::kW && o.force_path == 0 && !o.element_level && N <= rsh::kNarrow && rsh::narrow_pays(*csr, part, n_user)) {
-            rsh_plan_opts_t residual = o;
-            residual.force_path = 1;
-            rsh::partition_rows(*csr, residual, h.order, tau_nnz, tau_inc, part, threads);
-            h.narrow_in_order = true;
+        // 16-row windows join the residual rows where that pays; those of up to 8 features in the order in which the windows had them
+        if (choose_w && o.window_rows == rsh::kW && o.force_path == 0 && !o.element_level) {
+            const bool in_order = N <= rsh::kNarrow && rsh::narrow_pays(*csr, part, n_user);
+            rsh_plan_opts_t usual;   // whoever asks for another partition, or for anything of windows, gets them
+            rsh_plan_opts_default(&usual);
+            const bool asked = o.partition != usual.partition || o.min_reuse != usual.min_reuse || o.hub_windows || o.long_row_nnz || o.tau_nnz >= 0 || o.tau_inc >= 0 ||
+                               o.max_tiles_per_item > 0 || o.side_stream;
+            if (in_order || (!asked && rsh::windows_lose(*csr, part, n_user))) {
+                rsh_plan_opts_t residual = o;
+                residual.force_path = 1;
+                rsh::partition_rows(*csr, residual, h.order, tau_nnz, tau_inc, part, threads);
+                h.narrow_in_order = in_order;
+            }
         }
         // Fragments of 16 columns in 16-row windows, of 32 where rows of B are two 16-byte pieces: a wave's one load per
         // fragment then names 32 rows and not 16 twice (27-point stencil on 80^3, 16 features, 42.7 us and 31.5; on 24^3 8.4 and

@@ -1012,8 +1012,20 @@ int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int thr
     }
 
     // residual rows: entries of a slice, and from which length on a row is cut by column group (both explained below)
-    const int64_t slice_max = plan.opts.max_nnz_per_slice > 0 ? plan.opts.max_nnz_per_slice : 512;
-    const int64_t xp_auto = std::max<int64_t>(128, 16384 / geo.irr_panel);
+    int64_t slice_auto = 512, xp_auto = std::max<int64_t>(128, 16384 / geo.irr_panel);
+    if (geo.N <= kNarrow) {
+        // Lanes that own or share rows take a row of up to 4096 entries in a wave, 64 or 128 a lane, and read the row of B of an entry in one
+        // or two requests, whichever XCD it is near to.  Power-law graphs, whole rows against slices of 512 and pieces by column
+        // group from 1024 entries on, 2^12 vertices 2 features 11.9 us and 8.8, 2^14 11.9 and 8.6 (no combine pass is left); from
+        // 2^19 entries on, where rows are longer, slices of 2048: 2^17 vertices 1 feature 20.0 and 17.2, 8 26.6 and 24.7; 2^19
+        // 82.9 and 72.9, 120.1 and 112.9, 16 138.9 and 128.4; 2^20 168.2 and 149.4, 239.6 and 229.0 (2^15 vertices, 16 features, in
+        // slices of 4096 17.2, of 2048 12.2).
+        int64_t entries = 0;
+        for (int32_t r : part.irregular) entries += row_len(a, r);
+        slice_auto = entries < (1 << 19) ? 4096 : 2048;
+        xp_auto = 0;
+    }
+    const int64_t slice_max = plan.opts.max_nnz_per_slice > 0 ? plan.opts.max_nnz_per_slice : slice_auto;
     const int64_t xp_min = plan.opts.xcd_partition_nnz == 0 ? xp_auto : plan.opts.xcd_partition_nnz;
 
     // ---- tile work items (bounded fragments per item, Section 3.3.3) --------------------
@@ -1476,6 +1488,44 @@ bool narrow_pays(const rsh_csr_t& a, const Partition& part, int n) {
     }
     if (entries > 10 * columns && entries * n_win >= windows << 22) return false;
     return a.n_cols * row_bytes <= (int64_t)3 << 20 || 2 * lines <= columns;
+}
+
+// Whether the 16-row windows of `part` are better off as residual rows because they hardly share columns (less than two
+// entries to a column), in small plans of 2^14 entries and more.  A window is one wave, or one a panel, that goes through its
+// columns sixteen at a time; residual rows are spread over as many waves as there are rows.
+//   * Beside residual rows that are more than half of the entries they cost a launch of their own, up to 2^27 entries times
+//     features.  Power-law graph of 2^14 vertices (419 windows of rows of medium length), with and without windows: 16 features
+//     14.4 us and 10.7, 50 26.6 and 14.1, 128 34.0 and 17.4, 256 42.2 and 22.6; 2^15 (180 windows) 50 29.3 and 19.2, 256 55.0 and 41.0,
+//     512 83.6 and 71.3.
+//   * Where an XCD's L2 holds all of B, up to 3 of its 4 MB, entries cost little: 1000 columns, 40 entries a row, 1000 rows, 64
+//     features 14.0 and 9.0, 256 23.1 and 9.1; 20000 rows 13.4 and 10.1, 33.8 and 25.3; 100000 rows (4 M entries) 35.6 and 41.1, 101.5
+//     and 101.4, but 16 features 18.4 and 13.6.  1100 columns, 20 a row, 100000 rows 16 features 16.3 and 9.2, 64 26.6 and
+//     21.4, 256 72.4 and 76.1.
+// Windows that share more keep theirs: communities (2.7 entries to a column), 25600 rows, 128 features 11.1 and 17.5; 27-point
+// stencil on 30^3 12.3 and 16.0.
+bool windows_lose(const rsh_csr_t& a, const Partition& part, int n) {
+    const int64_t n_win = (int64_t)part.win_row.size() / kW;
+    if (n_win == 0 || a.nnz < (1 << 14)) return false;
+    int64_t in_windows = 0;
+    for (int32_t r : part.win_row)
+        if (r >= 0) in_windows += row_len(a, r);
+    const bool beside = 2 * in_windows < a.nnz && in_windows * n <= (1ll << 27);
+    const bool cached = a.n_cols * 2 * n <= (int64_t)3 << 20 && (n <= kNarrow || (a.nnz * n <= (1ll << 28) && a.nnz < (3ll << 20)));
+    if (!beside && !cached) return false;
+    const int64_t step = std::max<int64_t>(1, n_win / 64);
+    int64_t entries = 0, columns = 0;   // of the sample
+    std::vector<int32_t> cols;
+    for (int64_t w = 0; w < n_win; w += step) {
+        cols.clear();
+        for (int r = 0; r < kW; ++r) {
+            const int32_t row = part.win_row[(size_t)(w * kW + r)];
+            if (row >= 0) cols.insert(cols.end(), a.col_idx + a.row_ptr[row], a.col_idx + a.row_ptr[row + 1]);
+        }
+        std::sort(cols.begin(), cols.end());
+        entries += (int64_t)cols.size();
+        columns += std::unique(cols.begin(), cols.end()) - cols.begin();
+    }
+    return entries < 2 * columns;
 }
 
 // Lanes that share a row of B in the residual part (narrow.hpp), or none for teams that share a wave (rsh_irregular_kernel).

@@ -824,3 +824,27 @@ def test_threads_that_cannot_be_started(room):
     done = subprocess.run([sys.executable, "-c", FEW_THREADS, root, str(room)], capture_output=True, text=True, timeout=120)
     assert done.returncode == 0 and done.stdout.strip() in ("made", "refused"), done.stderr[-2000:]
     assert room < 400 or done.stdout.strip() == "made"
+
+
+# Windows that hardly share columns (windows_lose): not where an XCD's L2 holds B, nor beside more residual rows than them; they stay
+# where they share more, in plans of a few entries and where the caller asks for windows.
+@pytest.mark.parametrize("cols,per_row,N,opts,windows", [(1000, 40, 64, {}, False), (1000, 40, 16, {}, False), (1000, 40, 64, dict(min_reuse=1.0), True),
+                                                         (1000, 40, 64, dict(window_rows=16), True), (400, 40, 64, {}, True), (1000, 40, 2000, {}, True)])
+def test_windows_that_hardly_share_columns(cols, per_row, N, opts, windows):
+    rng = np.random.default_rng(2)
+    rows = 2000
+    c = np.concatenate([rng.choice(cols, per_row, replace=False) for _ in range(rows)])
+    A = from_coo(np.repeat(np.arange(rows), per_row), c, rng.standard_normal(c.size), rows, cols)
+    st = host_plan(A, N, reorder=0, **opts).stats()
+    assert (st["nnz_tile"] > 0) == windows and (windows or st["nnz_irregular"] == A.nnz)
+
+
+@pytest.mark.parametrize("sparse_rows,windows", [(6000, False), (2000, True)])
+def test_windows_beside_many_residual_rows(sparse_rows, windows):
+    rng = np.random.default_rng(3)
+    c = np.concatenate([rng.choice(100000, 25, replace=False) for _ in range(sparse_rows)] +
+                       [rng.choice(1200, 48, replace=False) for _ in range(1600)])
+    r = np.concatenate([np.repeat(np.arange(sparse_rows), 25), sparse_rows + np.repeat(np.arange(1600), 48)])
+    A = from_coo(r, c, rng.standard_normal(c.size), sparse_rows + 1600, 100000)
+    st = host_plan(A, 128, reorder=0).stats()
+    assert (st["nnz_tile"] > 0) == windows and (windows or st["nnz_irregular"] == A.nnz)
