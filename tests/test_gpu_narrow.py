@@ -139,3 +139,14 @@ def test_small_plans_read_rows_of_any_width_where_they_lie(opts, N, fused):
     plan.destroy()
     assert bool(torch.isnan(flat[:65]).all()) and bool(torch.isnan(flat[65 + rows * N:]).all()), "stores outside C"
     assert np.all(np.abs(C.cpu().numpy().astype(np.float64) - want) <= bound)
+
+
+def test_products_go_to_the_current_stream():
+    import torch
+    from paper_2603_08734_amd import binding
+    torch.zeros(1, device="cuda")
+    side = torch.cuda.Stream()
+    assert binding.current_stream() == torch.cuda.current_stream().cuda_stream != side.cuda_stream
+    with torch.cuda.stream(side):
+        assert binding.current_stream() == side.cuda_stream
+    assert binding.current_stream() == torch.cuda.current_stream().cuda_stream
