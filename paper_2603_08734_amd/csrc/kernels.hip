@@ -11,7 +11,7 @@
 //                        (narrow.hpp)
 //   rsh_combine_kernel   fixed-order sum of the partial results of split windows / rows
 //   rsh_sum_narrow_kernel   the same for rows of up to 16 features, several rows per wave
-//   rsh_fragment_even_kernel, rsh_residual_even_kernel, rsh_sum_even_kernel   the first, third (its partial panel) and
+//   rsh_fragment_even_kernel, rsh_residual_even_kernel, rsh_sum_even_kernel   the first, third (widths that end in a partial panel) and
 //                        fourth for rows of an even number of features (device.hpp, Rows)
 //   rsh_fragment_any_kernel, rsh_residual_any_kernel, rsh_sum_any_kernel   the first, third and fourth
 //                        for rows of C of any length and alignment beside a padded copy of B
@@ -199,14 +199,14 @@ __device__ __forceinline__ void gather_steps(const BRows& Bp, int my_col, float 
     if (steps & 1) gather_group<1>(Bp, my_col, my_val, team_base + j, acc);
 }
 
-// PARTIAL: the panel (there is one, the last) holds fewer than 8 * TPR features.  Full panels carry no checks.
+// PARTIAL: the last panel holds fewer than 8 * TPR features.  Without one panels carry no checks.
 // N: features of a row of B; nv: of a row of C (N unless kAny); ns: of a partial row in scratch (N for whole rows).
 template <int TPR, class OUT, bool PARTIAL>
 __device__ __forceinline__ void irregular_body(
     const uint4* __restrict__ waves, const XcdSplit& xs,
     const int32_t* __restrict__ irr_row, const int32_t* __restrict__ irr_col,
     const uint16_t* __restrict__ irr_val, const __half* __restrict__ B, const OUT out,
-    float* __restrict__ scratch, int N, int feature0, int nv, int ns) {
+    float* __restrict__ scratch, int N, int nv, int ns) {
     constexpr int G = 64 / TPR;
     if constexpr (!OUT::kAny) nv = N;
     __shared__ __attribute__((aligned(16))) float lds_stage[kWavesPerBlock][64 * 8];
@@ -214,7 +214,8 @@ __device__ __forceinline__ void irregular_body(
     uint32_t wave;
     if (!xcd_work_item(xs, &wave)) return;
     const int team = lane / TPR, tl = lane % TPR, team_base = team * TPR;
-    const int panel = feature0 + blockIdx.y * (TPR * 8);
+    // a partial panel is the last; it begins early enough to hold eight features
+    const int first = (int)blockIdx.y * (TPR * 8), panel = PARTIAL && OUT::kRows != kRowsWhole ? min(first, N - 8) : first;
     float* stage = lds_stage[threadIdx.x >> 6] + team * (TPR * 8);
 
     const uint4 d = waves[wave];
@@ -301,11 +302,11 @@ __device__ __forceinline__ void irregular_body(
 #define RSH_IRREGULAR_PARAMS                                                                                                              \
     const uint4 *__restrict__ waves, XcdSplit xs, const int32_t *__restrict__ irr_row, const int32_t *__restrict__ irr_col,               \
         const uint16_t *__restrict__ irr_val, const __half *__restrict__ B, const OUT out, float *__restrict__ scratch, int N,            \
-        int feature0, int nv, int ns
+        int nv, int ns
 template <int TPR, class OUT, bool PARTIAL>
 __global__ __launch_bounds__(64 * kWavesPerBlock) __attribute__((amdgpu_waves_per_eu(8, 8))) void rsh_irregular_kernel(RSH_IRREGULAR_PARAMS) {
     static_assert(OUT::kRows == (PARTIAL ? kRowsWhole : kRowsEven));   // full panels of whole rows are no different
-    irregular_body<TPR, OUT, PARTIAL>(waves, xs, irr_row, irr_col, irr_val, B, out, scratch, N, feature0, nv, ns);
+    irregular_body<TPR, OUT, PARTIAL>(waves, xs, irr_row, irr_col, irr_val, B, out, scratch, N, nv, ns);
 }
 // Eight waves per SIMD take registers from the fp32 form's gather loops (rows of 100 features of the power-law graph of
 // 2^18 vertices: 157.0 us, 147.0 with seven; 50 features 110.1 and 101.5).  The binary16 form gains as much at panels
@@ -316,12 +317,12 @@ template <int TPR, class OUT>
 __global__ __launch_bounds__(64 * kWavesPerBlock) __attribute__((amdgpu_waves_per_eu(kEvenWaves<TPR, OUT>, kEvenWaves<TPR, OUT>)))
 void rsh_residual_even_kernel(RSH_IRREGULAR_PARAMS) {
     static_assert(OUT::kRows == kRowsEven);
-    irregular_body<TPR, OUT, true>(waves, xs, irr_row, irr_col, irr_val, B, out, scratch, N, feature0, nv, ns);
+    irregular_body<TPR, OUT, true>(waves, xs, irr_row, irr_col, irr_val, B, out, scratch, N, nv, ns);
 }
 template <int TPR, class OUT, bool PARTIAL>
 __global__ __launch_bounds__(64 * kWavesPerBlock) __attribute__((amdgpu_waves_per_eu(7, 7))) void rsh_residual_any_kernel(RSH_IRREGULAR_PARAMS) {
     static_assert(OUT::kAny);
-    irregular_body<TPR, OUT, PARTIAL>(waves, xs, irr_row, irr_col, irr_val, B, out, scratch, N, feature0, nv, ns);
+    irregular_body<TPR, OUT, PARTIAL>(waves, xs, irr_row, irr_col, irr_val, B, out, scratch, N, nv, ns);
 }
 #undef RSH_IRREGULAR_PARAMS
 
@@ -868,27 +869,29 @@ static inline uint32_t grid_for(const XcdSplit& xs) {
 // Feature widths of a launch: `nb` of a row of B, `nv` of a row of C.  Equal, even and at least 16 (whole rows: equal to
 // geo.N, a multiple of 16); or (OUT::kAny)
 // nb is the padded width, a multiple of 16, and nv any width up to it.  Partial sums have rows of geo.N >= nb.
-// Full panels in one launch; a last partial panel (nv not a multiple of the panel) in a launch of its own, which
-// starts early enough to hold eight features (those it shares with the panel before come out the same twice).
+// Full panels, or all panels of a width that ends in a partial one, which starts early enough to hold eight features (those
+// it shares with the panel before come out the same twice).  All in one launch of the partial panel's kernel: a launch of its
+// own ends with its longest waves, and the kernel of full panels gains less than that.  Power-law graphs, us, two launches and
+// one: 2^12 vertices 141 features 21.3 and 15.4, 2^14 176 29.7 and 21.2, 2^16 71.2 and 62.1, 254 89.5 and 81.3, 2^18 472 and 462,
+// 400 629 and 632.
 template <int TPR, class OUT>
 static void launch_irregular_t(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st, int nb, int nv) {
-    const int full = nv / d.geo.irr_panel;
-    const auto launch = [&](auto kernel, const auto& to, int panels, int feature0) {
-        hipLaunchKernelGGL(kernel, dim3(grid_for(d.irr_split), (unsigned)panels), dim3(64 * kWavesPerBlock),
+    const auto launch = [&](auto kernel, const auto& to) {
+        hipLaunchKernelGGL(kernel, dim3(grid_for(d.irr_split), (unsigned)(nv + d.geo.irr_panel - 1) / (unsigned)d.geo.irr_panel), dim3(64 * kWavesPerBlock),
                            0, st, (const uint4*)d.irr_wave, d.irr_split, d.irr_row, d.irr_col, d.irr_val, (const __half*)B, to,
-                           d.scratch, nb, feature0, nv, d.geo.N);
+                           d.scratch, nb, nv, d.geo.N);
     };
-    const int rest0 = std::min(full * d.geo.irr_panel, nb - 8);
+    const bool partial = nv % d.geo.irr_panel != 0;
     if constexpr (OUT::kAny) {
-        if (full > 0) launch(rsh_residual_any_kernel<TPR, OUT, false>, out, full, 0);
-        if (nv % d.geo.irr_panel) launch(rsh_residual_any_kernel<TPR, OUT, true>, out, 1, rest0);
-    } else {
+        if (partial) launch(rsh_residual_any_kernel<TPR, OUT, true>, out);
+        else launch(rsh_residual_any_kernel<TPR, OUT, false>, out);
+    } else if (!partial) {
         const auto even = out.general();
-        using Even = std::decay_t<decltype(even)>;
-        if (full > 0) launch(rsh_irregular_kernel<TPR, Even, false>, even, full, 0);
-        if (nv % d.geo.irr_panel == 0) return;
-        if constexpr (OUT::kWhole) launch(rsh_irregular_kernel<TPR, OUT, true>, out, 1, full * d.geo.irr_panel);
-        else launch(rsh_residual_even_kernel<TPR, OUT>, out, 1, rest0);
+        launch(rsh_irregular_kernel<TPR, std::decay_t<decltype(even)>, false>, even);
+    } else if constexpr (OUT::kWhole) {
+        launch(rsh_irregular_kernel<TPR, OUT, true>, out);
+    } else {
+        launch(rsh_residual_even_kernel<TPR, OUT>, out);
     }
 }
 
