@@ -841,7 +841,7 @@ static int lanes_per_row(const HostPlan& plan, const rsh_csr_t& a, const std::ve
 //   14000 x 4000     128    35.3   55.9  42.4  45.1  35.1  30.8
 //   15764 x 6465     200    80.5  205   134   169   117   103
 //   28672 x 8192     128    99.4  230   158   156   129   117
-// A wave's share has at most 32 fragments, so four waves take windows of up to 128.
+// A wave's share of 64 features has at most 32 fragments, so four waves take windows of up to 128.
 static int strip_form(const HostPlan& plan, int64_t n_win, uint32_t longest) {
     if (!plan.height_chosen || plan.opts.max_tiles_per_item > 0) return 0;
     // column ids and bytes of a row of B are multiplied as 24-bit numbers
@@ -850,7 +850,7 @@ static int strip_form(const HostPlan& plan, int64_t n_win, uint32_t longest) {
     const int64_t groups = n_win * plan.geo.panel_groups, small = groups * ((n + 31) / 32), blocks = groups * ((n + 63) / 64);
     const bool four = longest <= 128;
     if (small <= 256 || (n <= 32 && small <= 512)) return strip_code(32, 1, 8);
-    if (n <= 32) return strip_code(32, 2, four ? 4 : 8);
+    if (n <= 32) return strip_code(32, 2, 4);
     if (blocks <= 256) return strip_code(64, 1, 8);
     if (blocks <= 512) return strip_code(64, 2, 8);
     if (blocks <= 1024 && (four || n <= 64)) return strip_code(64, 2, four ? 4 : 8);

@@ -13,7 +13,8 @@
 //     features that are not stored, and the last pieces of B are read where they end with it.
 // What bounds it: a wave's instructions, some 52 vector ones a row group and fragment beside two multiply-adds (expansion of the
 // cells as in the panel kernel), and below some 100 workgroups the number of waves.
-// A share has at most 32 fragments = 1024 columns, which is the length of the fp32 chain of an output's partial sums.
+// A share has at most 32 fragments = 1024 columns, which is the length of the fp32 chain of an output's partial sums; or 64, whose
+// first half waits in LDS (four waves of 64 x 32; eight waves of half the share took 55.7 us at 28672 x 8192, 16 features, four 50.9).
 // Cells written out (wide.hpp) instead of packed, same split: 3000 x 3000 at density 0.2, 64 features 10.4 us and 9.5 packed, 14000 x
 // 4000 26.8 and 19.1, 28672 x 8192 99.7 and 66.6.  Four fragments of values in flight instead of two, at the price of
 // waves in flight: 28672 x 8192, 16 features 74 us against 64.  Times against the panel kernel's: strip_form in planner.cpp.
@@ -25,6 +26,8 @@
 namespace rsh {
 
 namespace {
+
+constexpr uint32_t kStripQuads = 8;   // of fragments that an fp32 chain may be long
 
 // RB row groups of 32 rows, panels of 32 * NCH32 features, WAVES waves, each a share of the window's fragments.
 template <int NCH32, int RB, int WAVES>
@@ -38,7 +41,11 @@ struct StripGeom {
     static constexpr int NBUF = 2;                        // tiles of a wave: one is read, the next is staged
     static constexpr int TILE_HALVES = kPanelK * LDB;
     static constexpr int LOOP_BYTES = NBUF * TILE_HALVES * 2, SUM_BYTES = RB * NCH32 * 32 * kStageStride * 4;
-    static constexpr int WAVE_BYTES = LOOP_BYTES > SUM_BYTES ? LOOP_BYTES : SUM_BYTES;
+    // Four waves of 64 x 32 take shares of up to 64 fragments: behind 32 the sums go to their stage, which then lies beside the
+    // tiles and not in their place (three workgroups still fit a compute unit).
+    static constexpr bool LONG = NCH32 == 1 && RB == 2 && WAVES == 4;
+    static constexpr int STAGE_AT = LONG ? LOOP_BYTES : 0;
+    static constexpr int WAVE_BYTES = LONG ? LOOP_BYTES + SUM_BYTES : LOOP_BYTES > SUM_BYTES ? LOOP_BYTES : SUM_BYTES;
 };
 
 // Rows of B of a wave's fragments, from memory through registers into its own LDS tiles.
@@ -115,11 +122,28 @@ struct StripRows {
     }
 };
 
+// A wave's sums to its stage, rows of 32 features; `more`: to what is there.
+template <int NCH32, int RB>
+__device__ __forceinline__ void strip_store_sums(float* stage, const float16_t (&acc)[RB][NCH32], bool more) {
+    const int lane = threadIdx.x & 63, n = lane & 31, hh = lane >> 5;
+#pragma unroll
+    for (int g = 0; g < RB; ++g)
+#pragma unroll
+        for (int c = 0; c < NCH32; ++c)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                float4_t* to = reinterpret_cast<float4_t*>(stage + (32 * (g * NCH32 + c) + n) * kStageStride + 8 * q + 4 * hh);
+                float4_t v = {acc[g][c][4 * q], acc[g][c][4 * q + 1], acc[g][c][4 * q + 2], acc[g][c][4 * q + 3]};
+                if (more) v += *to;
+                *to = v;
+            }
+}
+
 // The products of one wave, whole quads of fragments.
 template <class Gm, int NCH32, int RB, bool RUN, bool RAGGED>
 __device__ __forceinline__ void strip_share(StripRows<Gm, RUN, RAGGED> rows, const unsigned char* table, uint32_t quads, uint32_t quad, uint32_t nq,
-                                             const uint4_t* __restrict__ meta, const uint32_t* __restrict__ qoff, const uint32_t* __restrict__ val,
-                                             float16_t (&acc)[RB][NCH32]) {
+                                            const uint4_t* __restrict__ meta, const uint32_t* __restrict__ qoff, const uint32_t* __restrict__ val,
+                                            [[maybe_unused]] float* stage, float16_t (&acc)[RB][NCH32]) {
     constexpr int BR = Gm::BR, VR = Gm::VR, NBUF = Gm::NBUF;
     const int lane = threadIdx.x & 63;
     const uint4_t* my_meta[RB];
@@ -194,16 +218,27 @@ __device__ __forceinline__ void strip_share(StripRows<Gm, RUN, RAGGED> rows, con
 #pragma unroll
         for (int g = 0; g < RB; ++g) m_cur[g] = m_nxt[g];
         fetch_meta(q + 2, m_nxt);
+        if constexpr (Gm::LONG) {
+            if (q + 1 == kStripQuads && q + 1 < quads) {   // uniform
+                strip_store_sums<NCH32, RB>(stage, acc, false);
+#pragma unroll
+                for (int g = 0; g < RB; ++g)
+#pragma unroll
+                    for (int c = 0; c < NCH32; ++c)
+#pragma unroll
+                        for (int v = 0; v < 16; ++v) acc[g][c][v] = 0.f;
+            }
+        }
     }
 }
 
 // Waves per SIMD that a workgroup's registers are to leave room for: 128 registers where waves hide each other's latency, 168
-// at two row groups; at 64 features two waves (a second workgroup of four) are all that the sums allow.
-template <int NCH32, int RB>
-constexpr int kStripWaves = NCH32 == 2 ? 2 : RB == 2 ? 3 : 4;
+// at two row groups (more where broken pieces are moved); at 64 features two waves are all that the sums allow.
+template <int NCH32, int RB, bool RAGGED>
+constexpr int kStripWaves = NCH32 == 2 || (RB == 2 && RAGGED) ? 2 : RB == 2 ? 3 : 4;
 
 template <int NCH32, int RB, int WAVES, bool RAGGED, class OUT>
-__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(kStripWaves<NCH32, RB>))) void rsh_strip_kernel(
+__global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(kStripWaves<NCH32, RB, RAGGED>))) void rsh_strip_kernel(
     const int32_t* __restrict__ win_row, const uint32_t* __restrict__ win_tile_off, const int32_t* __restrict__ win_run,
     const int32_t* __restrict__ tile_colid, const uint4_t* __restrict__ meta, const uint32_t* __restrict__ quad0, const uint32_t* __restrict__ qoff,
     const uint32_t* __restrict__ val, const __half* __restrict__ B, const OUT out, uint32_t n_blocks, uint32_t groups, uint32_t panels, int N, int nv, uint32_t b_last) {
@@ -244,31 +279,22 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(kStr
         write_selectors(table, lane);   // every wave the same, ahead of its own reads
         const auto share = [&](auto run) {
             StripRows<Gm, decltype(run)::value, RAGGED> rows(reinterpret_cast<_Float16*>(mine), t0, nt - 1, 4 * qa, col0, col_last, tile_colid, B, N, panel, b_last);
-            strip_share<Gm, NCH32, RB>(rows, table, quads, quad0[win] + group * nq + qa, nq, meta, qoff, val, acc);
+            strip_share<Gm, NCH32, RB>(rows, table, quads, quad0[win] + group * nq + qa, nq, meta, qoff, val, reinterpret_cast<float*>(mine + Gm::STAGE_AT), acc);
         };
         if (col0 >= 0) share(std::true_type{});
         else share(std::false_type{});
     }
 
-    // every wave's sums to its stage, rows of 32 features, then added up in the order of the waves
-    float* const stage = reinterpret_cast<float*>(mine);
-    const int n = lane & 31, hh = lane >> 5;
+    // every wave's sums to its stage, then added up in the order of the waves
     __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int g = 0; g < RB; ++g)
-#pragma unroll
-        for (int c = 0; c < NCH32; ++c)
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                *reinterpret_cast<float4_t*>(stage + (32 * (g * NCH32 + c) + n) * kStageStride + 8 * q + 4 * hh) =
-                    (float4_t){acc[g][c][4 * q], acc[g][c][4 * q + 1], acc[g][c][4 * q + 2], acc[g][c][4 * q + 3]};
+    strip_store_sums<NCH32, RB>(reinterpret_cast<float*>(mine + Gm::STAGE_AT), acc, Gm::LONG && quads > kStripQuads);
     block_barrier();
     constexpr int kQuads = RB * 8 * P;      // quads of features: 32 rows of P / 4 each per row group
 #pragma unroll
     for (int i = 0; i < (kQuads + 64 * WAVES - 1) / (64 * WAVES); ++i) {
         const int id = i * 64 * WAVES + (int)threadIdx.x, fp = id & 7, pr = (id >> 3) & 31, gc = id >> 8;
         if (kQuads % (64 * WAVES) != 0 && id >= kQuads) break;
-        const float* from = reinterpret_cast<const float*>(smem) + (32 * gc + pr) * kStageStride + 4 * fp;
+        const float* from = reinterpret_cast<const float*>(smem + Gm::STAGE_AT) + (32 * gc + pr) * kStageStride + 4 * fp;
         float4_t s[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
         for (int w = 0; w < WAVES; ++w) s[w & 1] += *reinterpret_cast<const float4_t*>(from + w * (Gm::WAVE_BYTES / 4));
@@ -299,7 +325,6 @@ template <class OUT>
 int launch_strip(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st, int nb, int nv) {
     switch (d.geo.strip) {
         case strip_code(32, 1, 8): launch_strip_t<1, 1, 8>(d, B, out, st, nb, nv); break;
-        case strip_code(32, 2, 8): launch_strip_t<1, 2, 8>(d, B, out, st, nb, nv); break;
         case strip_code(32, 2, 4): launch_strip_t<1, 2, 4>(d, B, out, st, nb, nv); break;
         case strip_code(64, 1, 8): launch_strip_t<2, 1, 8>(d, B, out, st, nb, nv); break;
         case strip_code(64, 2, 8): launch_strip_t<2, 2, 8>(d, B, out, st, nb, nv); break;

@@ -20,7 +20,7 @@ def matrix(rows, cols, density, seed=3, holes=True):
     return from_coo(r, c, rng.standard_normal(r.size), rows, cols)
 
 
-A32, B32, B32L, A64, B64, B64L, E64 = (32, 1, 8), (32, 2, 4), (32, 2, 8), (64, 1, 8), (64, 2, 8), (64, 2, 8), (64, 2, 4)
+A32, B32, A64, B64, B64L, E64 = (32, 1, 8), (32, 2, 4), (64, 1, 8), (64, 2, 8), (64, 2, 8), (64, 2, 4)
 # Columns: less than a fragment, less than a quad (waves without work), quads that do not divide among the waves, the most that
 # four waves take and one fragment more.  Features: every place in which a row of B or C can end (inside pieces of 8 and 4, odd
 # ones, whole panels, one into the next panel).  Rows: a last window with absent groups and half a group.
@@ -28,7 +28,7 @@ CASES = [
     (1100, 20, 0.5, 1, A32), (1100, 20, 0.5, 16, A32), (1100, 130, 0.3, 7, A32), (1100, 1100, 0.2, 3, A32), (1100, 1100, 0.2, 8, A32),
     (1100, 1100, 0.2, 15, A32), (1100, 1100, 0.2, 17, A32), (1100, 1100, 0.2, 31, A32), (1100, 1100, 0.2, 32, A32), (1100, 300, 0.2, 33, A32),
     (1100, 300, 0.2, 100, A32), (1100, 300, 0.2, 191, A32), (1030, 8192, 0.15, 24, A32),
-    (16500, 40, 0.5, 3, B32), (16500, 130, 0.3, 9, B32), (16500, 130, 0.3, 16, B32), (16500, 300, 0.2, 31, B32), (16500, 4130, 0.1, 13, B32L),
+    (16500, 40, 0.5, 3, B32), (16500, 130, 0.3, 9, B32), (16500, 130, 0.3, 16, B32), (16500, 300, 0.2, 31, B32), (16500, 4130, 0.1, 13, B32), (16500, 8192, 0.1, 5, B32),
     (4300, 300, 0.2, 64, A64), (4300, 130, 0.3, 50, A64), (4300, 300, 0.2, 63, A64), (1100, 300, 0.2, 350, A64), (1100, 300, 0.2, 257, A64),
     (8300, 300, 0.2, 64, B64), (8300, 130, 0.3, 58, B64), (8300, 20, 0.5, 33, B64), (2143, 300, 0.2, 203, B64),
     (16600, 300, 0.2, 64, E64), (16600, 130, 0.3, 42, E64), (8300, 130, 0.3, 127, E64), (16500, 4130, 0.1, 62, B64L),
