@@ -79,10 +79,13 @@ typedef struct {
     int32_t knn_k;        /* neighbours kept per row in the kNN graph (Algorithm 3, step II)     */
     float alpha;          /* exponent of the column weight w_j = d_j^-alpha (Section 3.4)        */
     int32_t max_tiles_per_item; /* bound on fragments per tile work item; 0 = auto              */
-    int32_t max_nnz_per_slice;  /* bound on stored entries per wave slice of a long row; 0 = auto (512) */
+    int32_t max_nnz_per_slice;  /* bound on stored entries per wave slice of a long row; 0 = auto (512; run widths up to
+                             16: 4096, or 2048 from 2^19 residual entries on)                         */
     int32_t force_path;   /* 0 = hybrid, 1 = every row on the irregular path, 2 = every non-empty
                              row in a window (tests compare the three)                          */
-    float min_reuse;      /* partition == 1: dissolve windows with nnz/|U| below this           */
+    float min_reuse;      /* partition == 1: dissolve windows with nnz/|U| below this.  Small plans that leave this and the
+                             other options of windows at their defaults dissolve 16-row windows below 2 as well
+                             where B fits an XCD's L2 or residual rows hold most entries                */
     int32_t long_row_nnz; /* partition == 1: rows longer than this go to the irregular path; 0 = auto */
     int32_t window_schedule; /* 1 (default) = on square matrices the windows are issued in an order built over
                              "window u names a row that window v holds": breadth-first clusters, or a
@@ -95,7 +98,7 @@ typedef struct {
     int32_t xcd_partition_nnz; /* irregular rows with at least this many entries are cut by column group,
                              one group per XCD, so that each XCD gathers one eighth of B's columns for
                              them; 0 = auto (128 for feature panels of 128 columns, 16384 / panel
-                             columns for narrower ones), negative = off                            */
+                             columns for narrower ones, off at run widths up to 16), negative = off  */
     int32_t run_width;    /* feature width the kernels run at: a multiple of 16 that is >= N and <= 4096, or
                              0 = N rounded up to a multiple of 16 (see rsh_plan_create)                */
     int32_t transpose;    /* 1 = plan C = A^T * B instead (the product a backward pass needs): the CSR is
@@ -179,7 +182,8 @@ int rsh_plan_opts_default(rsh_plan_opts_t *opts);
  * bias then need 16-byte alignment where N is a multiple of 16, else 4-byte alignment.  For other widths
  * (odd ones, those below 16, a run_width the caller chose, operands with less alignment) the kernels run at
  * a width NR > N (plans of up to 8 features without windows at a run width of 16: the next power of two, and where N is one
- * and B is aligned to its rows, N; small plans of tall windows alone read rows of fewer than 16 features where they lie;
+ * and B is aligned to its rows, N; small plans of tall windows alone, and plans of fewer than 2^18 entries without windows, read
+ * rows of fewer than 16 features where they lie, and products of tall windows whose waves divide the columns those of odd widths;
  * rsh_plan_operand answers for a plan): whenever N is not a multiple of 16 (or opts->run_width asks for it) the plan owns a
  * binary16 buffer [n_cols][NR] on the device, and such a product first copies B into it (pad columns zero);
  * the kernels then store the N columns of the result into C themselves.  B, C and bias then only need the

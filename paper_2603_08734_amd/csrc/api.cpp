@@ -404,7 +404,7 @@ int rsh_plan_create(const rsh_csr_t* csr, int32_t N, const rsh_plan_opts_t* opts
             rsh_plan_opts_default(&usual);
             const bool asked = o.partition != usual.partition || o.min_reuse != usual.min_reuse || o.hub_windows || o.long_row_nnz || o.tau_nnz >= 0 || o.tau_inc >= 0 ||
                                o.max_tiles_per_item > 0 || o.side_stream;
-            if (in_order || (!asked && rsh::windows_lose(*csr, part, n_user))) {
+            if (in_order || (!asked && rsh::windows_lose(*csr, part, n_user, o))) {
                 rsh_plan_opts_t residual = o;
                 residual.force_path = 1;
                 rsh::partition_rows(*csr, residual, h.order, tau_nnz, tau_inc, part, threads);

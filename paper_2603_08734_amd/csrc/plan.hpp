@@ -140,7 +140,7 @@ NarrowPart pack_narrow(const HostPlan& plan, int threads);
 // Whether the 16-row windows of `part` are better off as residual rows at n features (narrow.hpp).
 bool narrow_pays(const rsh_csr_t& a, const Partition& part, int n);
 // Whether they are at any number of features, because they hardly share columns.
-bool windows_lose(const rsh_csr_t& a, const Partition& part, int n);
+bool windows_lose(const rsh_csr_t& a, const Partition& part, int n, const rsh_plan_opts_t& o);
 // Features of a row of B as narrow.hpp reads it.
 inline int narrow_width(int n) {
     int w = 1;

@@ -1503,7 +1503,9 @@ bool narrow_pays(const rsh_csr_t& a, const Partition& part, int n) {
 //     21.4, 256 72.4 and 76.1.
 // Windows that share more keep theirs: communities (2.7 entries to a column), 25600 rows, 128 features 11.1 and 17.5; 27-point
 // stencil on 30^3 12.3 and 16.0.
-bool windows_lose(const rsh_csr_t& a, const Partition& part, int n) {
+// None of it where the partial sums of all rows together (an upper bound of them) would not fit the library-owned array: windows
+// keep the product in rsh_spmm_noalloc.
+bool windows_lose(const rsh_csr_t& a, const Partition& part, int n, const rsh_plan_opts_t& o) {
     const int64_t n_win = (int64_t)part.win_row.size() / kW;
     if (n_win == 0 || a.nnz < (1 << 14)) return false;
     int64_t in_windows = 0;
@@ -1512,6 +1514,15 @@ bool windows_lose(const rsh_csr_t& a, const Partition& part, int n) {
     const bool beside = 2 * in_windows < a.nnz && in_windows * n <= (1ll << 27);
     const bool cached = a.n_cols * 2 * n <= (int64_t)3 << 20 && (n <= kNarrow || (a.nnz * n <= (1ll << 28) && a.nnz < (3ll << 20)));
     if (!beside && !cached) return false;
+    const Geometry geo = make_geometry(o.run_width, kW, kW);
+    const int64_t slice = o.max_nnz_per_slice > 0 ? o.max_nnz_per_slice : 512, cut = o.xcd_partition_nnz == 0 ? std::max<int64_t>(128, 16384 / geo.irr_panel) : o.xcd_partition_nnz;
+    int64_t slots = 0;
+    for (const std::vector<int32_t>* rows : {&part.irregular, &part.win_row})
+        for (int32_t r : *rows) {
+            const int64_t len = r >= 0 ? row_len(a, r) : 0, slices = (len + slice - 1) / slice;
+            if (len > geo.irr_tpr) slots += cut > 0 && len >= cut ? std::min(len, slices + 8) : slices > 1 ? slices : 0;
+        }
+    if (slots * geo.N * (int64_t)sizeof(float) > (int64_t)kStaticScratchBytes) return false;
     const int64_t step = std::max<int64_t>(1, n_win / 64);
     int64_t entries = 0, columns = 0;   // of the sample
     std::vector<int32_t> cols;

@@ -848,3 +848,13 @@ def test_windows_beside_many_residual_rows(sparse_rows, windows):
     A = from_coo(r, c, rng.standard_normal(c.size), sparse_rows + 1600, 100000)
     st = host_plan(A, 128, reorder=0).stats()
     assert (st["nnz_tile"] > 0) == windows and (windows or st["nnz_irregular"] == A.nnz)
+
+
+def test_dissolved_windows_keep_their_product_in_the_library_owned_array():
+    """17000 rows of 130 entries in 4000 columns would leave eight partial rows each, 70 MB at 128 features; half as many do not."""
+    rng = np.random.default_rng(4)
+    for rows, windows in ((17000, True), (8000, False)):
+        c = np.sort(rng.integers(0, 4000 - 130, (rows, 130)), axis=1) + np.arange(130)
+        A = from_coo(np.repeat(np.arange(rows), 130), c.ravel(), np.ones(rows * 130), rows, 4000)
+        st = host_plan(A, 128, reorder=0, min_reuse=1.25).stats()
+        assert (st["nnz_tile"] > 0) == windows and st["n_scratch_slots"] * 128 * 4 <= 64 << 20
