@@ -852,7 +852,9 @@ static int strip_form(const HostPlan& plan, int64_t n_win, uint32_t longest) {
     if (small <= 256 || (n <= 32 && small <= 512)) return strip_code(32, 1, 8);
     if (n <= 32) return strip_code(32, 2, 4);
     if (blocks <= 256) return strip_code(64, 1, 8);
-    if (blocks <= 512) return strip_code(64, 2, 8);
+    // beyond 26 fragments a wave the chains of 64 x 64 would be longer than those of windows that are cut for want of others: relative
+    // error against 64 bits of a 10952 x 7178 weight (28 a wave), 48 features, 1.82e-7 and in the panel kernel 1.78e-7
+    if (blocks <= 512) return longest <= 208 ? strip_code(64, 2, 8) : 0;
     if (blocks <= 1024 && (four || n <= 64)) return strip_code(64, 2, four ? 4 : 8);
     return 0;
 }
@@ -1016,13 +1018,13 @@ int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int thr
     if (geo.N <= kNarrow) {
         // Lanes that own or share rows take a row of up to 4096 entries in a wave, 64 or 128 a lane, and read the row of B of an entry in one
         // or two requests, whichever XCD it is near to.  Power-law graphs, whole rows against slices of 512 and pieces by column
-        // group from 1024 entries on, 2^12 vertices 2 features 11.9 us and 8.8, 2^14 11.9 and 8.6 (no combine pass is left); from
-        // 2^19 entries on, where rows are longer, slices of 2048: 2^17 vertices 1 feature 20.0 and 17.2, 8 26.6 and 24.7; 2^19
-        // 82.9 and 72.9, 120.1 and 112.9, 16 138.9 and 128.4; 2^20 168.2 and 149.4, 239.6 and 229.0 (2^15 vertices, 16 features, in
-        // slices of 4096 17.2, of 2048 12.2).
+        // group from 1024 entries on, 2^12 vertices 2 features 11.9 us and 8.8, 2^14 11.9 and 8.6 (no combine pass is left).  From
+        // 2^19 entries on, where rows are longer and a wave with a whole one ends last, slices of 1024: 2^16 vertices, 8 features 17.8 and
+        // 15.7 (of 4096 17.8), 2^17 26.6 and 24.9.  From 2^22 on of 2048: 2^19 1 feature 82.9 and 72.9, 8 120.1 and 112.9, 16
+        // 138.9 and 128.4; 2^20 168.2 and 149.4 (of 1024 153.9), 239.6 and 229.0 (233.7).
         int64_t entries = 0;
         for (int32_t r : part.irregular) entries += row_len(a, r);
-        slice_auto = entries < (1 << 19) ? 4096 : 2048;
+        slice_auto = entries < (1 << 19) ? 4096 : entries < (1 << 22) ? 1024 : 2048;
         xp_auto = 0;
     }
     const int64_t slice_max = plan.opts.max_nnz_per_slice > 0 ? plan.opts.max_nnz_per_slice : slice_auto;

@@ -13,8 +13,9 @@
 //     features that are not stored, and the last pieces of B are read where they end with it.
 // What bounds it: a wave's instructions, some 52 vector ones a row group and fragment beside two multiply-adds (expansion of the
 // cells as in the panel kernel), and below some 100 workgroups the number of waves.
-// A share has at most 32 fragments = 1024 columns, which is the length of the fp32 chain of an output's partial sums; or 64, whose
-// first half waits in LDS (four waves of 64 x 32; eight waves of half the share took 55.7 us at 28672 x 8192, 16 features, four 50.9).
+// An output's fp32 chains have at most 32 fragments = 1024 columns, those of one row group 16: relative error against 64 bits of a
+// 2000 x 8000 weight, 16 features, 1.64e-7 in the panel kernel, 2.01e-7 with chains of 32, 1.52e-7 with 16.  (64 x 32 in four waves, whose
+// first half waits in LDS: 28672 x 8192, 16 features, 50.9 us, in eight waves of half the share 55.7.)
 // Cells written out (wide.hpp) instead of packed, same split: 3000 x 3000 at density 0.2, 64 features 10.4 us and 9.5 packed, 14000 x
 // 4000 26.8 and 19.1, 28672 x 8192 99.7 and 66.6.  Four fragments of values in flight instead of two, at the price of
 // waves in flight: 28672 x 8192, 16 features 74 us against 64.  Times against the panel kernel's: strip_form in planner.cpp.
@@ -26,8 +27,6 @@
 namespace rsh {
 
 namespace {
-
-constexpr uint32_t kStripQuads = 8;   // of fragments that an fp32 chain may be long
 
 // RB row groups of 32 rows, panels of 32 * NCH32 features, WAVES waves, each a share of the window's fragments.
 template <int NCH32, int RB, int WAVES>
@@ -41,9 +40,11 @@ struct StripGeom {
     static constexpr int NBUF = 2;                        // tiles of a wave: one is read, the next is staged
     static constexpr int TILE_HALVES = kPanelK * LDB;
     static constexpr int LOOP_BYTES = NBUF * TILE_HALVES * 2, SUM_BYTES = RB * NCH32 * 32 * kStageStride * 4;
-    // Four waves of 64 x 32 take shares of up to 64 fragments: behind 32 the sums go to their stage, which then lies beside the
-    // tiles and not in their place (three workgroups still fit a compute unit).
-    static constexpr bool LONG = NCH32 == 1 && RB == 2 && WAVES == 4;
+    // Quads of fragments that an fp32 chain may be long: 32 fragments, or 16 where the kernels of whole windows cut their few windows
+    // as finely.  Behind them the sums of 32 features go to their stage, which then lies beside the tiles and not in their place (as
+    // many workgroups fit a compute unit), those of 32 x 64 to a second set of registers; shares of 64 x 64 have no more.
+    static constexpr uint32_t CHAIN = RB == 1 ? 4 : 8;
+    static constexpr bool LONG = NCH32 == 1, SECOND = NCH32 == 2 && RB == 1;
     static constexpr int STAGE_AT = LONG ? LOOP_BYTES : 0;
     static constexpr int WAVE_BYTES = LONG ? LOOP_BYTES + SUM_BYTES : LOOP_BYTES > SUM_BYTES ? LOOP_BYTES : SUM_BYTES;
 };
@@ -163,6 +164,15 @@ __device__ __forceinline__ void strip_share(StripRows<Gm, RUN, RAGGED> rows, con
         my_meta[g] = meta + (size_t)(quad + (uint32_t)g * nq) * 64 + lane;
         vbase[g] = val + qoff[quad + (uint32_t)g * nq];
     }
+    [[maybe_unused]] float16_t first[RB][NCH32];   // sums of the share's first half
+    if constexpr (Gm::SECOND) {
+#pragma unroll
+        for (int g = 0; g < RB; ++g)
+#pragma unroll
+            for (int c = 0; c < NCH32; ++c)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) first[g][c][v] = 0.f;
+    }
     // Selectors of a fragment's cells, one fragment ahead.
     Selectors sel[RB][2];
     auto look_up = [&](int u, const uint4_t (&m)[RB]) {
@@ -218,24 +228,32 @@ __device__ __forceinline__ void strip_share(StripRows<Gm, RUN, RAGGED> rows, con
 #pragma unroll
         for (int g = 0; g < RB; ++g) m_cur[g] = m_nxt[g];
         fetch_meta(q + 2, m_nxt);
-        if constexpr (Gm::LONG) {
-            if (q + 1 == kStripQuads && q + 1 < quads) {   // uniform
-                strip_store_sums<NCH32, RB>(stage, acc, false);
+        if constexpr (Gm::LONG || Gm::SECOND) {
+            if (q + 1 == Gm::CHAIN && q + 1 < quads) {   // uniform; a share has at most twice as many
+                if constexpr (Gm::LONG) strip_store_sums<NCH32, RB>(stage, acc, false);
 #pragma unroll
                 for (int g = 0; g < RB; ++g)
 #pragma unroll
-                    for (int c = 0; c < NCH32; ++c)
+                    for (int c = 0; c < NCH32; ++c) {
+                        if constexpr (Gm::SECOND) first[g][c] = acc[g][c];
 #pragma unroll
                         for (int v = 0; v < 16; ++v) acc[g][c][v] = 0.f;
+                    }
             }
         }
+    }
+    if constexpr (Gm::SECOND) {
+#pragma unroll
+        for (int g = 0; g < RB; ++g)
+#pragma unroll
+            for (int c = 0; c < NCH32; ++c) acc[g][c] += first[g][c];
     }
 }
 
 // Waves per SIMD that a workgroup's registers are to leave room for: 128 registers where waves hide each other's latency, 168
 // at two row groups (more where broken pieces are moved); at 64 features two waves are all that the sums allow.
 template <int NCH32, int RB, bool RAGGED>
-constexpr int kStripWaves = NCH32 == 2 || (RB == 2 && RAGGED) ? 2 : RB == 2 ? 3 : 4;
+constexpr int kStripWaves = NCH32 == 2 || RAGGED ? 2 : RB == 2 ? 3 : 4;
 
 template <int NCH32, int RB, int WAVES, bool RAGGED, class OUT>
 __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(kStripWaves<NCH32, RB, RAGGED>))) void rsh_strip_kernel(
@@ -287,7 +305,7 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(kStr
 
     // every wave's sums to its stage, then added up in the order of the waves
     __builtin_amdgcn_wave_barrier();
-    strip_store_sums<NCH32, RB>(reinterpret_cast<float*>(mine + Gm::STAGE_AT), acc, Gm::LONG && quads > kStripQuads);
+    strip_store_sums<NCH32, RB>(reinterpret_cast<float*>(mine + Gm::STAGE_AT), acc, Gm::LONG && quads > Gm::CHAIN);
     block_barrier();
     constexpr int kQuads = RB * 8 * P;      // quads of features: 32 rows of P / 4 each per row group
 #pragma unroll
