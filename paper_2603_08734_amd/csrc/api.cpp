@@ -403,7 +403,7 @@ int rsh_plan_create(const rsh_csr_t* csr, int32_t N, const rsh_plan_opts_t* opts
             rsh_plan_opts_t usual;   // whoever asks for another partition, or for anything of windows, gets them
             rsh_plan_opts_default(&usual);
             const bool asked = o.partition != usual.partition || o.min_reuse != usual.min_reuse || o.hub_windows || o.long_row_nnz || o.tau_nnz >= 0 || o.tau_inc >= 0 ||
-                               o.max_tiles_per_item > 0 || o.side_stream;
+                               o.max_tiles_per_item > 0 || o.tile_k != usual.tile_k || o.window_schedule != usual.window_schedule || o.side_stream;
             if (in_order || (!asked && rsh::windows_lose(*csr, part, n_user, o))) {
                 rsh_plan_opts_t residual = o;
                 residual.force_path = 1;

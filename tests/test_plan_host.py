@@ -839,6 +839,16 @@ def test_windows_that_hardly_share_columns(cols, per_row, N, opts, windows):
     assert (st["nnz_tile"] > 0) == windows and (windows or st["nnz_irregular"] == A.nnz)
 
 
+@pytest.mark.parametrize("opts", [dict(tile_k=16), dict(tile_k=32), dict(window_schedule=0), dict(tau_nnz=1), dict(tau_inc=0), dict(max_tiles_per_item=8),
+                                  dict(side_stream=1), dict(partition=0), dict(hub_windows=1), dict(long_row_nnz=1000)])
+def test_callers_who_ask_anything_of_windows_get_them(opts):
+    rng = np.random.default_rng(2)
+    c = np.concatenate([rng.choice(1000, 40, replace=False) for _ in range(2000)])
+    A = from_coo(np.repeat(np.arange(2000), 40), c, rng.standard_normal(c.size), 2000, 1000)
+    assert host_plan(A, 64, reorder=0).stats()["nnz_tile"] == 0
+    assert host_plan(A, 64, reorder=0, **opts).stats()["nnz_tile"] > 0
+
+
 @pytest.mark.parametrize("sparse_rows,windows", [(6000, False), (2000, True)])
 def test_windows_beside_many_residual_rows(sparse_rows, windows):
     rng = np.random.default_rng(3)
