@@ -80,7 +80,7 @@ typedef struct {
     float alpha;          /* exponent of the column weight w_j = d_j^-alpha (Section 3.4)        */
     int32_t max_tiles_per_item; /* bound on fragments per tile work item; 0 = auto              */
     int32_t max_nnz_per_slice;  /* bound on stored entries per wave slice of a long row; 0 = auto (512; run widths up to
-                             16: 4096, 1024 from 2^19 residual entries on, 2048 from 2^22 on)         */
+                             16: 512 to 4096, by the entries, the longest row and the size of B)       */
     int32_t force_path;   /* 0 = hybrid, 1 = every row on the irregular path, 2 = every non-empty
                              row in a window (tests compare the three)                          */
     float min_reuse;      /* partition == 1: dissolve windows with nnz/|U| below this.  Small plans that leave this and the

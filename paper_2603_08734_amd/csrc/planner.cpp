@@ -822,6 +822,38 @@ static std::vector<uint32_t> cut_tall_windows(const HostPlan& plan, int64_t n_wi
 
 static int lanes_per_row(const HostPlan& plan, const rsh_csr_t& a, const std::vector<int32_t>& rows, int64_t entries);
 
+// Entries of a slice of a residual row where lanes own or share rows (run widths up to 16).  They read the row of B of an entry in one or two
+// requests, whichever XCD it is near to, so rows are not cut by column group; a row that no wave takes whole costs a combine
+// pass, 2 to 4 us, a wave that takes a long one ends last.  Times in us of slices of 512 with pieces by column group from 1024 entries
+// on, and of longer slices without:
+//   * Below 2^19 entries rows stay whole while the gathers of the longest take less than that pass: up to 1024 entries always, up to 4096
+//     (2560 where two lanes share a row) as far as B lies near enough.  Power-law graph of 2^12 vertices 2 features 7.2 and 4.8 (whole), of 2^14 8
+//     features 9.0 and 7.6, 16 features (rows of 3626) 9.8 and 10.5, in slices of 512 9.0; 64 rows of 4000 entries in 100000 columns 4 features
+//     (0.8 MB) 10.4 and 9.2, 8 features (1.6 MB) 10.5 and 13.4, of 3000 8.8 and 8.0; in 1000000 columns 1 feature (2 MB) rows of 2000 9.0 and
+//     7.4, of 4000 10.4 and 18.7, 2 features rows of 2000 (4 MB) 8.5 and 12.4; 16 features rows of 1000 8.7 and 5.5, of 1500 7.2 and 8.5.
+//   * Beyond, where rows of more than 1024 entries hold most of the entries, slices that make some 768 waves of them.  500 rows of 3000 entries
+//     in 500000 columns, 16 features 21.2 and in slices of 1024 24.4, 2048 20.7; 2000 rows of 2000 37.5, 50.1 and 34.8; 3000 rows of 4000 in
+//     1000000 columns 148, 179, 158.8 and of 4096 121; 250 rows of 4000 in 100000, 8 features 12.6 and of 1024 10.2.
+//   * Where they do not, the waves of long rows end last: 1024, from 2^22 entries on 2048.  Power-law graphs, 8 features, 2^16 vertices 16.6 and
+//     in slices of 1024 14.7, 4096 16.1; 2^17 26.1, 24.3 and 28.3; 2^18 49.5 and of 2048 48.1; 2^19 102.7, 94.1, of 4096 100.8; 20 rows of
+//     4000 beside 500000 of 5 45.1, of 1024 44.5, 4096 50.7.
+static int64_t narrow_slice(const HostPlan& plan, const rsh_csr_t& a, const std::vector<int32_t>& rows) {
+    int64_t entries = 0, in_long = 0, longest = 0;
+    for (int32_t r : rows) {
+        const int64_t len = row_len(a, r);
+        entries += len;
+        longest = std::max(longest, len);
+        if (len > 1024) in_long += len;
+    }
+    if (entries < (1 << 19)) {
+        const bool owned = plan.n_user <= 8;   // a row of B is one lane's
+        const int64_t reach = owned ? 4096 : 2560, bytes = longest * a.n_cols * 2 * plan.n_user;
+        return longest <= 1024 || (longest <= reach && bytes <= (owned ? 5ll << 30 : 1ll << 30)) ? 4096 : 512;
+    }
+    if (2 * in_long > entries) return std::min<int64_t>(4096, std::max<int64_t>(512, in_long / 768));
+    return entries < (1 << 22) ? 1024 : 2048;
+}
+
 // Form of strip.hpp in which a plan of tall windows runs, 0 for the kernels of whole windows (panel.hpp, wide.hpp).  A
 // compute unit holds two workgroups of 32 rows x 32 features, three of 64 x 32, one of 32 x 64 (or 64 x 64 in eight waves) and
 // two of 64 x 64 in four; the smallest that fill the chip once are taken, and no strip where 64 x 64 would run more than one
@@ -1016,15 +1048,7 @@ int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int thr
     // residual rows: entries of a slice, and from which length on a row is cut by column group (both explained below)
     int64_t slice_auto = 512, xp_auto = std::max<int64_t>(128, 16384 / geo.irr_panel);
     if (geo.N <= kNarrow) {
-        // Lanes that own or share rows take a row of up to 4096 entries in a wave, 64 or 128 a lane, and read the row of B of an entry in one
-        // or two requests, whichever XCD it is near to.  Power-law graphs, whole rows against slices of 512 and pieces by column
-        // group from 1024 entries on, 2^12 vertices 2 features 11.9 us and 8.8, 2^14 11.9 and 8.6 (no combine pass is left).  From
-        // 2^19 entries on, where rows are longer and a wave with a whole one ends last, slices of 1024: 2^16 vertices, 8 features 17.8 and
-        // 15.7 (of 4096 17.8), 2^17 26.6 and 24.9.  From 2^22 on of 2048: 2^19 1 feature 82.9 and 72.9, 8 120.1 and 112.9, 16
-        // 138.9 and 128.4; 2^20 168.2 and 149.4 (of 1024 153.9), 239.6 and 229.0 (233.7).
-        int64_t entries = 0;
-        for (int32_t r : part.irregular) entries += row_len(a, r);
-        slice_auto = entries < (1 << 19) ? 4096 : entries < (1 << 22) ? 1024 : 2048;
+        slice_auto = narrow_slice(plan, a, part.irregular);
         xp_auto = 0;
     }
     const int64_t slice_max = plan.opts.max_nnz_per_slice > 0 ? plan.opts.max_nnz_per_slice : slice_auto;

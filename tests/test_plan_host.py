@@ -868,3 +868,22 @@ def test_dissolved_windows_keep_their_product_in_the_library_owned_array():
         A = from_coo(np.repeat(np.arange(rows), 130), c.ravel(), np.ones(rows * 130), rows, 4000)
         st = host_plan(A, 128, reorder=0, min_reuse=1.25).stats()
         assert (st["nnz_tile"] > 0) == windows and st["n_scratch_slots"] * 128 * 4 <= 64 << 20
+
+
+# Rows of narrow products (narrow_slice): whole while that costs less than a combine pass, else slices that fill the chip; a few long
+# rows beside many short ones in slices of 1024.
+@pytest.mark.parametrize("rows,cols,per_row,N,short_rows,slices", [
+    (64, 20000, 1024, 16, 0, 1), (64, 1000000, 1024, 16, 0, 1), (64, 20000, 1025, 16, 0, 1), (64, 20000, 2560, 9, 0, 1), (64, 20000, 2561, 9, 0, 6), (64, 100000, 1025, 16, 0, 3),
+    (64, 20000, 4096, 8, 0, 1), (64, 20000, 4097, 8, 0, 9), (64, 100000, 4000, 4, 0, 1), (64, 100000, 4000, 8, 0, 8), (64, 1000000, 4000, 1, 0, 8),
+    (250, 100000, 2400, 16, 0, 4), (900, 100000, 2000, 8, 0, 1), (20, 200000, 4000, 4, 100000, 4)])
+def test_slices_of_narrow_rows(rows, cols, per_row, N, short_rows, slices):
+    rng = np.random.default_rng(5)
+    step = cols // per_row
+    c = (rng.integers(0, step, (rows, per_row)) + step * np.arange(per_row)).ravel()
+    r = np.repeat(np.arange(rows), per_row)
+    if short_rows:
+        c = np.concatenate([c, (rng.integers(0, cols // 8, (short_rows, 5)) + cols // 8 * np.arange(5)).ravel()])
+        r = np.concatenate([r, rows + np.repeat(np.arange(short_rows), 5)])
+    A = from_coo(r, c, np.ones(r.size), rows + short_rows, cols)
+    st = host_plan(A, N, reorder=0, force_path=1).stats()
+    assert st["n_scratch_slots"] == (rows * slices if slices > 1 else 0)
