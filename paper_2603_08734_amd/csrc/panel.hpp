@@ -176,9 +176,11 @@ __device__ __forceinline__ void issue_unit_values(uint32_t w, const uint32_t*& v
 }
 // The lane's 8 cells of K step h: the values of cells 0-3 start at the first register, those of cells
 // 4-7 behind them, i.e. at a half that depends on the lane: the registers are funnelled down by it.
-__device__ __forceinline__ half8_t expand_cells(uint32_t w, int h, const Dwords4& v, const Selectors& y) {
-    const uint32_t n = (uint32_t)__builtin_popcount(w & (h ? 0x0f000000u : 0x0f00u));   // values of cells 0-3
-    const uint32_t* d = v.d;
+// It takes the word of meta by its place and the values of both steps: handed over one by one, the compiler orders the fragment
+// loop of the panel kernel another way (band of 512 columns, 50000 rows, 64 features 23.7 us and 23.0).
+__device__ __forceinline__ half8_t expand_cells(const uint4_t& m, int i, int h, const Dwords4 (&v)[2], const Selectors& y) {
+    const uint32_t n = (uint32_t)__builtin_popcount(m[i] & (h ? 0x0f000000u : 0x0f00u));   // values of cells 0-3
+    const uint32_t* d = v[h].d;
     const bool two = n >= 2, four = n >= 4;
     uint32_t a0 = two ? d[1] : d[0], a1 = two ? d[2] : d[1];
     const uint32_t a2 = two ? d[3] : d[2];
@@ -341,7 +343,7 @@ __device__ __forceinline__ void panel_item(unsigned char* smem, uint32_t win, ui
         for (int c = 0; c < NCH32; ++c) x.b[c] = read_transposed<LDB>(sb + 32 * c);
     };
     auto look_up = [&](const uint4_t& m, int i, int h, Selectors& y) { look_up_selectors(smem, m[i], h, y); };
-    auto expand = [&](const uint4_t& m, int i, int h, const Dwords4 (&v)[2], const Selectors& y, Operands& x) { x.a = expand_cells(m[i], h, v[h], y); };
+    auto expand = [&](const uint4_t& m, int i, int h, const Dwords4 (&v)[2], const Selectors& y, Operands& x) { x.a = expand_cells(m, i, h, v, y); };
     auto multiply = [&](const Operands& x) {
 #pragma unroll
         for (int c = 0; c < NCH32; ++c)
@@ -450,7 +452,7 @@ __global__ __launch_bounds__(64 * NG) __attribute__((amdgpu_waves_per_eu(2, NCH3
     const int panel = feature0 + blockIdx.y * P;
     const int row = win_row[(size_t)win * (32 * NG) + wv * 32 + (lane & 31)];
 
-    if (threadIdx.x < 64) write_selectors(smem, lane);
+    if (threadIdx.x < 64) write_selectors(smem, (int)threadIdx.x);
 
     float16_t acc[NCH32], acc2[NCH32];
 #pragma unroll

@@ -209,7 +209,7 @@ __device__ __forceinline__ void strip_share(StripRows<Gm, RUN, RAGGED> rows, con
 #pragma unroll
             for (int h = 0; h < 2; ++h)
 #pragma unroll
-                for (int g = 0; g < RB; ++g) a[h][g] = expand_cells(m_cur[g][u], h, vals[k][g][h], sel[g][h]);
+                for (int g = 0; g < RB; ++g) a[h][g] = expand_cells(m_cur[g], u, h, vals[k][g], sel[g][h]);
             if (u < 3) look_up(u + 1, m_cur);
             else look_up(0, m_nxt);
 #pragma unroll
