@@ -323,7 +323,10 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(kStr
             const int other = shfl_i32(row[1], pr);
             prow = g ? other : prow;
         }
-        if (prow >= 0 && f < nv) panel_store(out, (size_t)prow, nv, f, v);
+        // one condition behind the other, none ends inside another (store_block in tall.hpp): other lanes' turns need `row`
+        if (prow >= 0 && f + 4 <= nv) panel_store_whole(out, (size_t)prow, nv, f, v);
+        keep_streaming_hint();
+        if (prow >= 0 && f < nv && f + 4 > nv) panel_store_tail(out, (size_t)prow, nv, f, v);
     }
 }
 

@@ -116,6 +116,16 @@ def test_panel_kernels_use_the_32_row_mfma_and_transposing_reads(kernels_asm):
             assert any("global_store_dword" in l and " nt" in l for l in body.splitlines()), name
 
 
+def test_strips_leave_with_the_streaming_hint(kernels_asm):
+    """Every store of a strip is one of C: no partial sums pass through memory."""
+    strips = {n: b for n, b in kernels_asm.items() if "rsh_strip_kernel" in n}
+    assert len(strips) == 40   # five forms, broken pieces or none, rows of even or any width, fp32 or binary16
+    for name, body in strips.items():
+        st = [l for l in body.splitlines() if "global_store" in l]
+        assert st and all(" nt" in l for l in st), f"{name}: {st}"
+        assert "v_mfma_f32_32x32x16_f16" in body and "ds_read_b64_tr_b16" in body, name
+
+
 def _registers(operand):
     m = re.match(r"([va])(?:(\d+)|\[(\d+):(\d+)\])$", operand)
     return {(m.group(1), i) for i in range(int(m.group(2) or m.group(3)), int(m.group(2) or m.group(4)) + 1)} if m else set()
@@ -126,7 +136,7 @@ def test_no_register_is_restored_for_some_lanes_only(kernels_asm):
     conditions that end together have made the compiler do that to the row numbers that lanes take from each other."""
     copy = re.compile(r"(?:v_mov_b32_e32|v_accvgpr_write_b32|v_accvgpr_read_b32|v_accvgpr_mov_b32) ([va]\d+), ([va]\d+)$")
     for name, body in kernels_asm.items():
-        if "rsh_wide_kernel" not in name and "rsh_panel_kernel" not in name:
+        if not any(k in name for k in ("rsh_wide_kernel", "rsh_panel_kernel", "rsh_strip_kernel")):
             continue
         held = {}      # register: (copied from, conditions opened since)
         for line in (l.strip() for l in body.splitlines()):
