@@ -35,25 +35,42 @@ CASES = [
 ]
 
 
+# Operands at their element's alignment where the width allows it; B is read where it lies but in the two plans whose loads at
+# 2-byte boundaries would cost more than a copy.
 @pytest.mark.gpu
 @pytest.mark.parametrize("fused", [False, True])
 @pytest.mark.parametrize("rows,cols,density,N,form", CASES)
 def test_waves_that_divide_the_columns(rows, cols, density, N, form, fused):
+    product(rows, cols, density, N, form, fused, N % 2, copied=(rows, cols, N) in ((16500, 4130, 13), (16500, 8192, 5)))
+
+
+# Rows of whole pieces, B at its element's alignment (N = 8) or at 4 bytes: the loads of the kernel of broken pieces.
+@pytest.mark.gpu
+@pytest.mark.parametrize("fused", [False, True])
+@pytest.mark.parametrize("rows,cols,density,N,form,shift", [(1100, 1100, 0.2, 8, A32, 1), (1100, 20, 0.5, 8, A32, 3), (1100, 1100, 0.2, 24, A32, 2), (16500, 300, 0.2, 24, B32, 2),
+                                                           (4300, 300, 0.2, 40, A64, 2), (8300, 300, 0.2, 40, B64, 6)])
+def test_rows_of_whole_pieces_at_other_alignments(rows, cols, density, N, form, shift, fused):
+    product(rows, cols, density, N, form, fused, shift, copied=False)
+
+
+def product(rows, cols, density, N, form, fused, shift, copied):
+    """`shift`: halves by which B lies behind an aligned address; what lies around B is not finite."""
     import torch
     from paper_2603_08734_amd import Plan
     A = matrix(rows, cols, density)
-    print(f"case strip rows={rows} cols={cols} N={N} fused={fused}", flush=True)
+    print(f"case strip rows={rows} cols={cols} N={N} fused={fused} shift={shift}", flush=True)
     plan = Plan(A.row_ptr, A.col_idx, A.val, A.n_cols, N, force_path=2, reorder=0)
     assert plan.strip() == form and plan.stats()["n_split_windows"] == 0
     B = dense_B(A.n_cols, N, "normal", seed=N)
-    odd = N % 2 == 1       # operands at their element's alignment where the width allows it
-    Bf = torch.empty(A.n_cols * N + 1, dtype=torch.float16, device="cuda")
-    Bd = Bf[1:].view(A.n_cols, N) if odd else Bf[:-1].view(A.n_cols, N)
+    odd = N % 2 == 1
+    Bf = torch.full((A.n_cols * N + shift + 8,), float("nan"), dtype=torch.float16, device="cuda")
+    Bd = Bf[shift:shift + A.n_cols * N].view(A.n_cols, N)
     Bd.copy_(torch.from_numpy(B.view(np.int16)).cuda().view(torch.float16))
     C_ref, S, _ = oracle.spmm(A.row_ptr, A.col_idx, A.val, B)
     pad = 65 if odd else 64
     flat = torch.full((A.n_rows * N + 2 * pad,), float("nan"), dtype=torch.float16 if fused else torch.float32, device="cuda")
     C = flat[pad:pad + A.n_rows * N].view(A.n_rows, N)
+    assert plan.operand(Bd.data_ptr(), C.data_ptr()) == (copied, (N + 15) // 16 * 16 if copied else N)
     bound = 1e-4 * S
     if fused:
         bias = torch.linspace(-1, 1, N, device="cuda")
@@ -85,7 +102,9 @@ def test_windows_beside_rows_without_entries(N):
     assert plan.strip() is not None and plan.stats()["n_empty_rows"] == np.count_nonzero(~keep)
     B = dense_B(A.n_cols, N, "normal", seed=N)
     C = torch.full((A.n_rows, N), float("nan"), dtype=torch.float32, device="cuda")
-    plan.spmm(torch.from_numpy(B.view(np.int16)).cuda().view(torch.float16), C)
+    Bd = torch.from_numpy(B.view(np.int16)).cuda().view(torch.float16)
+    assert plan.operand(Bd.data_ptr(), C.data_ptr())[0] == (N < 16 or N % 2 == 1)
+    plan.spmm(Bd, C)
     torch.cuda.synchronize()
     C_ref, S, _ = oracle.spmm(A.row_ptr, A.col_idx, A.val, B)
     assert np.all(np.abs(C.cpu().numpy().astype(np.float64) - C_ref) <= 1e-4 * S)
