@@ -692,10 +692,12 @@ static int pack_panel_windows(const rsh_csr_t& a, const Partition& part, HostPla
 }
 
 // Bytes on the device of what PANEL_ENT and PANEL_OFF hold.  Per quad masks and starts of the values (1 KB) and where its
-// first value lies, the values in dwords, and a window's first quad (panel.hpp); or every cell, and a K step of zeros (wide.hpp).
+// first value lies, the values in dwords, a window's first quad (panel.hpp) and, for strips, its run of columns; or every cell, and a K
+// step of zeros (wide.hpp).
 int64_t panel_device_bytes(const HostPlan& plan) {
     if (plan.geo.wide) return (2 * (int64_t)plan.win_tile_off.back() + 1) * (int64_t)kWideStepBytes;
-    return plan.geo.panel ? plan.panel_quads * 1028 + plan.panel_dwords * 4 + (int64_t)plan.win_tile_off.size() * 4 : 0;
+    const int64_t windows = (int64_t)plan.win_tile_off.size() - 1;
+    return plan.geo.panel ? plan.panel_quads * 1028 + plan.panel_dwords * 4 + (windows + 1) * 4 + (plan.geo.strip ? windows * 8 : 0) : 0;
 }
 
 // Parts that every tall window is cut into, when the caller leaves it open.  The kernel's workgroups (window parts x

@@ -592,21 +592,23 @@ def test_element_level_is_refused_out_of_range_and_ignored_by_tall_windows():
     assert int(path.sum()) == 0
 
 
-@pytest.mark.parametrize("window_rows", [128, 256])
+@pytest.mark.parametrize("window_rows", [128, 256, 0])
 def test_plan_bytes_of_tall_windows_are_those_of_the_packed_form(window_rows):
     """What the device holds for tall windows: per row group and quad of fragments 1 KB of cell masks and starts and 4 bytes
-    for where its values begin, and every lane's values (8 cells of a row) in whole dwords."""
-    rng = np.random.default_rng(3)
-    r, c = np.nonzero(rng.random((300, 500)) < rng.random((300, 1)) * 0.4)
-    p = host_plan(from_coo(r, c, rng.standard_normal(r.size), 300, 500), 64, window_rows=window_rows, force_path=2)
-    st, G = p.stats(), window_rows // 32
+    for where its values begin, and every lane's values (8 cells of a row) in whole dwords.  Strips (the planner's
+    choice, of windows of 256 rows) have the first and last column of a window's run beside."""
+    rng, rows = np.random.default_rng(3), 300 if window_rows else 1100
+    r, c = np.nonzero(rng.random((rows, 500)) < rng.random((rows, 1)) * 0.4)
+    p = host_plan(from_coo(r, c, rng.standard_normal(r.size), rows, 500), 64, window_rows=window_rows, force_path=2)
+    st, G = p.stats(), (window_rows or 256) // 32
+    assert st["window_rows"] == (window_rows or 256) and (p.strip() is not None) == (window_rows == 0)
     off, ent = p.array(B_.RSH_ARR_PANEL_OFF), p.array(B_.RSH_ARR_PANEL_ENT)
     dwords = 0
     for u in range(len(off) - 1):
         addr = ent[off[u]:off[u + 1]] >> 16
         dwords += int(((np.bincount(addr[addr < 1024] >> 4, minlength=64) + 1) // 2).sum())
     fragments = np.diff(p.array(B_.RSH_ARR_WIN_TILE_OFF).astype(np.int64))
-    packed = 1028 * int((G * -(-fragments // 4)).sum()) + 4 * dwords + 4 * (len(fragments) + 1)
+    packed = 1028 * int((G * -(-fragments // 4)).sum()) + 4 * dwords + 4 * (len(fragments) + 1) + (8 * len(fragments) if p.strip() else 0)
     tile = sum(p.array(getattr(B_, "RSH_ARR_" + n)).nbytes for n in ("WIN_ROW", "TILE_COLID", "TILE_ITEM", "PANEL_COL0"))
     tile += sum(p.array(getattr(B_, "RSH_ARR_" + n)).nbytes for n in ("TILE_MASK", "TILE_VAL_OFF", "TILE_VAL"))
     assert st["tile_part_bytes"] == tile + packed
