@@ -185,6 +185,7 @@ int upload_arrays(rsh_plan& p) {
     d.n_cols = h.n_cols;
     d.n_tile_items = (int64_t)h.tile_item.size() / 4;
     d.n_irr_waves = (int64_t)(h.geo.narrow ? h.narrow.wave : h.irr_wave).size() / 4;
+    d.irr_entries = h.stats.nnz_irregular;
     d.n_combine = (int64_t)h.combine.size() / 4;
     d.n_scratch_slots = h.n_scratch_slots;
     d.n_split_rows = h.stats.n_split_rows;

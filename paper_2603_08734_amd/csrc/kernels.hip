@@ -206,7 +206,7 @@ __device__ __forceinline__ void irregular_body(
     const uint4* __restrict__ waves, const XcdSplit& xs,
     const int32_t* __restrict__ irr_row, const int32_t* __restrict__ irr_col,
     const uint16_t* __restrict__ irr_val, const __half* __restrict__ B, const OUT out,
-    float* __restrict__ scratch, int N, int nv, int ns) {
+    float* __restrict__ scratch, int N, int panel0, int nv, int ns) {
     constexpr int G = 64 / TPR;
     if constexpr (!OUT::kAny) nv = N;
     __shared__ __attribute__((aligned(16))) float lds_stage[kWavesPerBlock][64 * 8];
@@ -215,7 +215,7 @@ __device__ __forceinline__ void irregular_body(
     if (!xcd_work_item(xs, &wave)) return;
     const int team = lane / TPR, tl = lane % TPR, team_base = team * TPR;
     // a partial panel is the last; it begins early enough to hold eight features
-    const int first = (int)blockIdx.y * (TPR * 8), panel = PARTIAL && OUT::kRows != kRowsWhole ? min(first, N - 8) : first;
+    const int first = (panel0 + (int)blockIdx.y) * (TPR * 8), panel = PARTIAL && OUT::kRows != kRowsWhole ? min(first, N - 8) : first;
     float* stage = lds_stage[threadIdx.x >> 6] + team * (TPR * 8);
 
     const uint4 d = waves[wave];
@@ -302,11 +302,11 @@ __device__ __forceinline__ void irregular_body(
 #define RSH_IRREGULAR_PARAMS                                                                                                              \
     const uint4 *__restrict__ waves, XcdSplit xs, const int32_t *__restrict__ irr_row, const int32_t *__restrict__ irr_col,               \
         const uint16_t *__restrict__ irr_val, const __half *__restrict__ B, const OUT out, float *__restrict__ scratch, int N,            \
-        int nv, int ns
+        int panel0, int nv, int ns
 template <int TPR, class OUT, bool PARTIAL>
 __global__ __launch_bounds__(64 * kWavesPerBlock) __attribute__((amdgpu_waves_per_eu(8, 8))) void rsh_irregular_kernel(RSH_IRREGULAR_PARAMS) {
     static_assert(OUT::kRows == (PARTIAL ? kRowsWhole : kRowsEven));   // full panels of whole rows are no different
-    irregular_body<TPR, OUT, PARTIAL>(waves, xs, irr_row, irr_col, irr_val, B, out, scratch, N, nv, ns);
+    irregular_body<TPR, OUT, PARTIAL>(waves, xs, irr_row, irr_col, irr_val, B, out, scratch, N, panel0, nv, ns);
 }
 // Eight waves per SIMD take registers from the fp32 form's gather loops (rows of 100 features of the power-law graph of
 // 2^18 vertices: 157.0 us, 147.0 with seven; 50 features 110.1 and 101.5).  The binary16 form gains as much at panels
@@ -317,12 +317,12 @@ template <int TPR, class OUT>
 __global__ __launch_bounds__(64 * kWavesPerBlock) __attribute__((amdgpu_waves_per_eu(kEvenWaves<TPR, OUT>, kEvenWaves<TPR, OUT>)))
 void rsh_residual_even_kernel(RSH_IRREGULAR_PARAMS) {
     static_assert(OUT::kRows == kRowsEven);
-    irregular_body<TPR, OUT, true>(waves, xs, irr_row, irr_col, irr_val, B, out, scratch, N, nv, ns);
+    irregular_body<TPR, OUT, true>(waves, xs, irr_row, irr_col, irr_val, B, out, scratch, N, panel0, nv, ns);
 }
 template <int TPR, class OUT, bool PARTIAL>
 __global__ __launch_bounds__(64 * kWavesPerBlock) __attribute__((amdgpu_waves_per_eu(7, 7))) void rsh_residual_any_kernel(RSH_IRREGULAR_PARAMS) {
     static_assert(OUT::kAny);
-    irregular_body<TPR, OUT, PARTIAL>(waves, xs, irr_row, irr_col, irr_val, B, out, scratch, N, nv, ns);
+    irregular_body<TPR, OUT, PARTIAL>(waves, xs, irr_row, irr_col, irr_val, B, out, scratch, N, panel0, nv, ns);
 }
 #undef RSH_IRREGULAR_PARAMS
 
@@ -872,26 +872,33 @@ static inline uint32_t grid_for(const XcdSplit& xs) {
 // Full panels, or all panels of a width that ends in a partial one, which starts early enough to hold eight features (those
 // it shares with the panel before come out the same twice).  All in one launch of the partial panel's kernel: a launch of its
 // own ends with its longest waves, and the kernel of full panels gains less than that.  Power-law graphs, us, two launches and
-// one: 2^12 vertices 141 features 21.3 and 15.4, 2^14 176 29.7 and 21.2, 2^16 71.2 and 62.1, 254 89.5 and 81.3, 2^18 472 and 462,
-// 400 629 and 632.
+// one: 2^12 vertices 141 features 21.3 and 15.4, 2^14 176 43.6 and 21.1, 2^16 67.2 and 62.1, 254 88.6 and 81.4, 2^18 471 and 461, 2^20
+// 200 1556 and 1547, binary16 result 272 1998 and 1984.
+// Whole rows of an fp32 result leave by the same stores in both kernels, so the panel checks cost the full panels 1 % and nothing
+// comes back: entries x full panels from which that is more than a launch.  2^18 vertices (7.8 M entries) 272 features 445.4 and 443.8, 400
+// 621.9 and 623.0, 528 797 and 802; 2^19 (16 M) 176 591.0 and 590.8, 272 947.7 and 954.0, 528 1695 and 1716; 2^20 144 1246 and
+// 1249, 272 2115 and 2133; 200000 rows of 30 entries 400 963 and 958.
+constexpr int64_t kPanelsApart = 3ll << 23;
 template <int TPR, class OUT>
 static void launch_irregular_t(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st, int nb, int nv) {
-    const auto launch = [&](auto kernel, const auto& to) {
-        hipLaunchKernelGGL(kernel, dim3(grid_for(d.irr_split), (unsigned)(nv + d.geo.irr_panel - 1) / (unsigned)d.geo.irr_panel), dim3(64 * kWavesPerBlock),
+    const auto launch = [&](auto kernel, const auto& to, int first, int panels) {
+        hipLaunchKernelGGL(kernel, dim3(grid_for(d.irr_split), (unsigned)panels), dim3(64 * kWavesPerBlock),
                            0, st, (const uint4*)d.irr_wave, d.irr_split, d.irr_row, d.irr_col, d.irr_val, (const __half*)B, to,
-                           d.scratch, nb, nv, d.geo.N);
+                           d.scratch, nb, first, nv, d.geo.N);
     };
+    const int full = nv / d.geo.irr_panel;
     const bool partial = nv % d.geo.irr_panel != 0;
     if constexpr (OUT::kAny) {
-        if (partial) launch(rsh_residual_any_kernel<TPR, OUT, true>, out);
-        else launch(rsh_residual_any_kernel<TPR, OUT, false>, out);
-    } else if (!partial) {
-        const auto even = out.general();
-        launch(rsh_irregular_kernel<TPR, std::decay_t<decltype(even)>, false>, even);
-    } else if constexpr (OUT::kWhole) {
-        launch(rsh_irregular_kernel<TPR, OUT, true>, out);
+        if (partial) launch(rsh_residual_any_kernel<TPR, OUT, true>, out, 0, full + 1);
+        else launch(rsh_residual_any_kernel<TPR, OUT, false>, out, 0, full);
     } else {
-        launch(rsh_residual_even_kernel<TPR, OUT>, out);
+        const auto even = out.general();
+        using Even = std::decay_t<decltype(even)>;
+        const bool apart = OUT::kWhole && !OUT::kFused && d.irr_entries * full >= kPanelsApart;
+        if (!partial || apart) launch(rsh_irregular_kernel<TPR, Even, false>, even, 0, full);
+        if (!partial) return;
+        if constexpr (OUT::kWhole) launch(rsh_irregular_kernel<TPR, OUT, true>, out, apart ? full : 0, apart ? 1 : full + 1);
+        else launch(rsh_residual_even_kernel<TPR, OUT>, out, 0, full + 1);
     }
 }
 

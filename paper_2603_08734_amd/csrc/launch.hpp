@@ -9,7 +9,7 @@ namespace rsh {
 
 struct DevicePlan {
     Geometry geo;
-    int64_t n_tile_items = 0, n_irr_waves = 0, n_combine = 0, n_scratch_slots = 0;
+    int64_t n_tile_items = 0, n_irr_waves = 0, irr_entries = 0, n_combine = 0, n_scratch_slots = 0;
     int64_t n_split_rows = 0;          // combine entries that add up slices of one row; the others add up parts of a window
     XcdSplit tile_split, irr_split;
     int32_t* win_row = nullptr;

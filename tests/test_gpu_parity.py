@@ -407,6 +407,31 @@ def test_feature_widths_that_the_kernels_do_not_run_at(N, run_width, mode):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("rows,N", [(1100, 4080), (1000, 4080)])
+def test_full_panels_of_many_entries_in_a_launch_of_their_own(rows, N):
+    """Whole rows of an fp32 result that end in a partial panel, on both sides of 3 * 2^23 entries times full panels.  Bound: that of
+    every product here (a row of 800 entries is two slices, chains of at most 512 / 4 products and a tree behind them)."""
+    torch = _torch()
+    from paper_2603_08734_amd import Plan
+    rng = np.random.default_rng(5)
+    cols = np.sort(rng.permuted(np.tile(np.arange(2000, dtype=np.int32), (rows, 1)), axis=1)[:, :800], axis=1)
+    ptr, val = 800 * np.arange(rows + 1, dtype=np.int64), rng.standard_normal((rows, 800)).astype(np.float16)
+    print(f"case full panels apart rows={rows} N={N}", flush=True)
+    assert (rows * 800 * (N // 128) >= 3 << 23) == (rows == 1100)
+    plan = Plan(ptr, cols.ravel(), val.ravel(), 2000, N, force_path=1, reorder=0)
+    B = dense_B(2000, N, "normal", seed=N)
+    Bd = torch.from_numpy(B.view(np.int16)).cuda().view(torch.float16)
+    C = torch.full((rows, N), float("nan"), dtype=torch.float32, device="cuda")
+    plan.spmm(Bd, C)
+    torch.cuda.synchronize()
+    A = torch.zeros((rows, 2000), dtype=torch.float64)
+    A.scatter_(1, torch.from_numpy(cols.astype(np.int64)), torch.from_numpy(val.astype(np.float64)))
+    B64 = torch.from_numpy(B.view(np.float16).astype(np.float64))
+    assert_parity(C.cpu().numpy(), (A @ B64).numpy(), (A.abs() @ B64.abs()).numpy(), f"rows={rows}")
+    plan.destroy()
+
+
+@pytest.mark.gpu
 def test_padded_width_under_graph_replay():
     """At a width the kernels do not run at, rsh_spmm is five kernel launches (copy in, three kernels,
     copy out) on plan-owned buffers: still capturable, and every replay equals the eager call."""
