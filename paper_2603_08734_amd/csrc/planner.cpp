@@ -856,11 +856,26 @@ static int64_t narrow_slice(const HostPlan& plan, const rsh_csr_t& a, const std:
     return entries < (1 << 22) ? 1024 : 2048;
 }
 
+// Rows of B of odd widths and of fewer than 16 features are read where they lie while that costs a compute unit's loads less than
+// the 3 us of a copy's launch: a load at 2-byte boundaries takes 59 cycles of the vector memory path instead of 16, however few of its
+// lanes have a piece of a row.  In place and with the copy, us: 1300 x 1500 weight (94 loads) 9.2 and 12; 6000 x 2500 (158) 12.4 both;
+// 4444 x 5903 (370) 19.1 and 15.8, 85 features (1480) 34.4 and 27.4.  Not beyond the 512 workgroups of 64 x 32 that the chip holds
+// while pieces are moved (768 otherwise), where whole windows take the copy as well: 44800 x 128 (700), 31 features 9.7, without the copy
+// (32 features) 5.7, whole windows 9.0.
+static bool strip_reads_in_place(const HostPlan& plan, int form, int64_t n_win, uint32_t longest) {
+    const int n = plan.n_user, features = strip_features(form);
+    if ((n >= 16 && n % 2 == 0) || plan.geo.N != (n + 15) / 16 * 16) return false;
+    const int64_t blocks = n_win * plan.geo.panel_groups / strip_row_groups(form) * ((n + features - 1) / features);
+    if (n > 16 && form == strip_code(32, 2, 4) && blocks > 512) return false;
+    return (int64_t)longest * (features / 16) * ((blocks + 255) / 256) <= 150;
+}
+
 // Form of strip.hpp in which a plan of tall windows runs, 0 for the kernels of whole windows (panel.hpp, wide.hpp).  A
 // compute unit holds two workgroups of 32 rows x 32 features, three of 64 x 32, one of 32 x 64 (or 64 x 64 in eight waves) and
-// two of 64 x 64 in four; the smallest that fill the chip once are taken, and no strip where 64 x 64 would run more than one
-// round.  Weights at densities of 0.1 to 0.35, us, kernels of whole windows and, in this order, 32 x 32 (eight waves), 64 x 32
-// (four), 32 x 64, 64 x 64 in eight waves and in four:
+// two of 64 x 64 in four; where rows of B end inside a 16-byte piece and are read where they lie (139 and 172 registers instead of
+// 128 and 168) one of 32 x 32 and two of 64 x 32.  The smallest that fill the chip once are taken, and no strip beyond 32
+// features where 64 x 64 would run more than one round.  Weights at densities of 0.1 to 0.35, us, kernels of whole windows and, in
+// this order, 32 x 32 (eight waves), 64 x 32 (four), 32 x 64, 64 x 64 in eight waves and in four:
 //   rows x columns  features
 //    4736 x 1871       2    16.0    9.1  11.5   9.2  12.1  14.3
 //    5000 x 4000      16    14.5   10.5  18.8  12.6  17.2  22.2
@@ -875,33 +890,39 @@ static int64_t narrow_slice(const HostPlan& plan, const rsh_csr_t& a, const std:
 //   14000 x 4000     128    35.3   55.9  42.4  45.1  35.1  30.8
 //   15764 x 6465     200    80.5  205   134   169   117   103
 //   28672 x 8192     128    99.4  230   158   156   129   117
-// A wave's share of 64 features has at most 32 fragments, so four waves take windows of up to 128.
-static int strip_form(const HostPlan& plan, int64_t n_win, uint32_t longest) {
+// A wave's share of 64 features has at most 32 fragments, so four waves take windows of up to 128.  Where strips lose within these bounds
+// (whole windows and strips, us):
+//   * up to 32 features in more than one round of 64 x 32, short windows: a strip's start and end are not amortised.  Of 2 fragments
+//     256000 rows, 32 features 20.9 and 24.9, of 4 20.5 and 25.0, of 8 28.1 and 29.0, of 16 41.1 and 35.4; 102400 rows of 8 13.5 and
+//     13.2.  With rows of B in pieces, from 512 workgroups on: 44800 rows (700), 18 features, of 4 6.3 and 9.3, of 8 7.8 and 9.6, of 16 10.6 and
+//     9.9; 256000 rows of 16 41.5 and 44.2; 102400 of 32 36.0 and 30.8.
+//   * beyond 32 features with rows of B in pieces and hardly a fragment a wave: 22400 x 128, 50 features 7.0 and 7.5.
+// `alone`: no residual rows beside the windows (they read the copy of B, and then so do strips).
+static int strip_form(const HostPlan& plan, int64_t n_win, uint32_t longest, bool alone) {
     if (!plan.height_chosen || plan.opts.max_tiles_per_item > 0) return 0;
     // column ids and bytes of a row of B are multiplied as 24-bit numbers
     if (longest == 0 || longest > 256 || plan.n_cols >= (1 << 24) || plan.n_cols * plan.n_user < 8) return 0;
     const int n = plan.n_user;
     const int64_t groups = n_win * plan.geo.panel_groups, small = groups * ((n + 31) / 32), blocks = groups * ((n + 63) / 64);
-    const bool four = longest <= 128;
-    if (small <= 256 || (n <= 32 && small <= 512)) return strip_code(32, 1, 8);
-    if (n <= 32) return strip_code(32, 2, 4);
+    const int form32 = strip_code(32, 1, 8), form64 = strip_code(32, 2, 4);
+    if (n <= 32) {
+        const auto pieces = [&](int form) { return n % 8 != 0 && plan.geo.N == (n + 15) / 16 * 16 && ((n >= 16 && n % 2 == 0) || (alone && strip_reads_in_place(plan, form, n_win, longest))); };
+        if (small <= 256) return form32;
+        if (small <= 512) return form32;
+        const bool broken = pieces(form64);
+        const int64_t pairs = groups / 2;
+        if (pairs <= 512) return form64;
+        if (pairs <= 768) return broken && longest < 16 ? 0 : form64;
+        return longest < (broken ? 32 : 16) ? 0 : form64;
+    }
+    if (small <= 256) return form32;
     if (blocks <= 256) return strip_code(64, 1, 8);
     // beyond 26 fragments a wave the chains of 64 x 64 would be longer than those of windows that are cut for want of others: relative
     // error against 64 bits of a 10952 x 7178 weight (28 a wave), 48 features, 1.82e-7 and in the panel kernel 1.78e-7
     if (blocks <= 512) return longest <= 208 ? strip_code(64, 2, 8) : 0;
-    if (blocks <= 1024 && (four || n <= 64)) return strip_code(64, 2, four ? 4 : 8);
-    return 0;
-}
-
-// Rows of B of odd widths and of fewer than 16 features are read where they lie while that costs a compute unit's loads less than
-// the 3 us of a copy's launch: a load at 2-byte boundaries takes 59 cycles of the vector memory path instead of 16, however few of its
-// lanes have a piece of a row.  In place and with the copy, us: 1300 x 1500 weight (94 loads) 9.2 and 12; 6000 x 2500 (158) 12.4 both;
-// 4444 x 5903 (370) 19.1 and 15.8, 85 features (1480) 34.4 and 27.4.
-static bool strip_reads_in_place(const HostPlan& plan, int64_t n_win, uint32_t longest) {
-    const int n = plan.n_user, features = strip_features(plan.geo.strip);
-    if ((n >= 16 && n % 2 == 0) || plan.geo.N != (n + 15) / 16 * 16) return false;
-    const int64_t blocks = n_win * plan.geo.panel_groups / strip_row_groups(plan.geo.strip) * ((n + features - 1) / features);
-    return (int64_t)longest * (features / 16) * ((blocks + 255) / 256) <= 150;
+    if (blocks > 1024) return 0;
+    if (n <= 64) return n % 2 == 0 && n % 8 != 0 && longest <= 4 ? 0 : strip_code(64, 2, longest <= 128 ? 4 : 8);
+    return longest <= 128 ? strip_code(64, 2, 4) : 0;
 }
 
 int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int threads) {
@@ -927,8 +948,8 @@ int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int thr
         geo.wide = geo.win_rows == 256 && plan.n_user > 128 && n_tiles > 0 && nnz_tile * 16 >= n_tiles * (int64_t)K * W;
         uint32_t longest = 0;
         for (int64_t w = 0; w < n_win; ++w) longest = std::max(longest, plan.win_tile_off[(size_t)w + 1] - plan.win_tile_off[(size_t)w]);
-        geo.strip = strip_form(plan, n_win, longest);
-        plan.strip_in_place = geo.strip && strip_reads_in_place(plan, n_win, longest);
+        geo.strip = strip_form(plan, n_win, longest, part.irregular.empty() && part.empty.empty());
+        plan.strip_in_place = geo.strip && strip_reads_in_place(plan, geo.strip, n_win, longest);
         if (geo.strip) geo.wide = 0;
     } else {
         // ---- pass 1: fragments and padded value count per window ---------------------------

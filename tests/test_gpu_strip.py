@@ -111,6 +111,21 @@ def test_windows_beside_rows_without_entries(N):
     plan.destroy()
 
 
+# Both sides of the lines up to which strips are taken: short windows in several rounds.
+@pytest.mark.parametrize("rows,cols,density,N,form", [
+    (44800, 128, 0.3, 18, None), (44800, 128, 0.3, 16, B32), (44800, 500, 0.1, 18, B32), (30000, 64, 0.4, 18, B32), (44800, 128, 0.3, 31, B32),
+    (64000, 300, 0.1, 32, None), (64000, 500, 0.1, 32, B32), (64000, 500, 0.1, 18, None), (64000, 1000, 0.1, 18, B32),
+    (64000, 500, 0.1, 31, B32), (64000, 300, 0.1, 31, None), (64000, 300, 0.1, 1, None),
+    (22400, 128, 0.3, 50, None), (22400, 160, 0.3, 50, E64), (22400, 128, 0.3, 56, E64),
+])
+def test_where_strips_end(rows, cols, density, N, form):
+    from paper_2603_08734_amd import Plan
+    A = matrix(rows, cols, density, holes=False)
+    plan = Plan(A.row_ptr, A.col_idx, A.val, A.n_cols, N, force_path=2, reorder=0, upload=0)
+    assert plan.strip() == form
+    plan.destroy()
+
+
 @pytest.mark.parametrize("N,opts,form", [(16, {}, A32), (16, dict(window_rows=256), None), (16, dict(max_tiles_per_item=4), None), (700, {}, B64), (1024, {}, E64),
                                          (4096, {}, None)])
 def test_plans_that_take_the_form(N, opts, form):
