@@ -879,7 +879,10 @@ static bool strip_reads_in_place(const HostPlan& plan, int form, int64_t n_win, 
 //   rows x columns  features
 //    4736 x 1871       2    16.0    9.1  11.5   9.2  12.1  14.3
 //    5000 x 4000      16    14.5   10.5  18.8  12.6  17.2  22.2
+//    9000 x 1500      18    16.2   11.5   9.0
 //   12985 x 1028      32    17.7    9.4   9.8  13.3  10.4  10.8
+//   13000 x 1500      13    14.3   10.7   9.4
+//   13000 x 1500      32    16.6    8.5   8.3
 //   28672 x 2000      16    22.4   19.9  15.4  28.0  21.9  17.9
 //    1848 x 3452      48    17.1    9.9  16.2  11.3  15.7  19.6
 //    5000 x 4000      64    17.5   19.1  18.9  12.7  17.4  22.7
@@ -896,6 +899,8 @@ static bool strip_reads_in_place(const HostPlan& plan, int form, int64_t n_win, 
 //     256000 rows, 32 features 20.9 and 24.9, of 4 20.5 and 25.0, of 8 28.1 and 29.0, of 16 41.1 and 35.4; 102400 rows of 8 13.5 and
 //     13.2.  With rows of B in pieces, from 512 workgroups on: 44800 rows (700), 18 features, of 4 6.3 and 9.3, of 8 7.8 and 9.6, of 16 10.6 and
 //     9.9; 256000 rows of 16 41.5 and 44.2; 102400 of 32 36.0 and 30.8.
+//   * rows of B in pieces, long windows of which few workgroups of 32 x 32 run a second time: 8200 x 5500 (257 of them),
+//     18 features 23.5 and 25.6, x 8192 25.6 and 28.7; 12000 x 5500 24.2 and 23.1.
 //   * beyond 32 features with rows of B in pieces and hardly a fragment a wave: 22400 x 128, 50 features 7.0 and 7.5.
 // `alone`: no residual rows beside the windows (they read the copy of B, and then so do strips).
 static int strip_form(const HostPlan& plan, int64_t n_win, uint32_t longest, bool alone) {
@@ -908,7 +913,10 @@ static int strip_form(const HostPlan& plan, int64_t n_win, uint32_t longest, boo
     if (n <= 32) {
         const auto pieces = [&](int form) { return n % 8 != 0 && plan.geo.N == (n + 15) / 16 * 16 && ((n >= 16 && n % 2 == 0) || (alone && strip_reads_in_place(plan, form, n_win, longest))); };
         if (small <= 256) return form32;
-        if (small <= 512) return form32;
+        if (small <= 512) {
+            if (longest <= 75 && pieces(form64)) return form64;
+            return small <= 352 && longest > 144 && pieces(form32) ? 0 : form32;
+        }
         const bool broken = pieces(form64);
         const int64_t pairs = groups / 2;
         if (pairs <= 512) return form64;

@@ -111,12 +111,14 @@ def test_windows_beside_rows_without_entries(N):
     plan.destroy()
 
 
-# Both sides of the lines up to which strips are taken: short windows in several rounds.
+# Both sides of the lines up to which strips are taken: short windows in several rounds, rows of B in pieces or whole.
 @pytest.mark.parametrize("rows,cols,density,N,form", [
     (44800, 128, 0.3, 18, None), (44800, 128, 0.3, 16, B32), (44800, 500, 0.1, 18, B32), (30000, 64, 0.4, 18, B32), (44800, 128, 0.3, 31, B32),
     (64000, 300, 0.1, 32, None), (64000, 500, 0.1, 32, B32), (64000, 500, 0.1, 18, None), (64000, 1000, 0.1, 18, B32),
     (64000, 500, 0.1, 31, B32), (64000, 300, 0.1, 31, None), (64000, 300, 0.1, 1, None),
     (22400, 128, 0.3, 50, None), (22400, 160, 0.3, 50, E64), (22400, 128, 0.3, 56, E64),
+    (9000, 300, 0.2, 18, B32), (9000, 300, 0.2, 24, A32), (9000, 300, 0.2, 13, B32), (9000, 2500, 0.1, 18, A32),
+    (8300, 4700, 0.1, 18, None), (8300, 4500, 0.1, 18, A32), (8300, 4700, 0.1, 24, A32), (11400, 4700, 0.1, 18, A32),
 ])
 def test_where_strips_end(rows, cols, density, N, form):
     from paper_2603_08734_amd import Plan
