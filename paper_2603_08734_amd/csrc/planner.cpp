@@ -901,7 +901,11 @@ static bool strip_reads_in_place(const HostPlan& plan, int form, int64_t n_win, 
 //     9.9; 256000 rows of 16 41.5 and 44.2; 102400 of 32 36.0 and 30.8.
 //   * rows of B in pieces, long windows of which few workgroups of 32 x 32 run a second time: 8200 x 5500 (257 of them),
 //     18 features 23.5 and 25.6, x 8192 25.6 and 28.7; 12000 x 5500 24.2 and 23.1.
-//   * beyond 32 features with rows of B in pieces and hardly a fragment a wave: 22400 x 128, 50 features 7.0 and 7.5.
+//   * beyond 64 features where whole windows are long enough for their kernels: 64 x 64 in four waves 1200 x 3000, 1000 features 26.1 both,
+//     x 4090 26.9 and 31.0; 4800 rows, 200 features, 3000 columns 21.4 and 21.9, 4090 24.4 and 27.6; 128 features, 9600 x 4090 33.4 and 31.8.
+//     In eight 1200 rows, 500 features, 4000 columns 22.0 and 20.9, 5000 23.2 and 23.9, 6600 25.7 and 29.8; 128 features, 4800 x 6600 28.0
+//     and 26.9.  32 x 64 1440 rows, 200 features, 5500 columns 19.3 and 18.0, 7000 20.7 and 21.7, 8192 20.7 and 24.3.
+//   * the same beyond 32 features with rows of B in pieces and hardly a fragment a wave: 22400 x 128, 50 features 7.0 and 7.5.
 // `alone`: no residual rows beside the windows (they read the copy of B, and then so do strips).
 static int strip_form(const HostPlan& plan, int64_t n_win, uint32_t longest, bool alone) {
     if (!plan.height_chosen || plan.opts.max_tiles_per_item > 0) return 0;
@@ -924,13 +928,14 @@ static int strip_form(const HostPlan& plan, int64_t n_win, uint32_t longest, boo
         return longest < (broken ? 32 : 16) ? 0 : form64;
     }
     if (small <= 256) return form32;
-    if (blocks <= 256) return strip_code(64, 1, 8);
+    const bool whole = n % 64 == 0;   // no panel is computed for features that are not there
+    if (blocks <= 256) return n <= 128 || whole || longest <= 192 ? strip_code(64, 1, 8) : 0;
     // beyond 26 fragments a wave the chains of 64 x 64 would be longer than those of windows that are cut for want of others: relative
     // error against 64 bits of a 10952 x 7178 weight (28 a wave), 48 features, 1.82e-7 and in the panel kernel 1.78e-7
-    if (blocks <= 512) return longest <= 208 ? strip_code(64, 2, 8) : 0;
+    if (blocks <= 512) return longest <= (n <= 64 || n == 128 ? 208 : 144) ? strip_code(64, 2, 8) : 0;
     if (blocks > 1024) return 0;
     if (n <= 64) return n % 2 == 0 && n % 8 != 0 && longest <= 4 ? 0 : strip_code(64, 2, longest <= 128 ? 4 : 8);
-    return longest <= 128 ? strip_code(64, 2, 4) : 0;
+    return longest <= (n == 128 ? 128 : 96) ? strip_code(64, 2, 4) : 0;
 }
 
 int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int threads) {
