@@ -470,12 +470,9 @@ bool copies_operand(const rsh::HostPlan& h, uintptr_t B, uintptr_t C, int* width
         padded = false;
         *width = n;
     }
-    // Tall windows without residual rows beside them read rows of fewer than 16 features where they lie (panel.hpp).  That
-    // saves a launch and costs the loop 0.08 us per fragment of a workgroup, so not beyond 32 fragments per compute unit: weights
-    // of 1024 x 1024, 5 features, 15.4 us with the copy and 13.9, 5000 x 3000 16.9 and 15.1, 17000 x 2000 (16 fragments) 20.3
-    // and 19.1; 28672 x 8192 (112) 59.9 and 65.1.  Where waves divide the columns (strip.hpp) so are rows of odd widths: strip_form.
-    if (h.geo.strip ? h.strip_in_place && h.irr_wave.empty() : n < 16 && h.geo.panel && h.geo.N <= 16 && h.irr_wave.empty() && h.n_cols * n >= 8 &&
-        (int64_t)h.win_tile_off.back() * h.geo.win_rows <= 32 * 256 * 256) {
+    // Tall windows without residual rows beside them read rows of fewer than 16 features where they lie, and where waves divide the
+    // columns (strip.hpp) those of odd widths.
+    if ((h.geo.strip ? h.strip_in_place : rsh::whole_windows_read_in_place(h)) && h.irr_wave.empty()) {
         padded = false;
         *width = n;
     }

@@ -136,6 +136,14 @@ void partition_rows(const rsh_csr_t& a, const rsh_plan_opts_t& o, const std::vec
 int choose_window_rows(const rsh_csr_t& a, const Partition& part16);
 int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int threads);
 int64_t panel_device_bytes(const HostPlan& plan);
+// Whether the kernels of whole tall windows (panel.hpp) read rows of fewer than 16 features where they lie, if no residual rows are beside them.
+// That saves the copy's launch and costs the loop 0.08 us per fragment of a workgroup, so not beyond 32 fragments per compute unit: weights
+// of 1024 x 1024, 5 features, 15.4 us with the copy and 13.9, 5000 x 3000 16.9 and 15.1, 17000 x 2000 (16 fragments) 20.3
+// and 19.1; 28672 x 8192 (112) 59.9 and 65.1.
+inline bool whole_windows_read_in_place(const HostPlan& plan) {
+    const int n = plan.n_user;
+    return n < 16 && plan.geo.panel && plan.geo.N <= 16 && plan.n_cols * n >= 8 && (int64_t)plan.win_tile_off.back() * plan.geo.win_rows <= 32 * 256 * 256;
+}
 NarrowPart pack_narrow(const HostPlan& plan, int threads);
 // Whether the 16-row windows of `part` are better off as residual rows at n features (narrow.hpp).
 bool narrow_pays(const rsh_csr_t& a, const Partition& part, int n);

@@ -899,6 +899,9 @@ static bool strip_reads_in_place(const HostPlan& plan, int form, int64_t n_win, 
 //     256000 rows, 32 features 20.9 and 24.9, of 4 20.5 and 25.0, of 8 28.1 and 29.0, of 16 41.1 and 35.4; 102400 rows of 8 13.5 and
 //     13.2.  With rows of B in pieces, from 512 workgroups on: 44800 rows (700), 18 features, of 4 6.3 and 9.3, of 8 7.8 and 9.6, of 16 10.6 and
 //     9.9; 256000 rows of 16 41.5 and 44.2; 102400 of 32 36.0 and 30.8.
+//   * below 16 features where they need the copy of B and whole windows do not (copies_operand): band of 1024, 50000 rows (784
+//     workgroups of 64 x 32, 16 more than one round), 1 feature 21.9 and 23.2, but 102400 x 512 (1600) 21.7 and 18.6; 2000 x 8192 13.7 and
+//     16.6, of 7000 columns 15.0 and 15.2.
 //   * rows of B in pieces, long windows of which few workgroups of 32 x 32 run a second time: 8200 x 5500 (257 of them),
 //     18 features 23.5 and 25.6, x 8192 25.6 and 28.7; 12000 x 5500 24.2 and 23.1.
 //   * beyond 64 features where whole windows are long enough for their kernels: 64 x 64 in four waves 1200 x 3000, 1000 features 26.1 both,
@@ -914,9 +917,12 @@ static int strip_form(const HostPlan& plan, int64_t n_win, uint32_t longest, boo
     const int n = plan.n_user;
     const int64_t groups = n_win * plan.geo.panel_groups, small = groups * ((n + 31) / 32), blocks = groups * ((n + 63) / 64);
     const int form32 = strip_code(32, 1, 8), form64 = strip_code(32, 2, 4);
+    const auto copied = [&](int form) {   // by strips, where whole windows read rows in place
+        return alone && whole_windows_read_in_place(plan) && !strip_reads_in_place(plan, form, n_win, longest);
+    };
     if (n <= 32) {
         const auto pieces = [&](int form) { return n % 8 != 0 && plan.geo.N == (n + 15) / 16 * 16 && ((n >= 16 && n % 2 == 0) || (alone && strip_reads_in_place(plan, form, n_win, longest))); };
-        if (small <= 256) return form32;
+        if (small <= 256) return small <= 128 && longest > 208 && copied(form32) ? 0 : form32;
         if (small <= 512) {
             if (longest <= 75 && pieces(form64)) return form64;
             return small <= 352 && longest > 144 && pieces(form32) ? 0 : form32;
@@ -925,7 +931,7 @@ static int strip_form(const HostPlan& plan, int64_t n_win, uint32_t longest, boo
         const int64_t pairs = groups / 2;
         if (pairs <= 512) return form64;
         if (pairs <= 768) return broken && longest < 16 ? 0 : form64;
-        return longest < (broken ? 32 : 16) ? 0 : form64;
+        return longest < (broken ? 32 : 16) || (pairs <= 960 && copied(form64)) ? 0 : form64;
     }
     if (small <= 256) return form32;
     const bool whole = n % 64 == 0;   // no panel is computed for features that are not there

@@ -112,7 +112,7 @@ def test_windows_beside_rows_without_entries(N):
 
 
 # Both sides of the lines up to which strips are taken: short windows in several rounds, rows of B in pieces or whole, long windows of
-# many features.
+# many features, the copy of B that whole windows do without.
 @pytest.mark.parametrize("rows,cols,density,N,form", [
     (44800, 128, 0.3, 18, None), (44800, 128, 0.3, 16, B32), (44800, 500, 0.1, 18, B32), (30000, 64, 0.4, 18, B32), (44800, 128, 0.3, 31, B32),
     (64000, 300, 0.1, 32, None), (64000, 500, 0.1, 32, B32), (64000, 500, 0.1, 18, None), (64000, 1000, 0.1, 18, B32),
@@ -123,6 +123,7 @@ def test_windows_beside_rows_without_entries(N):
     (1440, 8192, 0.1, 200, None), (1440, 6000, 0.1, 200, A64), (1440, 8192, 0.1, 256, A64),
     (1200, 5000, 0.1, 500, None), (1200, 4500, 0.1, 500, B64), (4800, 6500, 0.1, 128, B64), (4800, 6500, 0.1, 100, None),
     (1200, 3500, 0.1, 1000, None), (1200, 3000, 0.1, 1000, E64), (9600, 4000, 0.1, 128, E64), (9600, 4000, 0.1, 100, None),
+    (2000, 8192, 0.1, 1, None), (2000, 6500, 0.1, 1, A32), (2000, 8192, 0.1, 16, A32), (50000, 1000, 0.1, 13, None), (64000, 1000, 0.1, 13, B32),
 ])
 def test_where_strips_end(rows, cols, density, N, form):
     from paper_2603_08734_amd import Plan
