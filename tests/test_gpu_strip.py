@@ -111,6 +111,30 @@ def test_windows_beside_rows_without_entries(N):
     plan.destroy()
 
 
+# Windows that name different columns, from 128 on: an XCD takes the strips of a window one behind the other.  The last window lacks
+# row groups; 128 and 130 windows: the last turn of the XCDs is full, or two of them have it alone.
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,N,form", [(32700, 64, E64), (33200, 31, B32), (33200, 18, B32), (33200, 16, B32)])
+def test_strips_of_a_window_one_behind_the_other(rows, N, form):
+    import torch
+    from paper_2603_08734_amd import Plan
+    rng = np.random.default_rng(4)
+    r, c = np.nonzero(rng.random((rows, 512), dtype=np.float32) < 0.3)
+    A = from_coo(r, r * (rows - 512) // (rows - 1) + c, rng.standard_normal(r.size), rows, rows)
+    print(f"case strips of a band rows={rows} N={N}", flush=True)
+    plan = Plan(A.row_ptr, A.col_idx, A.val, A.n_cols, N, force_path=2, reorder=0)
+    st = plan.stats()
+    assert plan.strip() == form and st["n_windows"] == -(-rows // 256) >= 128 and 64 * st["n_tiles"] < st["n_windows"] * rows
+    B = dense_B(A.n_cols, N, "normal", seed=N)
+    C = torch.full((rows, N), float("nan"), dtype=torch.float32, device="cuda")
+    plan.spmm(torch.from_numpy(B.view(np.int16)).cuda().view(torch.float16), C)
+    torch.cuda.synchronize()
+    C_ref, S, _ = oracle.spmm(A.row_ptr, A.col_idx, A.val, B)
+    got = C.cpu().numpy().astype(np.float64)
+    assert not np.isnan(got).any() and np.all(np.abs(got - C_ref) <= 1e-4 * S)
+    plan.destroy()
+
+
 # Both sides of the lines up to which strips are taken: short windows in several rounds, rows of B in pieces or whole, long windows of
 # many features, the copy of B that whole windows do without.
 @pytest.mark.parametrize("rows,cols,density,N,form", [
