@@ -872,6 +872,17 @@ def test_dissolved_windows_keep_their_product_in_the_library_owned_array():
         assert (st["nnz_tile"] > 0) == windows and st["n_scratch_slots"] * 128 * 4 <= 64 << 20
 
 
+# Slices of narrow rows (narrow_slice) where B is copied first (odd widths from 2^18 entries on).
+@pytest.mark.parametrize("rows,cols,per_row,N,slices", [(110, 20000, 2560, 3, 0), (110, 20000, 2561, 3, 6), (110, 20000, 2561, 4, 0), (100, 100000, 3000, 5, 6), (200, 50000, 2000, 3, 0),
+                                                        (200, 50000, 2000, 5, 4), (200, 50000, 2000, 8, 0), (300, 100000, 1024, 7, 0), (70, 200000, 4000, 3, 8)])
+def test_slices_of_narrow_rows_beside_a_copy(rows, cols, per_row, N, slices):
+    rng = np.random.default_rng(5)
+    step = cols // per_row
+    c = (rng.integers(0, step, (rows, per_row)) + step * np.arange(per_row)).ravel()
+    A = from_coo(np.repeat(np.arange(rows), per_row), c, np.ones(c.size), rows, cols)
+    assert host_plan(A, N, reorder=0, force_path=1).stats()["n_scratch_slots"] == (rows * slices)
+
+
 # Rows of narrow products (narrow_slice): whole while that costs less than a combine pass, else slices that fill the chip; a few long
 # rows beside many short ones in slices of 1024.
 @pytest.mark.parametrize("rows,cols,per_row,N,short_rows,slices", [
