@@ -96,8 +96,8 @@ __device__ __forceinline__ void keep_streaming_hint() { asm volatile("" ::: "mem
 //               2^18 vertices, 160 features: 247.2 us and 243.9; 27-point stencil on 80^3 in binary16, 64 features:
 //               58.2 and 56.8)
 //   kRowsEven   equally long, an even number of features from 16 on, 4-byte aligned
-//   kRowsAny    rows of C of any number of features, aligned to their element only, shorter than the rows of B (a
-//               padded copy); features from nv on are not stored and have no bias
+//   kRowsAny    rows of C of any number of features, aligned to their element only; those of B are longer (a padded copy), or as
+//               long where the kernels read odd widths and those below 16 as they lie.  Features from nv on are not stored and have no bias
 enum Rows { kRowsWhole, kRowsEven, kRowsAny };
 template <int ROWS>
 struct OutPlainT {

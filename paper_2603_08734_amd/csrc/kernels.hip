@@ -867,8 +867,8 @@ static inline uint32_t grid_for(const XcdSplit& xs) {
 }
 
 // Feature widths of a launch: `nb` of a row of B, `nv` of a row of C.  Equal, even and at least 16 (whole rows: equal to
-// geo.N, a multiple of 16); or (OUT::kAny)
-// nb is the padded width, a multiple of 16, and nv any width up to it.  Partial sums have rows of geo.N >= nb.
+// geo.N, a multiple of 16); or (OUT::kAny) nb is the width of a padded copy, a multiple of 16 here, and nv any width up to it (lanes that own
+// or share rows and strips also take nb == nv, any width).  Partial sums have rows of geo.N >= nb.
 // Full panels, or all panels of a width that ends in a partial one, which starts early enough to hold eight features (those
 // it shares with the panel before come out the same twice).  All in one launch of the partial panel's kernel: a launch of its
 // own ends with its longest waves, and the kernel of full panels gains less than that.  Power-law graphs, us, two launches and

@@ -5,7 +5,8 @@
 // places).  Here, up to 8 features, a lane takes an entry's whole row of B and adds it to sums of its own; of more features
 // two, four or eight lanes share it (rsh_shared_kernel):
 //   * T = 1 .. 64 places (lanes, or groups of lanes that share a row of B) share a row (or a slice of a long one) and are added
-//     up once at its end; rows of up to 32 entries, in a large matrix, have a place each and need no addition across lanes at all.
+//     up once at its end; rows of up to 32 entries, in a large matrix, have a place each and need no addition across lanes at all,
+//     longer ones as many places as leave each at most 32, up to all of a wave: 64 entries a place in a row of 4096, 128 where two lanes share.
 //   * Column ids and values lie in the order in which the lanes take them (pack_narrow in planner.cpp), in pairs of
 //     entries: one 8-byte and one 4-byte load per lane for two entries, whole lines per wave.
 //   * Rows of B of up to 8 features are read at the next power of two of their width NP: one load per entry.  Rows of
@@ -76,10 +77,11 @@ __device__ __forceinline__ float half_of(const uint32_t* w, int i) {
     return i % 2 ? __high2float(h) : __low2float(h);
 }
 // sums += the entries of one turn.  Products of two binary16 values are exact in fp32; they are added up in pairs, the pairs in
-// 64 bits: a lane takes up to 32 entries, and fp32 sums one behind the other lose up to 1.7 times as much as those of teams,
-// which add up across a wave.  Relative error against 64 bits of what ran before lanes did, of lanes in fp32 and so: 27-point
+// 64 bits: a lane takes 32 entries and more (128 at most, see above), and fp32 sums one behind the other lose up to 1.7 times as much as
+// those of teams, which add up across a wave.  Relative error against 64 bits of what ran before lanes did, of lanes in fp32 and so: 27-point
 // stencil on 80^3 6.4e-8, 9.1e-8, 3.5e-8; rows of 30 random entries 5.3e-8, 8.6e-8, 2.8e-8; power-law graph of 2^17 vertices
-// 1.23e-8, 1.23e-8, 1.02e-8.  Lanes in fp32 took, and these take: that graph at 2^18 vertices, 8 features 49.6 us and 49.8, 32
+// 1.23e-8, 1.23e-8, 1.02e-8.  Whole rows of 4096 entries, 8 features 3.0e-8 (in slices of 512 with an fp32 combine pass 6.2e-8), of 4000, 16
+// features 3.0e-8 (5.9e-8).  Lanes in fp32 took, and these take: that graph at 2^18 vertices, 8 features 49.6 us and 49.8, 32
 // 62.6 and 63.7, 64 86.8 and 89.7; 150000 rows of 12 entries, 64 features 36.0 and 36.2.
 template <int PAIRS, int F, class ROW>
 __device__ __forceinline__ void add_turn(const uint32_t (&w)[PAIRS], const ROW (&b)[2 * PAIRS], float zero, double (&acc)[F]) {

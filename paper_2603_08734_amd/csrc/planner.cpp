@@ -1661,7 +1661,8 @@ static int lanes_per_row(const HostPlan& plan, const rsh_csr_t& a, const std::ve
 // Residual rows in the form of narrow.hpp.  The waves of IRR_WAVE are taken apart into segments -- a row, or a slice of one --
 // and these dealt to the S places of a wave (its lanes, or groups of geo.narrow lanes that share a row of B): T = 1, 2, .. S
 // places take a segment, entry e being place e % T's, S / T segments make a wave.  A place takes up to twice `per_lane`
-// entries: 16, or fewer where the plan would have too few waves to fill the chip.  Segments that write C are dealt to the
+// entries (16, or fewer where the plan would have too few waves to fill the chip) as long as there are places; a segment that has all S
+// of them gives each its S-th part, 128 at most (4096 entries, 32 places).  Segments that write C are dealt to the
 // XCDs in contiguous runs of rows of equal cost, so that lines of C that hold several short rows are written by one L2 (dealt
 // in runs of 64 to 2048 rows nothing changes); partial sums stay on the XCD that the plan chose for their columns.
 // Inside a run they are ordered by length within blocks of rows, so that the places of a wave end together: 8192 rows, or, for

@@ -11,14 +11,16 @@
 //     kernel where windows are many and features more than 64; two row groups share every read of B from LDS.
 //   * Rows of B of any width and alignment are read where they lie; what a piece holds past the row's end lands in
 //     features that are not stored, and the last pieces of B are read where they end with it.
-// What bounds it: a wave's instructions, some 52 vector ones a row group and fragment beside two multiply-adds (expansion of the
-// cells as in the panel kernel), and below some 100 workgroups the number of waves.
+// What bounds it: a wave's own pace, some 52 vector instructions a row group and fragment beside two multiply-adds (expansion of the
+// cells as in the panel kernel) and the loads that they wait for.  28672 x 8192, 16 features, 54 us: a wave issues in 49 % of its
+// cycles and waits for loads in 35; vector instructions take 38 % of the SIMDs' cycles, multiply-adds 11, and compute units idle 22 (64
+// of 256 have one workgroup of the 448, the others two); 184 MB from memory, 3.4 TB/s.  Below some 100 workgroups the number of waves.
 // An output's fp32 chains have at most 32 fragments = 1024 columns, those of one row group 16: relative error against 64 bits of a
 // 2000 x 8000 weight, 16 features, 1.64e-7 in the panel kernel, 2.01e-7 with chains of 32, 1.52e-7 with 16.  (64 x 32 in four waves, whose
 // first half waits in LDS: 28672 x 8192, 16 features, 50.9 us, in eight waves of half the share 55.7.)
 // Cells written out (wide.hpp) instead of packed, same split: 3000 x 3000 at density 0.2, 64 features 10.4 us and 9.5 packed, 14000 x
-// 4000 26.8 and 19.1, 28672 x 8192 99.7 and 66.6.  Four fragments of values in flight instead of two, at the price of
-// waves in flight: 28672 x 8192, 16 features 74 us against 64.  Times against the panel kernel's: strip_form in planner.cpp.
+// 4000 26.8 and 19.1, 28672 x 8192 99.7 and 66.6.  Four fragments of values in flight instead of two cost waves
+// in flight and a sixth of the rate (28672 x 8192, 16 features).  Times against the panel kernel's: strip_form in planner.cpp.
 #pragma once
 #include <algorithm>
 
