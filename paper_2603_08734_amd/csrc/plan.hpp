@@ -48,7 +48,7 @@ struct Geometry {
     int panel = 0;      // 1 = tall windows in the panel form (win_rows == 128 or 256, tile_k == 32)
     int wide = 0;       // panel form whose cells are written out on the device (wide.hpp); win_rows == 256
     int strip = 0;      // panel form of small products, whose waves share rows and divide the columns (strip.hpp): strip_code; windows are not cut
-    int strip_turn = 1; // blocks of rows of strip.hpp that an XCD takes one behind the other
+    int strip_log_turn = 0; // log2 of the blocks of rows of strip.hpp that an XCD takes one behind the other
     int narrow = 0;     // residual rows in the form of narrow.hpp: lanes that share a row of B (1, 2, 4 or 8), 0 = teams
     int panel_groups = 0; // panel form: row groups of 32 rows per window = win_rows / 32
 };

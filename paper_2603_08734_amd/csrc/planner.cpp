@@ -948,13 +948,18 @@ static int strip_form(const HostPlan& plan, int64_t n_win, uint32_t longest, boo
     return longest <= (n == 128 ? 128 : 96) ? strip_code(64, 2, 4) : 0;
 }
 
-// Blocks of rows that an XCD takes one behind the other: those of a window where windows name different columns (on average less than
-// half of them), so that the window's rows of B come from memory once and not for every XCD; else 1, which deals the blocks out more
+// Whether tall windows name different columns: on average less than half of all.
+static bool windows_differ(const HostPlan& plan, int64_t n_win) { return 2 * kPanelK * (int64_t)plan.win_tile_off.back() < n_win * plan.n_cols; }
+
+// Log2 of the blocks of rows that an XCD takes one behind the other: those of a window (2, 4 or 8) where windows name different columns, so that the window's rows of B come from memory once and not for every XCD; else 0, which deals the blocks out more
 // evenly.  Bands, us, blocks dealt one by one and by window: 512 wide, 50000 rows, 32 features 18.9 and 17.2, 100000 33.0 and 27.5; 1024 wide,
 // 50000 31 features 30.5 and 25.6, 64000 28.2 and 22.2 at 32 (kernels of whole windows 21.7).  Weights, whose windows name all columns: 28672 x
 // 8192 16 features 41.9 and 43.9, 14000 x 4000 1 feature 17.2 and 18.3.  From 128 windows on, 16 an XCD.
-static int strip_turn(const HostPlan& plan, int64_t n_win, int64_t n_tiles) {
-    return n_win >= 128 && 2 * kPanelK * n_tiles < n_win * plan.n_cols ? plan.geo.panel_groups / strip_row_groups(plan.geo.strip) : 1;
+static int strip_log_turn(const HostPlan& plan, int64_t n_win) {
+    if (n_win < 128 || !windows_differ(plan, n_win)) return 0;
+    int log = 0;
+    while (2 << log <= plan.geo.panel_groups / strip_row_groups(plan.geo.strip)) ++log;
+    return log;
 }
 
 int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int threads) {
@@ -984,7 +989,7 @@ int pack_plan(const rsh_csr_t& a, const Partition& part, HostPlan& plan, int thr
         plan.strip_in_place = geo.strip && strip_reads_in_place(plan, geo.strip, n_win, longest);
         if (geo.strip) {
             geo.wide = 0;
-            geo.strip_turn = strip_turn(plan, n_win, n_tiles);
+            geo.strip_log_turn = strip_log_turn(plan, n_win);
         }
     } else {
         // ---- pass 1: fragments and padded value count per window ---------------------------

@@ -261,7 +261,7 @@ template <int NCH32, int RB, int WAVES, bool RAGGED, class OUT>
 __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(kStripWaves<NCH32, RB, RAGGED>))) void rsh_strip_kernel(
     const int32_t* __restrict__ win_row, const uint32_t* __restrict__ win_tile_off, const int32_t* __restrict__ win_run,
     const int32_t* __restrict__ tile_colid, const uint4_t* __restrict__ meta, const uint32_t* __restrict__ quad0, const uint32_t* __restrict__ qoff,
-    const uint32_t* __restrict__ val, const __half* __restrict__ B, const OUT out, uint32_t n_blocks, uint32_t groups, uint32_t panels, uint32_t turn, int N, int nv,
+    const uint32_t* __restrict__ val, const __half* __restrict__ B, const OUT out, uint32_t n_blocks, uint32_t groups, uint32_t panels, uint32_t log_turn, int N, int nv,
     uint32_t b_last) {
     using Gm = StripGeom<NCH32, RB, WAVES>;
     constexpr int P = Gm::P;
@@ -269,8 +269,9 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(kStr
     __shared__ __attribute__((aligned(16))) unsigned char smem[WAVES * Gm::WAVE_BYTES + kSelectorBytes];
     const int lane = threadIdx.x & 63;
     const uint32_t wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    // all panels of a block of rows run at the same time on one XCD, and `turn` blocks of rows one behind the other
-    const uint32_t at = blockIdx.x >> 3, py = at % panels, i = at / panels, q = i / turn, block = (q * 8 + (blockIdx.x & 7u)) * turn + (i - q * turn);
+    // all panels of a block of rows run at the same time on one XCD, and 2^log_turn blocks of rows one behind the other
+    const uint32_t at = blockIdx.x >> 3, py = at % panels, i = at / panels;
+    const uint32_t block = (((i >> log_turn) * 8 + (blockIdx.x & 7u)) << log_turn) + (i & ((1u << log_turn) - 1u));
     if (block >= n_blocks) return;   // uniform
     const uint32_t blocks = groups / RB;   // of a window
     const uint32_t win = block / blocks, group = (block - win * blocks) * RB;
@@ -336,10 +337,10 @@ __global__ __launch_bounds__(64 * WAVES) __attribute__((amdgpu_waves_per_eu(kStr
 template <int NCH32, int RB, int WAVES, class OUT>
 void launch_strip_t(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st, int nb, int nv) {
     const uint32_t groups = (uint32_t)d.geo.panel_groups, n_blocks = (uint32_t)d.n_tile_items * (groups / RB), panels = (uint32_t)(nv + 32 * NCH32 - 1) / (32 * NCH32);
-    const uint32_t turn = (uint32_t)d.geo.strip_turn;
+    const uint32_t log_turn = (uint32_t)d.geo.strip_log_turn, turn = 1u << log_turn;
     const auto launch = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(8u * ((n_blocks + 8 * turn - 1) / (8 * turn)) * turn * panels), dim3(64 * WAVES), 0, st, d.win_row, d.win_tile_off, d.win_run,
-                           d.tile_colid, (const uint4_t*)d.panel_meta, d.panel_quad0, d.panel_qoff, d.panel_val, (const __half*)B, out, n_blocks, groups, panels, turn, nb, nv,
+                           d.tile_colid, (const uint4_t*)d.panel_meta, d.panel_quad0, d.panel_qoff, d.panel_val, (const __half*)B, out, n_blocks, groups, panels, log_turn, nb, nv,
                            2u * ((uint32_t)d.n_cols * (uint32_t)nb - 8u));
     };
     if (nb % 8 || ((uintptr_t)B & 15u)) launch(rsh_strip_kernel<NCH32, RB, WAVES, true, OUT>);
