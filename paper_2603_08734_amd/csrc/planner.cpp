@@ -874,6 +874,9 @@ static bool strip_reads_in_place(const HostPlan& plan, int form, int64_t n_win, 
     return (int64_t)longest * (features / 16) * ((blocks + 255) / 256) <= 150;
 }
 
+// Whether tall windows name different columns: on average less than half of all.
+static bool windows_differ(const HostPlan& plan, int64_t n_win) { return 2 * kPanelK * (int64_t)plan.win_tile_off.back() < n_win * plan.n_cols; }
+
 // Form of strip.hpp in which a plan of tall windows runs, 0 for the kernels of whole windows (panel.hpp, wide.hpp).  A
 // compute unit holds two workgroups of 32 rows x 32 features, three of 64 x 32, one of 32 x 64 (or 64 x 64 in eight waves) and
 // two of 64 x 64 in four; where rows of B end inside a 16-byte piece and are read where they lie (139 and 172 registers instead of
@@ -902,7 +905,9 @@ static bool strip_reads_in_place(const HostPlan& plan, int form, int64_t n_win, 
 //   * up to 32 features in more than one round of 64 x 32, short windows: a strip's start and end are not amortised.  Of 2 fragments
 //     256000 rows, 32 features 20.9 and 24.9, of 4 20.5 and 25.0, of 8 28.1 and 29.0, of 16 41.1 and 35.4; 102400 rows of 8 13.5 and
 //     13.2.  With rows of B in pieces, from 512 workgroups on: 44800 rows (700), 18 features, of 4 6.3 and 9.3, of 8 7.8 and 9.6, of 16 10.6 and
-//     9.9; 256000 rows of 16 41.5 and 44.2; 102400 of 32 36.0 and 30.8.
+//     9.9; beyond one round whole windows have one a compute unit up to 65536 rows, two up to 131072: 64000 rows of 28 16.4 18.2, of 29 19.5
+//     18.9, 90000 of 20 23.8 23.7, of 24 26.6 24.6, of 28 29.4 26.1, 140000 of 24 39.1 36.3, 256000 of 28 58.3 62.1, of 29 70.4 64.5; bands of some
+//     35 fragments, 64000 rows 21.0 22.9, 90000 40.3 32.4.
 //   * below 16 features where they need the copy of B and whole windows do not (copies_operand): band of 1024, 50000 rows (784
 //     workgroups of 64 x 32, 16 more than one round), 1 feature 21.9 and 23.2, but 102400 x 512 (1600) 21.7 and 18.6; 2000 x 8192 13.7 and
 //     16.6, of 7000 columns 15.0 and 15.2.
@@ -926,16 +931,18 @@ static int strip_form(const HostPlan& plan, int64_t n_win, uint32_t longest, boo
     };
     if (n <= 32) {
         const auto pieces = [&](int form) { return n % 8 != 0 && plan.geo.N == (n + 15) / 16 * 16 && ((n >= 16 && n % 2 == 0) || (alone && strip_reads_in_place(plan, form, n_win, longest))); };
-        if (small <= 256) return small <= 128 && longest > 208 && copied(form32) ? 0 : form32;
+        if (small <= 256) return small <= 128 && longest > 216 && copied(form32) ? 0 : form32;
         if (small <= 512) {
-            if (longest <= 75 && pieces(form64)) return form64;
+            if (longest <= (n < 16 || n % 2 ? 60 : 75) && pieces(form64)) return form64;
             return small <= 352 && longest > 144 && pieces(form32) ? 0 : form32;
         }
         const bool broken = pieces(form64);
         const int64_t pairs = groups / 2;
         if (pairs <= 512) return form64;
         if (pairs <= 768) return broken && longest < 16 ? 0 : form64;
-        return longest < (broken ? 32 : 16) || (pairs <= 960 && copied(form64)) ? 0 : form64;
+        if (pairs <= 960 && copied(form64)) return 0;
+        const uint32_t least = !broken ? 16 : n_win <= 256 ? (windows_differ(plan, n_win) ? 44 : 29) : n_win <= 640 ? 24 : 29;
+        return longest < least ? 0 : form64;
     }
     if (small <= 256) return form32;
     const bool whole = n % 64 == 0;   // no panel is computed for features that are not there
@@ -947,9 +954,6 @@ static int strip_form(const HostPlan& plan, int64_t n_win, uint32_t longest, boo
     if (n <= 64) return n % 2 == 0 && n % 8 != 0 && longest <= 4 ? 0 : strip_code(64, 2, longest <= 128 ? 4 : 8);
     return longest <= (n == 128 ? 128 : 96) ? strip_code(64, 2, 4) : 0;
 }
-
-// Whether tall windows name different columns: on average less than half of all.
-static bool windows_differ(const HostPlan& plan, int64_t n_win) { return 2 * kPanelK * (int64_t)plan.win_tile_off.back() < n_win * plan.n_cols; }
 
 // Log2 of the blocks of rows that an XCD takes one behind the other: those of a window (2, 4 or 8) where windows name different columns, so that the window's rows of B come from memory once and not for every XCD; else 0, which deals the blocks out more
 // evenly.  Bands, us, blocks dealt one by one and by window: 512 wide, 50000 rows, 32 features 18.9 and 17.2, 100000 33.0 and 27.5; 1024 wide,

@@ -140,14 +140,15 @@ def test_strips_of_a_window_one_behind_the_other(rows, N, form):
 @pytest.mark.parametrize("rows,cols,density,N,form", [
     (44800, 128, 0.3, 18, None), (44800, 128, 0.3, 16, B32), (44800, 500, 0.1, 18, B32), (30000, 64, 0.4, 18, B32), (44800, 128, 0.3, 31, B32),
     (64000, 300, 0.1, 32, None), (64000, 500, 0.1, 32, B32), (64000, 500, 0.1, 18, None), (64000, 1000, 0.1, 18, B32),
+    (64000, 890, 0.1, 18, None), (64000, 910, 0.1, 18, B32), (70000, 890, 0.1, 18, B32), (70000, 700, 0.1, 18, None),
     (64000, 500, 0.1, 31, B32), (64000, 300, 0.1, 31, None), (64000, 300, 0.1, 1, None),
     (22400, 128, 0.3, 50, None), (22400, 160, 0.3, 50, E64), (22400, 128, 0.3, 56, E64),
-    (9000, 300, 0.2, 18, B32), (9000, 300, 0.2, 24, A32), (9000, 300, 0.2, 13, B32), (9000, 2500, 0.1, 18, A32),
+    (9000, 300, 0.2, 18, B32), (9000, 300, 0.2, 24, A32), (9000, 300, 0.2, 13, B32), (9000, 2500, 0.1, 18, A32), (9000, 2000, 0.1, 18, B32), (9000, 2000, 0.1, 13, A32), (9000, 1900, 0.1, 13, B32),
     (8300, 4700, 0.1, 18, None), (8300, 4500, 0.1, 18, A32), (8300, 4700, 0.1, 24, A32), (11400, 4700, 0.1, 18, A32),
     (1440, 8192, 0.1, 200, None), (1440, 6000, 0.1, 200, A64), (1440, 8192, 0.1, 256, A64),
     (1200, 5000, 0.1, 500, None), (1200, 4500, 0.1, 500, B64), (4800, 6500, 0.1, 128, B64), (4800, 6500, 0.1, 100, None),
     (1200, 3500, 0.1, 1000, None), (1200, 3000, 0.1, 1000, E64), (9600, 4000, 0.1, 128, E64), (9600, 4000, 0.1, 100, None),
-    (2000, 8192, 0.1, 1, None), (2000, 6500, 0.1, 1, A32), (2000, 8192, 0.1, 16, A32), (50000, 1000, 0.1, 13, None), (64000, 1000, 0.1, 13, B32),
+    (2000, 8192, 0.1, 1, None), (2000, 6900, 0.1, 1, A32), (2000, 8192, 0.1, 16, A32), (50000, 1000, 0.1, 13, None), (64000, 1000, 0.1, 13, B32),
 ])
 def test_where_strips_end(rows, cols, density, N, form):
     from paper_2603_08734_amd import Plan
