@@ -1594,6 +1594,12 @@ bool narrow_pays(const rsh_csr_t& a, const Partition& part, int n) {
 //     features 14.0 and 9.0, 256 23.1 and 9.1; 20000 rows 13.4 and 10.1, 33.8 and 25.3; 100000 rows (4 M entries) 35.6 and 41.1, 101.5
 //     and 101.4, but 16 features 18.4 and 13.6.  1100 columns, 20 a row, 100000 rows 16 features 16.3 and 9.2, 64 26.6 and
 //     21.4, 256 72.4 and 76.1.
+//     A residual row longer than a team pass (16 entries) is a wave for every panel of 128 features, a full one also for the last 16; beyond
+//     64000 such waves windows stay where their own panels fit the width (128, 256, 16 behind them), beyond 100000 or with more than 1.4
+//     entries to a column at any (of 64 features from 48000 waves on, rows of more than 8 entries, by the latter alone).  1000 columns, 18 a row, 144 features, 20000 rows 22.9 and 16.5, 35000 (70000 waves) 24.6 and 25.7,
+//     49075 29.9 and 34.5, 70000 34.6 and 47.3; 272 features, 35000 rows 34.7 and 38.1, 49075 42.0 and 50.9; 128 features 70000 23.2 and
+//     24.8; 200 features, 35000 rows 29.3 and 26.0, 49075 40.0 and 35.1.  500 columns, 30 a row (1.6 entries to a column), 200
+//     features, 20000 rows 18.3 and 19.1, 35000 27.5 and 30.8; 100 features 70000 28.1 and 30.8, 64 16.4 and 18.2.
 // Windows that share more keep theirs: communities (2.7 entries to a column), 25600 rows, 128 features 11.1 and 17.5; 27-point
 // stencil on 30^3 12.3 and 16.0.
 // None of it where the partial sums of all rows together (an upper bound of them) would not fit the library-owned array: windows
@@ -1609,12 +1615,15 @@ bool windows_lose(const rsh_csr_t& a, const Partition& part, int n, const rsh_pl
     if (!beside && !cached) return false;
     const Geometry geo = make_geometry(o.run_width, kW, kW);
     const int64_t slice = o.max_nnz_per_slice > 0 ? o.max_nnz_per_slice : 512, cut = o.xcd_partition_nnz == 0 ? std::max<int64_t>(128, 16384 / geo.irr_panel) : o.xcd_partition_nnz;
-    int64_t slots = 0;
+    int64_t slots = 0, waves = 0;
     for (const std::vector<int32_t>* rows : {&part.irregular, &part.win_row})
         for (int32_t r : *rows) {
             const int64_t len = r >= 0 ? row_len(a, r) : 0, slices = (len + slice - 1) / slice;
-            if (len > geo.irr_tpr) slots += cut > 0 && len >= cut ? std::min(len, slices + 8) : slices > 1 ? slices : 0;
+            if (len > geo.irr_tpr) slots += cut > 0 && len >= cut ? std::min(len, slices + 8) : slices > 1 ? slices : 0, ++waves;
         }
+    waves *= (n + geo.irr_panel - 1) / geo.irr_panel;
+    const bool many = !beside && n > 32 && waves > (n > 64 ? 64000 : 48000);
+    if (many && n > 64 && (n % 128 <= 16 || waves > 100000)) return false;
     if (slots * geo.N * (int64_t)sizeof(float) > (int64_t)kStaticScratchBytes) return false;
     const int64_t step = std::max<int64_t>(1, n_win / 64);
     int64_t entries = 0, columns = 0;   // of the sample
@@ -1629,7 +1638,7 @@ bool windows_lose(const rsh_csr_t& a, const Partition& part, int n, const rsh_pl
         entries += (int64_t)cols.size();
         columns += std::unique(cols.begin(), cols.end()) - cols.begin();
     }
-    return entries < 2 * columns;
+    return many ? 5 * entries < 7 * columns : entries < 2 * columns;
 }
 
 // Lanes that share a row of B in the residual part (narrow.hpp), or none for teams that share a wave (rsh_irregular_kernel).

@@ -872,6 +872,17 @@ def test_dissolved_windows_keep_their_product_in_the_library_owned_array():
         assert (st["nnz_tile"] > 0) == windows and st["n_scratch_slots"] * 128 * 4 <= 64 << 20
 
 
+# Windows that hardly share columns stay windows where residual rows would be many waves: rows of more than a team pass times panels.
+@pytest.mark.parametrize("rows,cols,per_row,N,windows", [(63000, 540, 18, 128, False), (65000, 540, 18, 128, True), (65000, 540, 16, 128, False), (65000, 540, 18, 100, False),
+                                                         (31000, 540, 18, 144, False), (33000, 540, 18, 144, True), (33000, 540, 18, 200, False), (51000, 540, 18, 200, True),
+                                                         (31000, 500, 30, 200, False), (33000, 500, 30, 200, True), (65000, 540, 18, 64, False), (47000, 500, 30, 64, False), (49000, 500, 30, 64, True)])
+def test_windows_that_hardly_share_columns_in_long_launches(rows, cols, per_row, N, windows):
+    rng = np.random.default_rng(7)
+    c = (rng.integers(0, cols // per_row, (rows, per_row)) + cols // per_row * np.arange(per_row)).ravel()
+    A = from_coo(np.repeat(np.arange(rows), per_row), c, np.ones(c.size), rows, cols)
+    assert (host_plan(A, N, reorder=0).stats()["nnz_tile"] > 0) == windows
+
+
 # Slices of narrow rows (narrow_slice) where B is copied first (odd widths from 2^18 entries on).
 @pytest.mark.parametrize("rows,cols,per_row,N,slices", [(110, 20000, 2560, 3, 0), (110, 20000, 2561, 3, 6), (110, 20000, 2561, 4, 0), (100, 100000, 3000, 5, 6), (200, 50000, 2000, 3, 0),
                                                         (200, 50000, 2000, 5, 4), (200, 50000, 2000, 8, 0), (300, 100000, 1024, 7, 0), (70, 200000, 4000, 3, 8)])
