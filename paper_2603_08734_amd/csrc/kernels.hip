@@ -302,9 +302,9 @@ __device__ __forceinline__ void irregular_body(
 #define RSH_IRREGULAR_PARAMS                                                                                                              \
     const uint4 *__restrict__ waves, XcdSplit xs, const int32_t *__restrict__ irr_row, const int32_t *__restrict__ irr_col,               \
         const uint16_t *__restrict__ irr_val, const __half *__restrict__ B, const OUT out, float *__restrict__ scratch, int N,            \
-        int panel0, int nv, int ns
+        int nv, int ns
 template <int TPR, class OUT, bool PARTIAL>
-__global__ __launch_bounds__(64 * kWavesPerBlock) __attribute__((amdgpu_waves_per_eu(8, 8))) void rsh_irregular_kernel(RSH_IRREGULAR_PARAMS) {
+__global__ __launch_bounds__(64 * kWavesPerBlock) __attribute__((amdgpu_waves_per_eu(8, 8))) void rsh_irregular_kernel(RSH_IRREGULAR_PARAMS, int panel0) {
     static_assert(OUT::kRows == (PARTIAL ? kRowsWhole : kRowsEven));   // full panels of whole rows are no different
     irregular_body<TPR, OUT, PARTIAL>(waves, xs, irr_row, irr_col, irr_val, B, out, scratch, N, panel0, nv, ns);
 }
@@ -317,12 +317,12 @@ template <int TPR, class OUT>
 __global__ __launch_bounds__(64 * kWavesPerBlock) __attribute__((amdgpu_waves_per_eu(kEvenWaves<TPR, OUT>, kEvenWaves<TPR, OUT>)))
 void rsh_residual_even_kernel(RSH_IRREGULAR_PARAMS) {
     static_assert(OUT::kRows == kRowsEven);
-    irregular_body<TPR, OUT, true>(waves, xs, irr_row, irr_col, irr_val, B, out, scratch, N, panel0, nv, ns);
+    irregular_body<TPR, OUT, true>(waves, xs, irr_row, irr_col, irr_val, B, out, scratch, N, 0, nv, ns);
 }
 template <int TPR, class OUT, bool PARTIAL>
 __global__ __launch_bounds__(64 * kWavesPerBlock) __attribute__((amdgpu_waves_per_eu(7, 7))) void rsh_residual_any_kernel(RSH_IRREGULAR_PARAMS) {
     static_assert(OUT::kAny);
-    irregular_body<TPR, OUT, PARTIAL>(waves, xs, irr_row, irr_col, irr_val, B, out, scratch, N, panel0, nv, ns);
+    irregular_body<TPR, OUT, PARTIAL>(waves, xs, irr_row, irr_col, irr_val, B, out, scratch, N, 0, nv, ns);
 }
 #undef RSH_IRREGULAR_PARAMS
 
@@ -881,24 +881,24 @@ static inline uint32_t grid_for(const XcdSplit& xs) {
 constexpr int64_t kPanelsApart = 3ll << 23;
 template <int TPR, class OUT>
 static void launch_irregular_t(const DevicePlan& d, const void* B, const OUT& out, hipStream_t st, int nb, int nv) {
-    const auto launch = [&](auto kernel, const auto& to, int first, int panels) {
+    const auto launch = [&](auto kernel, const auto& to, int panels, auto... first) {
         hipLaunchKernelGGL(kernel, dim3(grid_for(d.irr_split), (unsigned)panels), dim3(64 * kWavesPerBlock),
                            0, st, (const uint4*)d.irr_wave, d.irr_split, d.irr_row, d.irr_col, d.irr_val, (const __half*)B, to,
-                           d.scratch, nb, first, nv, d.geo.N);
+                           d.scratch, nb, nv, d.geo.N, first...);
     };
     const int full = nv / d.geo.irr_panel;
     const bool partial = nv % d.geo.irr_panel != 0;
     if constexpr (OUT::kAny) {
-        if (partial) launch(rsh_residual_any_kernel<TPR, OUT, true>, out, 0, full + 1);
-        else launch(rsh_residual_any_kernel<TPR, OUT, false>, out, 0, full);
+        if (partial) launch(rsh_residual_any_kernel<TPR, OUT, true>, out, full + 1);
+        else launch(rsh_residual_any_kernel<TPR, OUT, false>, out, full);
     } else {
         const auto even = out.general();
         using Even = std::decay_t<decltype(even)>;
         const bool apart = OUT::kWhole && !OUT::kFused && d.irr_entries * full >= kPanelsApart;
-        if (!partial || apart) launch(rsh_irregular_kernel<TPR, Even, false>, even, 0, full);
+        if (!partial || apart) launch(rsh_irregular_kernel<TPR, Even, false>, even, full, 0);
         if (!partial) return;
-        if constexpr (OUT::kWhole) launch(rsh_irregular_kernel<TPR, OUT, true>, out, apart ? full : 0, apart ? 1 : full + 1);
-        else launch(rsh_residual_even_kernel<TPR, OUT>, out, 0, full + 1);
+        if constexpr (OUT::kWhole) launch(rsh_irregular_kernel<TPR, OUT, true>, out, apart ? 1 : full + 1, apart ? full : 0);
+        else launch(rsh_residual_even_kernel<TPR, OUT>, out, full + 1);
     }
 }
 
