@@ -1595,11 +1595,12 @@ bool narrow_pays(const rsh_csr_t& a, const Partition& part, int n) {
 //     and 101.4, but 16 features 18.4 and 13.6.  1100 columns, 20 a row, 100000 rows 16 features 16.3 and 9.2, 64 26.6 and
 //     21.4, 256 72.4 and 76.1.
 //     A residual row longer than a team pass (16 entries) is a wave for every panel of 128 features, a full one also for the last 16; beyond
-//     64000 such waves windows stay where their own panels fit the width (128, 256, 16 behind them), beyond 100000 or with more than 1.4
-//     entries to a column at any (of 64 features from 48000 waves on, rows of more than 8 entries, by the latter alone).  1000 columns, 18 a row, 144 features, 20000 rows 22.9 and 16.5, 35000 (70000 waves) 24.6 and 25.7,
-//     49075 29.9 and 34.5, 70000 34.6 and 47.3; 272 features, 35000 rows 34.7 and 38.1, 49075 42.0 and 50.9; 128 features 70000 23.2 and
+//     64000 such waves windows stay where their own panels fit the width (64, 128, 256, 16 behind them), beyond 100000 or with more than 1.4
+//     entries to a column at any (64 features: rows of more than 8 entries, by the latter alone).  1000 columns, 18 a row, 144
+//     features, 20000 rows 22.9 and 16.5, 35000 (70000 waves) 24.6 and 25.7, 49075 29.9 and 34.5, 70000 34.6 and 47.3; 272 features, 35000 rows 34.7 and 38.1, 49075 42.0 and 50.9; 128 features 70000 23.2 and
 //     24.8; 200 features, 35000 rows 29.3 and 26.0, 49075 40.0 and 35.1.  500 columns, 30 a row (1.6 entries to a column), 200
-//     features, 20000 rows 18.3 and 19.1, 35000 27.5 and 30.8; 100 features 70000 28.1 and 30.8, 64 16.4 and 18.2.
+//     features, 20000 rows 18.3 and 19.1, 35000 27.5 and 30.8; 100 features 70000 28.1 and 30.8, 64 16.4 and 18.2, but 49075 rows 13.7
+//     and 12.4, 48 18.6 and 12.6.  1000 columns, 18 a row, 80 features, 100000 rows 30.8 and 34.6.
 // Windows that share more keep theirs: communities (2.7 entries to a column), 25600 rows, 128 features 11.1 and 17.5; 27-point
 // stencil on 30^3 12.3 and 16.0.
 // None of it where the partial sums of all rows together (an upper bound of them) would not fit the library-owned array: windows
@@ -1622,8 +1623,8 @@ bool windows_lose(const rsh_csr_t& a, const Partition& part, int n, const rsh_pl
             if (len > geo.irr_tpr) slots += cut > 0 && len >= cut ? std::min(len, slices + 8) : slices > 1 ? slices : 0, ++waves;
         }
     waves *= (n + geo.irr_panel - 1) / geo.irr_panel;
-    const bool many = !beside && n > 32 && waves > (n > 64 ? 64000 : 48000);
-    if (many && n > 64 && (n % 128 <= 16 || waves > 100000)) return false;
+    const bool many = !beside && n >= 64 && waves > 64000;
+    if (many && n > 64 && (n <= 80 || n % 128 <= 16 || waves > 100000)) return false;
     if (slots * geo.N * (int64_t)sizeof(float) > (int64_t)kStaticScratchBytes) return false;
     const int64_t step = std::max<int64_t>(1, n_win / 64);
     int64_t entries = 0, columns = 0;   // of the sample

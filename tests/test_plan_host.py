@@ -875,7 +875,8 @@ def test_dissolved_windows_keep_their_product_in_the_library_owned_array():
 # Windows that hardly share columns stay windows where residual rows would be many waves: rows of more than a team pass times panels.
 @pytest.mark.parametrize("rows,cols,per_row,N,windows", [(63000, 540, 18, 128, False), (65000, 540, 18, 128, True), (65000, 540, 16, 128, False), (65000, 540, 18, 100, False),
                                                          (31000, 540, 18, 144, False), (33000, 540, 18, 144, True), (33000, 540, 18, 200, False), (51000, 540, 18, 200, True),
-                                                         (31000, 500, 30, 200, False), (33000, 500, 30, 200, True), (65000, 540, 18, 64, False), (47000, 500, 30, 64, False), (49000, 500, 30, 64, True)])
+                                                         (31000, 500, 30, 200, False), (33000, 500, 30, 200, True), (65000, 540, 18, 64, False), (63000, 500, 30, 64, False), (65000, 500, 30, 64, True),
+                                                         (65000, 500, 30, 48, False), (65000, 540, 18, 80, True)])
 def test_windows_that_hardly_share_columns_in_long_launches(rows, cols, per_row, N, windows):
     rng = np.random.default_rng(7)
     c = (rng.integers(0, cols // per_row, (rows, per_row)) + cols // per_row * np.arange(per_row)).ravel()
