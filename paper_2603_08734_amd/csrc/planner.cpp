@@ -835,7 +835,8 @@ static int lanes_per_row(const HostPlan& plan, const rsh_csr_t& a, const std::ve
 //     7.4, of 4000 10.4 and 18.7, 2 features rows of 2000 (4 MB) 8.5 and 12.4; 16 features rows of 1000 8.7 and 5.5, of 1500 7.2 and 8.5.
 //     A B that was just copied lies in no L2, so the gathers of a long row take longer: 2^14 vertices (rows of 3626) 5 features 12.0, in slices of
 //     512 11.1 (with pieces by column group 11.5); 100 rows of 3000 in 100000 columns 5 features 19.8 12.2 12.2, 70 of 4000 in 200000 3 features
-//     24.1 11.7 12.4, 200 of 2000 in 50000 3 features (0.6e9) 10.1 and 11.6 with pieces, 5 (1e9) 13.1, 7 10.8 in slices of 512.
+//     24.1 11.7 12.4, the graph 3 features (0.36e9) 9.1 9.7 10.0, 110 of
+//     4000 in 10000 5 features (0.4e9) 11.4 and 10.0 with pieces, 200 of 2000 in 50000 (0.6e9) 10.1 and 11.6 with pieces, 5 (1e9) 13.1, 7 10.8 in slices of 512.
 //   * Beyond, where rows of more than 1024 entries hold most of the entries, slices that make some 768 waves of them.  500 rows of 3000 entries
 //     in 500000 columns, 16 features 21.2 and in slices of 1024 24.4, 2048 20.7; 2000 rows of 2000 37.5, 50.1 and 34.8; 3000 rows of 4000 in
 //     1000000 columns 148, 179, 158.8 and of 4096 121; 250 rows of 4000 in 100000, 8 features 12.6 and of 1024 10.2.
@@ -853,8 +854,8 @@ static int64_t narrow_slice(const HostPlan& plan, const rsh_csr_t& a, const std:
     if (entries < (1 << 19)) {
         const int n = plan.n_user;
         const bool owned = n <= 8, copied = (n & (n - 1)) != 0 && a.nnz >= (1 << 18);   // a row of B is one lane's; copies_operand
-        const int64_t reach = owned && !copied ? 4096 : 2560, most = !owned ? 1ll << 30 : copied ? 3ll << 28 : 5ll << 30;
-        return longest <= 1024 || (longest <= reach && longest * a.n_cols * 2 * n <= most) ? 4096 : 512;
+        const int64_t bytes = longest * a.n_cols * 2 * n, reach = owned && (!copied || (n == 3 && bytes <= 3ll << 27)) ? 4096 : 2560;
+        return longest <= 1024 || (longest <= reach && bytes <= (!owned ? 1ll << 30 : copied ? 3ll << 28 : 5ll << 30)) ? 4096 : 512;
     }
     if (2 * in_long > entries) return std::min<int64_t>(4096, std::max<int64_t>(512, in_long / 768));
     return entries < (1 << 22) ? 1024 : 2048;

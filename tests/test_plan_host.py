@@ -885,7 +885,7 @@ def test_windows_that_hardly_share_columns_in_long_launches(rows, cols, per_row,
 
 
 # Slices of narrow rows (narrow_slice) where B is copied first (odd widths from 2^18 entries on).
-@pytest.mark.parametrize("rows,cols,per_row,N,slices", [(110, 20000, 2560, 3, 0), (110, 20000, 2561, 3, 6), (110, 20000, 2561, 4, 0), (100, 100000, 3000, 5, 6), (200, 50000, 2000, 3, 0),
+@pytest.mark.parametrize("rows,cols,per_row,N,slices", [(110, 20000, 2560, 3, 0), (110, 20000, 2561, 3, 0), (120, 20000, 3500, 3, 7), (110, 20000, 2561, 5, 6), (110, 10000, 4000, 5, 8), (110, 20000, 2561, 4, 0), (100, 100000, 3000, 5, 6), (200, 50000, 2000, 3, 0),
                                                         (200, 50000, 2000, 5, 4), (200, 50000, 2000, 8, 0), (300, 100000, 1024, 7, 0), (70, 200000, 4000, 3, 8)])
 def test_slices_of_narrow_rows_beside_a_copy(rows, cols, per_row, N, slices):
     rng = np.random.default_rng(5)
